@@ -1,0 +1,264 @@
+"""The work a program built on this package has it do, as cases that can be timed.
+
+A case is one pass through the package's entry points with the tensors such a program has in hand:
+an attention call of one layer, the conditional / unconditional pair of a guided denoising step,
+a whole block at a small resolution, a speculative round (stage, route, keep or undo), the rotary
+embedding, the commit. Sizes: 12 heads (drafter) or 40 heads (target) of 128 dims, 312 tokens per
+block (3 latent frames of 8 x 13) to 4680 (3 of 30 x 52), up to 6 cached blocks, 12 scored frames
+per block; a head-sharded rank holds a few heads of the target. `draw` covers what lies between,
+odd sizes included.
+"""
+import math
+
+import torch
+
+import paper_2604_17397_amd as P
+
+D = 128        # head_dim
+STEPS = 4      # denoising steps per block
+FRAMES = 12    # scored frames per block
+
+
+def listed():
+    return [
+        # one layer's attention at the smallest resolution: latency and launches count
+        {"name": "attn_tiny", "kind": "attn", "heads": 12, "tokens": 312, "cached": 2, "jitter": False},
+        # a block length that fills no tile, seam and tail inside tiles, in between small and large
+        {"name": "attn_ragged", "kind": "attn", "heads": 12, "tokens": 1031, "cached": 5, "jitter": False},
+        # the drafter's layer at full resolution, heads of different magnitude
+        {"name": "attn_drafter", "kind": "attn", "heads": 12, "tokens": 4680, "cached": 2, "jitter": True},
+        # the target's layer at full resolution and cache length: most of a generation's time
+        {"name": "attn_target", "kind": "attn", "heads": 40, "tokens": 4680, "cached": 6, "jitter": False},
+        # one rank's share of the target's heads when they are dealt out over eight GPUs; with few
+        # heads the library is handed a workspace and left to decide
+        {"name": "attn_rank", "kind": "batch", "items": 1, "heads": 5, "tokens": 4680, "cached": 6, "jitter": False},
+        # conditional and unconditional pass of classifier-free guidance in one launch (drafter)
+        {"name": "attn_guided", "kind": "batch", "items": 2, "heads": 12, "tokens": 4680, "cached": 3, "jitter": False},
+        # a whole block of the drafter at the smallest resolution: 30 layers x 4 steps of rotary
+        # embedding and attention, the last step with the commit fused in, then the router
+        {"name": "block_small", "kind": "block", "heads": 12, "tokens": 312, "cached": 2, "layers": 30},
+        # two speculative rounds of the target: a draft staged and kept, the next one staged, scored
+        # below the threshold and undone (decode-cache snapshot and restore, rollback)
+        {"name": "rounds_target", "kind": "rounds", "heads": 40, "tokens": 4680, "layers": 40, "head_major": False,
+         "decode_bytes": 256 << 20},
+        # the same loop on a head-major cache of the drafter at a middle resolution, odd snapshot
+        {"name": "rounds_head_major", "kind": "rounds", "heads": 12, "tokens": 1560, "layers": 30, "head_major": True,
+         "decode_bytes": (24 << 20) + 5},
+        # the drafter's commit with the rotation of K on the way
+        {"name": "commit_rope", "kind": "commit_rope", "heads": 12, "tokens": 4680, "layers": 30, "head_major": False},
+        # rotary embedding of one target layer's q and k rows
+        {"name": "rope_qk", "kind": "rope", "heads": 40, "tokens": 4680},
+        # the routing decision a generation loop waits for
+        {"name": "route", "kind": "route", "frames": FRAMES, "mode": "min"},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return min(hi, max(lo, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+def draw(rng):
+    kind = rng.choice(["attn", "attn", "attn", "attn", "batch", "batch", "block", "rounds", "commit_rope", "rope", "route"])
+    tokens = _log_int(rng, 312, 4680)
+    heads = _log_int(rng, 3, 40)
+    if kind == "attn":
+        return {"kind": kind, "heads": heads, "tokens": tokens, "cached": rng.randint(0, 6), "jitter": rng.random() < 0.3}
+    if kind == "batch":
+        items = rng.randint(1, 3)
+        return {"kind": kind, "items": items, "heads": _log_int(rng, 2, 40 // items), "tokens": tokens,
+                "cached": rng.randint(0, 6), "jitter": rng.random() < 0.3}
+    if kind == "block":
+        return {"kind": kind, "heads": _log_int(rng, 3, 16), "tokens": _log_int(rng, 312, 800), "cached": rng.randint(0, 4),
+                "layers": rng.randint(8, 30)}
+    if kind == "rounds":
+        return {"kind": kind, "heads": heads, "tokens": tokens, "layers": rng.randint(4, 40),
+                "head_major": rng.random() < 0.4, "decode_bytes": _log_int(rng, 1 << 20, 256 << 20)}
+    if kind == "commit_rope":
+        return {"kind": kind, "heads": heads, "tokens": tokens, "layers": rng.randint(4, 40), "head_major": rng.random() < 0.4}
+    if kind == "rope":
+        return {"kind": kind, "heads": heads, "tokens": tokens}
+    return {"kind": kind, "frames": rng.randint(1, 100), "mode": rng.choice(["min", "mean"])}
+
+
+# ---------------------------------------------------------------------------- inputs
+
+def _normal(gen, shape, scale=None):
+    """N(0,1) bfloat16 on the GPU, optionally one multiplier per head (second to last axis)."""
+    x = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+    x.normal_(generator=gen)
+    return x if scale is None else x.mul_(scale.view(-1, 1))
+
+
+def _tables(gen, n):
+    """cos / sin of one angle per (token, pair)."""
+    angle = torch.rand((n, D // 2), generator=gen, device="cuda") * (2 * math.pi)
+    return torch.cos(angle), torch.sin(angle)
+
+
+def _item(gen, case):
+    H, T, n = case["heads"], case["tokens"], case["cached"]
+    scales = [None] * 3
+    if case.get("jitter"):
+        scales = [(0.5 + 1.5 * torch.rand(H, generator=gen, device="cuda")).to(torch.bfloat16) for _ in range(3)]
+    it = {"q": _normal(gen, (T, H, D), scales[0]), "kb": _normal(gen, (T, H, D), scales[1]),
+          "vb": _normal(gen, (T, H, D), scales[2])}
+    # the layer's slice of the cache has room for the block that is being generated
+    it["kc"] = _normal(gen, ((n + 1) * T, H, D), scales[1])
+    it["vc"] = _normal(gen, ((n + 1) * T, H, D), scales[2])
+    return it
+
+
+def _cache(case, blocks):
+    L, H, T = case["layers"], case["heads"], case["tokens"]
+    shape = (L, H, blocks * T, D) if case["head_major"] else (L, blocks * T, H, D)
+    k = torch.zeros(shape, dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros(shape, dtype=torch.bfloat16, device="cuda")
+    return (k.transpose(1, 2), v.transpose(1, 2)) if case["head_major"] else (k, v)
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    st = {"case": case}
+    kind = case["kind"]
+    if kind == "attn":
+        st.update(_item(gen, case), cache_len=case["cached"] * case["tokens"])
+    elif kind == "batch":
+        items = [_item(gen, case) for _ in range(case["items"])]
+        for name in ("q", "kc", "vc", "kb", "vb"):
+            st[name] = [it[name] for it in items]
+        st["cache_len"] = case["cached"] * case["tokens"]
+        need = P.block_attn_workspace_bytes(st["q"][0], st["kc"][0], st["vc"][0], st["kb"][0], st["vb"][0],
+                                            st["cache_len"], n_items=len(items), split="auto")
+        st["workspace"] = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+    elif kind == "block":
+        H, T, L, n = case["heads"], case["tokens"], case["layers"], case["cached"]
+        # what the projections of every layer and step hand over
+        for name in ("q", "kb", "vb"):
+            whole = _normal(gen, (STEPS, L, T, H, D))
+            st[name] = [[whole[s, l] for l in range(L)] for s in range(STEPS)]
+        st["out"] = torch.zeros((STEPS, L, T, H, D), dtype=torch.bfloat16, device="cuda")
+        st["outs"] = [[st["out"][s, l] for l in range(L)] for s in range(STEPS)]
+        st["k"], st["v"] = _normal(gen, (L, (n + 1) * T, H, D)), _normal(gen, (L, (n + 1) * T, H, D))
+        st["qr"], st["kr"] = torch.empty_like(st["q"][0][0]), torch.empty_like(st["q"][0][0])
+        st["cos"], st["sin"] = _tables(gen, T)
+        st["scores"] = torch.randn(FRAMES, generator=gen, device="cuda") * 0.6 - 0.3
+    elif kind == "rounds":
+        H, T, L = case["heads"], case["tokens"], case["layers"]
+        st["k"], st["v"] = _cache(case, 3)
+        st["k"][:, :T], st["v"][:, :T] = _normal(gen, (L, T, H, D)), _normal(gen, (L, T, H, D))
+        st["drafts"] = [(_normal(gen, (L, T, H, D)), _normal(gen, (L, T, H, D))) for _ in range(2)]
+        # rewards of the two drafts' frames: one above the threshold, one below it
+        jitter = torch.randn((2, FRAMES), generator=gen, device="cuda") * 0.1
+        st["scores"] = [jitter[0] + 0.5, jitter[1] - 1.5]
+        n = case["decode_bytes"]
+        st["live"] = torch.randint(0, 256, (n,), generator=gen, dtype=torch.uint8, device="cuda")
+        st["snap"] = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        st["restored"] = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    elif kind == "commit_rope":
+        H, T, L = case["heads"], case["tokens"], case["layers"]
+        st["k"], st["v"] = _cache(case, 2)
+        st["kb"], st["vb"] = _normal(gen, (L, T, H, D)), _normal(gen, (L, T, H, D))
+        st["cos"], st["sin"] = _tables(gen, T)
+    elif kind == "rope":
+        shape = (case["tokens"], case["heads"], D)
+        st["q"], st["k"] = _normal(gen, shape), _normal(gen, shape)
+        st["cos"], st["sin"] = _tables(gen, case["tokens"])
+    else:
+        st["scores"] = torch.randn(case["frames"], generator=gen, device="cuda") * 0.6 - 0.3
+    return st
+
+
+# ---------------------------------------------------------------------------- one pass
+
+def _run_block(st):
+    case = st["case"]
+    L, T, n = case["layers"], case["tokens"], case["cached"]
+    cache = P.KVCache(st["k"], st["v"], T, cache_len=n * T)
+    for s in range(STEPS):
+        for l in range(L):
+            P.rope(st["q"][s][l], st["cos"], st["sin"], out=st["qr"])
+            P.rope(st["kb"][s][l], st["cos"], st["sin"], out=st["kr"])
+            kc, vc = cache.layer(l)
+            attn = P.block_attn_commit if s == STEPS - 1 else P.block_attn
+            attn(st["qr"], kc, vc, st["kr"], st["vb"][s][l], cache.cache_len, out=st["outs"][s][l])
+    P.kv_commit_mark(cache, n)
+    decision, q_b = P.worst_frame_route(st["scores"], -0.7, n)
+    # the cache as bit patterns: its rows are copies
+    return [st["out"], st["k"].view(torch.int16), st["v"].view(torch.int16), decision, q_b]
+
+
+def _run_rounds(st):
+    case = st["case"]
+    T = case["tokens"]
+    cache = P.KVCache(st["k"], st["v"], T, cache_len=T)
+    routed = []
+    for i, (kb, vb) in enumerate(st["drafts"]):
+        slot = 1 + i
+        P.buffer_snapshot(st["snap"], st["live"])          # clone before scoring
+        P.kv_commit(cache, kb, vb, slot)
+        decision, q_b = P.worst_frame_route(st["scores"][i], -0.7, slot)
+        routed += [decision, q_b]
+        if not decision:
+            P.buffer_snapshot(st["restored"], st["snap"])  # restore
+            P.kv_rollback(cache, slot * T)
+    return [st["k"].view(torch.int16), st["v"].view(torch.int16), st["restored"], routed, cache.cache_len]
+
+
+def run(st):
+    case = st["case"]
+    kind = case["kind"]
+    if kind == "attn":
+        return P.block_attn(st["q"], st["kc"], st["vc"], st["kb"], st["vb"], st["cache_len"])
+    if kind == "batch":
+        return P.block_attn_batch(st["q"], st["kc"], st["vc"], st["kb"], st["vb"], st["cache_len"],
+                                  workspace=st["workspace"], split="auto")
+    if kind == "block":
+        return _run_block(st)
+    if kind == "rounds":
+        return _run_rounds(st)
+    if kind == "commit_rope":
+        cache = P.KVCache(st["k"], st["v"], case["tokens"], cache_len=case["tokens"])
+        P.kv_commit_rope(cache, st["kb"], st["vb"], 1, st["cos"], st["sin"])
+        return [st["k"], st["v"]]
+    if kind == "rope":
+        return [P.rope(st["q"], st["cos"], st["sin"]), P.rope(st["k"], st["cos"], st["sin"])]
+    decision, q_b = P.worst_frame_route(st["scores"], -0.7, 3, mode=case["mode"])
+    return [decision, q_b]
+
+
+# ---------------------------------------------------------------------------- what a pass cannot do without
+
+def work(case):
+    kind = case["kind"]
+    if kind == "route":
+        return {"bytes": 4 * case["frames"] + 8, "flops": 0}
+    H, T = case["heads"], case["tokens"]
+    row = H * D * 2                    # bytes of one token's q, k or v
+    if kind in ("attn", "batch"):
+        n_k = (case["cached"] + 1) * T
+        items = case.get("items", 1)
+        return {"bytes": items * (2 * T + 2 * n_k) * row, "flops": items * 4.0 * T * n_k * D * H}
+    if kind == "rope":
+        return {"bytes": 4 * T * row + 2 * T * (D // 2) * 4, "flops": 0}
+    L = case["layers"]
+    if kind == "block":
+        n_k = (case["cached"] + 1) * T
+        attn = 2 * T + 2 * n_k         # q in, out, keys and values; rotated rows stay with the kernels
+        commit = 2 * T                 # k and v rows into the cache, once per layer
+        return {"bytes": L * row * (STEPS * attn + commit) + 2 * T * (D // 2) * 4,
+                "flops": STEPS * L * 4.0 * T * n_k * D * H}
+    if kind == "commit_rope":
+        return {"bytes": L * T * row * 4 + 2 * T * (D // 2) * 4, "flops": 0}
+    # rounds: two commits (K and V read and written), one slot zero-filled, three copies of the decode cache
+    return {"bytes": L * T * row * (2 * 4 + 2) + 6 * case["decode_bytes"], "flops": 0}
+
+
+def tolerance(case):
+    # Attention against float64 on the same bf16 inputs (a row sample of the attention cases): rel
+    # 2.2e-3 .. 2.4e-3, because probabilities and outputs are rounded to bf16, and max 0.010, with
+    # heads of different magnitude 0.020; four times that. Everything else is a copy, a rotation in
+    # a fixed order or a comparison, and stays bit for bit.
+    if case["kind"] in ("attn", "batch", "block"):
+        return {"rel": 1e-2, "max": 0.08, "differ": 0.0}
+    return "exact"
