@@ -262,3 +262,52 @@ def tolerance(case):
     if case["kind"] in ("attn", "batch", "block"):
         return {"rel": 1e-2, "max": 0.08, "differ": 0.0}
     return "exact"
+
+
+# ---------------------------------------------------------------------------- the same in 64 bits
+
+def _attn64(q, kc, vc, kb, vb, cache_len):
+    """softmax(q k^T / sqrt(D)) v over cache[:cache_len] followed by the block, one head at a time."""
+    out = torch.empty(q.shape, dtype=torch.float64, device=q.device)
+    for h in range(q.shape[1]):
+        k = torch.cat([kc[:cache_len, h], kb[:, h]]).double()
+        v = torch.cat([vc[:cache_len, h], vb[:, h]]).double()
+        s = q[:, h].double() @ k.t().contiguous()
+        out[:, h] = torch.softmax(s.mul_(1.0 / math.sqrt(D)), dim=1) @ v
+    return out
+
+
+def _rope64(x, cos, sin):
+    pair = x.double().unflatten(-1, (D // 2, 2))
+    re, im = pair[..., 0], pair[..., 1]
+    c, s = cos.double()[:, None, :], sin.double()[:, None, :]
+    return torch.stack([re * c - im * s, re * s + im * c], dim=-1).flatten(-2)
+
+
+def exact(case, seed):
+    """What `run` returns, in 64 bits. Copies and whole numbers have no other value and stay None."""
+    st = prepare(case, seed)
+    kind = case["kind"]
+    if kind == "attn":
+        return _attn64(st["q"], st["kc"], st["vc"], st["kb"], st["vb"], st["cache_len"])
+    if kind == "batch":
+        return [_attn64(st["q"][i], st["kc"][i], st["vc"][i], st["kb"][i], st["vb"][i], st["cache_len"])
+                for i in range(case["items"])]
+    if kind == "block":
+        L, T, n = case["layers"], case["tokens"], case["cached"]
+        out = torch.empty(st["out"].shape, dtype=torch.float64, device="cuda")
+        for s in range(STEPS):
+            for l in range(L):
+                # the rotated rows are bf16 tensors that the program hands on
+                q, kb = (_rope64(x, st["cos"], st["sin"]).bfloat16() for x in (st["q"][s][l], st["kb"][s][l]))
+                out[s, l] = _attn64(q, st["k"][l], st["v"][l], kb, st["vb"][s][l], n * T)
+        return [out, None, None, None, None]
+    if kind == "commit_rope":
+        T = case["tokens"]
+        k = torch.zeros(st["k"].shape, dtype=torch.float64, device="cuda")
+        for l in range(case["layers"]):
+            k[l, T:2 * T] = _rope64(st["kb"][l], st["cos"], st["sin"])
+        return [k, None]
+    if kind == "rope":
+        return [_rope64(st[name], st["cos"], st["sin"]) for name in ("q", "k")]
+    return None
