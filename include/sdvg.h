@@ -119,14 +119,16 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  * The same attention for up to 8 independent (q, cache, block, out) sets in ONE launch -- e.g. the
  * conditional and the unconditional pass of classifier-free guidance (paper Sec. 4.1 "Models":
  * guidance scale 3.0), which share shapes and cache length but have their own tensors. Result
- * item by item as n_items calls of sdvg_block_attn; one launch fills the chip better and halves
- * the launch count.
+ * item by item as n_items calls of sdvg_block_attn (same softmax, same error bounds; also the same
+ * bits where both take workgroups of the same shape, see below); one launch fills the chip better
+ * and halves the launch count.
  *   n_items   1 .. 8. q, k_cache, v_cache, k_blk, v_blk, out: HOST arrays of n_items device
  *             pointers (k_cache / v_cache and their entries may be NULL when cache_len == 0).
  *             All items share desc (shapes, strides, scale, dtype) and cache_len.
  *   workspace device, nullable, 16-byte aligned, workspace_bytes long; split_mode one of
- *             SDVG_SPLIT_*. Without a workspace (or with SDVG_SPLIT_NEVER) every query tile of
- *             256 rows is one workgroup. With a workspace of at least
+ *             SDVG_SPLIT_*. Without a workspace (or with SDVG_SPLIT_NEVER) every query tile is
+ *             one workgroup: 256 rows, or, when the launch has few of those, 128 or 64 rows whose
+ *             keys are dealt out over 2 or 4 groups of the workgroup's waves. With a workspace of at least
  *             sdvg_block_attn_workspace_bytes(desc, n_items, cache_len, split_mode) bytes the
  *             library may deal the (query tile, key tile) pairs out evenly over whole rounds of
  *             workgroups instead, so that a launch with few query tiles still fills the chip,

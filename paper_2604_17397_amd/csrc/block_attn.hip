@@ -29,21 +29,15 @@
 #include <mutex>
 #include <type_traits>
 
+#include "block_attn_device.h"
 #include "block_attn_index.h"
 #include "block_attn_params.h"
 #include "sdvg_common.h"
 
 namespace {
 
+using namespace sdvg::attn_dev;
 using sdvg::AttnParams;
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 namespace ix = sdvg::attn_index;
 using ix::kBN;         // keys per tile
@@ -51,136 +45,6 @@ using ix::kRing;       // LDS ring depth (tiles) for K and for V
 using ix::kTileBytes;  // one 64-key x 128-dim bf16 tile, unpadded
 using ix::kVBase;      // the V ring follows the K ring
 constexpr int kBM = 256;  // query rows per workgroup
-constexpr float kPSumLimit = 1048576.0f;  // 2^20: a tile whose P sums past this retakes the maximum
-
-// v_permlane32_swap(x, x) returns {own, partner} in the lower half-wave and {partner, own} in
-// the upper one (partner = the lane 32 away); only symmetric combinations are used.
-__device__ __forceinline__ float lane_max32(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float lane_sum32(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ __forceinline__ void wait_vmcnt0() {
-  // s_waitcnt vmcnt(0) only (expcnt = 7, lgkmcnt = 15 left unconstrained)
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-}
-
-// One wave-level 16-byte-per-lane global -> LDS copy: lane i's 16 bytes land at
-// lds_addr + 16 * i. Written as inline assembly so that the compiler does not serialise
-// successive copies with vmcnt(0) waits; completion is awaited explicitly (wait_vmcnt0)
-// before the workgroup barrier that publishes the tile. The statements write M0 and say so in
-// their clobber lists, so the compiler never assumes a value of its own survives them (clang
-// warns that M0 is a reserved register it will not save; that is the intent).
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(const void *gptr, uint32_t lds_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, off"
-      :
-      : "s"(lds_addr), "v"(gptr)
-      : "memory", "m0");
-}
-// Same copy with the 64-token pointer step folded in: the 64-bit add sits between the M0 write
-// and the copy (covering the wait state M0 needs) and the stepped pointer is returned.
-__device__ __forceinline__ const char *dma16_step(const char *gptr, uint64_t step, uint32_t lds_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %1\n\t"
-      "v_lshl_add_u64 %0, %0, 0, %2\n\t"
-      "global_load_lds_dwordx4 %0, off"
-      : "+v"(gptr)
-      : "s"(lds_addr), "s"(step)
-      : "memory", "m0");
-  return gptr;
-}
-#pragma clang diagnostic pop
-
-// Workgroup barrier without the fence of __syncthreads (which would also wait for the
-// prefetches still in flight); the compiler-level memory clobbers keep LDS accesses on
-// their side of it.
-__device__ __forceinline__ void wg_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// The `items` array of the kernels' single by-value AttnParams argument, read from the
-// kernel-argument segment (constant memory; the compiler turns the reads into scalar loads).
-__device__ __forceinline__ const sdvg::AttnItem *kernarg_items() {
-  const char *ka = (const char *)__builtin_amdgcn_kernarg_segment_ptr();
-  return reinterpret_cast<const sdvg::AttnItem *>(ka + offsetof(AttnParams, items));
-}
-
-// Rows of O^T held in the accumulator layout (lane = query row lane % 32, half-wave hh), scaled by
-// 1 / row sum, rounded to bf16 and stored; rows past n_q are not stored.
-__device__ __forceinline__ void store_rows(const AttnParams &p, const sdvg::AttnItem &it, int head, int q_row,
-                                           int hh, const f32x16 (&o_acc)[4], float inv_l) {
-  if (q_row >= p.n_q) return;
-  uint16_t *op = static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 4 * hh;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 o4 = {o_acc[u][4 * g] * inv_l, o_acc[u][4 * g + 1] * inv_l, o_acc[u][4 * g + 2] * inv_l,
-                        o_acc[u][4 * g + 3] * inv_l};
-      const bf16x4 ob = __builtin_convertvector(o4, bf16x4);
-      *reinterpret_cast<bf16x4 *>(op + 32 * u + 8 * g) = ob;
-    }
-  }
-}
-
-// Fused commit (paper Sec. 3 "Inference flow": the block the target keeps -- an accepted draft or
-// its own regeneration -- goes into the target's KV cache): workgroups appended to the attention
-// launch copy the block's K and V rows of this layer into cache tokens [cache_len, cache_len +
-// n_blk), 16 bytes per lane, while the attention workgroups (which only read tokens below
-// cache_len and the block itself) are still running. They are dispatched last and find their
-// compute units among those the last round of attention workgroups leaves idle.
-__device__ __forceinline__ void commit_block_rows(const AttnParams &p) {
-  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-  const sdvg::AttnItem it = kernarg_items()[0];
-  const int64_t chunks = static_cast<int64_t>(p.n_blk) * p.n_heads * 16;  // 16-byte chunks per tensor
-  const int64_t first = static_cast<int64_t>(blockIdx.x - p.copy_first_block) * 512 + threadIdx.x;
-  const int64_t stride = static_cast<int64_t>(p.n_copy_blocks) * 512;
-  auto locate = [&](int64_t g, const u32x4 *&src, u32x4 *&dst) __attribute__((always_inline)) {
-    const bool is_v = g >= chunks;
-    const int64_t c = is_v ? g - chunks : g;
-    const int64_t row = c >> 4;
-    const int ch = static_cast<int>(c & 15);
-    const int64_t tok = row / p.n_heads;
-    const int head = static_cast<int>(row - tok * p.n_heads);
-    src = reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(is_v ? it.v_blk : it.k_blk) + tok * p.blk_ts +
-                                          head * p.blk_hs + ch * 8);
-    dst = reinterpret_cast<u32x4 *>(static_cast<uint16_t *>(is_v ? p.v_commit_dst : p.k_commit_dst) + tok * p.kv_ts +
-                                    head * p.kv_hs + ch * 8);
-  };
-  // four chunks in flight per lane: the few workgroups that do this have to stream by themselves
-  int64_t g = first;
-  for (; g + 3 * stride < 2 * chunks; g += 4 * stride) {
-    const u32x4 *s0, *s1, *s2, *s3;
-    u32x4 *d0, *d1, *d2, *d3;
-    locate(g, s0, d0);
-    locate(g + stride, s1, d1);
-    locate(g + 2 * stride, s2, d2);
-    locate(g + 3 * stride, s3, d3);
-    const u32x4 a = __builtin_nontemporal_load(s0), b = __builtin_nontemporal_load(s1),
-                c = __builtin_nontemporal_load(s2), d = __builtin_nontemporal_load(s3);
-    __builtin_nontemporal_store(a, d0);
-    __builtin_nontemporal_store(b, d1);
-    __builtin_nontemporal_store(c, d2);
-    __builtin_nontemporal_store(d, d3);
-  }
-  for (; g < 2 * chunks; g += stride) {
-    const u32x4 *s0;
-    u32x4 *d0;
-    locate(g, s0, d0);
-    __builtin_nontemporal_store(__builtin_nontemporal_load(s0), d0);
-  }
-}
 
 // kSplit = false: one piece per workgroup (one query tile with all its key tiles; the hot case).
 // kSplit = true: the workgroup's run may hold several pieces, taken in a loop.
@@ -385,74 +249,6 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
     SDVG_SB();
   };
 
-  // Vector phase: P^T = exp2(scale*log2e * (S^T - m)) rounded to bf16 in B-operand order, plus
-  // this lane's share of the row sum, taken over the ROUNDED probabilities so that numerator
-  // and denominator of the softmax use the same weights. The shift by the running maximum m is
-  // already in the scores (s_init), so forming P costs one multiply and one exp2 per score.
-  // No maximum is computed on the fast path: m may lag the true maximum, which changes nothing
-  // (both sides carry the same factor) as long as exp2 stays in range. Only if the tile's sum
-  // of P comes out huge (a logit more than ~15 above m in log2 units) does the wave take the
-  // slow path: raise m to the true maximum, rescale O and l, form P again.
-  // The row sum unpacks the rounded pairs again (a shift and a mask) and adds them as fp32:
-  // four plain instructions per pair. The one-instruction alternative, v_dot2_f32_bf16 with a
-  // vector of ones, shares the matrix pipe with the partner wave's MFMAs and, queued behind
-  // them at lower priority, made the vector phase the longer of the two (measured: 16 of them
-  // per tile cost 250 cycles per phase; the 64 plain instructions that replace them cost none).
-  // The work is laid out in stages over all 32 scores (scale, exp2, convert, sum on four
-  // accumulators): no instruction depends on one issued just before it.
-  auto form_p = [&]() __attribute__((always_inline)) -> float {
-    float pexp[2][16];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) pexp[kb][i] = s_acc[kb][i] * p.scale_log2e;
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) pexp[kb][i] = __builtin_amdgcn_exp2f(pexp[kb][i]);
-    __builtin_amdgcn_sched_barrier(0);
-    bf16x2 pb[2][8];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const f32x2 pp = {pexp[kb][2 * i], pexp[kb][2 * i + 1]};
-        pb[kb][i] = __builtin_convertvector(pp, bf16x2);
-      }
-    __builtin_amdgcn_sched_barrier(0);
-    float dl[4];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        uint32_t pbits;
-        __builtin_memcpy(&pbits, &pb[kb][i], 4);
-        const float lo = __uint_as_float(pbits << 16), hi = __uint_as_float(pbits & 0xffff0000u);
-        if (kb == 0 && i < 2) {
-          dl[2 * i] = lo;
-          dl[2 * i + 1] = hi;
-        } else {
-          dl[(2 * i) & 3] += lo;
-          dl[(2 * i + 1) & 3] += hi;
-        }
-        pf[kb * 2 + (i >> 2)][(i & 3) * 2] = pb[kb][i][0];
-        pf[kb * 2 + (i >> 2)][(i & 3) * 2 + 1] = pb[kb][i][1];
-      }
-    __builtin_amdgcn_sched_barrier(0);
-    return (dl[0] + dl[1]) + (dl[2] + dl[3]);
-  };
-  // Largest score of the tile for this lane's query (both half-waves), relative to the shift.
-  auto tile_max = [&]() __attribute__((always_inline)) -> float {
-    float m4[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) m4[c] = fmaxf(s_acc[0][c], s_acc[1][c]);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 4; i < 16; ++i) m4[i & 3] = fmaxf(m4[i & 3], s_acc[kb][i]);
-    return lane_max32(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
-  };
   // Moves the running maximum up by d (score units, >= 0): the scores in hand and every later
   // accumulator start d lower, and what has been summed so far shrinks by 2^(-d * scale*log2e).
   auto raise_max = [&](float d) __attribute__((always_inline)) {
@@ -469,10 +265,10 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
     set_shift(s_shift - d);
   };
   auto softmax_tile = [&]() __attribute__((always_inline)) {
-    float dl = form_p();
+    float dl = form_p(s_acc, p.scale_log2e, pf);
     if (__builtin_amdgcn_ballot_w64(!(dl < kPSumLimit)) != 0) {
-      raise_max(fmaxf(tile_max(), 0.f));
-      dl = form_p();
+      raise_max(fmaxf(tile_max(s_acc), 0.f));
+      dl = form_p(s_acc, p.scale_log2e, pf);
     }
     l_run += dl;
   };
@@ -591,7 +387,7 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
     wait_lds0();
     if (t0 == geo.n_tiles - 1) mask_tail(t0);
     {  // the running maximum starts at the first tile's true maximum
-      const float mx = tile_max();
+      const float mx = tile_max(s_acc);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -714,6 +510,7 @@ int device_info(const DeviceInfo **out) {
     if (d.status == hipSuccess)
       d.status = hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_bf16_kernel<true>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (d.status == hipSuccess) d.status = sdvg::prepare_block_attn_groups();
     if (d.status == hipSuccess)
       d.status = hipDeviceGetAttribute(&d.n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (d.status == hipSuccess) d.status = hipGetSymbolAddress(&d.scratch, HIP_SYMBOL(scratch));
@@ -732,28 +529,63 @@ int device_info(const DeviceInfo **out) {
 struct Plan {
   int n_qtiles, n_hq, n_tiles, units, total_wg;
   int64_t workspace_bytes;  // 0 when nothing is split
+  int groups;               // key groups per workgroup (1: the kernel of this file)
 };
+
+// Key groups per workgroup. Estimated time: rounds of workgroups over the compute units, times a
+// fixed part plus the key tiles each group walks.
+// Measured on MI355X, us (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
+//   12 heads x 312 x 936 keys [24/36/60] 26.6 / 20.7 / 16.1; 12 x 1031 x 6186 [60/108/204] 109 / 69 / 54;
+//   12 x 1560 x 4680 [84/156/300] 87 / 59 / 80; 5 x 4680 x 32760 [95/185/370] 518 / 379 / 457;
+//   40 x 1031 x 3093 [200/360/680] 74 / 90 / 95; 16 x 4680 x 14040 [304/592/1184] 594 / 533 / 603;
+//   12 x 4680 x 14040 [228/444/888] 347 / 373 / 480; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
+// A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value; the
+// model picks the fastest in each of these cases.
+int choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu) {
+  if (n_cu <= 0) return 1;
+  const struct { int groups, keys; double fixed_us, tile_us; } variants[] = {
+      {1, 64, 4.0, 1.25}, {2, 64, 6.0, 1.35}, {4, 32, 6.0, 0.95}};
+  int best = 1;
+  double best_us = 0;
+  for (const auto &v : variants) {
+    const int rows = kBM / v.groups;
+    const int64_t wgs = static_cast<int64_t>(n_items) * n_heads * ((n_q + rows - 1) / rows);
+    const int64_t tiles = (n_k + v.keys - 1) / v.keys, its = (tiles + v.groups - 1) / v.groups;
+    const double us = static_cast<double>((wgs + n_cu - 1) / n_cu) * (v.fixed_us + static_cast<double>(its) * v.tile_us);
+    if (v.groups == 1 || us < best_us) {
+      best = v.groups;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
 Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode) {
-  Plan pl;
-  pl.n_qtiles = (n_q + kBM - 1) / kBM;
-  pl.n_hq = n_items * n_heads * pl.n_qtiles;
-  pl.n_tiles = static_cast<int>((n_k + kBN - 1) / kBN);
-  pl.units = pl.n_tiles;
-  pl.total_wg = pl.n_hq;
-  pl.workspace_bytes = 0;
-  if (split_mode == SDVG_SPLIT_NEVER || n_cu <= 0) return pl;
+  auto unsplit = [&](int groups) {
+    const int rows = kBM / groups, keys = groups == 4 ? 32 : kBN;
+    Plan pl;
+    pl.groups = groups;
+    pl.n_qtiles = (n_q + rows - 1) / rows;
+    pl.n_hq = pl.total_wg = n_items * n_heads * pl.n_qtiles;
+    pl.n_tiles = pl.units = static_cast<int>((n_k + keys - 1) / keys);
+    pl.workspace_bytes = 0;
+    return pl;
+  };
+  auto plain = [&]() { return unsplit(choose_groups(n_items, n_q, n_heads, n_k, n_cu)); };
+  if (split_mode == SDVG_SPLIT_NEVER || n_cu <= 0) return plain();
+  Plan pl = unsplit(1);
   const int rounds = (pl.n_hq + n_cu - 1) / n_cu;
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
   // a chip that is only partly busy clocks higher. Measured on MI355X (4680 queries): 12 heads
   // (11 % of the compute units idle) 15 % slower split than plain; 5 heads (63 % idle) 4 % faster;
   // 2 heads (85 % idle) 83 % faster. SDVG_SPLIT_AUTO therefore splits from 60 % idle on.
-  if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return pl;
-  if (split_mode == SDVG_SPLIT_AUTO && idle < 0.6) return pl;
+  if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
+  if (split_mode == SDVG_SPLIT_AUTO && idle < 0.6) return plain();
   const int64_t all = static_cast<int64_t>(pl.n_hq) * pl.n_tiles;
   const int64_t wgs = static_cast<int64_t>(rounds) * n_cu;
   pl.units = static_cast<int>((all + wgs - 1) / wgs);  // <= n_tiles, because wgs >= n_hq
-  if (pl.units < 16) return Plan{pl.n_qtiles, pl.n_hq, pl.n_tiles, pl.n_tiles, pl.n_hq, 0};
+  if (pl.units < 16) return plain();
   pl.total_wg = static_cast<int>((all + pl.units - 1) / pl.units);
   pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * sdvg::kPartialFloats * 4;
   return pl;
@@ -776,6 +608,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   // compute units idle (they then run beside it for its whole length); a full round otherwise.
   const int idle_cus = n_cu > 0 && p.total_work % n_cu ? n_cu - p.total_work % n_cu : 0;
   p.n_copy_blocks = !p.k_commit_dst ? 0 : (idle_cus >= 4 ? idle_cus : (n_cu > 0 ? n_cu : 256));
+  if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
   if (p.units == p.n_tiles)
     hipLaunchKernelGGL(block_attn_bf16_kernel<false>, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512),
                        lds_bytes, s, p);

@@ -1,0 +1,450 @@
+// Block-causal attention of one video block for launches with few query rows, for gfx950 (MI355X).
+//
+// Same operation and same per-wave arithmetic as block_attn.hip (paper Sec. 1 / Sec. 4.1 "Models").
+// There a workgroup owns 256 query rows and walks all keys; a layer with few heads or a small block
+// then has far fewer workgroups than the chip has compute units, each of them one long serial chain
+// of key tiles. Here the 8 waves of a workgroup form G key groups: the workgroup owns 8 / G x 32
+// query rows and every group walks every G-th key tile, so there are G times as many workgroups and
+// the chain is G times shorter. The groups' partial results (O, row sum, maximum) meet in LDS at the
+// end, in fp32; nothing goes through memory and no second kernel is needed.
+//
+// What it costs: a K / V tile in LDS serves 8 / G waves instead of 8, so the L2 -> LDS traffic per
+// query row is G times that of the 256-row kernel. Tiles are 64 keys (G = 2) or 32 keys (G = 4),
+// because G groups x (3 K + 2 V tiles) have to fit the LDS (160 KB in both cases).
+//
+// Schedule: ping-pong as in block_attn.hip (waves 0-3 and 4-7 half an iteration apart, vector phase
+// of one beside the matrix phase of the other). Matrix phase i of a group computes S(i+1) and
+// P(i) V(i) and starts the copies of V(i+1) and K(i+3), one or two behind each second MFMA, into the
+// slots last read in matrix phase i - 1 (three K and two V slots per group: all 160 KB of the LDS).
+//
+// What bounds it, and what that led to (12 heads x 1031 x 6186 keys, 4 groups, us per launch; the
+// 256-row kernel takes 109):
+//   copies started at the head of the vector phase (ring of 2 + 2, 128 KB)         66
+//   between the MFMAs, tile kinds told apart by branches at each tile               62
+//   one rarely taken branch per tile                                                57
+//   slots as offsets in registers instead of a loop unrolled by 6: short launches gain (a KB of
+//   code fetched cold costs about 1 us), but its bookkeeping in the vector phase    59
+//   bookkeeping moved into the gaps of the matrix phase                              53
+// Without any copies it would take 50 - 42 (the matrix phases alone); a quarter of the copies more or
+// less, or an LDS order without bank-conflict swizzle, changes nothing, so what the copies cost is
+// issue time next to the MFMAs, as in block_attn.hip.
+#include "block_attn_device.h"
+#include "block_attn_groups_index.h"
+#include "block_attn_params.h"
+#include "sdvg_common.h"
+
+namespace {
+
+using namespace sdvg::attn_dev;
+using sdvg::AttnParams;
+namespace ix = sdvg::attn_index;
+
+typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+#define SDVG_SB() __builtin_amdgcn_sched_barrier(0)
+
+// The quotients of the work index are the same in every lane, but the compiler divides in vector
+// registers; this tells it so, and everything derived from them stays scalar.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+template <int N>
+__device__ __forceinline__ void wait_lds() {  // all but the N most recent LDS reads have returned
+  __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+}
+
+constexpr int kMergeOFloats = ix::kWaves * 64 * 64;  // O of all waves; row sums and shifts follow
+constexpr int kMergeBytes = (kMergeOFloats + ix::kWaves * 2 * 64) * 4;
+
+template <int G>
+__global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams p) {
+  using C = ix::Groups<G>;
+  constexpr int R = C::kRowWaves, NK = C::kHalves;
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const uint32_t lds_addr0 =
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t *)smem));
+
+  if (static_cast<int>(blockIdx.x) >= p.copy_first_block) {
+    commit_block_rows(p);
+    return;
+  }
+  const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
+  if (work >= p.total_work) return;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave / R, wr = wave % R;
+  const bool half_b = wave >= 4;
+  const int r32 = lane & 31, hh = lane >> 5;
+
+  const int per_item = p.n_heads * p.n_qtiles;
+  const int item = uniform(work / per_item);
+  const int head = uniform((work - item * per_item) / p.n_qtiles);
+  const int qt = work - item * per_item - head * p.n_qtiles;
+  const sdvg::AttnItem it = kernarg_items()[item];
+
+  ix::Streams st;
+  st.kc = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.k_cache) + head * p.kv_hs);
+  st.vc = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.v_cache) + head * p.kv_hs);
+  st.kb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.k_blk) + head * p.blk_hs);
+  st.vb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.v_blk) + head * p.blk_hs);
+  st.kv_tsb = static_cast<uint32_t>(p.kv_ts * 2);
+  st.blk_tsb = static_cast<uint32_t>(p.blk_ts * 2);
+  st.c_len = static_cast<int>(p.cache_len);
+  st.n_k = p.n_k;
+  const int n_it = (p.n_tiles + G - 1) / G;  // the same for all groups: one past its tiles is masked
+  auto tile_of = [&](int i) __attribute__((always_inline)) { return grp + G * i; };
+
+  // ---- copies: the pointers of this lane's rows of a K tile and of a V tile. In a run of tiles of one
+  // source they are stepped by the copies themselves; elsewhere set_ptrs computes them, a few vector
+  // instructions per row that go into the vector phase, which is the shorter one.
+  const ix::GroupRuns runs = ix::group_runs<G>(st, grp);
+  ix::LaneBase k_lane[C::kVariants], v_lane;
+#pragma unroll
+  for (int v = 0; v < C::kVariants; ++v)
+    k_lane[v] = ix::group_lane_base(st, ix::group_copy_row<G>(wr, lane, v), lane, 0);
+  v_lane = ix::group_lane_base(st, ix::group_copy_row<G>(wr, lane, 0), lane, 1);
+  const int row0 = ix::group_copy_row<G>(wr, lane, 0);
+  const char *k_ptr[C::kCopies], *v_ptr[C::kCopies];
+  auto set_k_ptrs = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < C::kCopies; ++u)
+      k_ptr[u] = ix::group_key_ptr(st, k_lane[u % C::kVariants], t * C::kKeys + 4 * R * u + row0);
+  };
+  auto set_v_ptrs = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < C::kCopies; ++u) v_ptr[u] = ix::group_key_ptr(st, v_lane, t * C::kKeys + 4 * R * u + row0);
+  };
+  uint32_t k_dst = lds_addr0 + ix::group_copy_dst<G>(grp, wr, 0, 0, 0);
+  uint32_t v_dst = lds_addr0 + ix::group_copy_dst<G>(grp, wr, 0, 0, 1);
+  const uint32_t k_dst0 = k_dst, v_dst_sum = 2 * v_dst + C::kTile;
+#pragma unroll 1
+  for (int i = 0; i < 3; ++i) {  // K(0) .. K(2)
+    set_k_ptrs(tile_of(i));
+#pragma unroll
+    for (int u = 0; u < C::kCopies; ++u) dma16(k_ptr[u], k_dst + u * R * 1024);
+    k_dst += C::kTile;
+  }
+  k_dst = k_dst0;  // slot of K(3)
+  set_v_ptrs(tile_of(0));
+#pragma unroll
+  for (int u = 0; u < C::kCopies; ++u) dma16(v_ptr[u], v_dst + u * R * 1024);
+  v_dst += C::kTile;  // slot of V(1)
+
+  // ---- query rows (rows past the end re-read the last one and are not stored)
+  const int wt_count = ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem);
+  const int q_row = (ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem) + wr) * 32 + r32;
+  const int q_row_ld = q_row < p.n_q ? q_row : p.n_q - 1;
+  bf16x8 qf[8];
+  {
+    const uint16_t *qp = static_cast<const uint16_t *>(it.q) + q_row_ld * p.q_ts + head * p.q_hs + 8 * hh;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + 16 * s);
+  }
+
+  // ---- LDS read addresses (bytes), with the group's part of the LDS and the slot folded in
+  uint32_t k_off[8], v_off[4];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) k_off[s] = lds_addr0 + grp * C::kGroup + ix::k_read_offset(lane, s, 0);
+#pragma unroll
+  for (int db = 0; db < 4; ++db) v_off[db] = lds_addr0 + grp * C::kGroup + C::kVSlots + ix::v_read_offset(lane, 0, db, 0);
+
+  f32x16 o_acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o_acc[u][i] = 0.f;
+  float l_run = 0.f, s_shift = 0.f;
+  f32x16 s_acc[NK];
+  f32x16 s_init = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  bf16x8 pf[2 * NK];
+  bf16x8 f[2][4];  // two groups of 4 MFMA A-operands: one in use, one being fetched
+  auto set_shift = [&](float v) __attribute__((always_inline)) {
+    s_shift = v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s_init[i] = v;
+  };
+
+  // The MFMAs of a matrix phase in groups of 4: groups 0 .. 2 NK - 1 are S^T = K Q^T, groups
+  // 2 NK .. 4 NK - 1 are O^T += V^T P^T, one per step of 16 keys.
+  auto read_op = [&](bf16x8 &dst, int gi, int i) __attribute__((always_inline)) {
+    if (gi < 2 * NK) {
+      const int s = NK == 2 ? 2 * gi + (i >> 1) : 4 * gi + i, kb = NK == 2 ? i & 1 : 0;
+      dst = *(lds_bf16x8 *)(k_off[s] + kb * 32 * 256);
+    } else {
+      const uint32_t vp = v_off[i] + (gi - 2 * NK) * 16 * 256;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)vp);
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vp + 8 * 256));
+      const __attribute__((ext_vector_type(8))) short a16 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      __builtin_memcpy(&dst, &a16, sizeof(bf16x8));
+    }
+  };
+  auto mfma_op = [&](const bf16x8 &a, int gi, int i) __attribute__((always_inline)) {
+    if (gi < 2 * NK) {
+      const int s = NK == 2 ? 2 * gi + (i >> 1) : 4 * gi + i, kb = NK == 2 ? i & 1 : 0;
+      s_acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[s], s == 0 ? s_init : s_acc[kb], 0, 0, 0);
+    } else {
+      o_acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[gi - 2 * NK], o_acc[i], 0, 0, 0);
+    }
+  };
+  // The first two MFMAs of a group while the operands of the next group (if any) are fetched: half of
+  // the reads before the first MFMA, half behind it.
+  auto run_group = [&](int gi, bool fetch_next) __attribute__((always_inline)) {
+    bf16x8(&cur)[4] = f[gi & 1];
+    bf16x8(&nxt)[4] = f[(gi + 1) & 1];
+    SDVG_SB();
+    if (fetch_next) {
+      read_op(nxt[0], gi + 1, 0);
+      read_op(nxt[1], gi + 1, 1);
+      if (gi + 1 < 2 * NK)
+        wait_lds<2>();
+      else
+        wait_lds<4>();
+    } else {
+      wait_lds<0>();
+    }
+    SDVG_SB();
+    mfma_op(cur[0], gi, 0);
+    SDVG_SB();
+    if (fetch_next) {
+      read_op(nxt[2], gi + 1, 2);
+      read_op(nxt[3], gi + 1, 3);
+    }
+    SDVG_SB();
+    mfma_op(cur[1], gi, 1);
+    SDVG_SB();
+  };
+  // Keys past n_k get -inf (the scores of tile t are in hand).
+  auto mask_tail = [&](int t) __attribute__((always_inline)) {
+    const int key0 = t * C::kKeys + 4 * hh;
+#pragma unroll
+    for (int kb = 0; kb < NK; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (key0 + kb * 32 + 8 * (i >> 2) + (i & 3) >= p.n_k) s_acc[kb][i] = -INFINITY;
+  };
+  // Softmax with the lazy running maximum of block_attn.hip.
+  auto softmax_tile = [&]() __attribute__((always_inline)) {
+    float dl = form_p(s_acc, p.scale_log2e, pf);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(dl < kPSumLimit)) != 0, 0)) {
+      const float d = fmaxf(tile_max(s_acc), 0.f);
+      const float alpha = __builtin_amdgcn_exp2f(-d * p.scale_log2e);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o_acc[u][i] *= alpha;
+      l_run *= alpha;
+#pragma unroll
+      for (int kb = 0; kb < NK; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s_acc[kb][i] -= d;
+      set_shift(s_shift - d);
+      dl = form_p(s_acc, p.scale_log2e, pf);
+    }
+    l_run += dl;
+  };
+
+  wait_vmcnt0();
+  wg_barrier();
+  // ---- S of the group's first tile; its maximum starts the running maximum. A group without a
+  // single key keeps a finite maximum far below any score, so that its share of the merge is 0.
+  {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) read_op(f[0][i], 0, i);
+#pragma unroll
+    for (int gi = 0; gi < 2 * NK; ++gi) {
+      run_group(gi, gi + 1 < 2 * NK);
+      mfma_op(f[gi & 1][2], gi, 2);
+      mfma_op(f[gi & 1][3], gi, 3);
+    }
+    if ((tile_of(0) + 1) * C::kKeys > p.n_k) mask_tail(tile_of(0));
+    float mx = tile_max(s_acc);
+    if (mx == -INFINITY && tile_of(0) * C::kKeys >= p.n_k) mx = -1e30f;
+#pragma unroll
+    for (int kb = 0; kb < NK; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s_acc[kb][i] -= mx;
+    set_shift(-mx);
+  }
+  if (half_b) wg_barrier();  // waves 4-7 run one phase behind waves 0-3
+
+  // ---- one tile: vector phase (softmax of S(i)), barrier, matrix phase (copies of V(i+1) and K(i+3),
+  // S(i+1), then O += P(i) V(i)), barrier ahead of the last MFMA.
+  // What moves on from tile to tile (LDS offsets of the operands, slots and steps of the copies) is
+  // updated in the gaps between the MFMAs: in the vector phase, the longer one for 32-key tiles, the
+  // same instructions cost 0.1 us per iteration.
+  constexpr int kPerGroup = 2 * C::kCopies / (4 * NK);  // copies started per group of MFMAs
+  int k_slot = 0;                                       // slot of the K operands of the next S
+  int k_move = C::kTile, v_move = C::kTile;
+  auto next_k_slot = [&]() __attribute__((always_inline)) {
+    k_slot = k_slot == 2 ? 0 : k_slot + 1;
+    k_move = k_slot == 2 ? -2 * C::kTile : C::kTile;
+  };
+  int next_fresh = 1;
+  uint64_t next_step = 0;
+  auto plan_copies = [&](int i) __attribute__((always_inline)) {
+    asm volatile("" : "+s"(i));  // (where it stands, not earlier)
+    next_fresh = !ix::group_steady(runs, i);
+    next_step = ix::group_step(runs, i);
+  };
+  // Behind the third MFMA of group gi.
+  auto chores = [&](int gi, int i) __attribute__((always_inline)) {
+    if (gi == 0) plan_copies(i + 1);
+    if (gi == 2 * NK - 1) {  // all K operands are on their way
+#pragma unroll
+      for (int s = 0; s < 8; ++s) k_off[s] += k_move;
+    }
+    if (gi == 2 * NK) {  // so are the copies of V
+      next_k_slot();
+      v_dst = v_dst_sum - v_dst;
+    }
+    if (gi == 4 * NK - 1) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v_off[u] += v_move;
+      v_move = -v_move;
+      k_dst = k_dst == k_dst0 + 2 * C::kTile ? k_dst0 : k_dst + C::kTile;
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < 8; ++s) k_off[s] += k_move;
+  next_k_slot();
+  plan_copies(0);
+#pragma unroll 1
+  for (int i = 0; i + 1 < n_it; ++i) {
+    uint64_t step = next_step;
+    const int fresh = next_fresh;  // this iteration's copies need fresh pointers
+    if (__builtin_expect(fresh, 0)) {
+      asm volatile("" ::: "memory");  // a real branch: keep this arithmetic off the fast path
+      set_k_ptrs(tile_of(i + 3));
+      set_v_ptrs(tile_of(i + 1));
+      step = 0;
+    }
+    softmax_tile();
+    asm volatile("" : "+v"(s_init));
+#pragma unroll
+    for (int a = 0; a < 4; ++a) read_op(f[0][a], 0, a);
+#pragma unroll
+    for (int j = 0; j < 2 * NK; ++j) asm volatile("" : "+v"(pf[j]));
+    asm volatile("" : "+v"(l_run));
+    wait_vmcnt0();  // the copies started in the previous matrix phase have landed
+    wg_barrier();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int gi = 0; gi < 4 * NK; ++gi) {
+      run_group(gi, gi + 1 < 4 * NK);
+#pragma unroll
+      for (int c = gi * kPerGroup; c < (gi + 1) * kPerGroup; ++c) {
+        constexpr int n = C::kCopies;
+        if (c < n)
+          v_ptr[c] = dma16_step(v_ptr[c], step, v_dst + c * R * 1024);
+        else
+          k_ptr[c - n] = dma16_step(k_ptr[c - n], step, k_dst + (c - n) * R * 1024);
+      }
+      SDVG_SB();
+      mfma_op(f[gi & 1][2], gi, 2);
+      SDVG_SB();
+      chores(gi, i);
+      SDVG_SB();
+      if (gi + 1 < 4 * NK) mfma_op(f[gi & 1][3], gi, 3);
+      SDVG_SB();
+      if (gi == 2 * NK - 1 && __builtin_expect(fresh, 0)) {
+        if ((tile_of(i + 1) + 1) * C::kKeys > p.n_k) mask_tail(tile_of(i + 1));
+      }
+    }
+    __builtin_amdgcn_s_setprio(2);
+    wg_barrier();
+    SDVG_SB();
+    mfma_op(f[1][3], 4 * NK - 1, 3);
+    SDVG_SB();
+    __builtin_amdgcn_s_setprio(0);
+  }
+  // ---- the last tile: nothing left to copy and no next S
+  softmax_tile();
+#pragma unroll
+  for (int j = 0; j < 2 * NK; ++j) asm volatile("" : "+v"(pf[j]));
+  wait_vmcnt0();
+  wg_barrier();
+#pragma unroll
+  for (int a = 0; a < 4; ++a) read_op(f[0][a], 2 * NK, a);
+#pragma unroll
+  for (int gi = 2 * NK; gi < 4 * NK; ++gi) {
+    run_group(gi, gi + 1 < 4 * NK);
+    mfma_op(f[gi & 1][2], gi, 2);
+    mfma_op(f[gi & 1][3], gi, 3);
+  }
+  wg_barrier();
+  if (!half_b) wg_barrier();  // pairs with the extra barrier of waves 4-7: all LDS reads are done
+
+  // ---- merge: every wave leaves its O, row sum and shift in LDS and combines a 1 / G share of the
+  // dims of its rows over the groups: with m the largest running maximum,
+  //   O = sum_g 2^((m_g - m) scale*log2e) O_g, l likewise.
+  float *mg = reinterpret_cast<float *>(smem);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 o4 = {o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
+      *reinterpret_cast<f32x4 *>(mg + ((wave * 16 + 4 * u + g) * 64 + lane) * 4) = o4;
+    }
+  float *ml = mg + kMergeOFloats;
+  ml[(wave * 2) * 64 + lane] = l_run;
+  ml[(wave * 2 + 1) * 64 + lane] = s_shift;
+  __syncthreads();
+  if (wr >= wt_count) return;
+  float shift_min = ml[(wr * 2 + 1) * 64 + lane];
+#pragma unroll
+  for (int g = 1; g < G; ++g) shift_min = fminf(shift_min, ml[((g * R + wr) * 2 + 1) * 64 + lane]);
+  float factor[G], l_sum = 0.f;
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int w = g * R + wr;
+    factor[g] = __builtin_amdgcn_exp2f((shift_min - ml[(w * 2 + 1) * 64 + lane]) * p.scale_log2e);
+    l_sum += factor[g] * ml[(w * 2) * 64 + lane];
+  }
+  const float inv_l = 1.0f / lane_sum32(l_sum);
+  if (q_row >= p.n_q) return;
+  uint16_t *op = static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 4 * hh;
+#pragma unroll
+  for (int k = 0; k < 16 / G; ++k) {
+    const int q4 = grp * (16 / G) + k;  // dims 8 q4 + 4 hh .. + 3
+    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const f32x4 part = *reinterpret_cast<const f32x4 *>(mg + (((g * R + wr) * 16 + q4) * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o4[e] += factor[g] * part[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o4[e] *= inv_l;
+    *reinterpret_cast<bf16x4 *>(op + 8 * q4) = __builtin_convertvector(o4, bf16x4);
+  }
+}
+
+template <int G>
+constexpr size_t lds_bytes() {
+  return G * ix::Groups<G>::kGroup > kMergeBytes ? G * ix::Groups<G>::kGroup : kMergeBytes;
+}
+
+}  // namespace
+
+namespace sdvg {
+
+hipError_t prepare_block_attn_groups() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_groups_kernel<2>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<2>());
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_groups_kernel<4>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<4>());
+}
+
+int launch_block_attn_groups(const AttnParams &p, int groups, hipStream_t s) {
+  const dim3 grid(8 * p.work_per_xcd + p.n_copy_blocks);
+  if (groups == 2)
+    hipLaunchKernelGGL(block_attn_groups_kernel<2>, grid, dim3(512), lds_bytes<2>(), s, p);
+  else
+    hipLaunchKernelGGL(block_attn_groups_kernel<4>, grid, dim3(512), lds_bytes<4>(), s, p);
+  SDVG_HIP_CHECK(hipGetLastError());
+  return SDVG_OK;
+}
+
+}  // namespace sdvg

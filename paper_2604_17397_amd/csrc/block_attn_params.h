@@ -36,4 +36,9 @@ constexpr int64_t kPartialFloats = 8 * 66 * 64;
 // fp32 check path (block_attn_f32.hip): same mathematics, fp32 inputs / P / output; item 0 only.
 int launch_block_attn_f32(const AttnParams &p, hipStream_t stream);
 
+// Kernel for few query rows (block_attn_groups.hip): `groups` (2 or 4) key groups per workgroup.
+// p.n_qtiles / p.n_tiles count its own tiles (256 / groups query rows; 64 keys for 2 groups, 32 for 4).
+hipError_t prepare_block_attn_groups();  // once per device: raises the dynamic-LDS limit
+int launch_block_attn_groups(const AttnParams &p, int groups, hipStream_t stream);
+
 }  // namespace sdvg

@@ -1,0 +1,160 @@
+// Host replay of the grouped attention kernel's copy schedule, from the index header the kernel
+// compiles in. For every configuration all 8 waves x 64 lanes perform the copies of
+// block_attn_groups.hip in its order with fake base addresses; at each point of use K slot / V slot
+// of every group must hold exactly the keys of that group's tile (clamped at the last key) with the
+// swizzle the reads undo, no copy may address a token at or past c_len in the cache or at or past
+// n_blk in the block, and every LDS address stays inside the workgroup's part. Exit code 0 = passed.
+#include <cstdint>
+#include <cstdio>
+#include <vector>
+
+#include "block_attn_groups_index.h"
+
+namespace ix = sdvg::attn_index;
+
+namespace {
+
+constexpr uint64_t kSpan = uint64_t{1} << 44;
+const char *const kBase = reinterpret_cast<const char *>(uint64_t{1} << 48);
+
+template <int G>
+struct Replay {
+  using C = ix::Groups<G>;
+  ix::Streams s;
+  int n_blk = 0;
+  struct Cell {
+    int v, key, chunk;
+  };
+  std::vector<Cell> lds = std::vector<Cell>(G * C::kGroup / 16, Cell{-1, -1, -1});
+  const char *error = nullptr;
+
+  bool put(const char *src, uint32_t dst, int is_v) {
+    const uint64_t all = static_cast<uint64_t>(src - kBase);
+    const int region = static_cast<int>(all / kSpan);
+    if (region < 0 || region > 3 || (region & 1) != is_v) return error = "source in the wrong tensor", false;
+    const bool blk = region >= 2;
+    const uint32_t pitch = blk ? s.blk_tsb : s.kv_tsb;
+    const uint64_t tok = all % kSpan / pitch, inner = all % kSpan % pitch;
+    if (inner >= 256 || inner % 16 || tok >= static_cast<uint64_t>(blk ? n_blk : s.c_len))
+      return error = "source out of bounds", false;
+    if (dst % 16 || dst / 16 >= lds.size()) return error = "destination out of bounds", false;
+    lds[dst / 16] = Cell{is_v, static_cast<int>(blk ? s.c_len + tok : tok), static_cast<int>(inner / 16)};
+    return true;
+  }
+
+  // The lanes' copy pointers of one group, for K or for V: fresh or stepped, as the kernel does it.
+  struct Ptrs {
+    const char *p[C::kRowWaves][64][C::kCopies];
+  };
+  void set(Ptrs &x, int t, int is_v) {
+    for (int wr = 0; wr < C::kRowWaves; ++wr)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int u = 0; u < C::kCopies; ++u) {
+          const int variant = is_v ? 0 : u % C::kVariants;
+          const ix::LaneBase b = ix::group_lane_base(s, ix::group_copy_row<G>(wr, lane, variant), lane, is_v);
+          x.p[wr][lane][u] = ix::group_key_ptr(
+              s, b, t * C::kKeys + 4 * C::kRowWaves * u + ix::group_copy_row<G>(wr, lane, 0));
+        }
+  }
+  bool copy(Ptrs &x, uint64_t step, int grp, int is_v, int slot) {
+    for (int wr = 0; wr < C::kRowWaves; ++wr)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int u = 0; u < C::kCopies; ++u) {
+          x.p[wr][lane][u] += step;
+          if (!put(x.p[wr][lane][u], ix::group_copy_dst<G>(grp, wr, u, slot, is_v) + 16 * lane, is_v)) return false;
+        }
+    return true;
+  }
+
+  // Reads the tile exactly as the matrix phase does (every operand of every lane).
+  bool check(int grp, int is_v, int t, int slot) {
+    for (int lane = 0; lane < 64; ++lane) {
+      const int r32 = lane & 31, hh = lane >> 5, i16 = lane & 15, b16 = (lane >> 4) & 1;
+      const int base = grp * C::kGroup + is_v * C::kVSlots + slot * C::kTile;
+      auto want = [&](int off, int row, int byte_in_row) {
+        const int jr = t * C::kKeys + row, j = jr < s.n_k ? jr : s.n_k - 1;
+        const Cell &c = lds[(base + off) / 16];
+        if (c.v == is_v && c.key == j && c.chunk == byte_in_row / 16 && (base + off) % 16 == byte_in_row % 16) return true;
+        error = is_v ? "V tile holds the wrong rows" : "K tile holds the wrong rows";
+        return false;
+      };
+      if (!is_v) {
+        for (int sd = 0; sd < 8; ++sd)
+          for (int kb = 0; kb < C::kHalves; ++kb)
+            if (!want(ix::k_read_offset(lane, sd, 0) + kb * 32 * 256, 32 * kb + r32, (2 * sd + hh) * 16)) return false;
+      } else {
+        for (int j = 0; j < 2 * C::kHalves; ++j)
+          for (int db = 0; db < 4; ++db)
+            for (int hi = 0; hi < 2; ++hi)
+              if (!want(ix::v_read_offset(lane, 0, db, 0) + j * 16 * 256 + hi * 8 * 256,
+                        16 * j + 8 * hi + 4 * hh + (i16 >> 2), 64 * db + 32 * b16 + 8 * (i16 & 3)))
+                return false;
+      }
+    }
+    return true;
+  }
+
+  bool run(int c_len, int nb, uint32_t kv_tsb, uint32_t blk_tsb) {
+    s = ix::Streams{kBase, kBase + kSpan, kBase + 2 * kSpan, kBase + 3 * kSpan, kv_tsb, blk_tsb, c_len, c_len + nb};
+    n_blk = nb;
+    const int n_tiles = (s.n_k + C::kKeys - 1) / C::kKeys, n_it = (n_tiles + G - 1) / G;
+    std::vector<char> seen(n_tiles, 0);
+    for (int g = 0; g < G; ++g) {
+      auto tile_of = [&](int i) { return g + G * i; };
+      Ptrs k, v;
+      for (int i = 0; i < 3; ++i) {
+        set(k, tile_of(i), 0);
+        if (!copy(k, 0, g, 0, i)) return false;
+      }
+      set(v, tile_of(0), 1);
+      if (!copy(v, 0, g, 1, 0) || !check(g, 0, tile_of(0), 0)) return false;
+      const ix::GroupRuns runs = ix::group_runs<G>(s, g);
+      for (int i = 0; i < n_it; ++i) {
+        uint64_t step = ix::group_step(runs, i);
+        const bool fresh = !ix::group_steady(runs, i);
+        if (fresh) {
+          set(k, tile_of(i + 3), 0);
+          set(v, tile_of(i + 1), 1);
+          step = 0;
+        }
+        if (!fresh && (tile_of(i + 1) + 1) * C::kKeys > s.n_k) return error = "a tile that needs the mask is not fresh", false;
+        // matrix phase i reads K(i+1) and V(i); its copies of V(i+1) and K(i+3) land at any time in it
+        for (int late = 0; late < 2; ++late) {
+          if (late && i + 1 < n_it && (!copy(v, step, g, 1, (i + 1) % 2) || !copy(k, step, g, 0, i % 3))) return false;
+          if (i + 1 < n_it && !check(g, 0, tile_of(i + 1), (i + 1) % 3)) return false;
+          if (!check(g, 1, tile_of(i), i % 2)) return false;
+        }
+        if (tile_of(i) < n_tiles) seen[tile_of(i)]++;
+      }
+    }
+    for (char c : seen)
+      if (c != 1) return error = "a tile is not handled exactly once", false;
+    return true;
+  }
+};
+
+template <int G>
+long sweep(int &bad) {
+  long n = 0;
+  auto one = [&](int c, int nb, uint32_t kv, uint32_t bl) {
+    Replay<G> r;
+    if (!r.run(c, nb, kv, bl) && !bad++) std::printf("FAIL G=%d c_len=%d n_blk=%d: %s\n", G, c, nb, r.error);
+    ++n;
+  };
+  for (int c = 0; c < 200; c += (c < 70 ? 1 : 7))
+    for (int nb : {1, 2, 31, 32, 33, 63, 64, 65, 95, 97, 128, 129, 200, 312}) one(c, nb, 40 * 256, 12 * 256);
+  for (int k : {0, 1, 6})
+    for (int nb : {312, 1031, 4680}) one(k * nb, nb, 12 * 256, 256);
+  one(100, 100, 0xfffffff0u / 16 * 8, 0x7ffffff0u);  // the largest pitches
+  return n;
+}
+
+}  // namespace
+
+int main() {
+  int bad = 0;
+  const long n = sweep<2>(bad) + sweep<4>(bad);
+  if (bad) return 1;
+  std::printf("ok: %ld configurations\n", n);
+  return 0;
+}
