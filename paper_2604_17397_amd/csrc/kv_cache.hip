@@ -1,6 +1,7 @@
 // KV-cache commit and rollback: bandwidth-bound copy / zero-fill kernels, one launch for all
 // layers and for both K and V. Paper Sec. 3 "Inference flow": an accepted draft is committed
 // to the target's KV cache; a rejected one must leave no trace before the target regenerates.
+#include "row_map.h"
 #include "sdvg_common.h"
 
 namespace {
@@ -8,23 +9,6 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;  // one 16-byte chunk
 
 constexpr int kThreads = 256;
-
-struct RowMap {   // maps a (layer, token, head) row of 128 bf16 = 16 chunks into the cache
-  int64_t layer_stride, token_stride, head_stride;  // elements
-  int64_t first_token;                              // first destination token
-  int32_t n_tokens, n_heads;
-};
-
-// Destination element offset of 16-byte chunk g of the dense [L][n_tokens][H][128] index space.
-__device__ __forceinline__ int64_t dst_offset(const RowMap &m, int64_t g) {
-  const int64_t row = g >> 4;
-  const int c = static_cast<int>(g & 15);
-  const int64_t lt = row / m.n_heads;
-  const int h = static_cast<int>(row - lt * m.n_heads);
-  const int64_t l = lt / m.n_tokens;
-  const int64_t t = lt - l * m.n_tokens;
-  return l * m.layer_stride + (m.first_token + t) * m.token_stride + h * m.head_stride + c * 8;
-}
 
 // Contiguous fast path: every layer's destination range is one dense run of chunks_per_layer
 // chunks (token-major cache with head_stride == 128, token_stride == H*128).
@@ -43,16 +27,21 @@ __global__ __launch_bounds__(kThreads) void kv_commit_dense_kernel(
   __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
 }
 
-// General strides: one 16-byte chunk per thread per trip, destination computed per chunk.
+// General strides: one 16-byte chunk per thread, rows in the order of their destinations (RowMap).
+// On a head-major cache (30 layers x 12 heads x 1560 tokens, 575 MB moved) 99.5 us = 5.8 TB/s. With
+// the rows in the order of the source 103.6, with ordinary stores 113.6, and with 64-bit divisions
+// and a loop over chunks 111.
 __global__ __launch_bounds__(kThreads) void kv_commit_strided_kernel(
-    const u32x4 *__restrict__ k_src, const u32x4 *__restrict__ v_src, uint16_t *__restrict__ k_dst,
-    uint16_t *__restrict__ v_dst, RowMap m, int64_t total_chunks) {
-  const u32x4 *src = blockIdx.y == 0 ? k_src : v_src;
-  uint16_t *dst = blockIdx.y == 0 ? k_dst : v_dst;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
-  for (int64_t g = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; g < total_chunks;
-       g += stride)
-    *reinterpret_cast<u32x4 *>(dst + dst_offset(m, g)) = __builtin_nontemporal_load(src + g);
+    const uint16_t *__restrict__ k_src, const uint16_t *__restrict__ v_src, uint16_t *__restrict__ k_dst,
+    uint16_t *__restrict__ v_dst, sdvg::RowMap m, uint32_t n_rows) {
+  const uint32_t r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+  if (r >= n_rows) return;
+  const int ch = (threadIdx.x & 15) * 8;
+  const sdvg::RowMap::Row row = m.row(r);
+  const uint16_t *src = (blockIdx.y == 0 ? k_src : v_src) + m.src(row) + ch;
+  uint16_t *dst = (blockIdx.y == 0 ? k_dst : v_dst) + m.dst(row) + ch;
+  __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src)),
+                              reinterpret_cast<u32x4 *>(dst));
 }
 
 __global__ __launch_bounds__(kThreads) void kv_zero_dense_kernel(
@@ -67,14 +56,13 @@ __global__ __launch_bounds__(kThreads) void kv_zero_dense_kernel(
 }
 
 __global__ __launch_bounds__(kThreads) void kv_zero_strided_kernel(uint16_t *__restrict__ k_dst,
-                                                                   uint16_t *__restrict__ v_dst,
-                                                                   RowMap m, int64_t total_chunks) {
-  uint16_t *dst = blockIdx.y == 0 ? k_dst : v_dst;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+                                                                   uint16_t *__restrict__ v_dst, sdvg::RowMap m,
+                                                                   uint32_t n_rows) {
+  const uint32_t r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+  if (r >= n_rows) return;
+  uint16_t *dst = (blockIdx.y == 0 ? k_dst : v_dst) + m.dst(m.row(r)) + (threadIdx.x & 15) * 8;
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int64_t g = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; g < total_chunks;
-       g += stride)
-    *reinterpret_cast<u32x4 *>(dst + dst_offset(m, g)) = zero;
+  __builtin_nontemporal_store(zero, reinterpret_cast<u32x4 *>(dst));
 }
 
 // Plain device-to-device copy of an opaque buffer: 16-byte chunks, one per thread; the thread
@@ -134,6 +122,9 @@ dim3 dense_grid(int64_t chunks_per_layer, int n_layers) {
   return dim3(static_cast<unsigned>((chunks_per_layer + kThreads - 1) / kThreads), n_layers, 2);
 }
 
+// grid.x of the strided kernels: 16 rows of 256 bytes per workgroup.
+unsigned row_blocks(int64_t n_rows) { return static_cast<unsigned>((n_rows + kThreads / 16 - 1) / (kThreads / 16)); }
+
 }  // namespace
 
 namespace sdvg {
@@ -174,14 +165,13 @@ extern "C" int sdvg_kv_commit(sdvg_kv_cache *cache, const void *k_blk, const voi
                        static_cast<u32x4 *>(cache->v), chunks_per_layer, cache->layer_stride / 8,
                        slot * T * cache->token_stride / 8);
   } else {
-    RowMap m{cache->layer_stride, cache->token_stride, cache->head_stride, slot * T,
-             static_cast<int32_t>(T), cache->n_heads};
-    const int64_t total = chunks_per_layer * cache->n_layers;
-    const int64_t blocks = (total + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(kv_commit_strided_kernel, dim3(static_cast<unsigned>(blocks), 2),
-                       dim3(kThreads), 0, s, static_cast<const u32x4 *>(k_blk),
-                       static_cast<const u32x4 *>(v_blk), static_cast<uint16_t *>(cache->k),
-                       static_cast<uint16_t *>(cache->v), m, total);
+    const int64_t n_rows = T * cache->n_heads * cache->n_layers, first = slot * T * cache->token_stride;
+    if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(kv_commit_strided_kernel, dim3(row_blocks(n_rows), 2), dim3(kThreads), 0, s,
+                       static_cast<const uint16_t *>(k_blk), static_cast<const uint16_t *>(v_blk),
+                       static_cast<uint16_t *>(cache->k) + first, static_cast<uint16_t *>(cache->v) + first,
+                       sdvg::row_map(T, cache->n_heads, cache->layer_stride, cache->token_stride, cache->head_stride),
+                       static_cast<uint32_t>(n_rows));
   }
   SDVG_HIP_CHECK(hipGetLastError());
   cache->cache_len = (slot + 1) * T;
@@ -211,13 +201,12 @@ extern "C" int sdvg_kv_rollback(sdvg_kv_cache *cache, int64_t new_len, void *str
                        static_cast<u32x4 *>(cache->v), chunks_per_layer, cache->layer_stride / 8,
                        new_len * cache->token_stride / 8);
   } else {
-    RowMap m{cache->layer_stride, cache->token_stride, cache->head_stride, new_len,
-             static_cast<int32_t>(n_tok), cache->n_heads};
-    const int64_t total = chunks_per_layer * cache->n_layers;
-    const int64_t blocks = (total + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(kv_zero_strided_kernel, dim3(static_cast<unsigned>(blocks), 2),
-                       dim3(kThreads), 0, s, static_cast<uint16_t *>(cache->k),
-                       static_cast<uint16_t *>(cache->v), m, total);
+    const int64_t n_rows = n_tok * cache->n_heads * cache->n_layers, first = new_len * cache->token_stride;
+    if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(kv_zero_strided_kernel, dim3(row_blocks(n_rows), 2), dim3(kThreads), 0, s,
+                       static_cast<uint16_t *>(cache->k) + first, static_cast<uint16_t *>(cache->v) + first,
+                       sdvg::row_map(n_tok, cache->n_heads, cache->layer_stride, cache->token_stride, cache->head_stride),
+                       static_cast<uint32_t>(n_rows));
   }
   SDVG_HIP_CHECK(hipGetLastError());
   cache->cache_len = new_len;
