@@ -1,9 +1,12 @@
 """ctypes binding of libsdvg.so. Argument marshalling only: same names as the C entry points.
 
 PyTorch tensors supply device memory (`data_ptr()`) and the HIP stream; nothing is computed
-here and there is no fallback: a missing library raises.
+here and there is no fallback: a missing library raises. The most frequent calls are marshalled by
+the extension module _native.so (csrc/host/native.cpp), which makes the same checks in C++ and
+leaves every call it does not recognise as valid to the Python code here.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
@@ -12,6 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 # SDVG_LIBRARY names another build of the same library (e.g. one with host sanitizers); there is
 # still no fallback: whatever path is named must exist.
 LIB_PATH = os.environ.get("SDVG_LIBRARY") or os.path.join(HERE, "libsdvg.so")
+
+NATIVE_PATH = os.path.join(HERE, "_native.so")
 
 SDVG_BF16, SDVG_F32 = 0, 1
 SDVG_SPLIT_NEVER, SDVG_SPLIT_AUTO, SDVG_SPLIT_ALWAYS = 0, 1, 2
@@ -99,8 +104,37 @@ def lib():
         L.sdvg_last_device_error.restype = ctypes.c_int
         L.sdvg_version.restype = ctypes.c_int
         L.sdvg_shutdown.restype = None
+        _bind_native(L)
         _LIB = L
     return _LIB
+
+
+class _PythonOnly:
+    """Stands in for the marshalling module where there is none to call: Python handles every call."""
+    block_attn = rope = route = staticmethod(lambda *args: None)
+
+
+_NATIVE = None
+
+
+def _bind_native(L):
+    """Loads the marshalling module and hands it the entry points of the loaded libsdvg.so."""
+    global _NATIVE
+    if not os.path.exists(NATIVE_PATH):
+        raise RuntimeError("_native.so is missing: build it with `python -m paper_2604_17397_amd.build`")
+    import numpy as np
+    spec = importlib.util.spec_from_file_location("_native", NATIVE_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    entry = [ctypes.cast(f, ctypes.c_void_p).value for f in
+             (L.sdvg_block_attn, L.sdvg_block_attn_commit, L.sdvg_rope, L.sdvg_worst_frame_route, L.sdvg_avg_frame_route)]
+    module.init(*entry, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, np.float32)
+    _NATIVE = module
+
+
+def _native():
+    lib()
+    return _NATIVE or _PythonOnly
 
 
 def status_string(status):
@@ -187,6 +221,12 @@ def block_attn(q, k_cache, v_cache, k_blk, v_blk, cache_len, out=None, scale=Non
     """sdvg_block_attn: q, k_blk, v_blk [tokens, heads, 128]; k_cache, v_cache one layer's
     [>= cache_len, heads, 128] (may be None when cache_len == 0). `scale=None` passes 0, which the
     library reads as 1/sqrt(head_dim). Returns out."""
+    r = (_NATIVE or _native()).block_attn(q, k_cache, v_cache, k_blk, v_blk, cache_len, out, scale,
+                                         None if stream is None else stream.cuda_stream, False)
+    if r is not None:
+        if type(r) is int:
+            raise SdvgError(r, "sdvg_block_attn")
+        return r
     cache_len = int(cache_len)
     if out is None:
         out = torch.empty(q.shape, dtype=q.dtype, device=q.device)
@@ -201,6 +241,12 @@ def block_attn(q, k_cache, v_cache, k_blk, v_blk, cache_len, out=None, scale=Non
 def block_attn_commit(q, k_cache, v_cache, k_blk, v_blk, cache_len, out=None, scale=None, stream=None):
     """sdvg_block_attn_commit: block_attn for one layer that also copies k_blk / v_blk into tokens
     [cache_len, cache_len + n_blk) of k_cache / v_cache (which must be long enough). Returns out."""
+    r = (_NATIVE or _native()).block_attn(q, k_cache, v_cache, k_blk, v_blk, cache_len, out, scale,
+                                         None if stream is None else stream.cuda_stream, True)
+    if r is not None:
+        if type(r) is int:
+            raise SdvgError(r, "sdvg_block_attn_commit")
+        return r
     cache_len = int(cache_len)
     if out is None:
         out = torch.empty(q.shape, dtype=q.dtype, device=q.device)
@@ -313,6 +359,11 @@ def _check_tables(cos, sin, n_tokens, device):
 def rope(x, cos, sin, out=None, stream=None):
     """sdvg_rope: rotary embedding of bf16 rows x [tokens, heads, 128] by the angle tables cos, sin
     float32 [tokens, 64]. out defaults to a new tensor; pass out=x for in place."""
+    r = (_NATIVE or _native()).rope(x, cos, sin, out, None if stream is None else stream.cuda_stream)
+    if r is not None:
+        if type(r) is int:
+            raise SdvgError(r, "sdvg_rope")
+        return r
     _check_dev(x, out)
     if x.dtype != torch.bfloat16 or x.dim() != 3 or x.shape[2] != 128 or x.stride(2) != 1:
         raise ValueError("x must be bfloat16 [tokens, heads, 128] with unit dim stride")
@@ -370,6 +421,13 @@ def buffer_snapshot(dst, src, n_bytes=None, stream=None):
 def worst_frame_route(frame_scores, tau, block_idx, stream=None, mode="min"):
     """sdvg_worst_frame_route (mode "min") or sdvg_avg_frame_route (mode "mean"): returns
     (decision, q_b) with q_b a numpy float32 scalar."""
+    if mode in ("min", "mean"):
+        r = (_NATIVE or _native()).route(frame_scores, tau, block_idx, mode == "mean",
+                                        None if stream is None else stream.cuda_stream)
+        if r is not None:
+            if type(r) is int:
+                raise SdvgError(r, "sdvg_worst_frame_route")
+            return r
     import numpy as np
     fn = {"min": lib().sdvg_worst_frame_route, "mean": lib().sdvg_avg_frame_route}[mode]
     _check_dev(frame_scores)

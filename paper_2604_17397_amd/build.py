@@ -1,13 +1,16 @@
-"""Compile the HIP sources under csrc/ into libsdvg.so (gfx950) next to this file."""
+"""Compile the HIP sources under csrc/ into libsdvg.so (gfx950) next to this file, and the argument
+marshalling under csrc/host/ into the extension module _native.so."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsdvg.so")
+NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -37,5 +40,28 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
     return out
 
 
+def build_native(verbose: bool = False, out: str = NATIVE) -> str:
+    import torch
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+    for path in cpp_extension.include_paths():
+        cmd += ["-isystem", path]
+    cmd += [os.path.join(CSRC, "host", "native.cpp"), "-o", out]
+    for path in cpp_extension.library_paths():
+        cmd += ["-L", path]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("native module failed to build:\n" + res.stdout)
+    if verbose and res.stdout.strip():
+        print(res.stdout)
+    return out
+
+
 if __name__ == "__main__":
     print(build(verbose=True, extra_flags=sys.argv[1:]))
+    print(build_native(verbose=True))

@@ -170,11 +170,11 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   auto read_op = [&](bf16x8 &dst, int gi, int i) __attribute__((always_inline)) {
     if (gi < 2 * NK) {
       const int s = NK == 2 ? 2 * gi + (i >> 1) : 4 * gi + i, kb = NK == 2 ? i & 1 : 0;
-      dst = *(lds_bf16x8 *)(k_off[s] + kb * 32 * 256);
+      dst = *(lds_bf16x8 *)static_cast<uintptr_t>(k_off[s] + kb * 32 * 256);
     } else {
       const uint32_t vp = v_off[i] + (gi - 2 * NK) * 16 * 256;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)vp);
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vp + 8 * 256));
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp + 8 * 256));
       const __attribute__((ext_vector_type(8))) short a16 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       __builtin_memcpy(&dst, &a16, sizeof(bf16x8));
     }
