@@ -440,41 +440,52 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
 // with m_p the running maximum of piece p (its shift, negated) and m the largest of them,
 //   O = sum_p 2^((m_p - m) scale*log2e) O_p,   l = sum_p 2^((m_p - m) scale*log2e) l_p,
 // which is the same softmax as one pass over all keys (the factors only re-base the exponentials).
-// One workgroup per query tile, threads laid out as in the attention kernel.
-__global__ __launch_bounds__(512) void block_attn_merge_kernel(const AttnParams p) {
-  const int hq = blockIdx.x;
+// One workgroup per wave tile (32 rows) of a query tile, one wave per 32 of its dims, lanes laid out
+// as in the attention kernel; the pieces are added in their order. Few heads mean few query tiles of
+// many pieces, so what bounds this kernel is the chain of loads over the pieces: it needs many waves
+// and several pieces' loads in flight. 4680 queries x 32760 keys, main kernel + merge, us per call:
+// 1 head (19 query tiles of 13 to 15 pieces) 335 -> 93, 5 heads (95 of 2 to 4) 396 -> 329, of which the
+// merge takes 11; one 8-wave workgroup per query tile took the difference longer.
+__global__ __launch_bounds__(256) void block_attn_merge_kernel(const AttnParams p) {
+  const int hq = blockIdx.x, wt = blockIdx.y;
   const int w_first = ix::first_wg_of(hq, p.n_tiles, p.units), w_last = ix::last_wg_of(hq, p.n_tiles, p.units);
   if (w_first == w_last) return;  // one workgroup had all the keys and stored the rows itself
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hh = lane >> 5;
+  const int lane = threadIdx.x & 63, hh = lane >> 5;
+  const int u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int per_item = p.n_heads * p.n_qtiles;
   const int item = hq / per_item;
   const int head = (hq - item * per_item) / p.n_qtiles;
   const int qt = hq - item * per_item - head * p.n_qtiles;
-  if (wave >= ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem)) return;
-  const int q_row = (ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem) + wave) * 32 + (lane & 31);
-  auto part_of = [&](int w) {
-    return p.partials + static_cast<int64_t>(ix::partial_slot(hq, w)) * sdvg::kPartialFloats + wave * (66 * 64) + lane;
-  };
-  float shift_min = part_of(w_first)[65 * 64];
-  for (int w = w_first + 1; w <= w_last; ++w) shift_min = fminf(shift_min, part_of(w)[65 * 64]);
-  f32x16 o_acc[4];
+  if (wt >= ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem)) return;
+  const int q_row = (ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem) + wt) * 32 + (lane & 31);
+  const float *part0 = p.partials + static_cast<int64_t>(ix::partial_slot(hq, w_first)) * sdvg::kPartialFloats +
+                       wt * (66 * 64) + lane;  // slots of neighbouring workgroups are neighbours
+  const int n_pieces = w_last - w_first + 1;
+  float shift_min = part0[65 * 64];
+#pragma unroll 8
+  for (int w = 1; w < n_pieces; ++w)
+    shift_min = fminf(shift_min, part0[static_cast<int64_t>(w) * sdvg::kPartialFloats + 65 * 64]);
+  float o_acc[16];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o_acc[u][i] = 0.f;
+  for (int i = 0; i < 16; ++i) o_acc[i] = 0.f;
   float l_run = 0.f;
-  for (int w = w_first; w <= w_last; ++w) {
-    const float *part = part_of(w);
+#pragma unroll 4
+  for (int w = 0; w < n_pieces; ++w) {
+    const float *part = part0 + static_cast<int64_t>(w) * sdvg::kPartialFloats;
     const float f = __builtin_amdgcn_exp2f((shift_min - part[65 * 64]) * p.scale_log2e);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o_acc[u][i] += f * part[(16 * u + i) * 64];
+    for (int i = 0; i < 16; ++i) o_acc[i] += f * part[(16 * u + i) * 64];
     l_run += f * part[64 * 64];
   }
   const float inv_l = 1.0f / lane_sum32(l_run);
+  if (q_row >= p.n_q) return;
   const sdvg::AttnItem it = kernarg_items()[item];
-  store_rows(p, it, head, q_row, hh, o_acc, inv_l);
+  uint16_t *op = static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 4 * hh + 32 * u;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 o4 = {o_acc[4 * g] * inv_l, o_acc[4 * g + 1] * inv_l, o_acc[4 * g + 2] * inv_l, o_acc[4 * g + 3] * inv_l};
+    *reinterpret_cast<bf16x4 *>(op + 8 * g) = __builtin_convertvector(o4, bf16x4);
+  }
 }
 
 // Workspace of sdvg_block_attn_batch_static, the entry point that may not allocate: the partial
@@ -616,7 +627,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
     hipLaunchKernelGGL(block_attn_bf16_kernel<true>, dim3(8 * p.work_per_xcd), dim3(512), lds_bytes, s, p);
   SDVG_HIP_CHECK(hipGetLastError());
   if (p.units != p.n_tiles) {
-    hipLaunchKernelGGL(block_attn_merge_kernel, dim3(p.n_hq), dim3(512), 0, s, p);
+    hipLaunchKernelGGL(block_attn_merge_kernel, dim3(p.n_hq, ix::kWaves), dim3(256), 0, s, p);
     SDVG_HIP_CHECK(hipGetLastError());
   }
   return SDVG_OK;
