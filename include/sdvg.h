@@ -134,7 +134,8 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  *             workgroups instead, so that a launch with few query tiles still fills the chip,
  *             and merge the partial results of the query tiles that were cut in a second small
  *             kernel on the same stream. SDVG_SPLIT_AUTO does so when at least 60 % of the last
- *             round of workgroups would idle (very few heads or short blocks); SDVG_SPLIT_ALWAYS
+ *             round of workgroups would idle (very few heads or short blocks) and the keys are many
+ *             enough for it to be the faster way (otherwise the workspace stays unused); SDVG_SPLIT_ALWAYS
  *             whenever the query tiles do not fill whole rounds. For the paper's own shapes the
  *             split does not pay (a 12-head drafter layer has 228 query tiles for 256 compute
  *             units; the split costs more than the 11 % it could win) and AUTO leaves them alone.

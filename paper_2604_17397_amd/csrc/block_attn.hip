@@ -539,7 +539,7 @@ int device_info(const DeviceInfo **out) {
 // partial results that a second, small kernel merges.
 struct Plan {
   int n_qtiles, n_hq, n_tiles, units, total_wg;
-  int64_t workspace_bytes;  // 0 when nothing is split
+  int64_t workspace_bytes;  // what a caller is asked for; 0 when no split was considered
   int groups;               // key groups per workgroup (1: the kernel of this file)
 };
 
@@ -552,8 +552,12 @@ struct Plan {
 //   12 x 4680 x 14040 [228/444/888] 347 / 373 / 480; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
 // A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value; the
 // model picks the fastest in each of these cases.
-int choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu) {
-  if (n_cu <= 0) return 1;
+struct Groups {
+  int groups;
+  double us;  // the estimate
+};
+Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu) {
+  if (n_cu <= 0) return Groups{1, 0};
   const struct { int groups, keys; double fixed_us, tile_us; } variants[] = {
       {1, 64, 4.0, 1.25}, {2, 64, 6.0, 1.35}, {4, 32, 6.0, 0.95}};
   int best = 1;
@@ -568,7 +572,7 @@ int choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu) {
       best_us = us;
     }
   }
-  return best;
+  return Groups{best, best_us};
 }
 
 Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode) {
@@ -582,15 +586,16 @@ Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int spl
     pl.workspace_bytes = 0;
     return pl;
   };
-  auto plain = [&]() { return unsplit(choose_groups(n_items, n_q, n_heads, n_k, n_cu)); };
+  const Groups unsplit_best = choose_groups(n_items, n_q, n_heads, n_k, n_cu);
+  auto plain = [&]() { return unsplit(unsplit_best.groups); };
   if (split_mode == SDVG_SPLIT_NEVER || n_cu <= 0) return plain();
   Plan pl = unsplit(1);
   const int rounds = (pl.n_hq + n_cu - 1) / n_cu;
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
-  // a chip that is only partly busy clocks higher. Measured on MI355X (4680 queries): 12 heads
-  // (11 % of the compute units idle) 15 % slower split than plain; 5 heads (63 % idle) 4 % faster;
-  // 2 heads (85 % idle) 83 % faster. SDVG_SPLIT_AUTO therefore splits from 60 % idle on.
+  // a chip that is only partly busy clocks higher. Measured on MI355X: 12 heads x 4680 x 14040 (11 %
+  // of the compute units idle) 17 % slower split than plain. SDVG_SPLIT_AUTO therefore considers
+  // the split from 60 % idle on, and there it competes with key groups inside the workgroup (above).
   if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
   if (split_mode == SDVG_SPLIT_AUTO && idle < 0.6) return plain();
   const int64_t all = static_cast<int64_t>(pl.n_hq) * pl.n_tiles;
@@ -599,6 +604,17 @@ Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int spl
   if (pl.units < 16) return plain();
   pl.total_wg = static_cast<int>((all + pl.units - 1) / pl.units);
   pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * sdvg::kPartialFloats * 4;
+  // Launch, merge and 1.6 us per key tile of a workgroup, against the estimate without a split. Split /
+  // key groups, us: 1 head x 4680 x 32760 93 / 184, 5 heads 329 / 363; 4 x 4680 x 14040 128 / 141,
+  // 5 heads 157 / 159; 12 x 1560 x 4680 63 / 56, 16 x 1031 x 3093 49 / 41, 3 x 4680 x 4680 55 / 44. The
+  // workspace asked for stays that of the split, so that what a caller allocates does not depend on
+  // this choice.
+  const double split_us = 32.0 + 1.6 * rounds * static_cast<double>(pl.units);
+  if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us) {
+    Plan g = plain();
+    g.workspace_bytes = pl.workspace_bytes;
+    return g;
+  }
   return pl;
 }
 

@@ -32,3 +32,21 @@ def test_merge_matches_oracle_and_unsplit(H, n_q, c_len):
     # all rows: two roundings to bf16 of the same value, of P and of the result, apart
     plain = P.block_attn(*d, c_len).float()
     assert ((out.float() - plain).norm() / plain.norm()).item() <= 2 * BF16_REL_RMS
+
+
+# AUTO between the key split and key groups inside the workgroup: many keys for few rows are split,
+# a nearly full round of workgroups with few keys is not; both ask for the split's workspace.
+@pytest.mark.parametrize("H,n_q,c_len,same_as", [(4, 33, 65500, "always"), (16, 1031, 2062, "never")])
+def test_auto_takes_the_faster_plan(H, n_q, c_len, same_as):
+    import paper_2604_17397_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, kb, vb = (torch.randn((n_q, H, 128), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    kc, vc = (torch.randn((c_len, H, 128), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    d = (q, kc, vc, kb, vb)
+    need = P.block_attn_workspace_bytes(*d, c_len, split="auto")
+    assert need == P.block_attn_workspace_bytes(*d, c_len, split="always") > 0
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    out = {m: P.block_attn_batch(*[[x] for x in d], c_len, workspace=ws, split=m)[0].view(torch.int16)
+           for m in ("never", "auto", "always")}
+    assert not torch.equal(out["never"], out["always"])
+    assert torch.equal(out["auto"], out[same_as])
