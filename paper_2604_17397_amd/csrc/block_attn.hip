@@ -604,12 +604,12 @@ Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int spl
   if (pl.units < 16) return plain();
   pl.total_wg = static_cast<int>((all + pl.units - 1) / pl.units);
   pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * sdvg::kPartialFloats * 4;
-  // Launch, merge and 1.6 us per key tile of a workgroup, against the estimate without a split. Split /
+  // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
   // key groups, us: 1 head x 4680 x 32760 93 / 184, 5 heads 329 / 363; 4 x 4680 x 14040 128 / 141,
   // 5 heads 157 / 159; 12 x 1560 x 4680 63 / 56, 16 x 1031 x 3093 49 / 41, 3 x 4680 x 4680 55 / 44. The
   // workspace asked for stays that of the split, so that what a caller allocates does not depend on
   // this choice.
-  const double split_us = 32.0 + 1.6 * rounds * static_cast<double>(pl.units);
+  const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(pl.units);
   if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us) {
     Plan g = plain();
     g.workspace_bytes = pl.workspace_bytes;
