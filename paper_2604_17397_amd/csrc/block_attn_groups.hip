@@ -246,8 +246,14 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
 
   wait_vmcnt0();
   wg_barrier();
-  // ---- S of the group's first tile; its maximum starts the running maximum. A group without a
-  // single key keeps a finite maximum far below any score, so that its share of the merge is 0.
+  // ---- S of the group's first tile. All groups start from one maximum per row, that of the first 64
+  // keys, as the 256-row kernel does: the groups' first-tile maxima meet in LDS (in V slot 1, which is
+  // first written in matrix phase 0, a barrier after the values here are read). A group that started
+  // from its own tile alone would take its shift from keys that may be masked: with -inf there is
+  // nothing to subtract, and a large negative score as the accumulators' initial value leaves no bits
+  // for the scores of the group's other tiles. If a first tile past the first 64 keys holds scores
+  // that would raise this maximum anyway (2^20, as kPSumLimit), the row starts from those; if all
+  // first tiles are masked with -inf, from 0.
   {
 #pragma unroll
     for (int i = 0; i < 4; ++i) read_op(f[0][i], 0, i);
@@ -258,8 +264,21 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       mfma_op(f[gi & 1][3], gi, 3);
     }
     if ((tile_of(0) + 1) * C::kKeys > p.n_k) mask_tail(tile_of(0));
-    float mx = tile_max(s_acc);
-    if (mx == -INFINITY && tile_of(0) * C::kKeys >= p.n_k) mx = -1e30f;
+    auto first_max = [&](int g) __attribute__((always_inline)) -> float * {
+      return reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + g * C::kGroup + C::kVSlots + C::kTile) +
+             wr * 64 + lane;
+    };
+    *first_max(grp) = tile_max(s_acc);
+    __syncthreads();
+    float mx = *first_max(0), m_all;
+#pragma unroll
+    for (int g = 1; g * C::kKeys < ix::kBN; ++g) mx = fmaxf(mx, *first_max(g));
+    m_all = mx;
+#pragma unroll
+    for (int g = ix::kBN / C::kKeys; g < G; ++g) m_all = fmaxf(m_all, *first_max(g));
+    if ((m_all - mx) * p.scale_log2e > 20.f) mx = m_all;
+    if (mx == -INFINITY) mx = 0.f;
+    asm volatile("" : "+v"(mx));  // (all reads of V slot 1 have returned)
 #pragma unroll
     for (int kb = 0; kb < NK; ++kb)
 #pragma unroll

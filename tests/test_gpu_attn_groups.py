@@ -99,3 +99,45 @@ def test_nan_and_infinite_values_reach_the_rows_that_use_them():
     nan = torch.isnan(out)
     assert nan[7, 1].all() and not nan[8:].any() and not nan[:7].any() and not nan[7, 0].any()
     assert torch.isinf(out[:, 0, 5]).all() and torch.isfinite(out[:, 0, :5]).all() and torch.isfinite(out[8:, 1]).all()
+
+
+# ---------------------------------------------------------------- masked keys, infinite values
+
+# (heads, query rows): 3 x 70 rows take 4 groups of 32-key tiles at 936 keys, 36 x 449 rows 2 of 64
+SHAPES = {4: (3, 70), 2: (36, 449)}
+N_K = 936
+
+
+def masked_inputs(groups, lo, hi, value, seed):
+    """Random inputs whose keys lo .. hi - 1 score `value` / sqrt(128) in every head but the first: dim 0
+    is 1 in every query and `value` in these keys, 0 in the others."""
+    H, n_q = SHAPES[groups]
+    c_len = N_K - n_q
+    q, kc, vc, kb, vb = si.attn_inputs(H, n_q, c_len, seed=seed)
+    bits = lambda x: si.f32_to_bf16_bits(np.float32([x]))[0]
+    k = np.concatenate([kc, kb])
+    q[:, :, 0], k[:, :, 0], k[lo:hi, 1:, 0] = bits(1.0), 0, bits(value)
+    return q, np.ascontiguousarray(k[:c_len]), vc, np.ascontiguousarray(k[c_len:]), vb, c_len
+
+
+# One group's first tile (4 groups: 32 keys each; 2 groups: 64), several of them, and later tiles. All
+# first tiles only with -inf: a finite maximum of them is the maximum the scores start from.
+MASKED = [(lo, hi, value) for lo, hi in [(0, 32), (32, 64), (64, 96), (96, 128), (0, 64), (64, 128), (32, 128), (0, 96),
+                                         (128, 256), (904, 936)]
+          for value in (float("-inf"), -1e9, -1e30)] + [(0, 128, float("-inf"))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups", [2, 4])
+@pytest.mark.parametrize("lo,hi,value", MASKED)
+def test_masked_first_tiles(groups, lo, hi, value):
+    """A key far below the others has weight 0 and leaves the others as they are, whichever group's tile
+    it lies in. The bounds are the bf16 path's: the shift is a score of an unmasked key, or 0."""
+    import paper_2604_17397_amd as P
+    q, kc, vc, kb, vb, c_len = masked_inputs(groups, lo, hi, value, seed=lo + hi)
+    out = P.block_attn(*(to_dev_bf16(a) for a in (q, kc, vc, kb, vb)), c_len)
+    torch.cuda.synchronize()
+    rows = sorted({0, 1, 31, 32, 63, len(q) - 1})
+    max_abs, rel = attn_errors(bits_of(out)[rows], oracle.block_attn(q, kc, vc, kb, vb, c_len, rows=rows))
+    assert max_abs <= BF16_MAX_ABS and rel <= BF16_REL_RMS, (max_abs, rel)
+    assert torch.isfinite(out).all()
