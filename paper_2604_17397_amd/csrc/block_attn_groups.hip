@@ -383,13 +383,17 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   for (int j = 0; j < 2 * NK; ++j) asm volatile("" : "+v"(pf[j]));
   wait_vmcnt0();
   wg_barrier();
+  // A group that is past the last tile has only the last key's row there, with P = 0; it adds nothing,
+  // because 0 times an infinite value would be NaN.
+  if (tile_of(n_it - 1) < p.n_tiles) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a) read_op(f[0][a], 2 * NK, a);
+    for (int a = 0; a < 4; ++a) read_op(f[0][a], 2 * NK, a);
 #pragma unroll
-  for (int gi = 2 * NK; gi < 4 * NK; ++gi) {
-    run_group(gi, gi + 1 < 4 * NK);
-    mfma_op(f[gi & 1][2], gi, 2);
-    mfma_op(f[gi & 1][3], gi, 3);
+    for (int gi = 2 * NK; gi < 4 * NK; ++gi) {
+      run_group(gi, gi + 1 < 4 * NK);
+      mfma_op(f[gi & 1][2], gi, 2);
+      mfma_op(f[gi & 1][3], gi, 3);
+    }
   }
   wg_barrier();
   if (!half_b) wg_barrier();  // pairs with the extra barrier of waves 4-7: all LDS reads are done

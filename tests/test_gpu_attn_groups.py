@@ -141,3 +141,24 @@ def test_masked_first_tiles(groups, lo, hi, value):
     max_abs, rel = attn_errors(bits_of(out)[rows], oracle.block_attn(q, kc, vc, kb, vb, c_len, rows=rows))
     assert max_abs <= BF16_MAX_ABS and rel <= BF16_REL_RMS, (max_abs, rel)
     assert torch.isfinite(out).all()
+
+
+# n_k is a whole number of tiles but not of rounds of groups: 10 tiles of 32 keys, 15 of 64
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups,n_k", [(4, 320), (4, 352), (2, 960)])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_infinite_value_in_the_last_key(groups, n_k, value):
+    """The last key's value row is also what a group past the last tile has in hand; its weight there is
+    no key's weight, and 0 * inf is not part of any row."""
+    import paper_2604_17397_amd as P
+    H, n_q = SHAPES[groups]
+    c_len = n_k - n_q
+    q, kc, vc, kb, vb = si.attn_inputs(H, n_q, c_len, seed=n_k)
+    dev = [to_dev_bf16(a) for a in (q, kc, vc, kb, vb)]
+    plain = P.block_attn(*dev, c_len)
+    dev[4][-1, 0, 5] = value
+    out = P.block_attn(*dev, c_len)
+    torch.cuda.synchronize()
+    want = plain.clone()
+    want[:, 0, 5] = value
+    assert torch.equal(torch.nan_to_num(out, 1.5, 2.5, 3.5), torch.nan_to_num(want, 1.5, 2.5, 3.5))
