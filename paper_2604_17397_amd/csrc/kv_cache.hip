@@ -31,10 +31,10 @@ __global__ __launch_bounds__(kThreads) void kv_commit_dense_kernel(
 // On a head-major cache (30 layers x 12 heads x 1560 tokens, 575 MB moved) 99.5 us = 5.8 TB/s. With
 // the rows in the order of the source 103.6, with ordinary stores 113.6, and with 64-bit divisions
 // and a loop over chunks 111.
-__global__ __launch_bounds__(kThreads) void kv_commit_strided_kernel(
+__global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_strided_kernel(
     const uint16_t *__restrict__ k_src, const uint16_t *__restrict__ v_src, uint16_t *__restrict__ k_dst,
     uint16_t *__restrict__ v_dst, sdvg::RowMap m, uint32_t n_rows) {
-  const uint32_t r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+  const uint32_t r = sdvg::row_of(blockIdx.x, blockIdx.z, threadIdx.x);
   if (r >= n_rows) return;
   const int ch = (threadIdx.x & 15) * 8;
   const sdvg::RowMap::Row row = m.row(r);
@@ -55,10 +55,9 @@ __global__ __launch_bounds__(kThreads) void kv_zero_dense_kernel(
   __builtin_nontemporal_store(zero, dst + i);
 }
 
-__global__ __launch_bounds__(kThreads) void kv_zero_strided_kernel(uint16_t *__restrict__ k_dst,
-                                                                   uint16_t *__restrict__ v_dst, sdvg::RowMap m,
-                                                                   uint32_t n_rows) {
-  const uint32_t r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+__global__ __launch_bounds__(sdvg::kRowThreads) void kv_zero_strided_kernel(
+    uint16_t *__restrict__ k_dst, uint16_t *__restrict__ v_dst, sdvg::RowMap m, uint32_t n_rows) {
+  const uint32_t r = sdvg::row_of(blockIdx.x, blockIdx.z, threadIdx.x);
   if (r >= n_rows) return;
   uint16_t *dst = (blockIdx.y == 0 ? k_dst : v_dst) + m.dst(m.row(r)) + (threadIdx.x & 15) * 8;
   const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -122,8 +121,11 @@ dim3 dense_grid(int64_t chunks_per_layer, int n_layers) {
   return dim3(static_cast<unsigned>((chunks_per_layer + kThreads - 1) / kThreads), n_layers, 2);
 }
 
-// grid.x of the strided kernels: 16 rows of 256 bytes per workgroup.
-unsigned row_blocks(int64_t n_rows) { return static_cast<unsigned>((n_rows + kThreads / 16 - 1) / (kThreads / 16)); }
+// Grid of the strided kernels; y selects K or V.
+dim3 row_launch(int64_t n_rows) {
+  const sdvg::RowGrid g = sdvg::row_grid(n_rows);
+  return dim3(g.x, 2, g.z);
+}
 
 }  // namespace
 
@@ -167,7 +169,7 @@ extern "C" int sdvg_kv_commit(sdvg_kv_cache *cache, const void *k_blk, const voi
   } else {
     const int64_t n_rows = T * cache->n_heads * cache->n_layers, first = slot * T * cache->token_stride;
     if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(kv_commit_strided_kernel, dim3(row_blocks(n_rows), 2), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(kv_commit_strided_kernel, row_launch(n_rows), dim3(sdvg::kRowThreads), 0, s,
                        static_cast<const uint16_t *>(k_blk), static_cast<const uint16_t *>(v_blk),
                        static_cast<uint16_t *>(cache->k) + first, static_cast<uint16_t *>(cache->v) + first,
                        sdvg::row_map(T, cache->n_heads, cache->layer_stride, cache->token_stride, cache->head_stride),
@@ -203,7 +205,7 @@ extern "C" int sdvg_kv_rollback(sdvg_kv_cache *cache, int64_t new_len, void *str
   } else {
     const int64_t n_rows = n_tok * cache->n_heads * cache->n_layers, first = new_len * cache->token_stride;
     if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(kv_zero_strided_kernel, dim3(row_blocks(n_rows), 2), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(kv_zero_strided_kernel, row_launch(n_rows), dim3(sdvg::kRowThreads), 0, s,
                        static_cast<uint16_t *>(cache->k) + first, static_cast<uint16_t *>(cache->v) + first,
                        sdvg::row_map(n_tok, cache->n_heads, cache->layer_stride, cache->token_stride, cache->head_stride),
                        static_cast<uint32_t>(n_rows));

@@ -22,8 +22,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-constexpr int kThreads = 256;
-
 // Rotates the four pairs held in one 16-byte chunk (8 bf16) by the angles (c[i], s[i]).
 __device__ __forceinline__ u32x4 rotate_chunk(u32x4 x, f32x4 c, f32x4 s) {
   u32x4 y;
@@ -43,11 +41,10 @@ __device__ __forceinline__ u32x4 rotate_chunk(u32x4 x, f32x4 c, f32x4 s) {
 // One 16-byte chunk per thread: row r = token * n_heads + head. HBM bound: q of a target layer (48 MB
 // in, 48 MB out) takes 17.1 us; with ordinary stores, which displace what is still to be read, 19.6
 // (with a nontemporal load as well: 19.0).
-__global__ __launch_bounds__(kThreads) void rope_kernel(const uint16_t *__restrict__ x, const float *__restrict__ cos_t,
-                                                        const float *__restrict__ sin_t, uint16_t *out,
-                                                        uint32_t n_rows, sdvg::FastDiv heads, int64_t x_ts, int64_t x_hs,
-                                                        int64_t o_ts, int64_t o_hs) {
-  const uint32_t r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+__global__ __launch_bounds__(sdvg::kRowThreads) void rope_kernel(
+    const uint16_t *__restrict__ x, const float *__restrict__ cos_t, const float *__restrict__ sin_t, uint16_t *out,
+    uint32_t n_rows, sdvg::FastDiv heads, int64_t x_ts, int64_t x_hs, int64_t o_ts, int64_t o_hs) {
+  const uint32_t r = sdvg::row_of(blockIdx.x, blockIdx.z, threadIdx.x);
   if (r >= n_rows) return;
   const int ch = threadIdx.x & 15;
   const uint32_t tok = heads.div(r), head = r - tok * heads.d;
@@ -62,11 +59,11 @@ __global__ __launch_bounds__(kThreads) void rope_kernel(const uint16_t *__restri
 // of their destinations (RowMap). Source dense [L][T][H][128]. The drafter's commit (30 layers x 4680
 // tokens x 12 heads): 268 us = 6.45 TB/s, the rate of the plain commit; with a 64-bit division per
 // thread to find its row it was bound by the vector units: 287 us.
-__global__ __launch_bounds__(kThreads) void kv_commit_rope_kernel(
+__global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_rope_kernel(
     const uint16_t *__restrict__ k_src, const uint16_t *__restrict__ v_src, uint16_t *__restrict__ k_dst,
     uint16_t *__restrict__ v_dst, const float *__restrict__ cos_t, const float *__restrict__ sin_t, sdvg::RowMap m,
     uint32_t n_rows) {
-  const uint32_t r = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+  const uint32_t r = sdvg::row_of(blockIdx.x, blockIdx.z, threadIdx.x);
   if (r >= n_rows) return;
   const bool is_v = blockIdx.y != 0;
   const int ch = threadIdx.x & 15;
@@ -99,19 +96,14 @@ extern "C" int sdvg_rope(const void *x, const float *cos_table, const float *sin
                : SDVG_ERR_ALIGN;
   if (!sdvg::aligned16(x) || !sdvg::aligned16(out) || !sdvg::aligned16(cos_table) || !sdvg::aligned16(sin_table))
     return SDVG_ERR_ALIGN;
-  if ((n_tokens * n_heads * 16 + kThreads - 1) / kThreads > 0x7FFFFFFF) return SDVG_ERR_UNSUPPORTED;
-  // the kernel numbers rows in 31 bits: more than that go in several launches
-  const int64_t per_launch = (sdvg::kMaxRows - 1) / n_heads;
-  const sdvg::FastDiv heads = sdvg::FastDiv::of(n_heads);
-  for (int64_t t0 = 0; t0 < n_tokens; t0 += per_launch) {
-    const int64_t n_rows = (n_tokens - t0 < per_launch ? n_tokens - t0 : per_launch) * n_heads;
-    hipLaunchKernelGGL(rope_kernel, dim3(static_cast<unsigned>((n_rows + kThreads / 16 - 1) / (kThreads / 16))),
-                       dim3(kThreads), 0, static_cast<hipStream_t>(stream),
-                       static_cast<const uint16_t *>(x) + t0 * x_token_stride, cos_table + t0 * 64, sin_table + t0 * 64,
-                       static_cast<uint16_t *>(out) + t0 * out_token_stride, static_cast<uint32_t>(n_rows), heads,
-                       x_token_stride, x_head_stride, out_token_stride, out_head_stride);
-    SDVG_HIP_CHECK(hipGetLastError());
-  }
+  if (n_tokens > (sdvg::kMaxRows - 1) / n_heads) return SDVG_ERR_UNSUPPORTED;
+  const int64_t n_rows = n_tokens * n_heads;
+  const sdvg::RowGrid g = sdvg::row_grid(n_rows);
+  hipLaunchKernelGGL(rope_kernel, dim3(g.x, 1, g.z), dim3(sdvg::kRowThreads), 0, static_cast<hipStream_t>(stream),
+                     static_cast<const uint16_t *>(x), cos_table, sin_table, static_cast<uint16_t *>(out),
+                     static_cast<uint32_t>(n_rows), sdvg::FastDiv::of(n_heads), x_token_stride, x_head_stride,
+                     out_token_stride, out_head_stride);
+  SDVG_HIP_CHECK(hipGetLastError());
   return SDVG_OK;
 }
 
@@ -125,8 +117,9 @@ extern "C" int sdvg_kv_commit_rope(sdvg_kv_cache *cache, const void *k_blk, cons
   const int64_t T = cache->block_tokens;
   const int64_t n_rows = T * cache->n_heads * cache->n_layers, first = slot * T * cache->token_stride;
   if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(kv_commit_rope_kernel, dim3(static_cast<unsigned>((n_rows + kThreads / 16 - 1) / (kThreads / 16)), 2),
-                     dim3(kThreads), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t *>(k_blk),
+  const sdvg::RowGrid g = sdvg::row_grid(n_rows);
+  hipLaunchKernelGGL(kv_commit_rope_kernel, dim3(g.x, 2, g.z), dim3(sdvg::kRowThreads), 0,
+                     static_cast<hipStream_t>(stream), static_cast<const uint16_t *>(k_blk),
                      static_cast<const uint16_t *>(v_blk), static_cast<uint16_t *>(cache->k) + first,
                      static_cast<uint16_t *>(cache->v) + first, cos_table, sin_table,
                      sdvg::row_map(T, cache->n_heads, cache->layer_stride, cache->token_stride, cache->head_stride),

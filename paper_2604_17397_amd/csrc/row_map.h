@@ -61,4 +61,21 @@ inline RowMap row_map(int64_t n_tokens, int64_t n_heads, int64_t layer_stride, i
 // Rows of 256 bytes beyond this many (512 GiB) do not fit the device.
 constexpr int64_t kMaxRows = int64_t{1} << 31;
 
+// Launch shape of the kernels that give a row to 16 threads. A grid dimension holds fewer than 2^32
+// threads, which is 2^28 rows (64 GiB of one tensor, which does fit the device): x takes slices of
+// kSliceRows, z counts the slices. 1 <= n_rows < kMaxRows.
+constexpr int kRowThreads = 256;
+constexpr int64_t kSliceRows = int64_t{1} << 27;
+struct RowGrid {
+  uint32_t x, z;
+};
+inline RowGrid row_grid(int64_t n_rows) {
+  const int64_t in_x = n_rows < kSliceRows ? n_rows : kSliceRows;
+  return RowGrid{static_cast<uint32_t>((in_x + kRowThreads / 16 - 1) / (kRowThreads / 16)),
+                 static_cast<uint32_t>((n_rows + kSliceRows - 1) / kSliceRows)};
+}
+SDVG_ROW_HD uint32_t row_of(uint32_t block_x, uint32_t block_z, uint32_t thread) {
+  return block_z * static_cast<uint32_t>(kSliceRows) + block_x * (kRowThreads / 16) + (thread >> 4);
+}
+
 }  // namespace sdvg

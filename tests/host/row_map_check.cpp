@@ -1,5 +1,6 @@
 // Host check of csrc/row_map.h: FastDiv against the division operator at the edges of quotients,
-// and RowMap against plain loops for token-major, head-major and padded layouts. Exit code 0 = passed.
+// RowMap against plain loops for token-major, head-major and padded layouts, and the launch shape of
+// the row kernels against what a grid dimension can hold. Exit code 0 = passed.
 #include <cstdio>
 #include <vector>
 
@@ -43,6 +44,22 @@ int main() {
       if (m.dst(row) <= last) return std::printf("FAIL order\n"), 1;
       last = m.dst(row);
     }
+  }
+  // Every row below the limit is some workgroup's, and no grid dimension holds 2^32 threads.
+  const int64_t edge = int64_t{1} << 28;
+  for (int64_t n : {int64_t{1}, int64_t{16}, int64_t{17}, sdvg::kSliceRows - 1, sdvg::kSliceRows, sdvg::kSliceRows + 1, edge - 1,
+                    edge, edge + 1, 3 * edge + 5, sdvg::kMaxRows - 1}) {
+    const sdvg::RowGrid g = sdvg::row_grid(n);
+    if (g.x < 1 || g.z < 1 || uint64_t{g.x} * sdvg::kRowThreads >= uint64_t{1} << 32 || g.z > 65535)
+      return std::printf("FAIL grid of %lld rows\n", static_cast<long long>(n)), 1;
+    int64_t next = 0;  // rows come in order: each slice begins where the one before it ended
+    for (uint32_t z = 0; z < g.z; ++z) {
+      if (sdvg::row_of(0, z, 0) != next) return std::printf("FAIL first row of a slice\n"), 1;
+      next = int64_t{sdvg::row_of(g.x - 1, z, sdvg::kRowThreads - 1)} + 1;
+    }
+    if (next < n || sdvg::row_of(0, g.z - 1, 0) >= n) return std::printf("FAIL rows of %lld\n", static_cast<long long>(n)), 1;
+    for (int t : {0, 15, 16, 255})
+      if (sdvg::row_of(3, 0, t) != static_cast<uint32_t>(48 + t / 16)) return std::printf("FAIL row of a thread\n"), 1;
   }
   std::printf("ok\n");
   return 0;

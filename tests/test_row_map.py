@@ -56,3 +56,18 @@ def test_commit_and_rollback_by_layout(L, T, H, layout, rotate):
     oracle.kv_rollback(mirror, T + T // 2)
     torch.cuda.synchronize()
     assert np.array_equal(bits_of(k), mirror.k) and np.array_equal(bits_of(v), mirror.v)
+
+
+@pytest.mark.gpu
+def test_more_rows_than_a_grid_dimension_holds():
+    """2^28 rows and more are 2^32 threads and more. The rows overlap in memory (token and head stride are
+    one row), so that 17 MB hold them: all are written with the same values, and only the last row of
+    the last slice reaches the last address."""
+    import paper_2604_17397_amd as P
+    T, H = (1 << 12) + 1, 1 << 16
+    rows = torch.ones((T + H - 1, 128), dtype=torch.bfloat16, device="cuda")
+    out = torch.zeros_like(rows)
+    c, s = torch.ones((T, 64), device="cuda"), torch.zeros((T, 64), device="cuda")
+    P.rope(rows.as_strided((T, H, 128), (128, 128, 1)), c, s, out=out.as_strided((T, H, 128), (128, 128, 1)))
+    torch.cuda.synchronize()
+    assert torch.equal(out, rows)
