@@ -3,11 +3,12 @@
 PyTorch tensors supply device memory (`data_ptr()`) and the HIP stream; nothing is computed
 here and there is no fallback: a missing library raises. The most frequent calls are marshalled by
 the extension module _native.so (csrc/host/native.cpp), which makes the same checks in C++ and
-leaves every call it does not recognise as valid to the Python code here.
+leaves every call it does not recognise as valid to the Python code here, which also works alone.
 """
 import ctypes
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -110,7 +111,7 @@ def lib():
 
 
 class _PythonOnly:
-    """Stands in for the marshalling module where there is none to call: Python handles every call."""
+    """Stands in for the marshalling module where it has not been built: Python handles every call."""
     block_attn = rope = route = staticmethod(lambda *args: None)
 
 
@@ -118,10 +119,14 @@ _NATIVE = None
 
 
 def _bind_native(L):
-    """Loads the marshalling module and hands it the entry points of the loaded libsdvg.so."""
+    """Loads the marshalling module and hands it the entry points of the loaded libsdvg.so. The Python
+    code makes every call by itself, so a library built alone works too, and says that it is slower."""
     global _NATIVE
     if not os.path.exists(NATIVE_PATH):
-        raise RuntimeError("_native.so is missing: build it with `python -m paper_2604_17397_amd.build`")
+        warnings.warn("_native.so is missing, small calls take longer: build it with "
+                      "`python -m paper_2604_17397_amd.build`", RuntimeWarning, stacklevel=3)
+        _NATIVE = _PythonOnly
+        return
     import numpy as np
     spec = importlib.util.spec_from_file_location("_native", NATIVE_PATH)
     module = importlib.util.module_from_spec(spec)
@@ -134,7 +139,7 @@ def _bind_native(L):
 
 def _native():
     lib()
-    return _NATIVE or _PythonOnly
+    return _NATIVE
 
 
 def status_string(status):

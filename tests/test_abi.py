@@ -261,3 +261,19 @@ def test_missing_library_fails_loudly(P, monkeypatch):
     monkeypatch.setattr(b, "LIB_PATH", "/nonexistent/libsdvg.so")
     with pytest.raises(RuntimeError):
         b.lib()
+
+
+def test_library_without_the_marshalling_module(P, monkeypatch):
+    """The Python code makes every call by itself: a library built alone loads, with a warning."""
+    import torch
+    import paper_2604_17397_amd.binding as b
+    monkeypatch.setattr(b, "_LIB", None)
+    monkeypatch.setattr(b, "_NATIVE", None)
+    monkeypatch.setattr(b, "NATIVE_PATH", "/nonexistent/_native.so")
+    with pytest.warns(RuntimeWarning, match="_native.so"):
+        assert b.lib().sdvg_version() >= 100
+    x = torch.zeros((4, 2, 128), dtype=torch.bfloat16)
+    for call in (lambda: b.block_attn(x, None, None, x, x, 0), lambda: b.block_attn_commit(x, x, x, x, x, 0),
+                 lambda: b.rope(x, x, x), lambda: b.worst_frame_route(torch.zeros(3), 0.0, 1)):
+        with pytest.raises(ValueError):
+            call()
