@@ -22,16 +22,13 @@ struct AttnParams {
   int32_t n_blk, copy_first_block, n_copy_blocks;
   int32_t n_items, n_q, n_k, n_heads, n_qtiles;
   int32_t n_hq;       // query tiles of the launch: n_items * n_heads * n_qtiles
-  int32_t n_tiles;    // key tiles: ceil(n_k / 64)
+  int32_t n_tiles;    // key tiles: n_k / 64, rounded up (4 key groups: of 32 keys)
   int32_t units;      // (query tile, key tile) pairs per workgroup; == n_tiles when nothing is split
   int32_t total_work; // workgroups with work
   int32_t work_per_xcd;
-  int32_t wt_base, wt_rem;  // 32-row wave tiles per workgroup: wt_base, plus one for the first wt_rem
+  int32_t wt_base, wt_rem;  // 32-row wave tiles per query tile: wt_base, plus one for the first wt_rem
   float scale_log2e;  // scale * log2(e)
 };
-
-// Floats one workgroup writes per partial result: 8 waves x (64 accumulators + row sum + shift) x 64 lanes.
-constexpr int64_t kPartialFloats = 8 * 66 * 64;
 
 // fp32 check path (block_attn_f32.hip): same mathematics, fp32 inputs / P / output; item 0 only.
 int launch_block_attn_f32(const AttnParams &p, hipStream_t stream);

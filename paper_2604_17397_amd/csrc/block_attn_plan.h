@@ -1,0 +1,104 @@
+// The launch plan of the bf16 attention kernels: which kernel a call takes, and how it is cut into
+// workgroups. Host arithmetic only, from sizes and the number of compute units; the tests compile it
+// (tests/host/attn_plan.cpp) to tell which kernel each of their cases runs.
+#pragma once
+#include <stdint.h>
+
+#include "block_attn_index.h"
+#include "sdvg.h"
+
+namespace sdvg {
+
+// Floats one workgroup writes per partial result: 8 waves x (64 accumulators + row sum + shift) x 64 lanes.
+constexpr int64_t kPartialFloats = 8 * 66 * 64;
+
+constexpr int kPlanRows = 256;  // query rows of a workgroup without key groups
+
+// How a launch is cut into workgroups. Plain: one workgroup per query tile (units == n_tiles).
+// Key split: when the query tiles would leave a good part of the last round of workgroups idle
+// (a drafter-shaped layer has 12 heads x 19 query tiles = 228 workgroups for 256 compute units),
+// the (query tile, key tile) pairs are dealt out evenly over whole rounds instead, every
+// workgroup taking the same number of pairs; query tiles cut by a workgroup boundary leave
+// partial results that a second, small kernel merges.
+struct Plan {
+  int n_qtiles, n_hq, n_tiles, units, total_wg;
+  int64_t workspace_bytes;  // what a caller is asked for; 0 when no split was considered
+  int groups;               // key groups per workgroup (1: block_attn.hip, 2 or 4: block_attn_groups.hip)
+};
+
+// Key groups per workgroup. Estimated time: rounds of workgroups over the compute units, times a
+// fixed part plus the key tiles each group walks.
+// Measured on MI355X, us (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
+//   12 heads x 312 x 936 keys [24/36/60] 26.6 / 20.7 / 16.1; 12 x 1031 x 6186 [60/108/204] 109 / 69 / 54;
+//   12 x 1560 x 4680 [84/156/300] 87 / 59 / 80; 5 x 4680 x 32760 [95/185/370] 518 / 379 / 457;
+//   40 x 1031 x 3093 [200/360/680] 74 / 90 / 95; 16 x 4680 x 14040 [304/592/1184] 594 / 533 / 603;
+//   12 x 4680 x 14040 [228/444/888] 347 / 373 / 480; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
+// A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value; the
+// model picks the fastest in each of these cases.
+struct Groups {
+  int groups;
+  double us;  // the estimate
+};
+inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu) {
+  if (n_cu <= 0) return Groups{1, 0};
+  const struct { int groups, keys; double fixed_us, tile_us; } variants[] = {
+      {1, 64, 4.0, 1.25}, {2, 64, 6.0, 1.35}, {4, 32, 6.0, 0.95}};
+  int best = 1;
+  double best_us = 0;
+  for (const auto &v : variants) {
+    const int rows = kPlanRows / v.groups;
+    const int64_t wgs = static_cast<int64_t>(n_items) * n_heads * ((n_q + rows - 1) / rows);
+    const int64_t tiles = (n_k + v.keys - 1) / v.keys, its = (tiles + v.groups - 1) / v.groups;
+    const double us = static_cast<double>((wgs + n_cu - 1) / n_cu) * (v.fixed_us + static_cast<double>(its) * v.tile_us);
+    if (v.groups == 1 || us < best_us) {
+      best = v.groups;
+      best_us = us;
+    }
+  }
+  return Groups{best, best_us};
+}
+
+inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode) {
+  auto unsplit = [&](int groups) {
+    const int rows = kPlanRows / groups, keys = groups == 4 ? 32 : attn_index::kBN;
+    Plan pl;
+    pl.groups = groups;
+    pl.n_qtiles = (n_q + rows - 1) / rows;
+    pl.n_hq = pl.total_wg = n_items * n_heads * pl.n_qtiles;
+    pl.n_tiles = pl.units = static_cast<int>((n_k + keys - 1) / keys);
+    pl.workspace_bytes = 0;
+    return pl;
+  };
+  const Groups unsplit_best = choose_groups(n_items, n_q, n_heads, n_k, n_cu);
+  auto plain = [&]() { return unsplit(unsplit_best.groups); };
+  if (split_mode == SDVG_SPLIT_NEVER || n_cu <= 0) return plain();
+  Plan pl = unsplit(1);
+  const int rounds = (pl.n_hq + n_cu - 1) / n_cu;
+  const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
+  // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
+  // a chip that is only partly busy clocks higher. Measured on MI355X: 12 heads x 4680 x 14040 (11 %
+  // of the compute units idle) 17 % slower split than plain. SDVG_SPLIT_AUTO therefore considers
+  // the split from 60 % idle on, and there it competes with key groups inside the workgroup (above).
+  if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
+  if (split_mode == SDVG_SPLIT_AUTO && idle < 0.6) return plain();
+  const int64_t all = static_cast<int64_t>(pl.n_hq) * pl.n_tiles;
+  const int64_t wgs = static_cast<int64_t>(rounds) * n_cu;
+  pl.units = static_cast<int>((all + wgs - 1) / wgs);  // <= n_tiles, because wgs >= n_hq
+  if (pl.units < 16) return plain();
+  pl.total_wg = static_cast<int>((all + pl.units - 1) / pl.units);
+  pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * kPartialFloats * 4;
+  // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
+  // key groups, us: 1 head x 4680 x 32760 93 / 184, 5 heads 329 / 363; 4 x 4680 x 14040 128 / 141,
+  // 5 heads 157 / 159; 12 x 1560 x 4680 63 / 56, 16 x 1031 x 3093 49 / 41, 3 x 4680 x 4680 55 / 44. The
+  // workspace asked for stays that of the split, so that what a caller allocates does not depend on
+  // this choice.
+  const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(pl.units);
+  if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us) {
+    Plan g = plain();
+    g.workspace_bytes = pl.workspace_bytes;
+    return g;
+  }
+  return pl;
+}
+
+}  // namespace sdvg

@@ -1,4 +1,11 @@
-"""Helpers for the GPU parity tests: bit-exact host <-> device transfer and error metrics."""
+"""Helpers for the GPU parity tests: bit-exact host <-> device transfer, error metrics, launch plans."""
+import collections
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
 import numpy as np
 import torch
 
@@ -39,3 +46,32 @@ def attn_errors_by_head(gpu_bits, ref):
 BF16_MAX_ABS = 2e-2
 BF16_REL_RMS = 1e-2
 F32_MAX_ABS = 1e-4
+
+
+Plan = collections.namedtuple("Plan", "groups workgroups query_tiles split workspace")
+MI355X_CUS = 256
+
+
+@functools.lru_cache(maxsize=None)
+def _plan_library():
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with tempfile.TemporaryDirectory(prefix="sdvg_plan_") as tmp:
+        out = os.path.join(tmp, "attn_plan.so")
+        subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-fPIC", "-shared", "-I", os.path.join(root, "include"),
+                        "-I", os.path.join(root, "paper_2604_17397_amd", "csrc"),
+                        os.path.join(root, "tests", "host", "attn_plan.cpp"), "-o", out], check=True)
+        lib = ctypes.CDLL(out)
+    lib.attn_plan.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64, ctypes.c_int, ctypes.c_int,
+                                                   ctypes.POINTER(ctypes.c_int64)]
+    lib.attn_plan.restype = None
+    return lib
+
+
+def attn_plan(n_heads, n_q, n_k, n_items=1, split=0, n_cu=None):
+    """How a bf16 attention launch is cut into workgroups, from the library's own plan header, compiled
+    here: `groups` is 1 for the kernel of 256 rows per workgroup, 2 or 4 for the one with key groups."""
+    if n_cu is None:
+        n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    out = (ctypes.c_int64 * 5)()
+    _plan_library().attn_plan(n_items, n_q, n_heads, n_k, n_cu, split, out)
+    return Plan(*out)

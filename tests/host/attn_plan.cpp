@@ -1,0 +1,12 @@
+// The launch plan of csrc/block_attn_plan.h behind a C function, for the tests.
+#include "block_attn_plan.h"
+
+// out: key groups per workgroup, workgroups, query tiles, 1 if the keys are split, workspace bytes
+extern "C" void attn_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, int64_t out[5]) {
+  const sdvg::Plan p = sdvg::make_plan(n_items, n_q, n_heads, n_k, n_cu, split_mode);
+  out[0] = p.groups;
+  out[1] = p.total_wg;
+  out[2] = p.n_hq;
+  out[3] = p.units != p.n_tiles;
+  out[4] = p.workspace_bytes;
+}
