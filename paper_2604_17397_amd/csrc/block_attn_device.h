@@ -55,7 +55,7 @@ __device__ __forceinline__ void dma16(const void *gptr, uint32_t lds_addr) {
       : "s"(lds_addr), "v"(gptr)
       : "memory", "m0");
 }
-// Same copy with the 64-token pointer step folded in: the 64-bit add sits between the M0 write
+// Same copy with the pointer step to the next tile (`step` bytes) folded in: the 64-bit add sits between the M0 write
 // and the copy (covering the wait state M0 needs) and the stepped pointer is returned.
 __device__ __forceinline__ const char *dma16_step(const char *gptr, uint64_t step, uint32_t lds_addr) {
   asm volatile(

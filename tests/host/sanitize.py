@@ -3,13 +3,14 @@
 
 Builds (1) the C oracle with gcc -fsanitize=address,undefined, (2) libsdvg with the sanitizers
 applied to its HOST code only (the argument validation of every entry point; device code is left
-alone) and (3) the host replay of the attention kernel's index arithmetic, each into a temporary
-directory, and runs the `-m "not gpu"` tests that exercise them (or the replay itself) under the
-matching sanitizer runtime. Run from the repository root:
+alone) and (3) the host programs over the kernels' index headers (the replays of both attention
+kernels' copy schedules, the row numbering of the copy kernels), each into a temporary directory, and
+runs the `-m "not gpu"` tests that exercise them (or the program itself) under the matching sanitizer
+runtime. Run from the repository root:
 
     python tests/host/sanitize.py
 
-Exit code 0 = both test runs passed with no sanitizer report.
+Exit code 0 = all runs passed with no sanitizer report.
 """
 import os
 import subprocess
@@ -52,12 +53,13 @@ def main():
                         text=True).stdout.strip()
     env = dict(base, SDVG_LIBRARY=lib, LD_PRELOAD=rt)
     rc |= run([sys.executable, "-m", "pytest", "-x", "-q", "tests/test_abi.py"], env)
-    # (3) the host replay of the attention kernel's index arithmetic (same header as the kernel)
-    exe = os.path.join(tmp, "attn_index_replay_san")
-    rc |= run(["g++", "-O1", "-g", "-std=c++17", "-fopenmp", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
-               "-I", os.path.join(ROOT, "paper_2604_17397_amd", "csrc"),
-               os.path.join(ROOT, "tests", "host", "attn_index_replay.cpp"), "-o", exe], base)
-    rc |= run([exe], base)
+    # (3) the host programs over the kernels' index headers
+    for name in ("attn_index_replay", "attn_groups_replay", "row_map_check"):
+        exe = os.path.join(tmp, name + "_san")
+        rc |= run(["g++", "-O1", "-g", "-std=c++17", "-fopenmp", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
+                   "-I", os.path.join(ROOT, "paper_2604_17397_amd", "csrc"),
+                   os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe], base)
+        rc |= run([exe], base)
     print("sanitizer pass:", "clean" if rc == 0 else "FAILED")
     return rc
 
