@@ -17,17 +17,20 @@
 // P(i) V(i) and starts the copies of V(i+1) and K(i+3), one or two behind each second MFMA, into the
 // slots last read in matrix phase i - 1 (three K and two V slots per group: all 160 KB of the LDS).
 //
-// What bounds it, and what that led to (12 heads x 1031 x 6186 keys, 4 groups, us per launch; the
-// 256-row kernel takes 109):
+// What it went through (12 heads x 1031 x 6186 keys, 4 groups, us per launch; the 256-row kernel takes
+// 108):
 //   copies started at the head of the vector phase (ring of 2 + 2, 128 KB)         66
 //   between the MFMAs, tile kinds told apart by branches at each tile               62
 //   one rarely taken branch per tile                                                57
 //   slots as offsets in registers instead of a loop unrolled by 6: short launches gain (a KB of
 //   code fetched cold costs about 1 us), but its bookkeeping in the vector phase    59
-//   bookkeeping moved into the gaps of the matrix phase                              53
-// Without any copies it would take 50 - 42 (the matrix phases alone); a quarter of the copies more or
-// less, or an LDS order without bank-conflict swizzle, changes nothing, so what the copies cost is
-// issue time next to the MFMAs, as in block_attn.hip.
+//   bookkeeping moved into the gaps of the matrix phase                              52
+// What bounds it there, by counters: the matrix pipes are busy in 49 % of the SIMD cycles of the compute
+// units at work (2 groups 64 %, the 256-row kernel 84 %). Per 32 rows and 32 keys a wave issues 16 MFMAs
+// and, beside them, 115 other vector, 47 scalar and 25 LDS instructions and 8 copies, where the 256-row
+// kernel needs 78, 5, 24 and 2: issue slots, not memory (90 % of the reads hit the L2, no LDS bank
+// conflicts). 12 heads x 312 x 936 (15.5 us, 256-row kernel 26) is bound by latency: 60 workgroups, 8
+// iterations in series after the launch and the first loads, pipes busy in 22 %.
 #include "block_attn_device.h"
 #include "block_attn_groups_index.h"
 #include "block_attn_params.h"

@@ -33,8 +33,11 @@ struct Plan {
 //   12 x 1560 x 4680 [84/156/300] 87 / 59 / 80; 5 x 4680 x 32760 [95/185/370] 518 / 379 / 457;
 //   40 x 1031 x 3093 [200/360/680] 74 / 90 / 95; 16 x 4680 x 14040 [304/592/1184] 594 / 533 / 603;
 //   12 x 4680 x 14040 [228/444/888] 347 / 373 / 480; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
-// A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value; the
-// model picks the fastest in each of these cases.
+// A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value, and
+// the estimate is up to 25 % off in absolute terms; what counts is the order. Over 1 to 40 heads, 70
+// to 4680 rows and 210 to 32760 keys it picks the fastest of the three in each of 160 launches timed, and
+// AUTO is within 3 % of the better of that and the key split. Up to 192 keys it stays with 1 group,
+// where 4 are faster from 65 rows on (250 rows x 128 keys: 11.7 / 9.3 / 7.8).
 struct Groups {
   int groups;
   double us;  // the estimate
@@ -77,8 +80,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
   // a chip that is only partly busy clocks higher. Measured on MI355X: 12 heads x 4680 x 14040 (11 %
-  // of the compute units idle) 17 % slower split than plain. SDVG_SPLIT_AUTO therefore considers
-  // the split from 60 % idle on, and there it competes with key groups inside the workgroup (above).
+  // of the compute units idle) 328 us plain, 340 split; 24 heads (11 %) 643 / 678; 8 and 16 heads (41 %)
+  // 255 / 235 and 511 / 463, which the line below gives away. SDVG_SPLIT_AUTO considers the split
+  // from 60 % idle on, and there it competes with key groups inside the workgroup (above).
   if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
   if (split_mode == SDVG_SPLIT_AUTO && idle < 0.6) return plain();
   const int64_t all = static_cast<int64_t>(pl.n_hq) * pl.n_tiles;

@@ -12,7 +12,9 @@
 
 namespace sdvg {
 
-// n / d for 0 <= n < 2^31 and a divisor 1 <= d < 2^31 fixed at launch: n * m >> (31 + s) with
+// n / d for 0 <= n < 2^31 and a divisor 1 <= d < 2^31 fixed at launch, by multiplication with a rounded-up
+// reciprocal (Granlund and Montgomery, "Division by Invariant Integers using Multiplication", 1994): n * m
+// >> (31 + s) with
 // s = ceil(log2 d) and m = floor(2^(31+s) / d) + 1. m * d exceeds 2^(31+s) by e <= d <= 2^s, so the
 // quotient is exact because n * e < 2^(31+s). (A 64-bit division by a run-time value is some 100
 // vector instructions, more than everything else a copying thread does.)
