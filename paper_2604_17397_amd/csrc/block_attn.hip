@@ -33,6 +33,7 @@
 #include "block_attn_index.h"
 #include "block_attn_params.h"
 #include "block_attn_plan.h"
+#include "block_attn_rows32_index.h"
 #include "sdvg_common.h"
 
 namespace {
@@ -524,6 +525,7 @@ int device_info(const DeviceInfo **out) {
       d.status = hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_bf16_kernel<true>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (d.status == hipSuccess) d.status = sdvg::prepare_block_attn_groups();
+    if (d.status == hipSuccess) d.status = sdvg::prepare_block_attn_rows32();
     if (d.status == hipSuccess)
       d.status = hipDeviceGetAttribute(&d.n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (d.status == hipSuccess) d.status = hipGetSymbolAddress(&d.scratch, HIP_SYMBOL(scratch));
@@ -544,12 +546,15 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   const int n_wt = (p.n_q + 31) / 32;
   p.wt_base = n_wt / p.n_qtiles;
   p.wt_rem = n_wt % p.n_qtiles;
+  p.div_qtiles = sdvg::FastDiv::of(p.n_qtiles);
+  p.div_heads = sdvg::FastDiv::of(p.n_heads);
   constexpr size_t lds_bytes = 2 * kRing * kTileBytes;
   p.copy_first_block = 8 * p.work_per_xcd;
   // Fused commit: as many copying workgroups as the last round of attention workgroups leaves
   // compute units idle (they then run beside it for its whole length); a full round otherwise.
   const int idle_cus = n_cu > 0 && p.total_work % n_cu ? n_cu - p.total_work % n_cu : 0;
   p.n_copy_blocks = !p.k_commit_dst ? 0 : (idle_cus >= 4 ? idle_cus : (n_cu > 0 ? n_cu : 256));
+  if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, s);
   if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
   if (p.units == p.n_tiles)
     hipLaunchKernelGGL(block_attn_bf16_kernel<false>, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512),
@@ -562,6 +567,13 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
     SDVG_HIP_CHECK(hipGetLastError());
   }
   return SDVG_OK;
+}
+
+// The launch plan of a checked call.
+Plan plan_of(const AttnParams &p, int n_cu, int split_mode) {
+  const bool rows32_ok = ix::rows32_takes(static_cast<uint64_t>(p.blk_ts) * 2) &&
+                         (p.cache_len == 0 || ix::rows32_takes(static_cast<uint64_t>(p.kv_ts) * 2));
+  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok);
 }
 
 // Host-side validation shared by the entry points; fills the shape part of the parameters.
@@ -651,12 +663,12 @@ int attn_batch(const sdvg_attn_desc *desc, int32_t n_items, const void *const *q
     workspace = dev->scratch;
     workspace_bytes = kScratchBytes;
   }
-  Plan pl = make_plan(n_items, p.n_q, p.n_heads, p.n_k, dev->n_cu, workspace ? split_mode : SDVG_SPLIT_NEVER);
+  Plan pl = plan_of(p, dev->n_cu, workspace ? split_mode : SDVG_SPLIT_NEVER);
   if (pl.workspace_bytes > workspace_bytes) {
     // the split does not fit the workspace: an error for the entry point that owns its
     // workspace (its size is a documented limit), otherwise the plain launch is always possible
     if (own_workspace) return SDVG_ERR_RANGE;
-    pl = make_plan(n_items, p.n_q, p.n_heads, p.n_k, dev->n_cu, SDVG_SPLIT_NEVER);
+    pl = plan_of(p, dev->n_cu, SDVG_SPLIT_NEVER);
   }
   p.partials = static_cast<float *>(workspace);
   return launch_bf16(p, pl, dev->n_cu, static_cast<hipStream_t>(stream));
@@ -703,7 +715,7 @@ extern "C" int sdvg_block_attn_commit(const sdvg_attn_desc *desc, const void *q,
   const DeviceInfo *dev = nullptr;
   st = device_info(&dev);
   if (st != SDVG_OK) return st;
-  const Plan pl = make_plan(1, p.n_q, p.n_heads, p.n_k, dev->n_cu, SDVG_SPLIT_NEVER);
+  const Plan pl = plan_of(p, dev->n_cu, SDVG_SPLIT_NEVER);
   return launch_bf16(p, pl, dev->n_cu, static_cast<hipStream_t>(stream));
 }
 
@@ -739,5 +751,6 @@ extern "C" int64_t sdvg_block_attn_workspace_bytes(const sdvg_attn_desc *desc, i
   const DeviceInfo *dev = nullptr;
   st = device_info(&dev);
   if (st != SDVG_OK) return st;
-  return make_plan(n_items, p.n_q, p.n_heads, p.n_k, dev->n_cu, split_mode).workspace_bytes;
+  p.n_items = n_items;
+  return plan_of(p, dev->n_cu, split_mode).workspace_bytes;
 }

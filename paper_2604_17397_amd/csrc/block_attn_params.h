@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "row_map.h"
+
 namespace sdvg {
 
 constexpr int kMaxAttnItems = 8;  // (q, cache, block, out) sets one launch can take
@@ -27,6 +29,7 @@ struct AttnParams {
   int32_t total_work; // workgroups with work
   int32_t work_per_xcd;
   int32_t wt_base, wt_rem;  // 32-row wave tiles per query tile: wt_base, plus one for the first wt_rem
+  FastDiv div_qtiles, div_heads;  // by n_qtiles and by n_heads
   float scale_log2e;  // scale * log2(e)
 };
 
@@ -37,5 +40,9 @@ int launch_block_attn_f32(const AttnParams &p, hipStream_t stream);
 // p.n_qtiles / p.n_tiles count its own tiles (256 / groups query rows; 64 keys for 2 groups, 32 for 4).
 hipError_t prepare_block_attn_groups();  // once per device: raises the dynamic-LDS limit
 int launch_block_attn_groups(const AttnParams &p, int groups, hipStream_t stream);
+
+// Kernel for the smallest launches (block_attn_rows32.hip): 32 query rows per workgroup, tiles of 32 keys.
+hipError_t prepare_block_attn_rows32();  // once per device: raises the dynamic-LDS limit
+int launch_block_attn_rows32(AttnParams p, hipStream_t stream);
 
 }  // namespace sdvg

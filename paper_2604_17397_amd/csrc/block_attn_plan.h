@@ -24,10 +24,11 @@ struct Plan {
   int n_qtiles, n_hq, n_tiles, units, total_wg;
   int64_t workspace_bytes;  // what a caller is asked for; 0 when no split was considered
   int groups;               // key groups per workgroup (1: block_attn.hip, 2 or 4: block_attn_groups.hip)
+  int rows;                 // query rows per workgroup (32: block_attn_rows32.hip)
 };
 
-// Key groups per workgroup. Estimated time: rounds of workgroups over the compute units, times a
-// fixed part plus the key tiles each group walks.
+// Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
+// compute units, times a fixed part plus the key tiles each group walks.
 // Measured on MI355X, us (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
 //   12 heads x 312 x 936 keys [24/36/60] 26.6 / 20.7 / 16.1; 12 x 1031 x 6186 [60/108/204] 109 / 69 / 54;
 //   12 x 1560 x 4680 [84/156/300] 87 / 59 / 80; 5 x 4680 x 32760 [95/185/370] 518 / 379 / 457;
@@ -38,44 +39,47 @@ struct Plan {
 // to 4680 rows and 210 to 32760 keys it picks the fastest of the three in each of 160 launches timed, and
 // AUTO is within 3 % of the better of that and the key split. Up to 192 keys it stays with 1 group,
 // where 4 are faster from 65 rows on (250 rows x 128 keys: 11.7 / 9.3 / 7.8).
+// Of the launches of four groups, those whose 32-row workgroups fit one round take the kernel where the
+// two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32), us with 64 / 32
+// rows: 12 x 312 x 936 14.6 / 9.2; 16 x 500 x 1000 15.2 / 10.5; 8 x 1024 x 6144 41.4 / 35.5; 3 x 2700 x
+// 16200 99.8 / 93.5. In a second round every workgroup walks all keys again, and 64 rows are faster:
+// 12 x 1031 x 1031 16.3 / 19.3; 12 x 682 x 2046 22.3 / 29.2.
 struct Groups {
-  int groups;
+  int groups, rows;
   double us;  // the estimate
 };
-inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu) {
-  if (n_cu <= 0) return Groups{1, 0};
-  const struct { int groups, keys; double fixed_us, tile_us; } variants[] = {
-      {1, 64, 4.0, 1.25}, {2, 64, 6.0, 1.35}, {4, 32, 6.0, 0.95}};
-  int best = 1;
-  double best_us = 0;
+inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, bool rows32_ok) {
+  if (n_cu <= 0) return Groups{1, kPlanRows, 0};
+  const struct { int groups, rows, keys, walkers; double fixed_us, tile_us; } variants[] = {
+      {1, 256, 64, 1, 4.0, 1.25}, {2, 128, 64, 2, 6.0, 1.35}, {4, 64, 32, 4, 6.0, 0.95}, {4, 32, 32, 8, 3.5, 1.4}};
+  Groups best{1, kPlanRows, 0};
   for (const auto &v : variants) {
-    const int rows = kPlanRows / v.groups;
-    const int64_t wgs = static_cast<int64_t>(n_items) * n_heads * ((n_q + rows - 1) / rows);
-    const int64_t tiles = (n_k + v.keys - 1) / v.keys, its = (tiles + v.groups - 1) / v.groups;
+    if (v.rows == 32 && (best.groups != 4 || !rows32_ok)) continue;
+    const int64_t wgs = static_cast<int64_t>(n_items) * n_heads * ((n_q + v.rows - 1) / v.rows);
+    const int64_t tiles = (n_k + v.keys - 1) / v.keys, its = (tiles + v.walkers - 1) / v.walkers;
     const double us = static_cast<double>((wgs + n_cu - 1) / n_cu) * (v.fixed_us + static_cast<double>(its) * v.tile_us);
-    if (v.groups == 1 || us < best_us) {
-      best = v.groups;
-      best_us = us;
-    }
+    if (v.groups == 1 || us < best.us) best = Groups{v.groups, v.rows, us};
   }
-  return Groups{best, best_us};
+  return best;
 }
 
-inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode) {
-  auto unsplit = [&](int groups) {
-    const int rows = kPlanRows / groups, keys = groups == 4 ? 32 : attn_index::kBN;
+// rows32_ok: the strides are ones that the 32-row kernel takes.
+inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, bool rows32_ok = true) {
+  auto unsplit = [&](int groups, int rows) {
+    const int keys = groups == 4 ? 32 : attn_index::kBN;
     Plan pl;
     pl.groups = groups;
+    pl.rows = rows;
     pl.n_qtiles = (n_q + rows - 1) / rows;
     pl.n_hq = pl.total_wg = n_items * n_heads * pl.n_qtiles;
     pl.n_tiles = pl.units = static_cast<int>((n_k + keys - 1) / keys);
     pl.workspace_bytes = 0;
     return pl;
   };
-  const Groups unsplit_best = choose_groups(n_items, n_q, n_heads, n_k, n_cu);
-  auto plain = [&]() { return unsplit(unsplit_best.groups); };
+  const Groups unsplit_best = choose_groups(n_items, n_q, n_heads, n_k, n_cu, rows32_ok);
+  auto plain = [&]() { return unsplit(unsplit_best.groups, unsplit_best.rows); };
   if (split_mode == SDVG_SPLIT_NEVER || n_cu <= 0) return plain();
-  Plan pl = unsplit(1);
+  Plan pl = unsplit(1, kPlanRows);
   const int rounds = (pl.n_hq + n_cu - 1) / n_cu;
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and

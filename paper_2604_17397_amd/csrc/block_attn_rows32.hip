@@ -1,0 +1,349 @@
+// Block-causal attention of one video block for the smallest launches, for gfx950 (MI355X).
+//
+// Same operation and same arithmetic per 32 rows x 32 keys as block_attn_groups.hip with 4 groups (paper
+// Sec. 1 / Sec. 4.1 "Models"), for launches whose 32-row workgroups fit one round of the compute units
+// (block_attn_plan.h). There a launch is a chain of latencies, and the chain is what this kernel cuts:
+//   - 32 query rows per workgroup and all 8 waves on different key tiles: twice the workgroups of the 64-row
+//     kernel, half the tiles per wave;
+//   - a wave copies its tiles into its own part of the LDS and reads nothing else there, so the loop has no
+//     barrier; the waves meet at the start (one maximum for all) and at the end (merge);
+//   - a tile's K (and V) operands are read into registers at one go, so that the next tile's copies start
+//     into the same 8 KB a phase earlier than the products that use the operands end;
+//   - no tile holds keys of both sources: copies take a scalar address and a 32-bit offset per lane, four of
+//     them with one write of M0, where the 64-bit address of every row costs some ten vector instructions;
+//   - all kernel arguments are asked for at once, the query rows come through the LDS once per workgroup.
+// 12 heads x 312 x 936 keys takes 9.2 us among others in a graph (14.6 with 64 rows, 25.6 with 256): 0.9
+// launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1 merge and store;
+// 12 x 312 x 312 6.0 (10.3), 8 x 1024 x 6144 35.5 (41.4).
+// The loop is bound by the copies: 8 waves bring 128 KB per 8 x 32 keys, which takes 1.13 - 1.18 us, and a
+// loop of nothing but such copies from L2 reaches 62 bytes per clock and compute unit, 1.13 us. So
+// neither fewer scalar instructions (1 %), nor the copies placed before the products (1 % slower), nor
+// wave priorities (-3 to +11 %, by shape) are worth anything.
+#include "block_attn_device.h"
+#include "block_attn_params.h"
+#include "block_attn_rows32_index.h"
+#include "sdvg_common.h"
+
+namespace {
+
+using namespace sdvg::attn_dev;
+using sdvg::AttnParams;
+namespace ix = sdvg::attn_index;
+using R = ix::Rows32;
+
+typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) float lds_float;
+typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+
+#define SDVG_SB() __builtin_amdgcn_sched_barrier(0)
+
+template <int N>
+__device__ __forceinline__ void wait_copies() {  // all but the N most recent copies (or loads) have landed
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Four 1 KB copies (lane i's 16 bytes land at lds_addr + 1024 u + 16 i), each from a scalar address plus
+// the lanes' offsets; the immediates count for both addresses.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void copy4(const uint32_t (&off)[4], const uint64_t *base, uint32_t lds_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %8\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %4\n\t"
+      "global_load_lds_dwordx4 %1, %5 offset:1024\n\t"
+      "global_load_lds_dwordx4 %2, %6 offset:2048\n\t"
+      "global_load_lds_dwordx4 %3, %7 offset:3072"
+      :
+      : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base[0]), "s"(base[1]), "s"(base[2]), "s"(base[3]),
+        "s"(__builtin_amdgcn_readfirstlane(lds_addr))
+      : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+__global__ __launch_bounds__(512) void block_attn_rows32_kernel(const AttnParams p) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t *)smem));
+
+  sdvg::AttnItem it = p.items[0];
+  // All arguments are asked for at once, ahead of the first branch: a trip to memory each otherwise.
+  asm volatile("" ::"s"(it.q), "s"(it.k_cache), "s"(it.v_cache), "s"(it.k_blk), "s"(it.v_blk), "s"(it.out), "s"(p.q_ts),
+               "s"(p.q_hs), "s"(p.kv_ts), "s"(p.kv_hs), "s"(p.blk_ts), "s"(p.blk_hs), "s"(p.cache_len));
+  asm volatile("" ::"s"(p.n_blk), "s"(p.copy_first_block), "s"(p.n_q), "s"(p.n_heads), "s"(p.n_qtiles), "s"(p.n_tiles),
+               "s"(p.total_work), "s"(p.work_per_xcd), "s"(p.div_qtiles.m), "s"(p.div_qtiles.s), "s"(p.div_heads.m),
+               "s"(p.div_heads.s), "s"(p.scale_log2e), "s"(p.o_ts), "s"(p.o_hs));
+  if (static_cast<int>(blockIdx.x) >= p.copy_first_block) {
+    commit_block_rows(p);
+    return;
+  }
+  const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
+  if (work >= p.total_work) return;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r32 = lane & 31, hh = lane >> 5;
+
+  const int hq = static_cast<int>(p.div_qtiles.div(work)), qt = work - hq * p.n_qtiles;
+  const int item = static_cast<int>(p.div_heads.div(hq)), head = hq - item * p.n_heads;
+  if (item != 0) it = kernarg_items()[item];
+
+  const int c_len = static_cast<int>(p.cache_len), n_blk = p.n_blk;
+  const uint32_t c_pitch = static_cast<uint32_t>(p.kv_ts * 2), b_pitch = static_cast<uint32_t>(p.blk_ts * 2);
+  const uint64_t kc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.k_cache) + head * p.kv_hs);
+  const uint64_t vc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_cache) + head * p.kv_hs);
+  const uint64_t kb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.k_blk) + head * p.blk_hs);
+  const uint64_t vb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_blk) + head * p.blk_hs);
+  const int n_it = ix::rows32_tiles_of(wave, p.n_tiles);
+  // (a wave past the last tile takes the last one, masked as a whole)
+  auto tile_of = [&](int i) __attribute__((always_inline)) {
+    const int t = wave + ix::kWaves * i;
+    return ix::rows32_tile(c_len, n_blk, t < p.n_tiles ? t : p.n_tiles - 1);
+  };
+
+  // ---- copies
+  uint32_t k_chunk[4], v_chunk = ix::rows32_lane_offset(0, lane, 0, 1);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) k_chunk[u] = ix::rows32_lane_offset(0, lane, u, 0);
+  auto copy_tile = [&](const ix::Rows32Tile &t, int is_v) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + ix::rows32_copy_dst(wave, is_v, 0);
+    const uint32_t pitch = t.in_cache ? c_pitch : b_pitch;
+    uint64_t base[8];
+    base[0] = (t.in_cache ? (is_v ? vc : kc) : (is_v ? vb : kb)) + static_cast<uint64_t>(static_cast<uint32_t>(t.first)) * pitch;
+    uint32_t off[4];
+    if (__builtin_expect(t.keys == R::kKeys, 1)) {
+      const uint32_t row_off = static_cast<uint32_t>(lane >> 4) * pitch;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) off[u] = row_off + (is_v ? v_chunk : k_chunk[u]);
+#pragma unroll
+      for (int u = 0; u < 7; ++u) base[u + 1] = base[u] + static_cast<int64_t>(ix::rows32_copy_step(pitch, u));
+      copy4(off, base, dst);
+      copy4(off, base + 4, dst + 4096);
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          off[u] = ix::rows32_short_offset(pitch, t.keys, lane, 4 * h + u, is_v);
+          base[u] = base[0] - (u > 0 ? 1024 * u : 0);
+        }
+        copy4(off, base, dst + 4096 * h);
+      }
+    }
+  };
+  copy_tile(tile_of(0), 0);
+  // The query rows (rows past the end re-read the last one and are not stored): four per wave.
+  {
+    const int row = 4 * wave + (lane >> 4), q_row = qt * 32 + row;
+    const uint16_t *qp = static_cast<const uint16_t *>(it.q) + (q_row < p.n_q ? q_row : p.n_q - 1) * p.q_ts +
+                         head * p.q_hs + ix::swizzled_chunk(row, lane, 0) * 8;
+    dma16(qp, lds0 + R::kQ + wave * 1024);
+  }
+  copy_tile(tile_of(0), 1);
+
+  uint32_t k_off[8], v_off[4];  // LDS read addresses
+#pragma unroll
+  for (int s = 0; s < 8; ++s) k_off[s] = lds0 + ix::k_read_offset(lane, s, 0);
+#pragma unroll
+  for (int db = 0; db < 4; ++db) v_off[db] = lds0 + wave * R::kWavePart + R::kTile + ix::v_read_offset(lane, 0, db, 0);
+
+  f32x16 o_acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o_acc[u][i] = 0.f;
+  float l_run = 0.f, s_shift = 0.f;
+  f32x16 s_acc[1], s_init;
+  auto set_shift = [&](float v) __attribute__((always_inline)) {
+    s_shift = v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s_init[i] = v;
+  };
+  set_shift(0.f);
+  lds_float *const first_max = (lds_float *)static_cast<uintptr_t>(lds0 + R::kMax) + lane;
+  // The waves' first maxima meet in LDS: see block_attn_groups.hip for why all start from one.
+  auto common_start = [&](float own) __attribute__((always_inline)) {
+    first_max[wave * 64] = own;
+    wait_lds();
+    wg_barrier();
+    float mx = fmaxf(first_max[0], first_max[64]), m_all = mx;
+#pragma unroll
+    for (int w = 2; w < ix::kWaves; ++w) m_all = fmaxf(m_all, first_max[w * 64]);
+    if ((m_all - mx) * p.scale_log2e > 20.f) mx = m_all;
+    return mx == -INFINITY ? 0.f : mx;
+  };
+
+#pragma unroll
+  for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(o_acc[u]));  // (ready before the wait)
+  asm volatile("" : "+v"(s_init));
+  wait_copies<R::kCopies>();
+  wg_barrier();
+  bf16x8 qf[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) qf[s] = *(lds_bf16x8 *)static_cast<uintptr_t>(k_off[s] + R::kQ);
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    k_off[s] += wave * R::kWavePart;
+    asm volatile("" : "+v"(k_off[s]));
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(v_off[u]));
+
+#pragma unroll 1
+  for (int i = 0;; ++i) {
+    const bool more = i + 1 < n_it;
+    bf16x8 f[8];
+    asm volatile("" : "+v"(s_init));
+    // ---- S of the tile. Its operands are read at one go, so that the next tile's copies can start
+    wait_copies<R::kCopies>();  // K of this tile (V may still be on its way)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) f[s] = *(lds_bf16x8 *)static_cast<uintptr_t>(k_off[s]);
+    SDVG_SB();
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s], qf[s], s == 0 ? s_init : s_acc[0], 0, 0, 0);
+    SDVG_SB();
+    wait_lds();
+    if (more) copy_tile(tile_of(i + 1), 0);
+    SDVG_SB();
+#pragma unroll
+    for (int s = 4; s < 8; ++s) s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s], qf[s], s_acc[0], 0, 0, 0);
+    SDVG_SB();
+    const int keys = wave + ix::kWaves * i < p.n_tiles ? tile_of(i).keys : 0;
+    if (__builtin_expect(keys < R::kKeys, 0)) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (4 * hh + 8 * (j >> 2) + (j & 3) >= keys) s_acc[0][j] = -INFINITY;
+    }
+    if (i == 0) {
+      const float mx = common_start(tile_max(s_acc));
+#pragma unroll
+      for (int j = 0; j < 16; ++j) s_acc[0][j] -= mx;
+      set_shift(-mx);
+    }
+    // ---- softmax with the lazy running maximum of block_attn.hip
+    bf16x8 pf[2];
+    float dl = form_p(s_acc, p.scale_log2e, pf);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(dl < kPSumLimit)) != 0, 0)) {
+      const float d = fmaxf(tile_max(s_acc), 0.f);
+      const float alpha = __builtin_amdgcn_exp2f(-d * p.scale_log2e);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o_acc[u][j] *= alpha;
+      l_run *= alpha;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) s_acc[0][j] -= d;
+      set_shift(s_shift - d);
+      dl = form_p(s_acc, p.scale_log2e, pf);
+    }
+    l_run += dl;
+    // ---- O^T += V^T P^T
+    if (more)
+      wait_copies<R::kCopies>();  // V of this tile (K of the next one may still be on its way)
+    else
+      wait_copies<0>();
+    // The rows past a short tile's keys have P = 0, but 0 times an infinite value would be NaN.
+    if (__builtin_expect(keys < R::kKeys, 0)) {
+#pragma unroll
+      for (int u = 0; u < R::kCopies; ++u)
+        if (ix::rows32_copy_row(lane, u) >= keys)
+          *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + ix::rows32_copy_dst(wave, 1, 0) + u * 1024 + lane * 16) =
+              f32x4{0.f, 0.f, 0.f, 0.f};
+      wait_lds();
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t vp = v_off[u] + j * 16 * 256;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp + 8 * 256));
+        const __attribute__((ext_vector_type(8))) short a16 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        __builtin_memcpy(&f[4 * j + u], &a16, sizeof(bf16x8));
+      }
+    SDVG_SB();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o_acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[u], pf[0], o_acc[u], 0, 0, 0);
+    SDVG_SB();
+    wait_lds();
+    if (more) copy_tile(tile_of(i + 1), 1);
+    SDVG_SB();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o_acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[4 + u], pf[1], o_acc[u], 0, 0, 0);
+    SDVG_SB();
+    if (!more) break;
+  }
+
+  // ---- merge: every wave leaves its O in its own part of the LDS (nobody else reads there) and its row
+  // sums and shift where the query rows were (all waves read those two barriers ago); then it combines
+  // the eight waves' parts of 4 of the rows: with m the largest running maximum,
+  //   O = sum_w 2^((m_w - m) scale*log2e) O_w, l likewise.
+  const uint32_t part = lds0 + wave * R::kWavePart;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int c = 4 * u + g;
+      const f32x4 o4 = {o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
+      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::rows32_merge_offset(c, hh, r32)) = o4;
+    }
+  const float l_row = lane_sum32(l_run);
+  if (hh == 0) *(lds_f32x2 *)static_cast<uintptr_t>(lds0 + R::kQ + (wave * 32 + r32) * 8) = f32x2{l_row, s_shift};
+  wait_lds();
+  wg_barrier();
+  const int row = 4 * wave + (lane >> 4), q_row = qt * 32 + row, c = lane & 15;
+  float l_w[ix::kWaves], shift_w[ix::kWaves];
+#pragma unroll
+  for (int w = 0; w < ix::kWaves; ++w) {
+    const f32x2 v = *(lds_f32x2 *)static_cast<uintptr_t>(lds0 + R::kQ + (w * 32 + row) * 8);
+    l_w[w] = v[0];
+    shift_w[w] = v[1];
+  }
+  float shift_min = shift_w[0];
+#pragma unroll
+  for (int w = 1; w < ix::kWaves; ++w) shift_min = fminf(shift_min, shift_w[w]);
+  float l_sum = 0.f;
+  f32x4 o_lo = {0.f, 0.f, 0.f, 0.f}, o_hi = o_lo;
+#pragma unroll
+  for (int w = 0; w < ix::kWaves; ++w) {
+    const float factor = __builtin_amdgcn_exp2f((shift_min - shift_w[w]) * p.scale_log2e);
+    l_sum += factor * l_w[w];
+    const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::rows32_merge_offset(c, 0, row));
+    const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::rows32_merge_offset(c, 1, row));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o_lo[e] += factor * lo[e];
+      o_hi[e] += factor * hi[e];
+    }
+  }
+  if (q_row >= p.n_q) return;
+  const float inv_l = 1.0f / l_sum;
+  bf16x8 out;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    out[e] = static_cast<__bf16>(o_lo[e] * inv_l);
+    out[4 + e] = static_cast<__bf16>(o_hi[e] * inv_l);
+  }
+  *reinterpret_cast<bf16x8 *>(static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 8 * c) = out;
+}
+
+}  // namespace
+
+namespace sdvg {
+
+hipError_t prepare_block_attn_rows32() {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_rows32_kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, R::kLdsBytes);
+}
+
+int launch_block_attn_rows32(AttnParams p, hipStream_t s) {
+  p.n_tiles = ix::rows32_tiles(static_cast<int>(p.cache_len)) + ix::rows32_tiles(p.n_blk);
+  hipLaunchKernelGGL(block_attn_rows32_kernel, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512), R::kLdsBytes, s, p);
+  SDVG_HIP_CHECK(hipGetLastError());
+  return SDVG_OK;
+}
+
+}  // namespace sdvg

@@ -1,0 +1,75 @@
+// Index arithmetic of the 32-row attention kernel (block_attn_rows32.hip), on top of
+// block_attn_index.h (key streams, operand reads, work distribution) and block_attn_groups_index.h
+// (swizzle, address of a key's row); plain integer and pointer arithmetic, compiled into the kernel and
+// into tests/host/attn_rows32_replay.cpp.
+#pragma once
+#include "block_attn_groups_index.h"
+
+namespace sdvg {
+namespace attn_index {
+
+// All 8 waves of a workgroup share 32 query rows; wave w takes the key tiles w, w + 8, ... (32 keys), one
+// K and one V tile at a time in its own part of the LDS. Behind the waves' parts: the query rows, laid out
+// like a K tile, and the waves' first maxima.
+struct Rows32 {
+  static constexpr int kKeys = 32;
+  static constexpr int kTile = kKeys * 256;
+  static constexpr int kWavePart = 2 * kTile;             // K at 0, V at kTile
+  static constexpr int kQ = kWaves * kWavePart;
+  static constexpr int kMax = kQ + kTile;
+  static constexpr int kLdsBytes = kMax + kWaves * 64 * 4;
+  static constexpr int kCopies = kTile / 1024;            // 1 KB copies per tile and tensor
+};
+
+// Copy u of a tile moves tile rows 4 u .. 4 u + 3: lane i the physical 16-byte chunk i % 16 of this row.
+SDVG_HD int rows32_copy_row(int lane, int u) { return 4 * u + (lane >> 4); }
+// Copies 4 h .. 4 h + 3 share one destination register: copy u lands 1024 * (u % 4) past rows32_copy_dst
+// (+ 16 per lane), because the copy instruction adds its immediate to the LDS address as well as to the
+// source address, which rows32_copy_step takes into account.
+SDVG_HD uint32_t rows32_copy_dst(int wave, int is_v, int h) {
+  return static_cast<uint32_t>(wave * Rows32::kWavePart + is_v * Rows32::kTile + h * 4096);
+}
+
+// Key tiles. No tile holds keys of both the cache and the block: the cache's tiles come first, then the
+// block's, and the last tile of each may be short. All rows of a tile then lie at one pitch from one
+// scalar address, and a lane's offset from there fits 32 bits (rows32_takes). What follows the last key of
+// a short tile repeats that key's row and is masked.
+SDVG_HD int rows32_tiles(int n_keys) { return (n_keys + Rows32::kKeys - 1) / Rows32::kKeys; }
+struct Rows32Tile {
+  int in_cache;  // else in the block
+  int first;     // token of its first row, in the cache or in the block
+  int keys;      // 1 .. 32
+};
+SDVG_HD Rows32Tile rows32_tile(int c_len, int n_blk, int t) {
+  const int n_cache = rows32_tiles(c_len), in_cache = t < n_cache;
+  const int first = (in_cache ? t : t - n_cache) * Rows32::kKeys, left = (in_cache ? c_len : n_blk) - first;
+  return Rows32Tile{in_cache, first, left < Rows32::kKeys ? left : Rows32::kKeys};
+}
+// Pitches (bytes) this holds for.
+SDVG_HD bool rows32_takes(uint64_t pitch) { return pitch < (uint64_t{1} << 26); }
+
+// Whole tiles: the step from the rows of copy u to those of copy u + 1, less what the immediate moves on
+// (copies 3 and 4: back), and a lane's offset from there. The swizzle repeats every 16 rows (K: u and u + 4
+// agree; V: all u do).
+SDVG_HD int rows32_copy_step(uint32_t pitch, int u) { return static_cast<int>(4 * pitch) - (u % 4 == 3 ? -3072 : 1024); }
+SDVG_HD uint32_t rows32_lane_offset(uint32_t pitch, int lane, int u, int is_v) {
+  return static_cast<uint32_t>(lane >> 4) * pitch +
+         static_cast<uint32_t>(swizzled_chunk(rows32_copy_row(lane, u), lane, is_v) * 16);
+}
+// Short tiles: a lane's offset from the tile's first row, immediate not taken into account.
+SDVG_HD uint32_t rows32_short_offset(uint32_t pitch, int keys, int lane, int u, int is_v) {
+  const int row = rows32_copy_row(lane, u);
+  return static_cast<uint32_t>(row < keys ? row : keys - 1) * pitch +
+         static_cast<uint32_t>(swizzled_chunk(row, lane, is_v) * 16);
+}
+
+// Key tiles of a wave (at least one: a wave past the last tile goes through a tile that is masked).
+SDVG_HD int rows32_tiles_of(int wave, int n_tiles) { return wave < n_tiles ? (n_tiles - wave + kWaves - 1) / kWaves : 1; }
+
+// Where the merge keeps O: the 16 bytes holding dims 8 c + 4 hh .. + 3 of a row, in the part of the wave
+// they come from. The row is turned by c so that 16 lanes that read one row's chunks c = 0 .. 15 touch
+// every bank once.
+SDVG_HD int rows32_merge_offset(int c, int hh, int row) { return (c * 64 + hh * 32 + (row ^ c)) * 16; }
+
+}  // namespace attn_index
+}  // namespace sdvg

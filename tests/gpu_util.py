@@ -75,3 +75,10 @@ def attn_plan(n_heads, n_q, n_k, n_items=1, split=0, n_cu=None):
     out = (ctypes.c_int64 * 5)()
     _plan_library().attn_plan(n_items, n_q, n_heads, n_k, n_cu, split, out)
     return Plan(*out)
+
+
+def attn_plan_rows(n_heads, n_q, n_k, n_items=1, split=0, n_cu=None, rows32_ok=1):
+    """Query rows per workgroup of such a launch (32: the kernel for the smallest launches)."""
+    if n_cu is None:
+        n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    return _plan_library().attn_plan_rows(n_items, n_q, n_heads, ctypes.c_int64(n_k), n_cu, split, rows32_ok)

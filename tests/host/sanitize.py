@@ -54,7 +54,7 @@ def main():
     env = dict(base, SDVG_LIBRARY=lib, LD_PRELOAD=rt)
     rc |= run([sys.executable, "-m", "pytest", "-x", "-q", "tests/test_abi.py"], env)
     # (3) the host programs over the kernels' index headers
-    for name in ("attn_index_replay", "attn_groups_replay", "row_map_check"):
+    for name in ("attn_index_replay", "attn_groups_replay", "attn_rows32_replay", "row_map_check"):
         exe = os.path.join(tmp, name + "_san")
         rc |= run(["g++", "-O1", "-g", "-std=c++17", "-fopenmp", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
                    "-I", os.path.join(ROOT, "paper_2604_17397_amd", "csrc"),

@@ -1,0 +1,101 @@
+"""GPU parity of the 32-row attention kernel (the smallest launches of 4 key groups) at the edges of its
+tiles and rounds, and of the 64-row kernel with 4 groups, which keeps the launches of more than one round
+of 32-row workgroups. The launch plan is asked which of the two a case runs."""
+import os
+import subprocess
+
+import pytest
+import torch
+
+import test_gpu_attn_groups as by_groups
+from gpu_util import MI355X_CUS, attn_plan_rows
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+# 3 heads are one round of 32-row workgroups; 129 heads x 33 .. 64 rows are two, and one of 64 rows
+HEADS = {32: 3, 64: 129}
+
+
+def test_copies_on_the_host(tmp_path):
+    exe = str(tmp_path / "replay")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2604_17397_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host", "attn_rows32_replay.cpp"), "-o", exe], check=True)
+    res = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=300)
+    assert res.returncode == 0 and res.stdout.startswith("ok:"), res.stdout
+
+
+def test_plan_by_rounds_and_pitch():
+    rows = lambda H, n_q, n_k, **kw: attn_plan_rows(H, n_q, n_k, n_cu=MI355X_CUS, **kw)
+    assert [rows(16, 512, 1000), rows(16, 513, 1000), rows(1, 4680, 32760), rows(2, 33, 193), rows(2, 33, 192)] == [32, 64, 32, 32, 256]
+    assert rows(16, 512, 1000, rows32_ok=0) == 64
+    # whoever does not take 4 groups does not take 32 rows
+    assert [rows(12, 1560, 4680), rows(40, 4680, 32760), rows(12, 4680, 14040)] == [128, 256, 256]
+
+
+def run(rows, monkeypatch, n_q, n_blk, c_len, **kw):
+    monkeypatch.setitem(by_groups.HEADS, 4, HEADS[rows])
+    assert attn_plan_rows(HEADS[rows], n_q, c_len + n_blk) == rows
+    by_groups.run_planned(4, n_q, n_blk, c_len, **kw)
+
+
+# Tiles of 32 keys, of the cache first, then of the block; eight waves take them in turn. 193 keys leave a
+# wave without a tile, 256 are a round, 257 begin the next one.
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_k", [193, 224, 255, 256, 257, 288, 511, 513, 800])
+@pytest.mark.parametrize("c_len", [0, 1, 31, 32, 33, 63, 127, 160, 192])
+def test_edges_of_the_tiles(monkeypatch, n_k, c_len):
+    run(32, monkeypatch, [1, 31, 32, 33, 97][(n_k + c_len) % 5], n_k - c_len, c_len, seed=n_k + c_len)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,n_q", [(32, 65), (64, 33), (64, 64)])
+@pytest.mark.parametrize("head_major,jitter,scale", [(True, False, None), (False, True, None), (True, True, 0.05)])
+def test_strides_scale_and_commit(monkeypatch, rows, n_q, head_major, jitter, scale):
+    for n_blk, c_len in ((300, 407), (333, 0)):
+        run(rows, monkeypatch, n_q, n_blk, c_len, seed=660, head_major=head_major, jitter=jitter, scale=scale, commit=True)
+
+
+# What the 64-row kernel no longer gets from the cases of 3 heads
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_k", [193, 224, 225, 256, 257, 320, 385, 641])
+def test_edges_of_the_64_row_kernel(monkeypatch, n_k):
+    for i, c_len in enumerate([0, 1, 31, 33, 64, 95, 127, 161]):
+        if (i + n_k) % 2 == 0:
+            run(64, monkeypatch, 33 + i, n_k - c_len, c_len, seed=670 + i)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lo,hi,value", [(0, 32, float("-inf")), (32, 128, -1e9), (0, 128, float("-inf")), (904, 936, -1e30)])
+def test_masked_first_tiles_of_the_64_row_kernel(monkeypatch, lo, hi, value):
+    monkeypatch.setitem(by_groups.SHAPES, 4, (129, 64))
+    assert attn_plan_rows(129, 64, by_groups.N_K) == 64
+    by_groups.test_masked_first_tiles(4, lo, hi, value)
+
+
+# Short tiles repeat their last key; here both have one: the cache's ends at 218 keys, the block's at 70.
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_infinite_value_in_the_last_key_of_a_short_tile(value):
+    import paper_2604_17397_amd as P
+    import sdvg_inputs as si
+    from gpu_util import to_dev_bf16
+    assert attn_plan_rows(3, 70, 288) == 32
+    dev = [to_dev_bf16(a) for a in si.attn_inputs(3, 70, 218, seed=5)]
+    plain = P.block_attn(*dev, 218)
+    dev[2][217, 0, 5] = dev[4][-1, 1, 7] = value
+    out = P.block_attn(*dev, 218)
+    want = plain.clone()
+    want[:, 0, 5] = want[:, 1, 7] = value
+    assert torch.equal(torch.nan_to_num(out, 1.5, 2.5, 3.5), torch.nan_to_num(want, 1.5, 2.5, 3.5))
+
+
+@pytest.mark.gpu
+def test_several_items():
+    """The items of a batch are the same as one call each (both run the 32-row kernel)."""
+    import paper_2604_17397_amd as P
+    import sdvg_inputs as si
+    from gpu_util import to_dev_bf16
+    assert attn_plan_rows(3, 100, 430, n_items=3) == 32
+    items = [[to_dev_bf16(a) for a in si.attn_inputs(3, 100, 330, seed=s)] for s in (1, 2, 3)]
+    outs = P.block_attn_batch(*([it[i] for it in items] for i in range(5)), 330)
+    for it, out in zip(items, outs):
+        assert torch.equal(out, P.block_attn(*it, 330))
