@@ -85,6 +85,16 @@ __device__ __forceinline__ const AttnItem *kernarg_items() {
   return reinterpret_cast<const AttnItem *>(ka + offsetof(AttnParams, items));
 }
 
+// Asks for every argument of a launch's first item at once, ahead of the kernel's first branch: a trip to
+// memory each otherwise.
+__device__ __forceinline__ void load_arguments(const AttnParams &p, const AttnItem &it) {
+  asm volatile("" ::"s"(it.q), "s"(it.k_cache), "s"(it.v_cache), "s"(it.k_blk), "s"(it.v_blk), "s"(it.out), "s"(p.q_ts),
+               "s"(p.q_hs), "s"(p.kv_ts), "s"(p.kv_hs), "s"(p.blk_ts), "s"(p.blk_hs), "s"(p.cache_len));
+  asm volatile("" ::"s"(p.n_blk), "s"(p.copy_first_block), "s"(p.n_q), "s"(p.n_heads), "s"(p.n_qtiles), "s"(p.n_tiles),
+               "s"(p.total_work), "s"(p.work_per_xcd), "s"(p.div_qtiles.m), "s"(p.div_qtiles.s), "s"(p.div_heads.m),
+               "s"(p.div_heads.s), "s"(p.scale_log2e), "s"(p.o_ts), "s"(p.o_hs));
+}
+
 // Rows of O^T held in the accumulator layout (lane = query row lane % 32, half-wave hh), scaled by
 // 1 / row sum, rounded to bf16 and stored; rows past n_q are not stored.
 __device__ __forceinline__ void store_rows(const AttnParams &p, const AttnItem &it, int head, int q_row,

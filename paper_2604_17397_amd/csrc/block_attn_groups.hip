@@ -25,12 +25,16 @@
 //   slots as offsets in registers instead of a loop unrolled by 6: short launches gain (a KB of
 //   code fetched cold costs about 1 us), but its bookkeeping in the vector phase    59
 //   bookkeeping moved into the gaps of the matrix phase                              52
-// What bounds it there, by counters: the matrix pipes are busy in 49 % of the SIMD cycles of the compute
-// units at work (2 groups 64 %, the 256-row kernel 84 %). Per 32 rows and 32 keys a wave issues 16 MFMAs
-// and, beside them, 115 other vector, 47 scalar and 25 LDS instructions and 8 copies, where the 256-row
-// kernel needs 78, 5, 24 and 2: issue slots, not memory (90 % of the reads hit the L2, no LDS bank
-// conflicts). 12 heads x 312 x 936 (15.5 us, 256-row kernel 26) is bound by latency: 60 workgroups, 8
-// iterations in series after the launch and the first loads, pipes busy in 22 %.
+//   a shorter way in and out (below)                                                 49
+// What bounds it there, by counters: the matrix pipes are busy in about half of the SIMD cycles of the
+// compute units at work (2 groups 64 %, the 256-row kernel 84 %). With the copies, the softmax or the MFMAs
+// left out (not a result, a timing) a launch is 3, 7 and 11 % shorter: no unit is the limit, but the
+// hand-over between the phases, some 250 cycles for every 16 MFMAs (512 cycles) of a group's 32-key tile.
+// The way in and out: all arguments asked for at once, the work index by multiplication, the query rows
+// through the LDS, the first scores as soon as K(0) and those rows have landed, the merge by whole rows (16
+// lanes store 256 bytes side by side) take 2.0 to 2.6 us off every launch, us before / after:
+//   2 groups  24 heads x 1031 x 1031 keys 23.7 / 21.0   12 x 1560 x 4680 56.1 / 53.7   36 x 449 x 898 20.8 / 18.1
+//   4 groups  12 x 1031 x 1031            17.0 / 14.5   8 x 1024 x 6144 45.6 / 43.1    12 x 1031 x 6186 52.0 / 49.1
 #include "block_attn_device.h"
 #include "block_attn_groups_index.h"
 #include "block_attn_params.h"
@@ -44,20 +48,18 @@ namespace ix = sdvg::attn_index;
 
 typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 #define SDVG_SB() __builtin_amdgcn_sched_barrier(0)
-
-// The quotients of the work index are the same in every lane, but the compiler divides in vector
-// registers; this tells it so, and everything derived from them stays scalar.
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 template <int N>
 __device__ __forceinline__ void wait_lds() {  // all but the N most recent LDS reads have returned
   __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
 }
 
-constexpr int kMergeOFloats = ix::kWaves * 64 * 64;  // O of all waves; row sums and shifts follow
-constexpr int kMergeBytes = (kMergeOFloats + ix::kWaves * 2 * 64) * 4;
+constexpr int kMergeSums = ix::kWaves * 32 * 512;  // O of all waves; row sums and shifts follow
+constexpr int kMergeBytes = kMergeSums + ix::kWaves * 32 * 8;
 
 template <int G>
 __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams p) {
@@ -67,6 +69,8 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   const uint32_t lds_addr0 =
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t *)smem));
 
+  sdvg::AttnItem it = p.items[0];
+  load_arguments(p, it);
   if (static_cast<int>(blockIdx.x) >= p.copy_first_block) {
     commit_block_rows(p);
     return;
@@ -80,11 +84,9 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   const bool half_b = wave >= 4;
   const int r32 = lane & 31, hh = lane >> 5;
 
-  const int per_item = p.n_heads * p.n_qtiles;
-  const int item = uniform(work / per_item);
-  const int head = uniform((work - item * per_item) / p.n_qtiles);
-  const int qt = work - item * per_item - head * p.n_qtiles;
-  const sdvg::AttnItem it = kernarg_items()[item];
+  const int hq = static_cast<int>(p.div_qtiles.div(work)), qt = work - hq * p.n_qtiles;
+  const int item = static_cast<int>(p.div_heads.div(hq)), head = hq - item * p.n_heads;
+  if (item != 0) it = kernarg_items()[item];
 
   ix::Streams st;
   st.kc = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.k_cache) + head * p.kv_hs);
@@ -121,29 +123,30 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   uint32_t k_dst = lds_addr0 + ix::group_copy_dst<G>(grp, wr, 0, 0, 0);
   uint32_t v_dst = lds_addr0 + ix::group_copy_dst<G>(grp, wr, 0, 0, 1);
   const uint32_t k_dst0 = k_dst, v_dst_sum = 2 * v_dst + C::kTile;
-#pragma unroll 1
-  for (int i = 0; i < 3; ++i) {  // K(0) .. K(2)
+  auto copy_k = [&](int i) __attribute__((always_inline)) {
     set_k_ptrs(tile_of(i));
 #pragma unroll
     for (int u = 0; u < C::kCopies; ++u) dma16(k_ptr[u], k_dst + u * R * 1024);
     k_dst += C::kTile;
+  };
+  copy_k(0);
+  // The query rows (rows past the end re-read the last one and are not stored): 4 R per wave.
+  const int wt_count = ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem);
+  const int wt_first = ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem);
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const int row = 4 * wave + (lane >> 4), q_row = (wt_first + r) * 32 + row;
+    dma16(static_cast<const uint16_t *>(it.q) + (q_row < p.n_q ? q_row : p.n_q - 1) * p.q_ts + head * p.q_hs +
+              ix::swizzled_chunk(row, lane, 0) * 8,
+          lds_addr0 + ix::group_query_tile<G>(r) + wave * 1024);
   }
+#pragma unroll 1
+  for (int i = 1; i < 3; ++i) copy_k(i);
   k_dst = k_dst0;  // slot of K(3)
   set_v_ptrs(tile_of(0));
 #pragma unroll
   for (int u = 0; u < C::kCopies; ++u) dma16(v_ptr[u], v_dst + u * R * 1024);
   v_dst += C::kTile;  // slot of V(1)
-
-  // ---- query rows (rows past the end re-read the last one and are not stored)
-  const int wt_count = ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem);
-  const int q_row = (ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem) + wr) * 32 + r32;
-  const int q_row_ld = q_row < p.n_q ? q_row : p.n_q - 1;
-  bf16x8 qf[8];
-  {
-    const uint16_t *qp = static_cast<const uint16_t *>(it.q) + q_row_ld * p.q_ts + head * p.q_hs + 8 * hh;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + 16 * s);
-  }
 
   // ---- LDS read addresses (bytes), with the group's part of the LDS and the slot folded in
   uint32_t k_off[8], v_off[4];
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   float l_run = 0.f, s_shift = 0.f;
   f32x16 s_acc[NK];
   f32x16 s_init = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  bf16x8 pf[2 * NK];
+  bf16x8 qf[8], pf[2 * NK];
   bf16x8 f[2][4];  // two groups of 4 MFMA A-operands: one in use, one being fetched
   auto set_shift = [&](float v) __attribute__((always_inline)) {
     s_shift = v;
@@ -247,8 +250,11 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     l_run += dl;
   };
 
-  wait_vmcnt0();
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * C::kCopies) : "memory");  // K(0) and the query rows
   wg_barrier();
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+    qf[s] = *(lds_bf16x8 *)static_cast<uintptr_t>(lds_addr0 + ix::group_query_tile<G>(wr) + ix::k_read_offset(lane, s, 0));
   // ---- S of the group's first tile. All groups start from one maximum per row, that of the first 64
   // keys, as the 256-row kernel does: the groups' first-tile maxima meet in LDS (in V slot 1, which is
   // first written in matrix phase 0, a barrier after the values here are read). A group that started
@@ -271,7 +277,9 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       return reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + g * C::kGroup + C::kVSlots + C::kTile) +
              wr * 64 + lane;
     };
-    *first_max(grp) = tile_max(s_acc);
+    const float own = tile_max(s_acc);
+    wg_barrier();  // all have read their query rows
+    *first_max(grp) = own;
     __syncthreads();
     float mx = *first_max(0), m_all;
 #pragma unroll
@@ -401,48 +409,58 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   wg_barrier();
   if (!half_b) wg_barrier();  // pairs with the extra barrier of waves 4-7: all LDS reads are done
 
-  // ---- merge: every wave leaves its O, row sum and shift in LDS and combines a 1 / G share of the
-  // dims of its rows over the groups: with m the largest running maximum,
+  // ---- merge: every wave leaves its O, row sum and shift in LDS and combines the groups' parts of four
+  // rows of each row wave: with m the largest running maximum,
   //   O = sum_g 2^((m_g - m) scale*log2e) O_g, l likewise.
-  float *mg = reinterpret_cast<float *>(smem);
+  const uint32_t part = lds_addr0 + wave * 32 * 512;
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 o4 = {o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
-      *reinterpret_cast<f32x4 *>(mg + ((wave * 16 + 4 * u + g) * 64 + lane) * 4) = o4;
-    }
-  float *ml = mg + kMergeOFloats;
-  ml[(wave * 2) * 64 + lane] = l_run;
-  ml[(wave * 2 + 1) * 64 + lane] = s_shift;
+    for (int g = 0; g < 4; ++g)
+      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::rows32_merge_offset(4 * u + g, hh, r32)) =
+          f32x4{o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
+  const float l_row = lane_sum32(l_run);
+  if (hh == 0) *(lds_f32x2 *)static_cast<uintptr_t>(lds_addr0 + kMergeSums + (wave * 32 + r32) * 8) = f32x2{l_row, s_shift};
   __syncthreads();
-  if (wr >= wt_count) return;
-  float shift_min = ml[(wr * 2 + 1) * 64 + lane];
+  const int row = 4 * wave + (lane >> 4), c = lane & 15;
 #pragma unroll
-  for (int g = 1; g < G; ++g) shift_min = fminf(shift_min, ml[((g * R + wr) * 2 + 1) * 64 + lane]);
-  float factor[G], l_sum = 0.f;
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int w = g * R + wr;
-    factor[g] = __builtin_amdgcn_exp2f((shift_min - ml[(w * 2 + 1) * 64 + lane]) * p.scale_log2e);
-    l_sum += factor[g] * ml[(w * 2) * 64 + lane];
-  }
-  const float inv_l = 1.0f / lane_sum32(l_sum);
-  if (q_row >= p.n_q) return;
-  uint16_t *op = static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 4 * hh;
-#pragma unroll
-  for (int k = 0; k < 16 / G; ++k) {
-    const int q4 = grp * (16 / G) + k;  // dims 8 q4 + 4 hh .. + 3
-    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
+  for (int r = 0; r < R; ++r) {
+    if (r >= wt_count) return;
+    float l_g[G], shift_g[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const f32x4 part = *reinterpret_cast<const f32x4 *>(mg + (((g * R + wr) * 16 + q4) * 64 + lane) * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] += factor[g] * part[e];
+      const f32x2 v = *(lds_f32x2 *)static_cast<uintptr_t>(lds_addr0 + kMergeSums + ((g * R + r) * 32 + row) * 8);
+      l_g[g] = v[0];
+      shift_g[g] = v[1];
     }
+    float shift_min = shift_g[0];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o4[e] *= inv_l;
-    *reinterpret_cast<bf16x4 *>(op + 8 * q4) = __builtin_convertvector(o4, bf16x4);
+    for (int g = 1; g < G; ++g) shift_min = fminf(shift_min, shift_g[g]);
+    float l_sum = 0.f;
+    f32x4 o_lo = {0.f, 0.f, 0.f, 0.f}, o_hi = o_lo;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const float factor = __builtin_amdgcn_exp2f((shift_min - shift_g[g]) * p.scale_log2e);
+      l_sum += factor * l_g[g];
+      const uint32_t from = lds_addr0 + (g * R + r) * 32 * 512;
+      const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(from + ix::rows32_merge_offset(c, 0, row));
+      const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(from + ix::rows32_merge_offset(c, 1, row));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o_lo[e] += factor * lo[e];
+        o_hi[e] += factor * hi[e];
+      }
+    }
+    const float inv_l = 1.0f / l_sum;
+    bf16x8 out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      out[e] = static_cast<__bf16>(o_lo[e] * inv_l);
+      out[4 + e] = static_cast<__bf16>(o_hi[e] * inv_l);
+    }
+    const int q_row = (wt_first + r) * 32 + row;
+    if (q_row < p.n_q)
+      *reinterpret_cast<bf16x8 *>(static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 8 * c) = out;
   }
 }
 

@@ -35,6 +35,13 @@ SDVG_HD uint32_t group_copy_dst(int group, int wr, int u, int slot, int is_v) {
   return static_cast<uint32_t>(group * C::kGroup + is_v * C::kVSlots + slot * C::kTile +
                                (wr + C::kRowWaves * u) * 1024);
 }
+// Where the query rows of row wave wr pass through the LDS, laid out like 32 rows of a K tile: in the
+// groups' second V slots, which are written for the first time in matrix phase 0.
+template <int G>
+SDVG_HD uint32_t group_query_tile(int wr) {
+  using C = Groups<G>;
+  return static_cast<uint32_t>(wr / C::kHalves * C::kGroup + C::kVSlots + C::kTile + wr % C::kHalves * 8192);
+}
 SDVG_HD int swizzled_chunk(int row, int lane, int is_v) { return (lane & 15) ^ (is_v ? 4 * (row & 3) : (row & 15)); }
 
 // Iteration i of a group (its i-th tile) copies V of its tile i + 1 and K of its tile i + 3. The copy
@@ -76,6 +83,11 @@ SDVG_HD const char *group_key_ptr(const Streams &s, const LaneBase &b, int j) {
                                         static_cast<uint64_t>(static_cast<uint32_t>(j)) *
                                             (in_cache ? s.kv_tsb : s.blk_tsb));
 }
+
+// Where the merge keeps O: the 16 bytes holding dims 8 c + 4 hh .. + 3 of a row, in the part of the wave
+// they come from. The row is turned by c so that 16 lanes that read one row's chunks c = 0 .. 15 touch
+// every bank once.
+SDVG_HD int rows32_merge_offset(int c, int hh, int row) { return (c * 64 + hh * 32 + (row ^ c)) * 16; }
 
 }  // namespace attn_index
 }  // namespace sdvg

@@ -30,20 +30,20 @@ struct Plan {
 // Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
 // compute units, times a fixed part plus the key tiles each group walks.
 // Measured on MI355X, us (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
-//   12 heads x 312 x 936 keys [24/36/60] 26.6 / 20.7 / 16.1; 12 x 1031 x 6186 [60/108/204] 109 / 69 / 54;
-//   12 x 1560 x 4680 [84/156/300] 87 / 59 / 80; 5 x 4680 x 32760 [95/185/370] 518 / 379 / 457;
-//   40 x 1031 x 3093 [200/360/680] 74 / 90 / 95; 16 x 4680 x 14040 [304/592/1184] 594 / 533 / 603;
-//   12 x 4680 x 14040 [228/444/888] 347 / 373 / 480; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
+//   12 heads x 312 x 936 keys [24/36/60] 25.6 / 17.1 / 12.8; 12 x 1031 x 6186 [60/108/204] 113 / 68 / 51;
+//   12 x 1560 x 4680 [84/156/300] 87 / 54 / 76; 5 x 4680 x 32760 [95/185/370] 518 / 365 / 447;
+//   40 x 1031 x 3093 [200/360/680] 71 / 82 / 83; 16 x 4680 x 14040 [304/592/1184] 579 / 513 / 547;
+//   12 x 4680 x 14040 [228/444/888] 335 / 356 / 427; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
 // A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value, and
-// the estimate is up to 25 % off in absolute terms; what counts is the order. Over 1 to 40 heads, 70
-// to 4680 rows and 210 to 32760 keys it picks the fastest of the three in each of 160 launches timed, and
-// AUTO is within 3 % of the better of that and the key split. Up to 192 keys it stays with 1 group,
-// where 4 are faster from 65 rows on (250 rows x 128 keys: 11.7 / 9.3 / 7.8).
+// the estimate is up to 25 % off in absolute terms; what counts is the order. Over 2 to 40 heads, 312
+// to 4680 rows and 1 to 7 blocks of keys it was within 1.4 % of the fastest of the four in each of 87
+// launches drawn at random. Up to 192 keys it stays with 1 group, where 4 are faster from 65 rows on (250
+// rows x 128 keys, before the grouped kernels' way in was shortened: 11.7 / 9.3 / 7.8).
 // Of the launches of four groups, those whose 32-row workgroups fit one round take the kernel where the
 // two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32), us with 64 / 32
-// rows: 12 x 312 x 936 14.6 / 9.2; 16 x 500 x 1000 15.2 / 10.5; 8 x 1024 x 6144 41.4 / 35.5; 3 x 2700 x
-// 16200 99.8 / 93.5. In a second round every workgroup walks all keys again, and 64 rows are faster:
-// 12 x 1031 x 1031 16.3 / 19.3; 12 x 682 x 2046 22.3 / 29.2.
+// rows: 12 x 312 x 936 12.8 / 9.6; 16 x 500 x 1000 13.2 / 11.1; 8 x 1024 x 6144 43.1 / 37.1; 3 x 2700 x
+// 16200 103.3 / 96.8. In a second round every workgroup walks all keys again, and 64 rows are faster:
+// 12 x 1031 x 1031 14.1 / 19.7; 12 x 682 x 2046 20.0 / 28.3.
 struct Groups {
   int groups, rows;
   double us;  // the estimate
@@ -51,7 +51,7 @@ struct Groups {
 inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, bool rows32_ok) {
   if (n_cu <= 0) return Groups{1, kPlanRows, 0};
   const struct { int groups, rows, keys, walkers; double fixed_us, tile_us; } variants[] = {
-      {1, 256, 64, 1, 4.0, 1.25}, {2, 128, 64, 2, 6.0, 1.35}, {4, 64, 32, 4, 6.0, 0.95}, {4, 32, 32, 8, 3.5, 1.4}};
+      {1, 256, 64, 1, 4.0, 1.25}, {2, 128, 64, 2, 5.5, 1.3}, {4, 64, 32, 4, 6.0, 0.9}, {4, 32, 32, 8, 3.5, 1.4}};
   Groups best{1, kPlanRows, 0};
   for (const auto &v : variants) {
     if (v.rows == 32 && (best.groups != 4 || !rows32_ok)) continue;

@@ -69,12 +69,7 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(const AttnParams
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t *)smem));
 
   sdvg::AttnItem it = p.items[0];
-  // All arguments are asked for at once, ahead of the first branch: a trip to memory each otherwise.
-  asm volatile("" ::"s"(it.q), "s"(it.k_cache), "s"(it.v_cache), "s"(it.k_blk), "s"(it.v_blk), "s"(it.out), "s"(p.q_ts),
-               "s"(p.q_hs), "s"(p.kv_ts), "s"(p.kv_hs), "s"(p.blk_ts), "s"(p.blk_hs), "s"(p.cache_len));
-  asm volatile("" ::"s"(p.n_blk), "s"(p.copy_first_block), "s"(p.n_q), "s"(p.n_heads), "s"(p.n_qtiles), "s"(p.n_tiles),
-               "s"(p.total_work), "s"(p.work_per_xcd), "s"(p.div_qtiles.m), "s"(p.div_qtiles.s), "s"(p.div_heads.m),
-               "s"(p.div_heads.s), "s"(p.scale_log2e), "s"(p.o_ts), "s"(p.o_hs));
+  load_arguments(p, it);
   if (static_cast<int>(blockIdx.x) >= p.copy_first_block) {
     commit_block_rows(p);
     return;

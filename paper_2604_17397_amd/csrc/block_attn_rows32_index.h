@@ -66,10 +66,5 @@ SDVG_HD uint32_t rows32_short_offset(uint32_t pitch, int keys, int lane, int u, 
 // Key tiles of a wave (at least one: a wave past the last tile goes through a tile that is masked).
 SDVG_HD int rows32_tiles_of(int wave, int n_tiles) { return wave < n_tiles ? (n_tiles - wave + kWaves - 1) / kWaves : 1; }
 
-// Where the merge keeps O: the 16 bytes holding dims 8 c + 4 hh .. + 3 of a row, in the part of the wave
-// they come from. The row is turned by c so that 16 lanes that read one row's chunks c = 0 .. 15 touch
-// every bank once.
-SDVG_HD int rows32_merge_offset(int c, int hh, int row) { return (c * 64 + hh * 32 + (row ^ c)) * 16; }
-
 }  // namespace attn_index
 }  // namespace sdvg

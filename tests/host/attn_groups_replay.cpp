@@ -146,6 +146,14 @@ long sweep(int &bad) {
   for (int k : {0, 1, 6})
     for (int nb : {312, 1031, 4680}) one(k * nb, nb, 12 * 256, 256);
   one(100, 100, 0xfffffff0u / 16 * 8, 0x7ffffff0u);  // the largest pitches
+  // the query rows' tiles lie in second V slots, one beside the other
+  using C = ix::Groups<G>;
+  std::vector<char> taken(G * C::kGroup / 8192, 0);
+  for (int r = 0; r < C::kRowWaves; ++r) {
+    const int at = ix::group_query_tile<G>(r), in_group = at % C::kGroup - C::kVSlots;
+    if (at % 8192 || at >= G * C::kGroup || in_group < C::kTile || in_group + 8192 > 2 * C::kTile || taken[at / 8192]++)
+      std::printf("FAIL G=%d query tile %d\n", G, r), ++bad;
+  }
   return n;
 }
 
