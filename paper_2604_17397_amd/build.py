@@ -5,6 +5,8 @@ import os
 import subprocess
 import sys
 import sysconfig
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -18,6 +20,10 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
+# Sources compiled with a kernel's first 14 dwords of arguments preloaded into scalar registers: worth 0.3 us
+# of a launch where the arguments are what a short kernel waits for. The routers lose 0.2 us by it.
+PRELOADED = {"rope.hip"}
+PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def sources():
@@ -26,18 +32,29 @@ def sources():
 
 def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *extra_flags, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           *sources(), "-o", out]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    noise = "is not a recognized feature for this target"
-    out = "\n".join(ln for ln in res.stdout.splitlines() if noise not in ln)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
-    if verbose and out.strip():
-        print(out)
-    return out
+    flags = [*HIPCC_FLAGS, *extra_flags, "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+    def run(args):
+        cmd = [hipcc, *flags, *args]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        noise = "is not a recognized feature for this target"
+        log = "\n".join(ln for ln in res.stdout.splitlines() if noise not in ln)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + log)
+        if verbose and log.strip():
+            print(log)
+        return log
+
+    def compile_one(src, obj):
+        return run([*(PRELOAD_FLAGS if os.path.basename(src) in PRELOADED else []), "-c", src, "-o", obj])
+
+    with tempfile.TemporaryDirectory(prefix="sdvg_build_") as tmp, ThreadPoolExecutor(4) as pool:
+        objects = [os.path.join(tmp, os.path.basename(src) + ".o") for src in sources()]
+        logs = list(pool.map(compile_one, sources(), objects))
+        logs.append(run([*objects, "-o", out]))
+    return "\n".join(log for log in logs if log)
 
 
 def build_native(verbose: bool = False, out: str = NATIVE) -> str:

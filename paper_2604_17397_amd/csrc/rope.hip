@@ -38,21 +38,33 @@ __device__ __forceinline__ u32x4 rotate_chunk(u32x4 x, f32x4 c, f32x4 s) {
   return y;
 }
 
-// One 16-byte chunk per thread: row r = token * n_heads + head. HBM bound: q of a target layer (48 MB
-// in, 48 MB out) takes 17.1 us; with ordinary stores, which displace what is still to be read, 19.6
-// (with a nontemporal load as well: 19.0).
+// One 16-byte chunk per thread: row r = token * n_heads + head.
+// Small tensors: a chain of latencies. Every trip to memory for arguments costs 0.3 us, so this file is
+// compiled with the first 14 dwords of arguments preloaded into registers (build.py); kDense needs no more than
+// those. Two passes and an attention call of 12 heads x 312 rows took 17.8 us in a graph, 17.3 with
+// 9 dwords preloaded, 16.4 as it is now (with ordinary stores, below).
+// Large ones: HBM bound. q of a target layer (48 MB in, 48 MB out) takes 17.1 us; with ordinary stores, which
+// displace what is still to be read, 18.8 to 19.6 (with a nontemporal load as well: 19.0).
+template <bool kDense, bool kStream>
 __global__ __launch_bounds__(sdvg::kRowThreads) void rope_kernel(
-    const uint16_t *__restrict__ x, const float *__restrict__ cos_t, const float *__restrict__ sin_t, uint16_t *out,
-    uint32_t n_rows, sdvg::FastDiv heads, int64_t x_ts, int64_t x_hs, int64_t o_ts, int64_t o_hs) {
+    uint32_t n_rows, uint32_t heads_d, uint32_t heads_m, uint32_t heads_s, const uint16_t *__restrict__ x,
+    const float *__restrict__ cos_t, const float *__restrict__ sin_t, uint16_t *out, int64_t x_ts, int64_t x_hs,
+    int64_t o_ts, int64_t o_hs) {
   const uint32_t r = sdvg::row_of(blockIdx.x, blockIdx.z, threadIdx.x);
   if (r >= n_rows) return;
   const int ch = threadIdx.x & 15;
-  const uint32_t tok = heads.div(r), head = r - tok * heads.d;
-  const u32x4 v = *reinterpret_cast<const u32x4 *>(x + tok * x_ts + head * x_hs + ch * 8);
+  const uint32_t tok = sdvg::FastDiv{heads_d, heads_m, heads_s}.div(r), head = r - tok * heads_d;
+  const int64_t from = kDense ? static_cast<int64_t>(r) * 128 : tok * x_ts + head * x_hs;
+  const int64_t to = kDense ? static_cast<int64_t>(r) * 128 : tok * o_ts + head * o_hs;
+  const u32x4 v = *reinterpret_cast<const u32x4 *>(x + from + ch * 8);
   const f32x4 c = *reinterpret_cast<const f32x4 *>(cos_t + static_cast<int64_t>(tok) * 64 + ch * 4);
   const f32x4 s = *reinterpret_cast<const f32x4 *>(sin_t + static_cast<int64_t>(tok) * 64 + ch * 4);
-  __builtin_nontemporal_store(rotate_chunk(v, c, s),
-                              reinterpret_cast<u32x4 *>(out + tok * o_ts + head * o_hs + ch * 8));
+  const u32x4 y = rotate_chunk(v, c, s);
+  u32x4 *dst = reinterpret_cast<u32x4 *>(out + to + ch * 8);
+  if (kStream)
+    __builtin_nontemporal_store(y, dst);
+  else
+    *dst = y;
 }
 
 // Commit with the rotation of K fused in: grid.y = 0 (K, rotated) / 1 (V, copied), rows in the order
@@ -78,6 +90,13 @@ __global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_rope_kernel(
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
 }
 
+// Up to this many rows (4 MiB, an XCD's L2) the result is stored in the ordinary way, and dense tensors take the
+// kernel that needs no strides. us, a pair of passes alone / with the attention that reads them, nontemporal and ordinary
+// stores: 12 heads x 312 rows 4.27 / 12.1 and 4.27 / 11.4; 12 x 1031 5.2 / 23.5 and 5.3 / 22.8; 12 x 1560 (4.8 MB)
+// 5.9 / 34.3 and 6.2 / 33.5; 24 x 1560 8.5 / 52.5 and 9.4 / 52.1. Beyond 16 MB the dense kernel loses to the strided one
+// (40 x 4680: 38.0 and 35.1 a pair), presumably because its workgroups start closer together.
+constexpr int64_t kCachedRows = 1 << 14;
+
 bool stride_ok(int64_t st) { return st >= 128 && (st & 7) == 0; }
 
 }  // namespace
@@ -99,9 +118,14 @@ extern "C" int sdvg_rope(const void *x, const float *cos_table, const float *sin
   if (n_tokens > (sdvg::kMaxRows - 1) / n_heads) return SDVG_ERR_UNSUPPORTED;
   const int64_t n_rows = n_tokens * n_heads;
   const sdvg::RowGrid g = sdvg::row_grid(n_rows);
-  hipLaunchKernelGGL(rope_kernel, dim3(g.x, 1, g.z), dim3(sdvg::kRowThreads), 0, static_cast<hipStream_t>(stream),
-                     static_cast<const uint16_t *>(x), cos_table, sin_table, static_cast<uint16_t *>(out),
-                     static_cast<uint32_t>(n_rows), sdvg::FastDiv::of(n_heads), x_token_stride, x_head_stride,
+  const int64_t row_of_heads = int64_t{128} * n_heads;
+  const bool dense = (n_heads == 1 || (x_head_stride == 128 && out_head_stride == 128)) &&
+                     (n_tokens == 1 || (x_token_stride == row_of_heads && out_token_stride == row_of_heads));
+  const auto kernel = n_rows > kCachedRows ? rope_kernel<false, true> : dense ? rope_kernel<true, false> : rope_kernel<false, false>;
+  const sdvg::FastDiv heads = sdvg::FastDiv::of(n_heads);
+  hipLaunchKernelGGL(kernel, dim3(g.x, 1, g.z), dim3(sdvg::kRowThreads), 0, static_cast<hipStream_t>(stream),
+                     static_cast<uint32_t>(n_rows), heads.d, heads.m, heads.s, static_cast<const uint16_t *>(x),
+                     cos_table, sin_table, static_cast<uint16_t *>(out), x_token_stride, x_head_stride,
                      out_token_stride, out_head_stride);
   SDVG_HIP_CHECK(hipGetLastError());
   return SDVG_OK;

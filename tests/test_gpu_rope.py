@@ -47,6 +47,26 @@ def test_rope_bit_exact(n, H):
     assert np.array_equal(bits_of(y), want) and np.array_equal(bits_of(got_hm), want)
 
 
+# Dense or strided tensors on either side, up to 16384 rows and past that: the kernels the launch chooses from.
+@pytest.mark.parametrize("n,H", [(1, 3), (5, 1), (63, 2), (1024, 16), (1170, 14), (16385, 1)])
+@pytest.mark.parametrize("x_strided,out_strided", [(False, False), (True, False), (False, True), (True, True)])
+def test_rope_by_layout_and_size(n, H, x_strided, out_strided):
+    import paper_2604_17397_amd as P
+    x = si.normal_bf16(830 + n, 0, (n, H, 128))
+    c, s = angle_tables(n, seed=n + H)
+    dx, dc, ds = to_dev_bf16(x), torch.from_numpy(c).cuda(), torch.from_numpy(s).cuda()
+    if x_strided:  # the queries of a fused projection
+        fused = torch.full((n, H + 2, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+        fused[:, 1:H + 1] = dx
+        dx = fused[:, 1:H + 1]
+    whole = torch.full((n + 1, H + 1 if out_strided else H, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    out = whole[:n, :H]
+    P.rope(dx, dc, ds, out=out)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits_of(out), oracle.rope(x, c, s))
+    assert torch.isnan(whole[n]).all() and torch.isnan(whole[:, H:]).all()
+
+
 def test_rope_rejects_bad_arguments():
     import paper_2604_17397_amd as P
     x = torch.zeros((8, 2, 128), dtype=torch.bfloat16, device="cuda")
