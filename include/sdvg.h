@@ -133,8 +133,8 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  *             library may deal the (query tile, key tile) pairs out evenly over whole rounds of
  *             workgroups instead, so that a launch with few query tiles still fills the chip,
  *             and merge the partial results of the query tiles that were cut in a second small
- *             kernel on the same stream. SDVG_SPLIT_AUTO does so when at least 60 % of the last
- *             round of workgroups would idle (very few heads or short blocks) and the keys are many
+ *             kernel on the same stream. SDVG_SPLIT_AUTO does so when at least a quarter of the
+ *             workgroup slots of the launch's rounds would idle (few heads or short blocks) and the keys are many
  *             enough for it to be the faster way (otherwise the workspace stays unused); SDVG_SPLIT_ALWAYS
  *             whenever the query tiles do not fill whole rounds. For the paper's own shapes the
  *             split does not pay (a 12-head drafter layer has 228 query tiles for 256 compute
@@ -160,7 +160,8 @@ int sdvg_block_attn_batch(const sdvg_attn_desc *desc, int32_t n_items, const voi
  * held by every GPU the library runs on until the process ends) instead of caller memory.
  * The call allocates nothing and frees nothing. A shape whose split needs more than the array
  * holds returns SDVG_ERR_RANGE (nothing is launched); sdvg_block_attn_workspace_bytes tells the
- * need beforehand, and SDVG_SPLIT_NEVER needs none. Every call on a GPU uses that GPU's one
+ * need beforehand, and SDVG_SPLIT_NEVER needs none. SDVG_SPLIT_AUTO splits from 60 % idle slots on
+ * here, not from a quarter on. Every call on a GPU uses that GPU's one
  * array: calls that overlap in time on one GPU (different streams or threads) race -- serialise
  * them, or use sdvg_block_attn_batch with workspaces of their own. Nothing in the array has to
  * be cleared between calls: each call writes every partial result it later reads.

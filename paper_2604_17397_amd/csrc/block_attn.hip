@@ -570,10 +570,10 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
 }
 
 // The launch plan of a checked call.
-Plan plan_of(const AttnParams &p, int n_cu, int split_mode) {
+Plan plan_of(const AttnParams &p, int n_cu, int split_mode, double auto_idle = sdvg::kAutoIdle) {
   const bool rows32_ok = ix::rows32_takes(static_cast<uint64_t>(p.blk_ts) * 2) &&
                          (p.cache_len == 0 || ix::rows32_takes(static_cast<uint64_t>(p.kv_ts) * 2));
-  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok);
+  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok, auto_idle);
 }
 
 // Host-side validation shared by the entry points; fills the shape part of the parameters.
@@ -663,7 +663,8 @@ int attn_batch(const sdvg_attn_desc *desc, int32_t n_items, const void *const *q
     workspace = dev->scratch;
     workspace_bytes = kScratchBytes;
   }
-  Plan pl = plan_of(p, dev->n_cu, workspace ? split_mode : SDVG_SPLIT_NEVER);
+  Plan pl = plan_of(p, dev->n_cu, workspace ? split_mode : SDVG_SPLIT_NEVER,
+                    own_workspace ? sdvg::kAutoIdleStatic : sdvg::kAutoIdle);
   if (pl.workspace_bytes > workspace_bytes) {
     // the split does not fit the workspace: an error for the entry point that owns its
     // workspace (its size is a documented limit), otherwise the plain launch is always possible

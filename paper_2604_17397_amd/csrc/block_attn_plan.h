@@ -63,8 +63,14 @@ inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int 
   return best;
 }
 
+// SDVG_SPLIT_AUTO considers the split from this share of idle workgroup slots on: with a workspace of the caller's, and
+// with the library's own array, which holds fewer partial results and which calls that overlap must not share, so that no
+// more shapes split there than have to.
+constexpr double kAutoIdle = 0.25, kAutoIdleStatic = 0.6;
+
 // rows32_ok: the strides are ones that the 32-row kernel takes.
-inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, bool rows32_ok = true) {
+inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, bool rows32_ok = true,
+                      double auto_idle = kAutoIdle) {
   auto unsplit = [&](int groups, int rows) {
     const int keys = groups == 4 ? 32 : attn_index::kBN;
     Plan pl;
@@ -83,12 +89,13 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   const int rounds = (pl.n_hq + n_cu - 1) / n_cu;
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
-  // a chip that is only partly busy clocks higher. Measured on MI355X: 12 heads x 4680 x 14040 (11 %
-  // of the compute units idle) 328 us plain, 340 split; 24 heads (11 %) 643 / 678; 8 and 16 heads (41 %)
-  // 255 / 235 and 511 / 463, which the line below gives away. SDVG_SPLIT_AUTO considers the split
-  // from 60 % idle on, and there it competes with key groups inside the workgroup (above).
+  // a chip that is only partly busy clocks higher. Measured on MI355X, us plain / split, at 4680 rows:
+  //   11 % idle  12 heads x 14040 keys 335 / 356, x 32760 761 / 783, 24 x 14040 666 / 702
+  //   18 - 26 %  11 x 32760 723 / 716, 2 items x 5 heads x 32760 666 / 648, x 14040 298 / 297, 20 x 18720 769 / 770
+  //   33 - 48 %  9 x 32760 622 / 576, 8 x 32760 610 / 525, 8 x 14040 283 / 245, 14 x 23400 844 / 686
+  // From kAutoIdle on the estimates decide (below).
   if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
-  if (split_mode == SDVG_SPLIT_AUTO && idle < 0.6) return plain();
+  if (split_mode == SDVG_SPLIT_AUTO && idle < auto_idle) return plain();
   const int64_t all = static_cast<int64_t>(pl.n_hq) * pl.n_tiles;
   const int64_t wgs = static_cast<int64_t>(rounds) * n_cu;
   pl.units = static_cast<int>((all + wgs - 1) / wgs);  // <= n_tiles, because wgs >= n_hq
@@ -97,13 +104,16 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * kPartialFloats * 4;
   // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
   // key groups, us: 1 head x 4680 x 32760 93 / 184, 5 heads 329 / 363; 4 x 4680 x 14040 128 / 141,
-  // 5 heads 157 / 159; 12 x 1560 x 4680 63 / 56, 16 x 1031 x 3093 49 / 41, 3 x 4680 x 4680 55 / 44. The
-  // workspace asked for stays that of the split, so that what a caller allocates does not depend on
-  // this choice.
+  // 5 heads 157 / 159; 12 x 1560 x 4680 63 / 56, 16 x 1031 x 3093 49 / 41, 3 x 4680 x 4680 55 / 44.
+  // Below 60 % idle the unsplit estimate, made for a full chip, is a little high for one that is half busy: the split
+  // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (up to 40 heads, 312 to 4680 rows, 1 to 7
+  // blocks of keys) 32 were split, 1 to 21 % faster each; 10 more would have gained 4 to 10 %.
   const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(pl.units);
-  if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us) {
+  const bool few = idle >= kAutoIdleStatic;
+  if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us + (few ? 0.0 : 11.0)) {
     Plan g = plain();
-    g.workspace_bytes = pl.workspace_bytes;
+    // (from 60 % idle on, what a caller allocates does not depend on this choice)
+    if (few) g.workspace_bytes = pl.workspace_bytes;
     return g;
   }
   return pl;
