@@ -78,19 +78,20 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// The `items` array of the kernels' single by-value AttnParams argument, read from the
-// kernel-argument segment (constant memory; the compiler turns the reads into scalar loads).
+// The `items` array of the kernels' by-value AttnParams argument, kParamsAt bytes into the arguments, read from
+// the kernel-argument segment (constant memory; the compiler turns the reads into scalar loads).
+template <int kParamsAt = 0>
 __device__ __forceinline__ const AttnItem *kernarg_items() {
   const char *ka = (const char *)__builtin_amdgcn_kernarg_segment_ptr();
-  return reinterpret_cast<const AttnItem *>(ka + offsetof(AttnParams, items));
+  return reinterpret_cast<const AttnItem *>(ka + kParamsAt + offsetof(AttnParams, items));
 }
 
 // Asks for every argument of a launch's first item at once, ahead of the kernel's first branch: a trip to
 // memory each otherwise.
 __device__ __forceinline__ void load_arguments(const AttnParams &p, const AttnItem &it) {
   asm volatile("" ::"s"(it.q), "s"(it.k_cache), "s"(it.v_cache), "s"(it.k_blk), "s"(it.v_blk), "s"(it.out), "s"(p.q_ts),
-               "s"(p.q_hs), "s"(p.kv_ts), "s"(p.kv_hs), "s"(p.blk_ts), "s"(p.blk_hs), "s"(p.cache_len));
-  asm volatile("" ::"s"(p.n_blk), "s"(p.copy_first_block), "s"(p.n_q), "s"(p.n_heads), "s"(p.n_qtiles), "s"(p.n_tiles),
+               "s"(p.q_hs), "s"(p.kv_ts), "s"(p.kv_hs), "s"(p.blk_ts), "s"(p.blk_hs), "s"(p.cache_len),
+               "s"(p.n_blk), "s"(p.copy_first_block), "s"(p.n_q), "s"(p.n_heads), "s"(p.n_qtiles), "s"(p.n_tiles),
                "s"(p.total_work), "s"(p.work_per_xcd), "s"(p.div_qtiles.m), "s"(p.div_qtiles.s), "s"(p.div_heads.m),
                "s"(p.div_heads.s), "s"(p.scale_log2e), "s"(p.o_ts), "s"(p.o_hs));
 }
@@ -119,9 +120,10 @@ __device__ __forceinline__ void store_rows(const AttnParams &p, const AttnItem &
 // n_blk), 16 bytes per lane, while the attention workgroups (which only read tokens below
 // cache_len and the block itself) are still running. They are dispatched last and find their
 // compute units among those the last round of attention workgroups leaves idle.
+template <int kParamsAt = 0>
 __device__ __forceinline__ void commit_block_rows(const AttnParams &p) {
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-  const AttnItem it = kernarg_items()[0];
+  const AttnItem it = kernarg_items<kParamsAt>()[0];
   const int64_t chunks = static_cast<int64_t>(p.n_blk) * p.n_heads * 16;  // 16-byte chunks per tensor
   const int64_t first = static_cast<int64_t>(blockIdx.x - p.copy_first_block) * 512 + threadIdx.x;
   const int64_t stride = static_cast<int64_t>(p.n_copy_blocks) * 512;

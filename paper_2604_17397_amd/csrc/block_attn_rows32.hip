@@ -11,7 +11,8 @@
 //     into the same 8 KB a phase earlier than the products that use the operands end;
 //   - no tile holds keys of both sources: copies take a scalar address and a 32-bit offset per lane, four of
 //     them with one write of M0, where the 64-bit address of every row costs some ten vector instructions;
-//   - all kernel arguments are asked for at once, the query rows come through the LDS once per workgroup.
+//   - the arguments of the first copies are in registers when a wave starts, all others are asked for at once
+//     behind those copies; the query rows come through the LDS once per workgroup.
 // 12 heads x 312 x 936 keys takes 9.2 us among others in a graph (14.6 with 64 rows, 25.6 with 256): 0.9
 // launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1 merge and store;
 // 12 x 312 x 312 6.0 (10.3), 8 x 1024 x 6144 35.5 (41.4).
@@ -64,26 +65,95 @@ __device__ __forceinline__ void copy4(const uint32_t (&off)[4], const uint64_t *
 }
 #pragma clang diagnostic pop
 
-__global__ __launch_bounds__(512) void block_attn_rows32_kernel(const AttnParams p) {
+// What the first copies of a workgroup need, in the 12 dwords that are in registers when it starts (build.py):
+// they are under way before the first trip to memory for the other arguments, 0.3 us, has ended.
+struct Early {
+  const void *k, *q;               // keys of the first round of tiles (cache or block), and queries
+  uint32_t k_ts, k_hs, q_ts, q_hs;  // elements
+  int32_t n_q;
+  uint32_t div_m, div_s_qtiles;    // by n_qtiles: FastDiv::m, and s << 16 | n_qtiles
+  uint32_t work;                   // total_work << 16 | work_per_xcd
+};
+constexpr int kParamsAt = 48;  // where the AttnParams lie among the kernel's arguments
+static_assert(sizeof(Early) == kParamsAt && alignof(AttnParams) == 8, "");
+
+// kEarly: the `Early` arguments hold (early_of).
+template <bool kEarly>
+__global__ __launch_bounds__(512) void block_attn_rows32_kernel(
+    const void *e_k, const void *e_q, uint32_t e_k_ts, uint32_t e_k_hs, uint32_t e_q_ts, uint32_t e_q_hs, int32_t e_n_q,
+    uint32_t e_div_m, uint32_t e_div_s_qtiles, uint32_t e_work, const AttnParams all) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t *)smem));
-
-  sdvg::AttnItem it = p.items[0];
-  load_arguments(p, it);
-  if (static_cast<int>(blockIdx.x) >= p.copy_first_block) {
-    commit_block_rows(p);
-    return;
-  }
-  const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
-  if (work >= p.total_work) return;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r32 = lane & 31, hh = lane >> 5;
 
+  // ---- copies
+  uint32_t k_chunk[4], v_chunk = ix::rows32_lane_offset(0, lane, 0, 1);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) k_chunk[u] = ix::rows32_lane_offset(0, lane, u, 0);
+  // `keys` rows from `first_row` on
+  auto copy_rows = [&](uint64_t first_row, uint32_t pitch, int keys, int is_v) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + ix::rows32_copy_dst(wave, is_v, 0);
+    uint64_t base[8];
+    base[0] = first_row;
+    uint32_t off[4];
+    if (__builtin_expect(keys == R::kKeys, 1)) {
+      const uint32_t row_off = static_cast<uint32_t>(lane >> 4) * pitch;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) off[u] = row_off + (is_v ? v_chunk : k_chunk[u]);
+#pragma unroll
+      for (int u = 0; u < 7; ++u) base[u + 1] = base[u] + static_cast<int64_t>(ix::rows32_copy_step(pitch, u));
+      copy4(off, base, dst);
+      copy4(off, base + 4, dst + 4096);
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          off[u] = ix::rows32_short_offset(pitch, keys, lane, 4 * h + u, is_v);
+          base[u] = base[0] - (u > 0 ? 1024 * u : 0);
+        }
+        copy4(off, base, dst + 4096 * h);
+      }
+    }
+  };
+  // The query rows (rows past the end re-read the last one and are not stored): four per wave.
+  auto copy_query = [&](const void *q, int head, int qt, int n_q, int64_t q_ts, int64_t q_hs) __attribute__((always_inline)) {
+    const int row = 4 * wave + (lane >> 4), q_row = qt * 32 + row;
+    const uint16_t *qp = static_cast<const uint16_t *>(q) + (q_row < n_q ? q_row : n_q - 1) * q_ts + head * q_hs +
+                         ix::swizzled_chunk(row, lane, 0) * 8;
+    dma16(qp, lds0 + R::kQ + wave * 1024);
+  };
+
+  // Behind the early copies: loads that stood ahead of them would be waited for first.
+  auto *arguments = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (kEarly) {
+    const int work = ix::work_of_block(blockIdx.x, static_cast<int>(e_work & 0xffff)), n_qt = static_cast<int>(e_div_s_qtiles & 0xffff);
+    if (blockIdx.x < 8 * (e_work & 0xffff) && work < static_cast<int>(e_work >> 16)) {
+      const int head = static_cast<int>(sdvg::FastDiv{0, e_div_m, e_div_s_qtiles >> 16}.div(work));
+      const uint32_t pitch = e_k_ts * 2;
+      const uint64_t first_row = reinterpret_cast<uint64_t>(e_k) + static_cast<uint64_t>(head) * e_k_hs * 2 +
+                                 static_cast<uint64_t>(wave * R::kKeys) * pitch;
+      copy_rows(first_row, pitch, R::kKeys, 0);
+      copy_query(e_q, head, work - head * n_qt, e_n_q, e_q_ts, e_q_hs);
+    }
+    asm volatile("" : "+s"(arguments));
+  }
+  const AttnParams &p = kEarly ? *(const AttnParams *)(arguments + kParamsAt) : all;
+  sdvg::AttnItem it = p.items[0];
+  load_arguments(p, it);
+  if (static_cast<int>(blockIdx.x) >= p.copy_first_block) {
+    commit_block_rows<kParamsAt>(p);
+    return;
+  }
+  const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
+  if (work >= p.total_work) return;
+
   const int hq = static_cast<int>(p.div_qtiles.div(work)), qt = work - hq * p.n_qtiles;
   const int item = static_cast<int>(p.div_heads.div(hq)), head = hq - item * p.n_heads;
-  if (item != 0) it = kernarg_items()[item];
+  if (item != 0) it = kernarg_items<kParamsAt>()[item];
 
   const int c_len = static_cast<int>(p.cache_len), n_blk = p.n_blk;
   const uint32_t c_pitch = static_cast<uint32_t>(p.kv_ts * 2), b_pitch = static_cast<uint32_t>(p.blk_ts * 2);
@@ -98,43 +168,14 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(const AttnParams
     return ix::rows32_tile(c_len, n_blk, t < p.n_tiles ? t : p.n_tiles - 1);
   };
 
-  // ---- copies
-  uint32_t k_chunk[4], v_chunk = ix::rows32_lane_offset(0, lane, 0, 1);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) k_chunk[u] = ix::rows32_lane_offset(0, lane, u, 0);
   auto copy_tile = [&](const ix::Rows32Tile &t, int is_v) __attribute__((always_inline)) {
-    const uint32_t dst = lds0 + ix::rows32_copy_dst(wave, is_v, 0);
     const uint32_t pitch = t.in_cache ? c_pitch : b_pitch;
-    uint64_t base[8];
-    base[0] = (t.in_cache ? (is_v ? vc : kc) : (is_v ? vb : kb)) + static_cast<uint64_t>(static_cast<uint32_t>(t.first)) * pitch;
-    uint32_t off[4];
-    if (__builtin_expect(t.keys == R::kKeys, 1)) {
-      const uint32_t row_off = static_cast<uint32_t>(lane >> 4) * pitch;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) off[u] = row_off + (is_v ? v_chunk : k_chunk[u]);
-#pragma unroll
-      for (int u = 0; u < 7; ++u) base[u + 1] = base[u] + static_cast<int64_t>(ix::rows32_copy_step(pitch, u));
-      copy4(off, base, dst);
-      copy4(off, base + 4, dst + 4096);
-    } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          off[u] = ix::rows32_short_offset(pitch, t.keys, lane, 4 * h + u, is_v);
-          base[u] = base[0] - (u > 0 ? 1024 * u : 0);
-        }
-        copy4(off, base, dst + 4096 * h);
-      }
-    }
+    copy_rows((t.in_cache ? (is_v ? vc : kc) : (is_v ? vb : kb)) + static_cast<uint64_t>(static_cast<uint32_t>(t.first)) * pitch,
+              pitch, t.keys, is_v);
   };
-  copy_tile(tile_of(0), 0);
-  // The query rows (rows past the end re-read the last one and are not stored): four per wave.
-  {
-    const int row = 4 * wave + (lane >> 4), q_row = qt * 32 + row;
-    const uint16_t *qp = static_cast<const uint16_t *>(it.q) + (q_row < p.n_q ? q_row : p.n_q - 1) * p.q_ts +
-                         head * p.q_hs + ix::swizzled_chunk(row, lane, 0) * 8;
-    dma16(qp, lds0 + R::kQ + wave * 1024);
+  if constexpr (!kEarly) {
+    copy_tile(tile_of(0), 0);
+    copy_query(it.q, head, qt, p.n_q, p.q_ts, p.q_hs);
   }
   copy_tile(tile_of(0), 1);
 
@@ -325,18 +366,46 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(const AttnParams
   *reinterpret_cast<bf16x8 *>(static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 8 * c) = out;
 }
 
+// For one item whose first round of tiles lies wholly in the cache, or in the block if there is no cache, and for
+// numbers that fit their fields. (Other launches lose 0.15 us if they take the same way.)
+bool early_of(const AttnParams &p, Early &e) {
+  const bool in_cache = p.cache_len > 0;
+  if (p.n_items != 1 || (in_cache ? p.cache_len : p.n_blk) < ix::kWaves * R::kKeys || p.total_work > 0xffff ||
+      p.work_per_xcd > 0xffff || p.n_qtiles > 0xffff)
+    return false;
+  const sdvg::AttnItem &it = p.items[0];
+  e = Early{in_cache ? it.k_cache : it.k_blk,
+            it.q,
+            static_cast<uint32_t>(in_cache ? p.kv_ts : p.blk_ts),
+            static_cast<uint32_t>(in_cache ? p.kv_hs : p.blk_hs),
+            static_cast<uint32_t>(p.q_ts),
+            static_cast<uint32_t>(p.q_hs),
+            p.n_q,
+            p.div_qtiles.m,
+            p.div_qtiles.s << 16 | static_cast<uint32_t>(p.n_qtiles),
+            static_cast<uint32_t>(p.total_work) << 16 | static_cast<uint32_t>(p.work_per_xcd)};
+  return true;
+}
+
 }  // namespace
 
 namespace sdvg {
 
 hipError_t prepare_block_attn_rows32() {
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_rows32_kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, R::kLdsBytes);
+  for (const auto kernel : {block_attn_rows32_kernel<false>, block_attn_rows32_kernel<true>}) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, R::kLdsBytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 int launch_block_attn_rows32(AttnParams p, hipStream_t s) {
   p.n_tiles = ix::rows32_tiles(static_cast<int>(p.cache_len)) + ix::rows32_tiles(p.n_blk);
-  hipLaunchKernelGGL(block_attn_rows32_kernel, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512), R::kLdsBytes, s, p);
+  Early e{};
+  const auto kernel = early_of(p, e) ? block_attn_rows32_kernel<true> : block_attn_rows32_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512), R::kLdsBytes, s, e.k, e.q, e.k_ts,
+                     e.k_hs, e.q_ts, e.q_hs, e.n_q, e.div_m, e.div_s_qtiles, e.work, p);
   SDVG_HIP_CHECK(hipGetLastError());
   return SDVG_OK;
 }

@@ -99,3 +99,13 @@ def test_several_items():
     outs = P.block_attn_batch(*([it[i] for it in items] for i in range(5)), 330)
     for it, out in zip(items, outs):
         assert torch.equal(out, P.block_attn(*it, 330))
+
+
+# Whole first rounds of tiles (256 keys) in the cache, or in the block if there is no cache, and one key fewer: what
+# the workgroups' first copies are told by. Cache and block have strides of their own.
+@pytest.mark.gpu
+@pytest.mark.parametrize("c_len,n_blk", [(255, 40), (256, 40), (257, 33), (600, 1), (0, 255), (0, 256), (0, 257), (1, 300)])
+@pytest.mark.parametrize("head_major", [False, True])
+def test_first_copies(monkeypatch, c_len, n_blk, head_major):
+    for n_q in (33, 64):
+        run(32, monkeypatch, n_q, n_blk, c_len, seed=690 + c_len, head_major=head_major, commit=c_len > 0)
