@@ -114,3 +114,39 @@ def test_attention_reads_what_commit_wrote():
 
 
 # ------------------------------------------------------------------ routing
+
+
+# The copy kernels read sources of up to 64 MiB (K and V together; a snapshot's buffer) in one way and larger ones in
+# another: both sides of the line, against the copy's definition.
+@pytest.mark.parametrize("L,T", [(8, 1024), (8, 1025)])
+@pytest.mark.parametrize("head_major", [False, True])
+def test_commit_on_both_sides_of_the_read_rule(L, T, head_major):
+    import paper_2604_17397_amd as P
+    H = 16
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    kb, vb = (torch.randn((L, T, H, 128), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    angle = torch.rand((T, 64), generator=gen, device="cuda") * 6.0
+    cos, sin = torch.cos(angle), torch.sin(angle)
+    assert (2 * kb.numel() * 2 > 64 << 20) == (T == 1025)
+    for rotate in (False, True):
+        shape = (L, H, 2 * T, 128) if head_major else (L, 2 * T, H, 128)
+        k, v = (torch.full(shape, 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        if head_major:
+            k, v = k.transpose(1, 2), v.transpose(1, 2)
+        cache = P.KVCache(k, v, T, cache_len=T)
+        if rotate:
+            P.kv_commit_rope(cache, kb, vb, 1, cos, sin)
+        else:
+            P.kv_commit(cache, kb, vb, 1)
+        want = torch.stack([P.rope(kb[l], cos, sin) for l in range(L)]) if rotate else kb
+        assert torch.equal(k[:, T:], want) and torch.equal(v[:, T:], vb)
+        assert bool((k[:, :T] == 3.0).all()) and bool((v[:, :T] == 3.0).all())
+
+
+@pytest.mark.parametrize("n", [64 << 20, (64 << 20) + 5])
+def test_snapshot_on_both_sides_of_the_read_rule(n):
+    import paper_2604_17397_amd as P
+    src = torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda")
+    dst = torch.zeros(n + 16, dtype=torch.uint8, device="cuda")
+    P.buffer_snapshot(dst, src, n)
+    assert torch.equal(dst[:n], src) and not dst[n:].any()
