@@ -250,7 +250,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     l_run += dl;
   };
 
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * C::kCopies) : "memory");  // K(0) and the query rows
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ix::group_left_at_scores<G>()) : "memory");  // K(0) and the query rows
   wg_barrier();
 #pragma unroll
   for (int s = 0; s < 8; ++s)
@@ -280,6 +280,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     const float own = tile_max(s_acc);
     wg_barrier();  // all have read their query rows
     *first_max(grp) = own;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ix::group_left_at_maximum<G>()) : "memory");  // K(1), for the reads below
     __syncthreads();
     float mx = *first_max(0), m_all;
 #pragma unroll

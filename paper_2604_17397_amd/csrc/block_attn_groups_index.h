@@ -23,6 +23,24 @@ struct Groups {
   static constexpr int kVariants = kCopies < 16 / (4 * kRowWaves) ? kCopies : 16 / (4 * kRowWaves);
 };
 
+// What a wave starts before the loop, in this order: K(0), its share of the query rows, K(1), K(2), V(0). How many
+// of these copies may still be under way at the barrier ahead of the first scores (which read K(0) and the query rows),
+// and at the barrier of the common maximum: behind that one the first operands of K(1) are read, before
+// the loop's first wait and barrier.
+enum GroupStart { kStartK0, kStartQ, kStartK1, kStartK2, kStartV0 };
+template <int G>
+SDVG_HD constexpr int group_start_copies(GroupStart what) {
+  return what == kStartQ ? Groups<G>::kRowWaves : Groups<G>::kCopies;
+}
+template <int G>
+SDVG_HD constexpr int group_left_at_scores() {
+  return group_start_copies<G>(kStartK1) + group_start_copies<G>(kStartK2) + group_start_copies<G>(kStartV0);
+}
+template <int G>
+SDVG_HD constexpr int group_left_at_maximum() {
+  return group_start_copies<G>(kStartK2) + group_start_copies<G>(kStartV0);
+}
+
 // Rows and bytes of copy u of row wave wr: lane i moves physical chunk i % 16 of tile row
 // group_copy_row to group_copy_dst + 16 * i.
 template <int G>

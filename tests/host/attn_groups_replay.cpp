@@ -159,9 +159,26 @@ long sweep(int &bad) {
 
 }  // namespace
 
+// The waits ahead of the loop: copies land in the order in which they were started, so what has landed at a
+// wait that leaves n under way is all but the last n.
+template <int G>
+bool start_waits() {
+  std::vector<ix::GroupStart> order;
+  for (ix::GroupStart w : {ix::kStartK0, ix::kStartQ, ix::kStartK1, ix::kStartK2, ix::kStartV0})
+    order.insert(order.end(), ix::group_start_copies<G>(w), w);
+  auto landed = [&](ix::GroupStart w, int left) {
+    for (size_t i = order.size() - left; i < order.size(); ++i)
+      if (order[i] == w) return false;
+    return true;
+  };
+  return landed(ix::kStartK0, ix::group_left_at_scores<G>()) && landed(ix::kStartQ, ix::group_left_at_scores<G>()) &&
+         landed(ix::kStartK1, ix::group_left_at_maximum<G>());
+}
+
 int main() {
   int bad = 0;
   const long n = sweep<2>(bad) + sweep<4>(bad);
+  if (!start_waits<2>() || !start_waits<4>()) return std::printf("FAIL waits ahead of the loop\n"), 1;
   if (bad) return 1;
   std::printf("ok: %ld configurations\n", n);
   return 0;

@@ -261,3 +261,23 @@ def test_infinite_value_in_the_last_key(groups, n_k, value):
     want = plain.clone()
     want[:, 0, 5] = value
     assert torch.equal(torch.nan_to_num(out, 1.5, 2.5, 3.5), torch.nan_to_num(want, 1.5, 2.5, 3.5))
+
+
+# K(1) is read ahead of the loop's first wait and barrier: cold keys beside a commit's copies, many times. Between the
+# launches 512 MiB are written, so that neither L2 nor the memory-side cache holds the keys.
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups,n_q", [(4, 64), (2, 100)])
+def test_second_tile_has_landed_when_it_is_read(groups, n_q):
+    import paper_2604_17397_amd as P
+    H, n_blk, c_len = 129, 300, 407
+    assert attn_plan(H, n_q, c_len + n_blk).groups == groups
+    gen = torch.Generator(device="cuda").manual_seed(710)
+    q, kb, vb = (torch.randn((n, H, 128), generator=gen, device="cuda").bfloat16() for n in (n_q, n_blk, n_blk))
+    kc, vc = (torch.randn((c_len + n_blk, H, 128), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    flush = torch.empty(512 << 20, dtype=torch.uint8, device="cuda")
+    want = P.block_attn(q, kc, vc, kb, vb, c_len)
+    for i in range(40):
+        flush.fill_(i)
+        assert torch.equal(P.block_attn(q, kc, vc, kb, vb, c_len), want)
+        flush.fill_(i)
+        assert torch.equal(P.block_attn_commit(q, kc, vc, kb, vb, c_len), want)
