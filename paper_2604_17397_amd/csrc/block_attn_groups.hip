@@ -26,6 +26,8 @@
 //   code fetched cold costs about 1 us), but its bookkeeping in the vector phase    59
 //   bookkeeping moved into the gaps of the matrix phase                              52
 //   a shorter way in and out (below)                                                 49
+// (Arguments of the first copies preloaded into registers, as in block_attn_rows32.hip: no gain. 64 rows per wave, every
+// wave with key tiles of its own, which halves the LDS reads and needs no barrier: 53, bound by the copies.)
 // What bounds it there, by counters: the matrix pipes are busy in about half of the SIMD cycles of the
 // compute units at work (2 groups 64 %, the 256-row kernel 84 %). With the copies, the softmax or the MFMAs
 // left out (not a result, a timing) a launch is 3, 7 and 11 % shorter: no unit is the limit, but the

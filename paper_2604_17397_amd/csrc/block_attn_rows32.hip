@@ -13,8 +13,8 @@
 //     them with one write of M0, where the 64-bit address of every row costs some ten vector instructions;
 //   - the arguments of the first copies are in registers when a wave starts, all others are asked for at once
 //     behind those copies; the query rows come through the LDS once per workgroup.
-// 12 heads x 312 x 936 keys takes 9.2 us among others in a graph (14.6 with 64 rows, 25.6 with 256): 0.9
-// launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1 merge and store;
+// 12 heads x 312 x 936 keys takes 9.6 us a call; it took 10.0, or 9.2 among others in a graph (14.6 with 64 rows, 25.6 with
+// 256), while the first copies waited for their arguments: 0.9 launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1 merge and store;
 // 12 x 312 x 312 6.0 (10.3), 8 x 1024 x 6144 35.5 (41.4).
 // The loop is bound by the copies: 8 waves bring 128 KB per 8 x 32 keys, which takes 1.13 - 1.18 us, and a
 // loop of nothing but such copies from L2 reaches 62 bytes per clock and compute unit, 1.13 us. So
