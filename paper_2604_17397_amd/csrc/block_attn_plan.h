@@ -39,11 +39,12 @@ struct Plan {
 // to 4680 rows and 1 to 7 blocks of keys it was within 1.4 % of the fastest of the four in each of 87
 // launches drawn at random. Up to 192 keys it stays with 1 group, where 4 are faster from 65 rows on (250
 // rows x 128 keys, before the grouped kernels' way in was shortened: 11.7 / 9.3 / 7.8).
-// Of the launches of four groups, those whose 32-row workgroups fit one round take the kernel where the
-// two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32), us with 64 / 32
-// rows: 12 x 312 x 936 12.8 / 9.6; 16 x 500 x 1000 13.2 / 11.1; 8 x 1024 x 6144 43.1 / 37.1; 3 x 2700 x
-// 16200 103.3 / 96.8. In a second round every workgroup walks all keys again, and 64 rows are faster:
-// 12 x 1031 x 1031 14.1 / 19.7; 12 x 682 x 2046 20.0 / 28.3.
+// Of the launches of four groups, those whose 32-row workgroups need no more rounds than 64-row ones take the kernel
+// where the two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32). One round, us
+// with 64 / 32 rows: 12 x 312 x 936 13.5 / 10.7; 16 x 500 x 1000 13.6 / 11.6; 8 x 1024 x 6144 43.9 / 37.8. More rounds with as
+// many workgroups (up to 32 rows): 300 x 32 x 512 24.4 / 22.5; 259 x 1 x 936 34.2 / 32.9. In a round more than with 64
+// rows every workgroup walks all keys again: 12 x 1031 x 1031 15.1 / 20.9; 320 x 33 x 256 16.3 / 19.8; 300 x 64 x
+// 256 17.1 / 17.9.
 struct Groups {
   int groups, rows;
   double us;  // the estimate
@@ -53,12 +54,18 @@ inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int 
   const struct { int groups, rows, keys, walkers; double fixed_us, tile_us; } variants[] = {
       {1, 256, 64, 1, 4.0, 1.25}, {2, 128, 64, 2, 5.5, 1.3}, {4, 64, 32, 4, 6.0, 0.9}, {4, 32, 32, 8, 3.5, 1.4}};
   Groups best{1, kPlanRows, 0};
+  int64_t best_rounds = 0;
   for (const auto &v : variants) {
     if (v.rows == 32 && (best.groups != 4 || !rows32_ok)) continue;
     const int64_t wgs = static_cast<int64_t>(n_items) * n_heads * ((n_q + v.rows - 1) / v.rows);
     const int64_t tiles = (n_k + v.keys - 1) / v.keys, its = (tiles + v.walkers - 1) / v.walkers;
-    const double us = static_cast<double>((wgs + n_cu - 1) / n_cu) * (v.fixed_us + static_cast<double>(its) * v.tile_us);
-    if (v.groups == 1 || us < best.us) best = Groups{v.groups, v.rows, us};
+    const int64_t rounds = (wgs + n_cu - 1) / n_cu;
+    if (v.rows == 32 && rounds > best_rounds) continue;
+    const double us = static_cast<double>(rounds) * (v.fixed_us + static_cast<double>(its) * v.tile_us);
+    if (v.groups == 1 || us < best.us) {
+      best = Groups{v.groups, v.rows, us};
+      best_rounds = rounds;
+    }
   }
   return best;
 }

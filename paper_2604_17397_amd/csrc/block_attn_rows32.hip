@@ -1,8 +1,8 @@
 // Block-causal attention of one video block for the smallest launches, for gfx950 (MI355X).
 //
 // Same operation and same arithmetic per 32 rows x 32 keys as block_attn_groups.hip with 4 groups (paper
-// Sec. 1 / Sec. 4.1 "Models"), for launches whose 32-row workgroups fit one round of the compute units
-// (block_attn_plan.h). There a launch is a chain of latencies, and the chain is what this kernel cuts:
+// Sec. 1 / Sec. 4.1 "Models"), for launches whose 32-row workgroups fit one round of the compute units, or need no
+// more rounds than 64-row ones (block_attn_plan.h). There a launch is a chain of latencies, and the chain is what this kernel cuts:
 //   - 32 query rows per workgroup and all 8 waves on different key tiles: twice the workgroups of the 64-row
 //     kernel, half the tiles per wave;
 //   - a wave copies its tiles into its own part of the LDS and reads nothing else there, so the loop has no

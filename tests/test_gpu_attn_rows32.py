@@ -109,3 +109,19 @@ def test_several_items():
 def test_first_copies(monkeypatch, c_len, n_blk, head_major):
     for n_q in (33, 64):
         run(32, monkeypatch, n_q, n_blk, c_len, seed=690 + c_len, head_major=head_major, commit=c_len > 0)
+
+
+def test_plan_beyond_one_round():
+    """32-row workgroups are taken as long as they need no more rounds than 64-row ones: one round, or any number with
+    so few rows that both kernels have the same workgroups."""
+    rows = lambda H, n_q, n_k, **kw: attn_plan_rows(H, n_q, n_k, n_cu=MI355X_CUS, **kw)
+    assert [rows(300, 64, 256), rows(40, 33, 256, n_items=8), rows(257, 33, 193), rows(129, 64, 480)] == [64] * 4
+    assert [rows(37, 1, 256, n_items=7), rows(300, 32, 512), rows(600, 20, 300), rows(128, 64, 480)] == [32] * 4
+
+
+# Two and three rounds of 32-row workgroups; two rounds of 64-row ones, where 32 rows would need a third
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,n_q,rows", [(259, 1, 32), (300, 32, 32), (513, 20, 32), (257, 33, 64), (300, 64, 64)])
+def test_launches_beyond_one_round(monkeypatch, H, n_q, rows):
+    monkeypatch.setitem(HEADS, rows, H)
+    run(rows, monkeypatch, n_q, 150, 106, seed=680, commit=True)
