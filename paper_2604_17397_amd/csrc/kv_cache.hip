@@ -15,7 +15,11 @@ constexpr int kThreads = 256;
 // grid = (blocks_per_layer, n_layers, 2): z selects K or V. One 16-byte chunk per thread and
 // no loop: on MI355X many small workgroups beat grid-stride loops and deeper unrolling for a
 // pure copy (measured 6.4 TB/s of read+write traffic against 5.1-5.8 TB/s for the looped forms).
-template <bool kStream>
+// All copy kernels read with nontemporal loads. Ordinary ones are faster where the memory-side cache (256 MiB) holds the
+// source and slower where it does not, which is what a generation loop meets: it reads gigabytes of weights between
+// two commits. us, nontemporal / ordinary, three sets in turn and sets of 1.6 GB in turn: 55 MB dense 19.2 / 17.4 and
+// 20.2 / 21.0, head-major 19.6 / 17.8 and 20.5 / 21.2, with rotation 19.7 / 18.3 and 20.4 / 21.3; 12 MB head-major
+// 5.5 / 5.0 and 5.7 / 6.4; snapshots of 64 MiB 22.2 / 20.3 and 23.3 / 24.1, 4 MiB 2.9 / 2.7 and 2.7 / 3.1.
 __global__ __launch_bounds__(kThreads) void kv_commit_dense_kernel(
     const u32x4 *__restrict__ k_src, const u32x4 *__restrict__ v_src, u32x4 *__restrict__ k_dst,
     u32x4 *__restrict__ v_dst, int64_t chunks_per_layer, int64_t dst_layer_stride_chunks,
@@ -25,14 +29,13 @@ __global__ __launch_bounds__(kThreads) void kv_commit_dense_kernel(
   const u32x4 *src = (blockIdx.z == 0 ? k_src : v_src) + blockIdx.y * chunks_per_layer;
   u32x4 *dst = (blockIdx.z == 0 ? k_dst : v_dst) + blockIdx.y * dst_layer_stride_chunks +
                dst_first_chunk;
-  __builtin_nontemporal_store(sdvg::load_chunk<kStream>(src + i), dst + i);
+  __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
 }
 
 // General strides: one 16-byte chunk per thread, rows in the order of their destinations (RowMap).
 // On a head-major cache (30 layers x 12 heads x 1560 tokens, 575 MB moved) 99.5 us = 5.8 TB/s. With
 // the rows in the order of the source 103.6, with ordinary stores 113.6, and with 64-bit divisions
 // and a loop over chunks 111.
-template <bool kStream>
 __global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_strided_kernel(
     const uint16_t *__restrict__ k_src, const uint16_t *__restrict__ v_src, uint16_t *__restrict__ k_dst,
     uint16_t *__restrict__ v_dst, sdvg::RowMap m, uint32_t n_rows) {
@@ -42,7 +45,7 @@ __global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_strided_kernel(
   const sdvg::RowMap::Row row = m.row(r);
   const uint16_t *src = (blockIdx.y == 0 ? k_src : v_src) + m.src(row) + ch;
   uint16_t *dst = (blockIdx.y == 0 ? k_dst : v_dst) + m.dst(row) + ch;
-  __builtin_nontemporal_store(sdvg::load_chunk<kStream>(reinterpret_cast<const u32x4 *>(src)),
+  __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src)),
                               reinterpret_cast<u32x4 *>(dst));
 }
 
@@ -68,13 +71,12 @@ __global__ __launch_bounds__(sdvg::kRowThreads) void kv_zero_strided_kernel(
 
 // Plain device-to-device copy of an opaque buffer: 16-byte chunks, one per thread; the thread
 // after the last full chunk moves the 0-15 tail bytes.
-template <bool kStream>
 __global__ __launch_bounds__(kThreads) void buffer_copy_kernel(const u32x4 *__restrict__ src,
                                                                u32x4 *__restrict__ dst, int64_t chunks,
                                                                int tail_bytes) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
   if (i < chunks) {
-    __builtin_nontemporal_store(sdvg::load_chunk<kStream>(src + i), dst + i);
+    __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
   } else if (i == chunks) {
     const uint8_t *sb = reinterpret_cast<const uint8_t *>(src + chunks);
     uint8_t *db = reinterpret_cast<uint8_t *>(dst + chunks);
@@ -163,10 +165,8 @@ extern "C" int sdvg_kv_commit(sdvg_kv_cache *cache, const void *k_blk, const voi
   const int64_t T = cache->block_tokens;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t chunks_per_layer = T * cache->n_heads * 16;
-  const bool stream_in = sdvg::streams_in(2 * cache->n_layers * chunks_per_layer * 16);
   if (dense_token_major(cache)) {
-    const auto kernel = stream_in ? kv_commit_dense_kernel<true> : kv_commit_dense_kernel<false>;
-    hipLaunchKernelGGL(kernel, dense_grid(chunks_per_layer, cache->n_layers),
+    hipLaunchKernelGGL(kv_commit_dense_kernel, dense_grid(chunks_per_layer, cache->n_layers),
                        dim3(kThreads), 0, s, static_cast<const u32x4 *>(k_blk),
                        static_cast<const u32x4 *>(v_blk), static_cast<u32x4 *>(cache->k),
                        static_cast<u32x4 *>(cache->v), chunks_per_layer, cache->layer_stride / 8,
@@ -174,8 +174,7 @@ extern "C" int sdvg_kv_commit(sdvg_kv_cache *cache, const void *k_blk, const voi
   } else {
     const int64_t n_rows = T * cache->n_heads * cache->n_layers, first = slot * T * cache->token_stride;
     if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
-    const auto kernel = stream_in ? kv_commit_strided_kernel<true> : kv_commit_strided_kernel<false>;
-    hipLaunchKernelGGL(kernel, row_launch(n_rows), dim3(sdvg::kRowThreads), 0, s,
+    hipLaunchKernelGGL(kv_commit_strided_kernel, row_launch(n_rows), dim3(sdvg::kRowThreads), 0, s,
                        static_cast<const uint16_t *>(k_blk), static_cast<const uint16_t *>(v_blk),
                        static_cast<uint16_t *>(cache->k) + first, static_cast<uint16_t *>(cache->v) + first,
                        sdvg::row_map(T, cache->n_heads, cache->layer_stride, cache->token_stride, cache->head_stride),
@@ -232,8 +231,7 @@ extern "C" int sdvg_buffer_snapshot(void *dst, const void *src, int64_t n_bytes,
   const int tail = static_cast<int>(n_bytes % 16);
   const int64_t blocks = (chunks + 1 + kThreads - 1) / kThreads;
   if (blocks > 0x7FFFFFFF) return SDVG_ERR_UNSUPPORTED;  // more than 8 TiB
-  const auto kernel = sdvg::streams_in(n_bytes) ? buffer_copy_kernel<true> : buffer_copy_kernel<false>;
-  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0,
+  hipLaunchKernelGGL(buffer_copy_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0,
                      static_cast<hipStream_t>(stream), static_cast<const u32x4 *>(src),
                      static_cast<u32x4 *>(dst), chunks, tail);
   SDVG_HIP_CHECK(hipGetLastError());

@@ -71,7 +71,6 @@ __global__ __launch_bounds__(sdvg::kRowThreads) void rope_kernel(
 // of their destinations (RowMap). Source dense [L][T][H][128]. The drafter's commit (30 layers x 4680
 // tokens x 12 heads): 268 us = 6.45 TB/s, the rate of the plain commit; with a 64-bit division per
 // thread to find its row it was bound by the vector units: 287 us.
-template <bool kStream>
 __global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_rope_kernel(
     const uint16_t *__restrict__ k_src, const uint16_t *__restrict__ v_src, uint16_t *__restrict__ k_dst,
     uint16_t *__restrict__ v_dst, const float *__restrict__ cos_t, const float *__restrict__ sin_t, sdvg::RowMap m,
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(sdvg::kRowThreads) void kv_commit_rope_kernel(
   const sdvg::RowMap::Row row = m.row(r);
   const uint16_t *src = (is_v ? v_src : k_src) + m.src(row) + ch * 8;
   uint16_t *dst = (is_v ? v_dst : k_dst) + m.dst(row) + ch * 8;
-  u32x4 v = sdvg::load_chunk<kStream>(reinterpret_cast<const u32x4 *>(src));
+  u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src));
   if (!is_v) {
     const int64_t t = static_cast<int64_t>(m.token(row)) * 64 + ch * 4;
     v = rotate_chunk(v, *reinterpret_cast<const f32x4 *>(cos_t + t), *reinterpret_cast<const f32x4 *>(sin_t + t));
@@ -143,8 +142,7 @@ extern "C" int sdvg_kv_commit_rope(sdvg_kv_cache *cache, const void *k_blk, cons
   const int64_t n_rows = T * cache->n_heads * cache->n_layers, first = slot * T * cache->token_stride;
   if (n_rows >= sdvg::kMaxRows) return SDVG_ERR_UNSUPPORTED;
   const sdvg::RowGrid g = sdvg::row_grid(n_rows);
-  const auto kernel = sdvg::streams_in(2 * n_rows * 256) ? kv_commit_rope_kernel<true> : kv_commit_rope_kernel<false>;
-  hipLaunchKernelGGL(kernel, dim3(g.x, 2, g.z), dim3(sdvg::kRowThreads), 0,
+  hipLaunchKernelGGL(kv_commit_rope_kernel, dim3(g.x, 2, g.z), dim3(sdvg::kRowThreads), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint16_t *>(k_blk),
                      static_cast<const uint16_t *>(v_blk), static_cast<uint16_t *>(cache->k) + first,
                      static_cast<uint16_t *>(cache->v) + first, cos_table, sin_table,

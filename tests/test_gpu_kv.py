@@ -116,11 +116,10 @@ def test_attention_reads_what_commit_wrote():
 # ------------------------------------------------------------------ routing
 
 
-# The copy kernels read sources of up to 64 MiB (K and V together; a snapshot's buffer) in one way and larger ones in
-# another: both sides of the line, against the copy's definition.
+# Sources just below and above 64 MiB (K and V together; a snapshot's buffer), against the copy's definition.
 @pytest.mark.parametrize("L,T", [(8, 1024), (8, 1025)])
 @pytest.mark.parametrize("head_major", [False, True])
-def test_commit_on_both_sides_of_the_read_rule(L, T, head_major):
+def test_commit_of_about_64_mib(L, T, head_major):
     import paper_2604_17397_amd as P
     H = 16
     gen = torch.Generator(device="cuda").manual_seed(T)
@@ -144,7 +143,7 @@ def test_commit_on_both_sides_of_the_read_rule(L, T, head_major):
 
 
 @pytest.mark.parametrize("n", [64 << 20, (64 << 20) + 5])
-def test_snapshot_on_both_sides_of_the_read_rule(n):
+def test_snapshot_of_about_64_mib(n):
     import paper_2604_17397_amd as P
     src = torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda")
     dst = torch.zeros(n + 16, dtype=torch.uint8, device="cuda")
