@@ -127,8 +127,8 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  *             All items share desc (shapes, strides, scale, dtype) and cache_len.
  *   workspace device, nullable, 16-byte aligned, workspace_bytes long; split_mode one of
  *             SDVG_SPLIT_*. Without a workspace (or with SDVG_SPLIT_NEVER) every query tile is
- *             one workgroup: 256 rows, or, when the launch has few of those, 128 or 64 rows whose
- *             keys are dealt out over 2 or 4 groups of the workgroup's waves. With a workspace of at least
+ *             one workgroup: 256 rows, or, when the launch has few of those, 128, 64 or 32 rows whose
+ *             keys are dealt out over 2, 4 or 8 parts of the workgroup's waves. With a workspace of at least
  *             sdvg_block_attn_workspace_bytes(desc, n_items, cache_len, split_mode) bytes the
  *             library may deal the (query tile, key tile) pairs out evenly over whole rounds of
  *             workgroups instead, so that a launch with few query tiles still fills the chip,
@@ -159,9 +159,12 @@ int sdvg_block_attn_batch(const sdvg_attn_desc *desc, int32_t n_items, const voi
  * array inside the library's device image (sdvg_block_attn_static_workspace_limit() bytes,
  * held by every GPU the library runs on until the process ends) instead of caller memory.
  * The call allocates nothing and frees nothing. A shape whose split needs more than the array
- * holds returns SDVG_ERR_RANGE (nothing is launched); sdvg_block_attn_workspace_bytes tells the
- * need beforehand, and SDVG_SPLIT_NEVER needs none. SDVG_SPLIT_AUTO splits from 60 % idle slots on
- * here, not from a quarter on. Every call on a GPU uses that GPU's one
+ * holds returns SDVG_ERR_RANGE (nothing is launched). Only SDVG_SPLIT_ALWAYS can need that much:
+ * sdvg_block_attn_workspace_bytes with SDVG_SPLIT_ALWAYS tells the need beforehand. SDVG_SPLIT_NEVER
+ * needs none. SDVG_SPLIT_AUTO splits from 60 % idle slots on here, not from a quarter on, and always
+ * fits the array on a GPU with 256 compute units; what sdvg_block_attn_workspace_bytes returns for
+ * SDVG_SPLIT_AUTO holds for sdvg_block_attn_batch alone and may be more than the limit where this call
+ * does not split. Every call on a GPU uses that GPU's one
  * array: calls that overlap in time on one GPU (different streams or threads) race -- serialise
  * them, or use sdvg_block_attn_batch with workspaces of their own. Nothing in the array has to
  * be cleared between calls: each call writes every partial result it later reads.
@@ -173,9 +176,11 @@ int sdvg_block_attn_batch_static(const sdvg_attn_desc *desc, int32_t n_items, co
 int64_t sdvg_block_attn_static_workspace_limit(void);
 
 /*
- * Bytes of workspace with which sdvg_block_attn_batch would split keys for this shape and
- * split_mode on the current device; 0 if it would not split (then no workspace is needed).
- * Negative sdvg_status on a bad descriptor.
+ * Bytes of workspace with which sdvg_block_attn_batch may split keys for this shape and
+ * split_mode on the current device; 0 if it would not split (then no workspace is needed). From 60 %
+ * idle workgroup slots on, the size under SDVG_SPLIT_AUTO is that of the split, taken or not. On 256
+ * compute units at most 277 MB, under SDVG_SPLIT_AUTO 182 MB. Negative sdvg_status on a bad
+ * descriptor.
  */
 int64_t sdvg_block_attn_workspace_bytes(const sdvg_attn_desc *desc, int32_t n_items, int64_t cache_len,
                                         int32_t split_mode);

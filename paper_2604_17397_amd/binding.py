@@ -279,7 +279,7 @@ def _desc_key(d):
 
 def block_attn_workspace_bytes(q, k_cache, v_cache, k_blk, v_blk, cache_len, n_items=1, split="auto", scale=None):
     """sdvg_block_attn_workspace_bytes for the shape of these tensors; split is "never", "auto" or
-    "always"."""
+    "always". For block_attn_batch; of block_attn_batch_static it tells the need under "always" only."""
     cache_len = int(cache_len)
     d = _attn_desc(q, k_cache, v_cache, k_blk, v_blk, cache_len, q, scale)
     n = lib().sdvg_block_attn_workspace_bytes(ctypes.byref(d), int(n_items), cache_len, _SPLIT[split])

@@ -64,6 +64,7 @@ def _plan_library():
     lib.attn_plan.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64, ctypes.c_int, ctypes.c_int,
                                                    ctypes.POINTER(ctypes.c_int64)]
     lib.attn_plan.restype = None
+    lib.attn_plan_static_workspace.restype = ctypes.c_int64
     return lib
 
 
@@ -82,3 +83,8 @@ def attn_plan_rows(n_heads, n_q, n_k, n_items=1, split=0, n_cu=None, rows32_ok=1
     if n_cu is None:
         n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     return _plan_library().attn_plan_rows(n_items, n_q, n_heads, ctypes.c_int64(n_k), n_cu, split, rows32_ok)
+
+
+def attn_plan_static_workspace(n_heads, n_q, n_k, n_items=1, split=1, n_cu=MI355X_CUS):
+    """Bytes of the library's own array that sdvg_block_attn_batch_static needs for such a launch."""
+    return _plan_library().attn_plan_static_workspace(n_items, n_q, n_heads, ctypes.c_int64(n_k), n_cu, split)

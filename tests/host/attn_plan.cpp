@@ -11,6 +11,11 @@ extern "C" void attn_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_
   out[4] = p.workspace_bytes;
 }
 
+// Workspace of the call that uses the library's own array.
+extern "C" int64_t attn_plan_static_workspace(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode) {
+  return sdvg::make_plan(n_items, n_q, n_heads, n_k, n_cu, split_mode, true, sdvg::kAutoIdleStatic).workspace_bytes;
+}
+
 extern "C" int attn_plan_rows(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, int rows32_ok) {
   return sdvg::make_plan(n_items, n_q, n_heads, n_k, n_cu, split_mode, rows32_ok != 0).rows;
 }

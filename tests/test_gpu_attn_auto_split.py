@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import BF16_MAX_ABS, BF16_REL_RMS, MI355X_CUS, attn_errors, attn_plan, bits_of
+from gpu_util import BF16_MAX_ABS, BF16_REL_RMS, MI355X_CUS, attn_errors, attn_plan, attn_plan_static_workspace, bits_of
 
 
 def test_auto_plan_with_a_quarter_to_60_percent_idle():
@@ -13,6 +13,21 @@ def test_auto_plan_with_a_quarter_to_60_percent_idle():
         assert plan(*args).split and plan(*args) == plan(*args, split=2)
     for args in [(11, 4680, 32760), (12, 4680, 14040), (5, 4680, 14040, 2), (20, 4680, 18720), (5, 2383, 7149, 3)]:
         assert not plan(*args).split and plan(*args).workspace == 0
+
+
+def test_need_of_the_static_call():
+    """The query's answer under AUTO is the batch call's: where only that one splits it exceeds the static call's array,
+    of which the static call needs nothing. Under ALWAYS the two agree, and under AUTO the static call always fits."""
+    limit = 64 << 20
+    assert attn_plan(14, 4680, 9360, split=1, n_cu=MI355X_CUS).workspace == 104620032 > limit
+    assert attn_plan_static_workspace(14, 4680, 9360) == 0
+    for H in list(range(1, 41)) + [257]:
+        for n_q in (256, 312, 1031, 1560, 2300, 3100, 4404, 4641, 4680):
+            for n_k, n_items in ((n_q, 1), (3 * n_q, 2), (7 * n_q, 1), (65536, 1), (9360, 8)):
+                always = attn_plan(H, n_q, n_k, n_items=n_items, split=2, n_cu=MI355X_CUS).workspace
+                auto = attn_plan(H, n_q, n_k, n_items=n_items, split=1, n_cu=MI355X_CUS).workspace
+                assert attn_plan_static_workspace(H, n_q, n_k, n_items, split=2) == always <= 277 * 10**6
+                assert auto <= 182 * 10**6 and attn_plan_static_workspace(H, n_q, n_k, n_items) <= min(limit, always)
 
 
 @pytest.mark.gpu
