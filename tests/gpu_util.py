@@ -48,7 +48,7 @@ BF16_REL_RMS = 1e-2
 F32_MAX_ABS = 1e-4
 
 
-Plan = collections.namedtuple("Plan", "groups workgroups query_tiles split workspace")
+Plan = collections.namedtuple("Plan", "groups rows workgroups query_tiles split workspace")
 MI355X_CUS = 256
 
 
@@ -70,10 +70,11 @@ def _plan_library():
 
 def attn_plan(n_heads, n_q, n_k, n_items=1, split=0, n_cu=None):
     """How a bf16 attention launch is cut into workgroups, from the library's own plan header, compiled
-    here: `groups` is 1 for the kernel of 256 rows per workgroup, 2 or 4 for the one with key groups."""
+    here: `groups` is 1 for the kernel of 256 rows per workgroup, 2 or 4 for the one with key groups. With 4 groups
+    `rows` tells the kernel: 64 that one, 32 the one for the smallest launches."""
     if n_cu is None:
         n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    out = (ctypes.c_int64 * 5)()
+    out = (ctypes.c_int64 * 6)()
     _plan_library().attn_plan(n_items, n_q, n_heads, n_k, n_cu, split, out)
     return Plan(*out)
 

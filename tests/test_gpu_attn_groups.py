@@ -1,6 +1,7 @@
 """GPU parity of the bf16 attention kernels by kernel: the one whose workgroups own 256 query rows (1
 group) and the one that splits a workgroup's keys over 2 or 4 groups of waves (few query rows), against
-the fp64 oracle. Tile and seam edges, a group past the last tile, a running maximum that rises late or
+the fp64 oracle. Where a few heads take 4 groups here, the launch is so small that the 32-row kernel runs
+it (`rows`); the 64-row kernel of 4 groups has the same cases in test_gpu_attn_rows32.py. Tile and seam edges, a group past the last tile, a running maximum that rises late or
 lives in one group only, masked first tiles, infinite values, strides, scale, fused commit. The launch
 plan decides which kernel runs, so every case asks it and asserts the answer.
 The bounds are the bf16 path's (probabilities and output rounded to bf16, fp32 sums)."""
@@ -145,13 +146,14 @@ def test_strides_scale_and_commit_by_kernel(groups, n_q, head_major, jitter, sca
     run_planned(groups, n_q, 333, 0, seed=651, head_major=head_major, jitter=jitter, scale=scale, commit=True)
 
 
-# The 4-group kernel takes the same profiles from 2 heads x 70 rows in test_gpu_attn.py.
+# The 32-row kernel takes the same profiles from 2 heads x 70 rows in test_gpu_attn.py, the 64-row kernel with 4 groups
+# in test_gpu_attn_rows32.py.
 @pytest.mark.gpu
 @pytest.mark.parametrize("groups,n_q", [(2, 70), (1, 200)])
 @pytest.mark.parametrize("pattern", ["rising", "falling", "spike_last"])
 @pytest.mark.parametrize("amp", [8.0, 40.0, 150.0])
 def test_score_profiles_by_kernel(groups, n_q, pattern, amp):
-    assert attn_plan(2, 70, 700).groups == 4 and attn_plan(HEADS[groups], n_q, 700).groups == groups
+    assert attn_plan(2, 70, 700).rows == 32 and attn_plan(HEADS[groups], n_q, 700).groups == groups
     max_abs, rel = structured_case(pattern, n_q=n_q, H=HEADS[groups], amp=amp)
     assert max_abs <= BF16_MAX_ABS and rel <= BF16_REL_RMS, (max_abs, rel)
 
@@ -160,12 +162,16 @@ def test_score_profiles_by_kernel(groups, n_q, pattern, amp):
 @pytest.mark.parametrize("groups", [4, 2])
 @pytest.mark.parametrize("n_k,hot", [(300, 299), (300, 0), (300, 40), (1100, 1099), (1100, 700)])
 def test_maximum_in_one_group_only(n_k, hot, groups):
+    maximum_in_one_group_only({4: 2, 2: 129}[groups], 70, n_k, hot, rows={4: 32, 2: 128}[groups])
+
+
+def maximum_in_one_group_only(H, n_q, n_k, hot, rows):
     """One key's score towers above the others (by 2^40 in the softmax), so that the other groups'
     shares of the merge vanish; rows below a gain of 1 stay diffuse."""
     import paper_2604_17397_amd as P
     rng = np.random.default_rng(3)
-    H, n_q, c_len = {4: 2, 2: 129}[groups], 70, 123
-    assert attn_plan(H, n_q, n_k).groups == groups
+    c_len = 123
+    assert attn_plan(H, n_q, n_k).rows == rows
     u = rng.standard_normal(128)
     u /= np.linalg.norm(u)
     q = np.linspace(0.0, 25.0, n_q)[:, None, None] * u[None, None, :].repeat(H, 1)
@@ -183,11 +189,15 @@ def test_maximum_in_one_group_only(n_k, hot, groups):
 
 @pytest.mark.gpu
 def test_nan_and_infinite_values_reach_the_rows_that_use_them():
+    nan_and_infinite_values(2, 100, rows=32)
+
+
+def nan_and_infinite_values(H, n_q, rows):
     """A NaN query row is NaN, its neighbours are not; an infinite value is infinite where its weight
     is positive and leaves the other dims alone."""
     import paper_2604_17397_amd as P
-    assert attn_plan(2, 100, 230).groups == 4
-    q, kc, vc, kb, vb = si.attn_inputs(2, 100, 130, seed=77)
+    assert attn_plan(H, n_q, 130 + n_q).rows == rows
+    q, kc, vc, kb, vb = si.attn_inputs(H, n_q, 130, seed=77)
     dev = [to_dev_bf16(a) for a in (q, kc, vc, kb, vb)]
     dev[0][7, 1] = float("nan")
     dev[2][50, 0, 5] = float("inf")
@@ -200,7 +210,7 @@ def test_nan_and_infinite_values_reach_the_rows_that_use_them():
 
 # ---------------------------------------------------------------- masked keys, infinite values
 
-# (heads, query rows): 3 x 70 rows take 4 groups of 32-key tiles at 936 keys, 36 x 449 rows 2 of 64
+# (heads, query rows): 3 x 70 rows take 4 groups of 32-key tiles at 936 keys (the 32-row kernel), 36 x 449 rows 2 of 64
 SHAPES = {4: (3, 70), 2: (36, 449)}
 N_K = 936
 

@@ -8,7 +8,8 @@ import pytest
 import torch
 
 import test_gpu_attn_groups as by_groups
-from gpu_util import MI355X_CUS, attn_plan_rows
+from gpu_util import BF16_MAX_ABS, BF16_REL_RMS, MI355X_CUS, attn_plan_rows
+from test_gpu_attn import structured_case
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # 3 heads are one round of 32-row workgroups; 129 heads x 33 .. 64 rows are two, and one of 64 rows
@@ -64,11 +65,43 @@ def test_edges_of_the_64_row_kernel(monkeypatch, n_k):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("lo,hi,value", [(0, 32, float("-inf")), (32, 128, -1e9), (0, 128, float("-inf")), (904, 936, -1e30)])
+@pytest.mark.parametrize("lo,hi,value", by_groups.MASKED)
 def test_masked_first_tiles_of_the_64_row_kernel(monkeypatch, lo, hi, value):
     monkeypatch.setitem(by_groups.SHAPES, 4, (129, 64))
     assert attn_plan_rows(129, 64, by_groups.N_K) == 64
     by_groups.test_masked_first_tiles(4, lo, hi, value)
+
+
+# A maximum that rises from tile to tile (the rescaling in the loop), falls, or comes with the last key
+@pytest.mark.gpu
+@pytest.mark.parametrize("pattern", ["rising", "falling", "spike_last"])
+@pytest.mark.parametrize("amp", [8.0, 40.0, 150.0])
+def test_score_profiles_of_the_64_row_kernel(pattern, amp):
+    assert attn_plan_rows(129, 63, 700) == 64
+    max_abs, rel = structured_case(pattern, n_q=63, H=129, amp=amp)
+    assert max_abs <= BF16_MAX_ABS and rel <= BF16_REL_RMS, (max_abs, rel)
+
+
+# Every group in turn (32-key tiles 0, 1, 2 and 3 of a round), the first round, the last and one between
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_k,hot", [(300, 299), (300, 0), (300, 40), (300, 70), (300, 100), (1100, 1099), (1100, 700)])
+def test_maximum_in_one_group_of_the_64_row_kernel(n_k, hot):
+    by_groups.maximum_in_one_group_only(129, 64, n_k, hot, rows=64)
+
+
+@pytest.mark.gpu
+def test_nan_and_infinite_values_in_the_64_row_kernel():
+    by_groups.nan_and_infinite_values(129, 64, rows=64)
+
+
+# Groups 2 and 3 (320 keys), or group 3 alone (352), have no tile in the last round
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_k", [320, 352])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_infinite_value_in_the_last_key_of_the_64_row_kernel(monkeypatch, n_k, value):
+    monkeypatch.setitem(by_groups.SHAPES, 4, (129, 64))
+    assert attn_plan_rows(129, 64, n_k) == 64
+    by_groups.test_infinite_value_in_the_last_key(4, n_k, value)
 
 
 # Short tiles repeat their last key; here both have one: the cache's ends at 218 keys, the block's at 70.
