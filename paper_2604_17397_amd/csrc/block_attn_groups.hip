@@ -131,24 +131,32 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     for (int u = 0; u < C::kCopies; ++u) dma16(k_ptr[u], k_dst + u * R * 1024);
     k_dst += C::kTile;
   };
-  copy_k(0);
-  // The query rows (rows past the end re-read the last one and are not stored): 4 R per wave.
-  const int wt_count = ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem);
-  const int wt_first = ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem);
+  int wt_count, wt_first;  // (computed behind the first copies)
+  ix::group_start_steps([&](auto what) __attribute__((always_inline)) {
+    if constexpr (what == ix::kStartK0) {
+      copy_k(0);
+    } else if constexpr (what == ix::kStartQ) {
+      // The query rows (rows past the end re-read the last one and are not stored): 4 R per wave.
+      wt_count = ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem);
+      wt_first = ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem);
 #pragma unroll 1
-  for (int r = 0; r < R; ++r) {
-    const int row = 4 * wave + (lane >> 4), q_row = (wt_first + r) * 32 + row;
-    dma16(static_cast<const uint16_t *>(it.q) + (q_row < p.n_q ? q_row : p.n_q - 1) * p.q_ts + head * p.q_hs +
-              ix::swizzled_chunk(row, lane, 0) * 8,
-          lds_addr0 + ix::group_query_tile<G>(r) + wave * 1024);
-  }
+      for (int r = 0; r < R; ++r) {
+        const int row = 4 * wave + (lane >> 4), q_row = (wt_first + r) * 32 + row;
+        dma16(static_cast<const uint16_t *>(it.q) + (q_row < p.n_q ? q_row : p.n_q - 1) * p.q_ts + head * p.q_hs +
+                  ix::swizzled_chunk(row, lane, 0) * 8,
+              lds_addr0 + ix::group_query_tile<G>(r) + wave * 1024);
+      }
+    } else if constexpr (what == ix::kStartK1K2) {
 #pragma unroll 1
-  for (int i = 1; i < 3; ++i) copy_k(i);
-  k_dst = k_dst0;  // slot of K(3)
-  set_v_ptrs(tile_of(0));
+      for (int i = 1; i < 3; ++i) copy_k(i);
+      k_dst = k_dst0;  // slot of K(3)
+    } else {
+      set_v_ptrs(tile_of(0));
 #pragma unroll
-  for (int u = 0; u < C::kCopies; ++u) dma16(v_ptr[u], v_dst + u * R * 1024);
-  v_dst += C::kTile;  // slot of V(1)
+      for (int u = 0; u < C::kCopies; ++u) dma16(v_ptr[u], v_dst + u * R * 1024);
+      v_dst += C::kTile;  // slot of V(1)
+    }
+  });
 
   // ---- LDS read addresses (bytes), with the group's part of the LDS and the slot folded in
   uint32_t k_off[8], v_off[4];

@@ -2,6 +2,11 @@
 // block_attn_index.h (key streams, swizzle, operand reads, work distribution); plain integer and
 // pointer arithmetic, compiled into the kernel and into tests/host/attn_groups_replay.cpp.
 #pragma once
+#include <stddef.h>
+
+#include <type_traits>
+#include <utility>
+
 #include "block_attn_index.h"
 
 namespace sdvg {
@@ -23,22 +28,44 @@ struct Groups {
   static constexpr int kVariants = kCopies < 16 / (4 * kRowWaves) ? kCopies : 16 / (4 * kRowWaves);
 };
 
-// What a wave starts before the loop, in this order: K(0), its share of the query rows, K(1), K(2), V(0). How many
-// of these copies may still be under way at the barrier ahead of the first scores (which read K(0) and the query rows),
-// and at the barrier of the common maximum: behind that one the first operands of K(1) are read, before
-// the loop's first wait and barrier.
-enum GroupStart { kStartK0, kStartQ, kStartK1, kStartK2, kStartV0 };
+// What a wave starts before the loop: K(0), its share of the query rows, K(1) and then K(2), V(0). The kernel goes through
+// kGroupStart, and copies land in the order in which they were started. How many may still be under way at the
+// barrier ahead of the first scores (which read K(0) and the query rows), and at the barrier of the common maximum:
+// behind that one the first operands of K(1) are read, before the loop's first wait and barrier.
+enum GroupStart { kStartK0, kStartQ, kStartK1K2, kStartV0 };
+constexpr GroupStart kGroupStart[] = {kStartK0, kStartQ, kStartK1K2, kStartV0};
 template <int G>
 SDVG_HD constexpr int group_start_copies(GroupStart what) {
-  return what == kStartQ ? Groups<G>::kRowWaves : Groups<G>::kCopies;
+  return what == kStartQ ? Groups<G>::kRowWaves : what == kStartK1K2 ? 2 * Groups<G>::kCopies : Groups<G>::kCopies;
+}
+// Copies started behind `what`.
+template <int G>
+SDVG_HD constexpr int group_started_after(GroupStart what) {
+  int n = 0;
+  bool behind = false;
+  for (GroupStart w : kGroupStart) {
+    if (behind) n += group_start_copies<G>(w);
+    behind = behind || w == what;
+  }
+  return n;
 }
 template <int G>
 SDVG_HD constexpr int group_left_at_scores() {
-  return group_start_copies<G>(kStartK1) + group_start_copies<G>(kStartK2) + group_start_copies<G>(kStartV0);
+  const int k0 = group_started_after<G>(kStartK0), q = group_started_after<G>(kStartQ);
+  return k0 < q ? k0 : q;
 }
 template <int G>
 SDVG_HD constexpr int group_left_at_maximum() {
-  return group_start_copies<G>(kStartK2) + group_start_copies<G>(kStartV0);
+  return group_started_after<G>(kStartK1K2) + Groups<G>::kCopies;  // (and K(2))
+}
+// Calls f with every step of kGroupStart as a constant, in order.
+template <class F, size_t... N>
+SDVG_HD void group_start_steps(F f, std::index_sequence<N...>) {
+  (f(std::integral_constant<GroupStart, kGroupStart[N]>{}), ...);
+}
+template <class F>
+SDVG_HD void group_start_steps(F f) {
+  group_start_steps(f, std::make_index_sequence<sizeof(kGroupStart) / sizeof(kGroupStart[0])>{});
 }
 
 // Rows and bytes of copy u of row wave wr: lane i moves physical chunk i % 16 of tile row

@@ -159,20 +159,33 @@ long sweep(int &bad) {
 
 }  // namespace
 
-// The waits ahead of the loop: copies land in the order in which they were started, so what has landed at a
-// wait that leaves n under way is all but the last n.
+// The counts of the two waits ahead of the loop against the order in which the kernel starts its copies (kGroupStart):
+// what has landed at a wait that leaves n under way is all but the last n. Which operands are read behind which
+// barrier is the kernel's own affair; test_second_tile_has_landed_when_it_is_read looks at that on the GPU.
 template <int G>
 bool start_waits() {
-  std::vector<ix::GroupStart> order;
-  for (ix::GroupStart w : {ix::kStartK0, ix::kStartQ, ix::kStartK1, ix::kStartK2, ix::kStartV0})
-    order.insert(order.end(), ix::group_start_copies<G>(w), w);
-  auto landed = [&](ix::GroupStart w, int left) {
-    for (size_t i = order.size() - left; i < order.size(); ++i)
-      if (order[i] == w) return false;
-    return true;
+  enum Tile { kK0, kQ, kK1, kK2, kV0 };
+  std::vector<Tile> order;
+  ix::group_start_steps([&](auto what) {
+    const int n = ix::group_start_copies<G>(what);
+    switch (what) {
+      case ix::kStartK0: order.insert(order.end(), n, kK0); break;
+      case ix::kStartQ: order.insert(order.end(), n, kQ); break;
+      case ix::kStartK1K2: order.insert(order.end(), n / 2, kK1), order.insert(order.end(), n / 2, kK2); break;
+      case ix::kStartV0: order.insert(order.end(), n, kV0); break;
+    }
+  });
+  auto landed = [&](Tile t, int left) {
+    bool started = false;
+    for (size_t i = 0; i < order.size(); ++i) {
+      if (order[i] != t) continue;
+      if (i + left >= order.size()) return false;
+      started = true;
+    }
+    return started;
   };
-  return landed(ix::kStartK0, ix::group_left_at_scores<G>()) && landed(ix::kStartQ, ix::group_left_at_scores<G>()) &&
-         landed(ix::kStartK1, ix::group_left_at_maximum<G>());
+  return landed(kK0, ix::group_left_at_scores<G>()) && landed(kQ, ix::group_left_at_scores<G>()) &&
+         landed(kK1, ix::group_left_at_maximum<G>());
 }
 
 int main() {
