@@ -28,13 +28,13 @@
 //   a shorter way in and out (below)                                                 49
 // (Arguments of the first copies preloaded into registers, as in block_attn_rows32.hip: no gain. 64 rows per wave, every
 // wave with key tiles of its own, which halves the LDS reads and needs no barrier: 53, bound by the copies.)
-// What bounds it there, by counters: the matrix pipes are busy in about half of the SIMD cycles of the
-// compute units at work (2 groups 64 %, the 256-row kernel 84 %). With the copies, the softmax or the MFMAs
+// What bounds it there, by counters: the matrix pipes are busy in 52 % of the SIMD cycles of the
+// compute units at work (2 groups 66 %, the 256-row kernel 84 %). With the copies, the softmax or the MFMAs
 // left out (not a result, a timing) a launch is 3, 7 and 11 % shorter: no unit is the limit, but the
 // hand-over between the phases, some 250 cycles for every 16 MFMAs (512 cycles) of a group's 32-key tile.
 // The way in and out: all arguments asked for at once, the work index by multiplication, the query rows
 // through the LDS, the first scores as soon as K(0) and those rows have landed, the merge by whole rows (16
-// lanes store 256 bytes side by side) take 2.0 to 2.6 us off every launch, us before / after:
+// lanes store 256 bytes side by side) take 2.4 to 2.9 us off every launch, us before / after:
 //   2 groups  24 heads x 1031 x 1031 keys 23.7 / 21.0   12 x 1560 x 4680 56.1 / 53.7   36 x 449 x 898 20.8 / 18.1
 //   4 groups  12 x 1031 x 1031            17.0 / 14.5   8 x 1024 x 6144 45.6 / 43.1    12 x 1031 x 6186 52.0 / 49.1
 #include "block_attn_device.h"
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::rows32_merge_offset(4 * u + g, hh, r32)) =
+      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::merge_offset(4 * u + g, hh, r32)) =
           f32x4{o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
   const float l_row = lane_sum32(l_run);
   if (hh == 0) *(lds_f32x2 *)static_cast<uintptr_t>(lds_addr0 + kMergeSums + (wave * 32 + r32) * 8) = f32x2{l_row, s_shift};
@@ -454,8 +454,8 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       const float factor = __builtin_amdgcn_exp2f((shift_min - shift_g[g]) * p.scale_log2e);
       l_sum += factor * l_g[g];
       const uint32_t from = lds_addr0 + (g * R + r) * 32 * 512;
-      const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(from + ix::rows32_merge_offset(c, 0, row));
-      const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(from + ix::rows32_merge_offset(c, 1, row));
+      const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(from + ix::merge_offset(c, 0, row));
+      const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(from + ix::merge_offset(c, 1, row));
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         o_lo[e] += factor * lo[e];

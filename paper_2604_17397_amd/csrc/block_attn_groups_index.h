@@ -129,10 +129,10 @@ SDVG_HD const char *group_key_ptr(const Streams &s, const LaneBase &b, int j) {
                                             (in_cache ? s.kv_tsb : s.blk_tsb));
 }
 
-// Where the merge keeps O: the 16 bytes holding dims 8 c + 4 hh .. + 3 of a row, in the part of the wave
+// Where the merge (of the 32-row kernel too) keeps O: the 16 bytes holding dims 8 c + 4 hh .. + 3 of a row, in the part of the wave
 // they come from. The row is turned by c so that 16 lanes that read one row's chunks c = 0 .. 15 touch
 // every bank once.
-SDVG_HD int rows32_merge_offset(int c, int hh, int row) { return (c * 64 + hh * 32 + (row ^ c)) * 16; }
+SDVG_HD int merge_offset(int c, int hh, int row) { return (c * 64 + hh * 32 + (row ^ c)) * 16; }
 
 }  // namespace attn_index
 }  // namespace sdvg

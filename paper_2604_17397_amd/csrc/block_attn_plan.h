@@ -29,22 +29,23 @@ struct Plan {
 
 // Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
 // compute units, times a fixed part plus the key tiles each group walks.
-// Measured on MI355X, us (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
-//   12 heads x 312 x 936 keys [24/36/60] 25.6 / 17.1 / 12.8; 12 x 1031 x 6186 [60/108/204] 113 / 68 / 51;
-//   12 x 1560 x 4680 [84/156/300] 87 / 54 / 76; 5 x 4680 x 32760 [95/185/370] 518 / 365 / 447;
-//   40 x 1031 x 3093 [200/360/680] 71 / 82 / 83; 16 x 4680 x 14040 [304/592/1184] 579 / 513 / 547;
-//   12 x 4680 x 14040 [228/444/888] 335 / 356 / 427; 1 x 8 x 8 [1/1/1] 5.4 / 7.2 / 6.5.
+// Measured on MI355X, us among others in a graph (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
+//   12 heads x 312 x 936 keys [24/36/60] 26.4 / 17.8 / 13.4; 12 x 1031 x 6186 [60/108/204] 107 / 65 / 50;
+//   12 x 1560 x 4680 [84/156/300] 85 / 53 / 75; 5 x 4680 x 32760 [95/185/370] 529 / 374 / 494;
+//   40 x 1031 x 3093 [200/360/680] 74 / 90 / 101; 16 x 4680 x 14040 [304/592/1184] 587 / 522 / 586;
+//   12 x 4680 x 14040 [228/444/888] 335 / 360 / 474.
 // A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value, and
-// the estimate is up to 25 % off in absolute terms; what counts is the order. Over 2 to 40 heads, 312
-// to 4680 rows and 1 to 7 blocks of keys it was within 1.4 % of the fastest of the four in each of 87
-// launches drawn at random. Up to 192 keys it stays with 1 group, where 4 are faster from 65 rows on (250
-// rows x 128 keys, before the grouped kernels' way in was shortened: 11.7 / 9.3 / 7.8).
+// the estimate is up to 25 % off in absolute terms; what counts is the order. Over 1 to 40 heads, 156
+// to 4680 rows and 193 to 32760 keys it is within 1.7 % of the fastest of the four in each of 299 launches
+// (profiles/attn_plan_sweep.txt, as the other figures here). Up to 192 keys it stays with 1 group, where more are
+// faster (3 heads x 250 rows x 128 keys 11.9 / 7.1 / 6.0).
 // Of the launches of four groups, those whose 32-row workgroups need no more rounds than 64-row ones take the kernel
 // where the two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32). One round, us
-// with 64 / 32 rows: 12 x 312 x 936 13.5 / 10.7; 16 x 500 x 1000 13.6 / 11.6; 8 x 1024 x 6144 43.9 / 37.8. More rounds with as
-// many workgroups (up to 32 rows): 300 x 32 x 512 24.4 / 22.5; 259 x 1 x 936 34.2 / 32.9. In a round more than with 64
-// rows every workgroup walks all keys again: 12 x 1031 x 1031 15.1 / 20.9; 320 x 33 x 256 16.3 / 19.8; 300 x 64 x
-// 256 17.1 / 17.9.
+// with 64 / 32 rows: 12 x 312 x 936 13.5 / 10.6; 16 x 500 x 1000 14.4 / 12.2; 8 x 1024 x 6144 45.9 / 39.3, with keys from
+// HBM 64.0 / 46.3. (4 x 2000 x 14000 loses, 90.5 / 99.0, where the memory-side cache holds the layer's 29 MB; the layers of
+// a model of this size come from HBM, 132 / 96.) More rounds with as many workgroups (up to 32 rows): 300 x 32 x 512
+// 24.6 / 22.7; 259 x 1 x 936 34.7 / 33.2. In a round more than with 64 rows every workgroup walks all keys again:
+// 12 x 1031 x 1031 15.4 / 21.0; 320 x 33 x 256 16.8 / 20.3; 300 x 64 x 256 17.7 / 18.5.
 struct Groups {
   int groups, rows;
   double us;  // the estimate
@@ -97,9 +98,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
   // a chip that is only partly busy clocks higher. Measured on MI355X, us plain / split, at 4680 rows:
-  //   11 % idle  12 heads x 14040 keys 335 / 356, x 32760 761 / 783, 24 x 14040 666 / 702
-  //   18 - 26 %  11 x 32760 723 / 716, 2 items x 5 heads x 32760 666 / 648, x 14040 298 / 297, 20 x 18720 769 / 770
-  //   33 - 48 %  9 x 32760 622 / 576, 8 x 32760 610 / 525, 8 x 14040 283 / 245, 14 x 23400 844 / 686
+  //   11 % idle  12 heads x 14040 keys 335 / 351, x 32760 761 / 774, 24 x 14040 661 / 692
+  //   18 - 26 %  11 x 32760 728 / 710, 20 x 18720 758 / 763
+  //   33 - 48 %  9 x 32760 629 / 576, 8 x 32760 618 / 526, 8 x 14040 259 / 243, 14 x 23400 843 / 664
   // From kAutoIdle on the estimates decide (below).
   if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
   if (split_mode == SDVG_SPLIT_AUTO && idle < auto_idle) return plain();
@@ -110,11 +111,11 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   pl.total_wg = static_cast<int>((all + pl.units - 1) / pl.units);
   pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * kPartialFloats * 4;
   // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
-  // key groups, us: 1 head x 4680 x 32760 93 / 184, 5 heads 329 / 363; 4 x 4680 x 14040 128 / 141,
-  // 5 heads 157 / 159; 12 x 1560 x 4680 63 / 56, 16 x 1031 x 3093 49 / 41, 3 x 4680 x 4680 55 / 44.
+  // unsplit, us: 1 head x 4680 x 32760 93 / 149, 5 heads 346 / 374; 4 x 4680 x 14040 132 / 141,
+  // 5 heads 160 / 162; 12 x 1560 x 4680 63 / 53, 16 x 1031 x 3093 49 / 38, 3 x 4680 x 4680 56 / 40.
   // Below 60 % idle the unsplit estimate, made for a full chip, is a little high for one that is half busy: the split
-  // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (up to 40 heads, 312 to 4680 rows, 1 to 7
-  // blocks of keys) 32 were split, 1 to 21 % faster each; 10 more would have gained 4 to 10 %.
+  // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (1 to 3 items, up to 40 heads, 312 to 4680 rows,
+  // 1 to 7 blocks of keys) 31 are split, 3 to 20 % faster each; 13 more would have gained 4 to 14 %.
   const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(pl.units);
   const bool few = idle >= kAutoIdleStatic;
   if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us + (few ? 0.0 : 11.0)) {

@@ -2,7 +2,8 @@
 //
 // Same operation and same arithmetic per 32 rows x 32 keys as block_attn_groups.hip with 4 groups (paper
 // Sec. 1 / Sec. 4.1 "Models"), for launches whose 32-row workgroups fit one round of the compute units, or need no
-// more rounds than 64-row ones (block_attn_plan.h). There a launch is a chain of latencies, and the chain is what this kernel cuts:
+// more rounds than 64-row ones (block_attn_plan.h). There a launch is a chain of latencies, and the chain is what this
+// kernel cuts:
 //   - 32 query rows per workgroup and all 8 waves on different key tiles: twice the workgroups of the 64-row
 //     kernel, half the tiles per wave;
 //   - a wave copies its tiles into its own part of the LDS and reads nothing else there, so the loop has no
@@ -13,9 +14,11 @@
 //     them with one write of M0, where the 64-bit address of every row costs some ten vector instructions;
 //   - the arguments of the first copies are in registers when a wave starts, all others are asked for at once
 //     behind those copies; the query rows come through the LDS once per workgroup.
-// 12 heads x 312 x 936 keys takes 9.6 us a call; it took 10.0, or 9.2 among others in a graph (14.6 with 64 rows, 25.6 with
-// 256), while the first copies waited for their arguments: 0.9 launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1 merge and store;
-// 12 x 312 x 312 6.0 (10.3), 8 x 1024 x 6144 35.5 (41.4).
+// us among others in a graph, four sets of tensors in turn, with 64 rows / here (profiles/attn_plan_sweep.txt): 12 heads x 312 x
+// 936 keys 13.5 / 10.6, 12 x 312 x 312 8.7 / 6.6, 8 x 1024 x 6144 45.9 / 39.3; with keys from HBM 15.6 / 12.6, 9.9 / 7.3, 64.0 / 46.3.
+// Where it went at 12 x 312 x 936 while the first copies still waited 0.3 us for their arguments (9.2 us with one set of tensors
+// again and again): 0.9 launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1
+// merge and store.
 // The loop is bound by the copies: 8 waves bring 128 KB per 8 x 32 keys, which takes 1.13 - 1.18 us, and a
 // loop of nothing but such copies from L2 reaches 62 bytes per clock and compute unit, 1.13 us. So
 // neither fewer scalar instructions (1 %), nor the copies placed before the products (1 % slower), nor
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
     for (int g = 0; g < 4; ++g) {
       const int c = 4 * u + g;
       const f32x4 o4 = {o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
-      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::rows32_merge_offset(c, hh, r32)) = o4;
+      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::merge_offset(c, hh, r32)) = o4;
     }
   const float l_row = lane_sum32(l_run);
   if (hh == 0) *(lds_f32x2 *)static_cast<uintptr_t>(lds0 + R::kQ + (wave * 32 + r32) * 8) = f32x2{l_row, s_shift};
@@ -347,8 +350,8 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   for (int w = 0; w < ix::kWaves; ++w) {
     const float factor = __builtin_amdgcn_exp2f((shift_min - shift_w[w]) * p.scale_log2e);
     l_sum += factor * l_w[w];
-    const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::rows32_merge_offset(c, 0, row));
-    const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::rows32_merge_offset(c, 1, row));
+    const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::merge_offset(c, 0, row));
+    const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::merge_offset(c, 1, row));
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       o_lo[e] += factor * lo[e];

@@ -131,7 +131,7 @@ int main() {
   std::vector<char> hit(R::kWavePart / 16, 0);
   for (int c = 0; c < 16; ++c)
     for (int hh = 0; hh < 2; ++hh)
-      for (int row = 0; row < 32; ++row) hit[ix::rows32_merge_offset(c, hh, row) / 16]++;
+      for (int row = 0; row < 32; ++row) hit[ix::merge_offset(c, hh, row) / 16]++;
   for (char h : hit) bad += h != 1;
   if (bad) return 1;
   std::printf("ok: %ld configurations\n", n);
