@@ -49,8 +49,16 @@ using ix::kVBase;      // the V ring follows the K ring
 using sdvg::Plan;
 using sdvg::make_plan;
 
-// kSplit = false: one piece per workgroup (one query tile with all its key tiles; the hot case).
-// kSplit = true: the workgroup's run may hold several pieces, taken in a loop.
+// ---- partial results of a key split. A wave's part of a slot: its accumulators, 16 groups of 4 floats per lane, then
+// 32 row sums and 32 shifts (minus the running maximum).
+constexpr int kWavePartial = 66 * 64;
+static_assert(ix::kWaves * kWavePartial == sdvg::kPartialFloats, "");
+__device__ __forceinline__ float *partial_of(const AttnParams &p, int slot, int wave) {
+  return p.partials + static_cast<int64_t>(slot) * sdvg::kPartialFloats + wave * kWavePartial;
+}
+
+// kSplit = false: a workgroup takes one query tile with all its key tiles (the hot case).
+// kSplit = true: a workgroup takes pieces of the key tiles (block_attn_index.h, "key split"), in a loop.
 template <bool kSplit>
 __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -73,20 +81,13 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
 #pragma unroll
   for (int db = 0; db < 4; ++db) v_off[db] = kVBase + ix::v_read_offset(lane, 0, db, 0);
 
-  // ---- this workgroup's run of (query tile, key tile) pairs (block_attn_index.h, "key split").
-  // Normally the run is exactly one query tile with all its key tiles; when the keys are split it
-  // may end one query tile and begin the next, and the loop below takes the pieces in turn.
   if (!kSplit && static_cast<int>(blockIdx.x) >= p.copy_first_block) {
     commit_block_rows(p);
     return;
   }
-  const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
-  if (work >= p.total_work) return;
-  int64_t u_next = static_cast<int64_t>(work) * p.units;
-  const int64_t u_all = static_cast<int64_t>(p.n_hq) * p.n_tiles;
-  const int64_t u_end = u_next + p.units < u_all ? u_next + p.units : u_all;
   // One piece: a query tile and a run [t_first, t_end) of its key tiles.
-  auto run_piece = [&](const ix::Piece pc) __attribute__((always_inline)) {
+  // Its partial result goes to slot `slot` (kSplit).
+  auto run_piece = [&](const AttnParams &p, const ix::Piece pc, int slot) __attribute__((always_inline)) {
   const int t0 = pc.t_first, t1 = pc.t_end;
   const int per_item = p.n_heads * p.n_qtiles;
   const int item = pc.hq / per_item;
@@ -412,75 +413,101 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
     wait_vmcnt0();               // the redundant copies of the last tiles must not outlive the piece
     if (!group_b) wg_barrier();  // pairs with group B's extra barrier at the start
 
-    // ---- epilogue: the finished rows, or this piece's partial sums for the merge kernel
-    if (pc.whole) {
+    // ---- epilogue: the finished rows, or this piece's partial result for the merge kernel
+    if (!kSplit) {
       const float inv_l = 1.0f / lane_sum32(l_run);
       store_rows(p, it, head, q_row, hh, o_acc, inv_l);
     } else {
-      float *part = p.partials + static_cast<int64_t>(ix::partial_slot(pc.hq, work)) * sdvg::kPartialFloats +
-                    wave * (66 * 64) + lane;
+      const float l = lane_sum32(l_run);
+      float *part = partial_of(p, slot, wave);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) part[(16 * u + i) * 64] = o_acc[u][i];
-      part[64 * 64] = l_run;
-      part[65 * 64] = s_shift;
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 o4 = {o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
+          *reinterpret_cast<f32x4 *>(part + ((4 * u + g) * 64 + lane) * 4) = o4;
+        }
+      part[64 * 64 + lane] = lane < 32 ? l : s_shift;
     }
   }
   };
-  // A run is never longer than one query tile's key tiles, so it holds one piece or two (the end
-  // of one query tile and the start of the next). Two calls rather than a loop: with the piece
-  // body inside a loop the compiler kept so much alive around the back edge that it spilled.
-  const ix::Piece first = ix::piece_at(u_next, u_end, p.n_tiles);
-  run_piece(first);
-  if (kSplit) {
-    u_next += first.t_end - first.t_first;
-    if (u_next < u_end) run_piece(ix::piece_at(u_next, u_end, p.n_tiles));
+  if constexpr (!kSplit) {
+    const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
+    if (work >= p.total_work) return;
+    run_piece(p, ix::Piece{work, 0, p.n_tiles, true}, 0);
+  } else {
+    const ix::SplitWork w = ix::split_work(p.split, p.n_hq, p.total_work, blockIdx.x, p.work_per_xcd);
+    if (!w.any) return;
+    // A column is one piece, a helper's run has several: one loop for both.
+    const int64_t u_all = static_cast<int64_t>(p.n_hq) * ix::split_rest(p.split, p.n_tiles);
+    int64_t u = w.helper ? static_cast<int64_t>(w.index) * p.split.run : 0;
+    const int64_t u_end = !w.helper ? 1 : (u + p.split.run < u_all ? u + p.split.run : u_all);
+    while (u < u_end) {
+      // The arguments are read again for every piece: kept over the loop they would take more registers than there are.
+      uintptr_t ka = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(ka));
+      const AttnParams &p = *(const AttnParams *)(const __attribute__((address_space(4))) AttnParams *)ka;
+      ix::Piece pc;
+      int slot;
+      if (w.helper) {
+        pc = ix::helper_piece(p.split, u, u_end, p.n_tiles);
+        slot = ix::helper_slot(p.split, pc.hq, w.index, p.n_hq);
+      } else {
+        const int hq = w.index / p.split.cols, column = w.index - hq * p.split.cols;
+        pc = ix::column_piece(p.split, hq, column, p.n_tiles);
+        slot = ix::column_slot(hq, column, p.n_hq);
+      }
+      run_piece(p, pc, slot);
+      u += pc.t_end - pc.t_first;
+    }
   }
 }
 
-// Combines the partial results of every query tile whose keys were split over several workgroups:
-// with m_p the running maximum of piece p (its shift, negated) and m the largest of them,
+// Combines the partial results of every query tile: with m_p the running maximum of piece p (its shift, negated) and m
+// the largest of them,
 //   O = sum_p 2^((m_p - m) scale*log2e) O_p,   l = sum_p 2^((m_p - m) scale*log2e) l_p,
 // which is the same softmax as one pass over all keys (the factors only re-base the exponentials).
 // One workgroup per wave tile (32 rows) of a query tile, one wave per 32 of its dims, lanes laid out
 // as in the attention kernel; the pieces are added in their order. Few heads mean few query tiles of
 // many pieces, so what bounds this kernel is the chain of loads over the pieces: it needs many waves
-// and several pieces' loads in flight. 4680 queries x 32760 keys, main kernel + merge, us per call:
-// 1 head (19 query tiles of 13 to 15 pieces) 335 -> 93, 5 heads (95 of 2 to 4) 396 -> 329, of which the
-// merge takes 11; one 8-wave workgroup per query tile took the difference longer.
+// and several pieces' loads in flight (one 8-wave workgroup per query tile took up to 250 us). The last workgroup of a
+// query tile to finish could merge instead, without a second kernel: it was slower (12 heads x 4680 x 14040 keys 406 us
+// against 376), because releasing and acquiring the partial results at device scope adds 5 to 12 us to every piece.
 __global__ __launch_bounds__(256) void block_attn_merge_kernel(const AttnParams p) {
   const int hq = blockIdx.x, wt = blockIdx.y;
-  const int w_first = ix::first_wg_of(hq, p.n_tiles, p.units), w_last = ix::last_wg_of(hq, p.n_tiles, p.units);
-  if (w_first == w_last) return;  // one workgroup had all the keys and stored the rows itself
-  const int lane = threadIdx.x & 63, hh = lane >> 5;
+  const int lane = threadIdx.x & 63, hh = lane >> 5, r32 = lane & 31;
   const int u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int per_item = p.n_heads * p.n_qtiles;
   const int item = hq / per_item;
   const int head = (hq - item * per_item) / p.n_qtiles;
   const int qt = hq - item * per_item - head * p.n_qtiles;
   if (wt >= ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem)) return;
-  const int q_row = (ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem) + wt) * 32 + (lane & 31);
-  const float *part0 = p.partials + static_cast<int64_t>(ix::partial_slot(hq, w_first)) * sdvg::kPartialFloats +
-                       wt * (66 * 64) + lane;  // slots of neighbouring workgroups are neighbours
-  const int n_pieces = w_last - w_first + 1;
-  float shift_min = part0[65 * 64];
+  const int q_row = (ix::first_wave_tile_of_qtile(qt, p.wt_base, p.wt_rem) + wt) * 32 + r32;
+  const int n_pieces = ix::split_pieces(p.split, hq, p.n_tiles);
+  const int helper0 = ix::first_helper_of(p.split, hq, p.n_tiles);
+  auto part_of = [&](int i) __attribute__((always_inline)) {
+    return partial_of(p, ix::piece_slot(p.split, hq, i, p.n_hq, helper0), wt);
+  };
+  float shift_min = part_of(0)[64 * 64 + 32 + r32];
 #pragma unroll 8
-  for (int w = 1; w < n_pieces; ++w)
-    shift_min = fminf(shift_min, part0[static_cast<int64_t>(w) * sdvg::kPartialFloats + 65 * 64]);
+  for (int i = 1; i < n_pieces; ++i) shift_min = fminf(shift_min, part_of(i)[64 * 64 + 32 + r32]);
   float o_acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) o_acc[i] = 0.f;
-  float l_run = 0.f;
+  float l = 0.f;
 #pragma unroll 4
-  for (int w = 0; w < n_pieces; ++w) {
-    const float *part = part0 + static_cast<int64_t>(w) * sdvg::kPartialFloats;
-    const float f = __builtin_amdgcn_exp2f((shift_min - part[65 * 64]) * p.scale_log2e);
+  for (int i = 0; i < n_pieces; ++i) {
+    const float *part = part_of(i);
+    const float f = __builtin_amdgcn_exp2f((shift_min - part[64 * 64 + 32 + r32]) * p.scale_log2e);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o_acc[i] += f * part[(16 * u + i) * 64];
-    l_run += f * part[64 * 64];
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 o4 = *reinterpret_cast<const f32x4 *>(part + ((4 * u + g) * 64 + lane) * 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o_acc[4 * g + j] += f * o4[j];
+    }
+    l += f * part[64 * 64 + r32];
   }
-  const float inv_l = 1.0f / lane_sum32(l_run);
+  const float inv_l = 1.0f / l;
   if (q_row >= p.n_q) return;
   const sdvg::AttnItem it = kernarg_items()[item];
   uint16_t *op = static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 4 * hh + 32 * u;
@@ -540,7 +567,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   p.n_qtiles = pl.n_qtiles;
   p.n_hq = pl.n_hq;
   p.n_tiles = pl.n_tiles;
-  p.units = pl.units;
+  p.split = pl.split;
   p.total_work = pl.total_wg;
   p.work_per_xcd = (p.total_work + 7) / 8;
   const int n_wt = (p.n_q + 31) / 32;
@@ -556,16 +583,16 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   p.n_copy_blocks = !p.k_commit_dst ? 0 : (idle_cus >= 4 ? idle_cus : (n_cu > 0 ? n_cu : 256));
   if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, s);
   if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
-  if (p.units == p.n_tiles)
+  if (!p.split.cols) {
     hipLaunchKernelGGL(block_attn_bf16_kernel<false>, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512),
                        lds_bytes, s, p);
-  else
-    hipLaunchKernelGGL(block_attn_bf16_kernel<true>, dim3(8 * p.work_per_xcd), dim3(512), lds_bytes, s, p);
-  SDVG_HIP_CHECK(hipGetLastError());
-  if (p.units != p.n_tiles) {
-    hipLaunchKernelGGL(block_attn_merge_kernel, dim3(p.n_hq, ix::kWaves), dim3(256), 0, s, p);
     SDVG_HIP_CHECK(hipGetLastError());
+    return SDVG_OK;
   }
+  hipLaunchKernelGGL(block_attn_bf16_kernel<true>, dim3(8 * p.work_per_xcd), dim3(512), lds_bytes, s, p);
+  SDVG_HIP_CHECK(hipGetLastError());
+  hipLaunchKernelGGL(block_attn_merge_kernel, dim3(p.n_hq, ix::kWaves), dim3(256), 0, s, p);
+  SDVG_HIP_CHECK(hipGetLastError());
   return SDVG_OK;
 }
 

@@ -167,13 +167,20 @@ SDVG_HD int v_read_offset(int lane, int j, int db, int hi) {
   return (16 * j + 8 * hi + 4 * hh + (i16 >> 2)) * 256 + ((db ^ (i16 >> 2)) * 64) + 32 * b16 + 8 * (i16 & 3);
 }
 
-// ---- key split. The (query tile, key tile) pairs of a launch are numbered hq * n_tiles + t and
-// cut into runs of `units` pairs, one run per workgroup, so that a workgroup may finish one
-// query tile's keys and begin the next one's: every workgroup then has the same amount of work
-// even when the query tiles do not fill the chip's compute units evenly. units == n_tiles is the
-// plain case (one workgroup per query tile). A query tile whose keys are spread over several
-// workgroups gets one partial result per workgroup, in slot hq + w of the partial buffer
-// (distinct for distinct (hq, w): along the runs either hq or w grows from one piece to the next).
+// ---- key split. Where the query tiles do not fill the chip's compute units evenly, their keys are cut so that every
+// workgroup has about the same amount of work. Key tiles [0, cols * col) of every query tile go to `cols` workgroups of
+// `col` tiles each (the columns), so that the workgroups of a head read the same
+// keys at the same time and the re-reads stay in the XCD's L2. What is left of all query tiles, `rest` = n_tiles - cols * col
+// each, is numbered hq * rest + t and cut into runs of `run` pairs, one per helper: a helper ends one query tile's rest
+// and begins the next one's. Every piece of a query tile leaves a partial result in a slot of its own.
+struct KeySplit {
+  int cols, col;     // columns, and the key tiles of each (the last one may be shorter where there are no helpers)
+  int n_help, run;   // helpers, and the pairs of each
+};
+
+// A run of pairs cut at the boundaries between query tiles; `n_tiles` is the key tiles of a query tile that the runs cover.
+// A query tile whose keys are spread over several runs has its partial results in slots hq + w (distinct for distinct
+// (hq, w): along the runs either hq or w grows from one piece to the next).
 struct Piece {
   int hq;        // query tile (item, head, q-tile flattened)
   int t_first, t_end;  // its key tiles handled here
@@ -188,7 +195,7 @@ SDVG_HD Piece piece_at(int64_t u, int64_t u_end, int n_tiles) {
   pc.whole = pc.t_first == 0 && pc.t_end == n_tiles;
   return pc;
 }
-// First and last workgroup that hold a piece of query tile hq.
+// First and last run that hold a piece of query tile hq.
 SDVG_HD int first_wg_of(int hq, int n_tiles, int units) {
   return static_cast<int>(static_cast<int64_t>(hq) * n_tiles / units);
 }
@@ -196,6 +203,53 @@ SDVG_HD int last_wg_of(int hq, int n_tiles, int units) {
   return static_cast<int>((static_cast<int64_t>(hq + 1) * n_tiles - 1) / units);
 }
 SDVG_HD int partial_slot(int hq, int wg) { return hq + wg; }
+
+SDVG_HD int split_rest(const KeySplit &ks, int n_tiles) { return ks.n_help ? n_tiles - ks.cols * ks.col : 0; }
+// Key tiles of column c, and piece `pc` of the helpers' runs as a piece of the query tile.
+SDVG_HD Piece column_piece(const KeySplit &ks, int hq, int c, int n_tiles) {
+  const int end = (c + 1) * ks.col;
+  return Piece{hq, c * ks.col, end < n_tiles ? end : n_tiles, false};
+}
+SDVG_HD Piece helper_piece(const KeySplit &ks, int64_t u, int64_t u_end, int n_tiles) {
+  const int rest = split_rest(ks, n_tiles);
+  Piece pc = piece_at(u, u_end, rest);
+  pc.t_first += n_tiles - rest;
+  pc.t_end += n_tiles - rest;
+  pc.whole = false;
+  return pc;
+}
+// Pieces of a query tile: the columns, then the helpers' in their order. Slot of piece i in the partial buffer.
+SDVG_HD int split_pieces(const KeySplit &ks, int hq, int n_tiles) {
+  const int rest = split_rest(ks, n_tiles);
+  return ks.cols + (rest ? last_wg_of(hq, rest, ks.run) - first_wg_of(hq, rest, ks.run) + 1 : 0);
+}
+SDVG_HD int first_helper_of(const KeySplit &ks, int hq, int n_tiles) {
+  return ks.n_help ? first_wg_of(hq, split_rest(ks, n_tiles), ks.run) : 0;
+}
+SDVG_HD int column_slot(int hq, int c, int n_hq) { return c * n_hq + hq; }
+SDVG_HD int helper_slot(const KeySplit &ks, int hq, int helper, int n_hq) {
+  return ks.cols * n_hq + partial_slot(hq, helper);
+}
+SDVG_HD int piece_slot(const KeySplit &ks, int hq, int i, int n_hq, int first_helper) {
+  return i < ks.cols ? column_slot(hq, i, n_hq) : helper_slot(ks, hq, first_helper + i - ks.cols, n_hq);
+}
+// Workgroup `block` of a split launch of `wgs` workgroups: a helper, or a column of a query tile, or none. XCD x has the
+// slots [x * per_xcd, (x + 1) * per_xcd); its share of the columns (in the order of the query tiles) and of the helpers is
+// the same part of all, so that a query tile's helper runs beside it. The helpers are dispatched first.
+struct SplitWork {
+  bool any, helper;
+  int index;  // helper number, or hq * cols + column
+};
+SDVG_HD SplitWork split_work(const KeySplit &ks, int n_hq, int wgs, int block, int per_xcd) {
+  const int all = n_hq * ks.cols, lo = (block % 8) * per_xcd, hi = lo + per_xcd < wgs ? lo + per_xcd : wgs;
+  const int i = block / 8;
+  if (lo + i >= wgs) return SplitWork{false, false, 0};
+  const int e_lo = static_cast<int>(static_cast<unsigned>(all) * static_cast<unsigned>(lo) / static_cast<unsigned>(wgs));
+  const int e_hi = static_cast<int>(static_cast<unsigned>(all) * static_cast<unsigned>(hi) / static_cast<unsigned>(wgs));
+  const int helpers = (hi - lo) - (e_hi - e_lo);
+  if (i < helpers) return SplitWork{true, true, lo - e_lo + i};
+  return SplitWork{true, false, e_lo + i - helpers};
+}
 
 // ---- work distribution. Workgroups are dealt round-robin to the 8 XCDs; giving XCD x the
 // contiguous range [x * work_per_xcd, (x + 1) * work_per_xcd) of (head, q-tile) work keeps the

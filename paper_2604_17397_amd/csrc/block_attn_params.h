@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "block_attn_index.h"
 #include "row_map.h"
 
 namespace sdvg {
@@ -25,7 +26,7 @@ struct AttnParams {
   int32_t n_items, n_q, n_k, n_heads, n_qtiles;
   int32_t n_hq;       // query tiles of the launch: n_items * n_heads * n_qtiles
   int32_t n_tiles;    // key tiles: n_k / 64, rounded up (4 key groups: of 32 keys)
-  int32_t units;      // (query tile, key tile) pairs per workgroup; == n_tiles when nothing is split
+  attn_index::KeySplit split;  // how the keys are cut over workgroups; cols == 0 when they are not
   int32_t total_work; // workgroups with work
   int32_t work_per_xcd;
   int32_t wt_base, wt_rem;  // 32-row wave tiles per query tile: wt_base, plus one for the first wt_rem

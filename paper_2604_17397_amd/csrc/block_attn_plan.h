@@ -18,10 +18,13 @@ constexpr int kPlanRows = 256;  // query rows of a workgroup without key groups
 // Key split: when the query tiles would leave a good part of the last round of workgroups idle
 // (a drafter-shaped layer has 12 heads x 19 query tiles = 228 workgroups for 256 compute units),
 // the (query tile, key tile) pairs are dealt out evenly over whole rounds instead, every
-// workgroup taking the same number of pairs; query tiles cut by a workgroup boundary leave
-// partial results that a second, small kernel merges.
+// workgroup taking about the same number of pairs; the query tiles' pieces leave partial
+// results that a second, small kernel merges.
 struct Plan {
-  int n_qtiles, n_hq, n_tiles, units, total_wg;
+  int n_qtiles, n_hq, n_tiles;
+  int units;     // key tiles of a workgroup; == n_tiles when nothing is split
+  int total_wg;  // workgroups
+  attn_index::KeySplit split;  // cols == 0 when nothing is split
   int64_t workspace_bytes;  // what a caller is asked for; 0 when no split was considered
   int groups;               // key groups per workgroup (1: block_attn.hip, 2 or 4: block_attn_groups.hip)
   int rows;                 // query rows per workgroup (32: block_attn_rows32.hip)
@@ -71,6 +74,30 @@ inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int 
   return best;
 }
 
+// Cuts n_tiles key tiles of each of n_hq query tiles over `wgs` >= n_hq workgroups (block_attn_index.h, "key split").
+// As many whole columns as there is room for; the workgroups left over are helpers. A piece costs some 10 us beside its
+// tiles (arguments, query rows and first tiles 7, partial result 3, by clock stamps in the kernel), and a helper has
+// several. With n_hq / n_help + 1 pieces of rest + kPieceTiles, helpers and columns are done at the same time where
+//   col = (n_tiles + kPieceTiles) * n_hq / wgs.
+// kPieceTiles = 2 / 6 / 10 / 14 / 20, us: 5 heads x 4680 x 32760 338 / 336 / 334 / 330 / 330, 16 x 4680 x 14040
+// 462 / 466 / 465 / 465 / 474, 20 x 4680 x 18720 744 / 752 / 750 / 755 / 763, 13 x 1560 x 9360 111 / 110 / 107 / 105 / 107.
+constexpr int kPieceTiles = 10;
+inline attn_index::KeySplit cut_keys(int n_hq, int n_tiles, int wgs) {
+  attn_index::KeySplit ks{wgs / n_hq, 0, wgs % n_hq, 0};
+  const int64_t part = static_cast<int64_t>(n_tiles + (ks.n_help ? kPieceTiles : 0)) * n_hq;
+  ks.col = static_cast<int>(ks.n_help ? (part + wgs - 1) / wgs : (n_tiles + ks.cols - 1) / ks.cols);
+  const int64_t rest = n_tiles - static_cast<int64_t>(ks.cols) * ks.col;
+  if (rest < 1) {  // nothing for helpers to do
+    ks.n_help = 0;
+    ks.col = (n_tiles + ks.cols - 1) / ks.cols;
+    ks.cols = ks.cols == 1 ? 0 : (n_tiles + ks.col - 1) / ks.col;
+    return ks;
+  }
+  ks.run = static_cast<int>((n_hq * rest + ks.n_help - 1) / ks.n_help);
+  ks.n_help = static_cast<int>((n_hq * rest + ks.run - 1) / ks.run);
+  return ks;
+}
+
 // SDVG_SPLIT_AUTO considers the split from this share of idle workgroup slots on: with a workspace of the caller's, and
 // with the library's own array, which holds fewer partial results and which calls that overlap must not share, so that no
 // more shapes split there than have to.
@@ -87,6 +114,7 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     pl.n_qtiles = (n_q + rows - 1) / rows;
     pl.n_hq = pl.total_wg = n_items * n_heads * pl.n_qtiles;
     pl.n_tiles = pl.units = static_cast<int>((n_k + keys - 1) / keys);
+    pl.split = attn_index::KeySplit{0, 0, 0, 0};
     pl.workspace_bytes = 0;
     return pl;
   };
@@ -106,17 +134,22 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   if (split_mode == SDVG_SPLIT_AUTO && idle < auto_idle) return plain();
   const int64_t all = static_cast<int64_t>(pl.n_hq) * pl.n_tiles;
   const int64_t wgs = static_cast<int64_t>(rounds) * n_cu;
-  pl.units = static_cast<int>((all + wgs - 1) / wgs);  // <= n_tiles, because wgs >= n_hq
-  if (pl.units < 16) return plain();
-  pl.total_wg = static_cast<int>((all + pl.units - 1) / pl.units);
-  pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + pl.total_wg) * kPartialFloats * 4;
+  const int even = static_cast<int>((all + wgs - 1) / wgs);  // pairs per workgroup; <= n_tiles, because wgs >= n_hq
+  if (even < 16 || all > INT32_MAX) return plain();  // (the cut is made in 32 bits)
+  const int max_wg = static_cast<int>((all + even - 1) / even);
+  pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + max_wg) * kPartialFloats * 4;
+  pl.split = cut_keys(pl.n_hq, pl.n_tiles, max_wg);
+  if (pl.split.cols) {
+    pl.units = pl.split.col;
+    pl.total_wg = pl.n_hq * pl.split.cols + pl.split.n_help;
+  }
   // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
   // unsplit, us: 1 head x 4680 x 32760 93 / 149, 5 heads 346 / 374; 4 x 4680 x 14040 132 / 141,
   // 5 heads 160 / 162; 12 x 1560 x 4680 63 / 53, 16 x 1031 x 3093 49 / 38, 3 x 4680 x 4680 56 / 40.
   // Below 60 % idle the unsplit estimate, made for a full chip, is a little high for one that is half busy: the split
   // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (1 to 3 items, up to 40 heads, 312 to 4680 rows,
   // 1 to 7 blocks of keys) 31 are split, 3 to 20 % faster each; 13 more would have gained 4 to 14 %.
-  const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(pl.units);
+  const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(even);
   const bool few = idle >= kAutoIdleStatic;
   if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us + (few ? 0.0 : 11.0)) {
     Plan g = plain();
