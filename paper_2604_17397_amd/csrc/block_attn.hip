@@ -581,7 +581,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   // compute units idle (they then run beside it for its whole length); a full round otherwise.
   const int idle_cus = n_cu > 0 && p.total_work % n_cu ? n_cu - p.total_work % n_cu : 0;
   p.n_copy_blocks = !p.k_commit_dst ? 0 : (idle_cus >= 4 ? idle_cus : (n_cu > 0 ? n_cu : 256));
-  if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, s);
+  if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, pl.halves, s);
   if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
   if (!p.split.cols) {
     hipLaunchKernelGGL(block_attn_bf16_kernel<false>, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512),

@@ -44,6 +44,7 @@ int launch_block_attn_groups(const AttnParams &p, int groups, hipStream_t stream
 
 // Kernel for the smallest launches (block_attn_rows32.hip): 32 query rows per workgroup, tiles of 32 keys.
 hipError_t prepare_block_attn_rows32();  // once per device: raises the dynamic-LDS limit
-int launch_block_attn_rows32(AttnParams p, hipStream_t stream);
+// `halves`: two workgroups per 32 rows, each with half of the output dims.
+int launch_block_attn_rows32(AttnParams p, bool halves, hipStream_t stream);
 
 }  // namespace sdvg

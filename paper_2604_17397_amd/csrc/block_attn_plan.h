@@ -28,6 +28,7 @@ struct Plan {
   int64_t workspace_bytes;  // what a caller is asked for; 0 when no split was considered
   int groups;               // key groups per workgroup (1: block_attn.hip, 2 or 4: block_attn_groups.hip)
   int rows;                 // query rows per workgroup (32: block_attn_rows32.hip)
+  bool halves;              // two workgroups per 32 rows, each with half of the output dims
 };
 
 // Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
@@ -115,6 +116,11 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     pl.n_hq = pl.total_wg = n_items * n_heads * pl.n_qtiles;
     pl.n_tiles = pl.units = static_cast<int>((n_k + keys - 1) / keys);
     pl.split = attn_index::KeySplit{0, 0, 0, 0};
+    // 32-row workgroups that leave half of the compute units idle are doubled: each of a pair copies all of K but half of V,
+    // and copies are what bounds them (block_attn_rows32.hip). Whole / halves, us: 12 heads x 312 x 936 keys 9.1 / 8.7, with
+    // keys from the memory-side cache 10.5 / 9.0; 4 x 1000 x 4000 22.4 / 21.4, 24.6 / 21.7; 3 x 1300 x 9100 50 / 43, 58 / 47;
+    // the same where there is nothing to halve (1 x 33 x 99, 6.4). In a second round every pair would copy K again.
+    pl.halves = rows == 32 && 2 * pl.total_wg <= n_cu;
     pl.workspace_bytes = 0;
     return pl;
   };

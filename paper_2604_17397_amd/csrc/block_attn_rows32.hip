@@ -19,6 +19,10 @@
 // Where it went at 12 x 312 x 936 while the first copies still waited 0.3 us for their arguments (9.2 us with one set of tensors
 // again and again): 0.9 launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1
 // merge and store.
+// Where these workgroups are few (block_attn_plan.h) there are two per 32 rows, each with half of the output dims: 96 KB of
+// copies per 8 x 32 keys instead of 128, and half of the merge. 12 x 312 x 936 9.1 -> 8.7, keys from the memory-side cache
+// 10.5 -> 9.0; 12 x 312 x 312 6.1 -> 5.6, 6.4 -> 5.7; 5 x 800 x 5600 32.5 -> 28.8, 40.1 -> 32.6. (The LDS that half a V tile leaves
+// free as a second K slot, K copied two tiles ahead: 1 us slower throughout, 9.0 -> 9.8.)
 // The loop is bound by the copies: 8 waves bring 128 KB per 8 x 32 keys, which takes 1.13 - 1.18 us, and a
 // loop of nothing but such copies from L2 reaches 62 bytes per clock and compute unit, 1.13 us. So
 // neither fewer scalar instructions (1 %), nor the copies placed before the products (1 % slower), nor
@@ -80,8 +84,8 @@ struct Early {
 constexpr int kParamsAt = 48;  // where the AttnParams lie among the kernel's arguments
 static_assert(sizeof(Early) == kParamsAt && alignof(AttnParams) == 8, "");
 
-// kEarly: the `Early` arguments hold (early_of).
-template <bool kEarly>
+// kEarly: the `Early` arguments hold (early_of). kHalves: two workgroups per 32 query rows, each with half of the output dims.
+template <bool kEarly, bool kHalves>
 __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
     const void *e_k, const void *e_q, uint32_t e_k_ts, uint32_t e_k_hs, uint32_t e_q_ts, uint32_t e_q_hs, int32_t e_n_q,
     uint32_t e_div_m, uint32_t e_div_s_qtiles, uint32_t e_work, const AttnParams all) {
@@ -91,6 +95,8 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r32 = lane & 31, hh = lane >> 5;
+  constexpr int kU = kHalves ? 2 : 4;                               // 32-dim blocks of the output
+  constexpr int kVCopies = kHalves ? ix::kHalfCopies : R::kCopies;  // copies of a V tile
 
   // ---- copies
   uint32_t k_chunk[4], v_chunk = ix::rows32_lane_offset(0, lane, 0, 1);
@@ -102,6 +108,21 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
     uint64_t base[8];
     base[0] = first_row;
     uint32_t off[4];
+    if (kHalves && is_v) {
+      if (__builtin_expect(keys == R::kKeys, 1)) {
+        off[0] = off[1] = off[2] = off[3] = ix::rows32_half_lane_offset(pitch, lane);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) base[u + 1] = base[u] + static_cast<int64_t>(ix::rows32_half_copy_step(pitch));
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          off[u] = ix::rows32_half_short_offset(pitch, keys, lane, u);
+          base[u] = base[0] - (u > 0 ? 1024 * u : 0);
+        }
+      }
+      copy4(off, base, dst);
+      return;
+    }
     if (__builtin_expect(keys == R::kKeys, 1)) {
       const uint32_t row_off = static_cast<uint32_t>(lane >> 4) * pitch;
 #pragma unroll
@@ -135,12 +156,12 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   if constexpr (kEarly) {
     const int work = ix::work_of_block(blockIdx.x, static_cast<int>(e_work & 0xffff)), n_qt = static_cast<int>(e_div_s_qtiles & 0xffff);
     if (blockIdx.x < 8 * (e_work & 0xffff) && work < static_cast<int>(e_work >> 16)) {
-      const int head = static_cast<int>(sdvg::FastDiv{0, e_div_m, e_div_s_qtiles >> 16}.div(work));
+      const int tile = kHalves ? work >> 1 : work, head = static_cast<int>(sdvg::FastDiv{0, e_div_m, e_div_s_qtiles >> 16}.div(tile));
       const uint32_t pitch = e_k_ts * 2;
       const uint64_t first_row = reinterpret_cast<uint64_t>(e_k) + static_cast<uint64_t>(head) * e_k_hs * 2 +
                                  static_cast<uint64_t>(wave * R::kKeys) * pitch;
       copy_rows(first_row, pitch, R::kKeys, 0);
-      copy_query(e_q, head, work - head * n_qt, e_n_q, e_q_ts, e_q_hs);
+      copy_query(e_q, head, tile - head * n_qt, e_n_q, e_q_ts, e_q_hs);
     }
     asm volatile("" : "+s"(arguments));
   }
@@ -154,16 +175,17 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
   if (work >= p.total_work) return;
 
-  const int hq = static_cast<int>(p.div_qtiles.div(work)), qt = work - hq * p.n_qtiles;
+  const int q_tile = kHalves ? work >> 1 : work, half = kHalves ? work & 1 : 0;
+  const int hq = static_cast<int>(p.div_qtiles.div(q_tile)), qt = q_tile - hq * p.n_qtiles;
   const int item = static_cast<int>(p.div_heads.div(hq)), head = hq - item * p.n_heads;
   if (item != 0) it = kernarg_items<kParamsAt>()[item];
 
   const int c_len = static_cast<int>(p.cache_len), n_blk = p.n_blk;
   const uint32_t c_pitch = static_cast<uint32_t>(p.kv_ts * 2), b_pitch = static_cast<uint32_t>(p.blk_ts * 2);
   const uint64_t kc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.k_cache) + head * p.kv_hs);
-  const uint64_t vc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_cache) + head * p.kv_hs);
+  const uint64_t vc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_cache) + head * p.kv_hs + 64 * half);
   const uint64_t kb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.k_blk) + head * p.blk_hs);
-  const uint64_t vb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_blk) + head * p.blk_hs);
+  const uint64_t vb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_blk) + head * p.blk_hs + 64 * half);
   const int n_it = ix::rows32_tiles_of(wave, p.n_tiles);
   // (a wave past the last tile takes the last one, masked as a whole)
   auto tile_of = [&](int i) __attribute__((always_inline)) {
@@ -182,15 +204,18 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   }
   copy_tile(tile_of(0), 1);
 
-  uint32_t k_off[8], v_off[4];  // LDS read addresses
+  uint32_t k_off[8], v_off[kU];  // LDS read addresses
 #pragma unroll
   for (int s = 0; s < 8; ++s) k_off[s] = lds0 + ix::k_read_offset(lane, s, 0);
 #pragma unroll
-  for (int db = 0; db < 4; ++db) v_off[db] = lds0 + wave * R::kWavePart + R::kTile + ix::v_read_offset(lane, 0, db, 0);
+  for (int db = 0; db < kU; ++db)
+    v_off[db] = lds0 + wave * R::kWavePart + R::kTile +
+                (kHalves ? ix::rows32_half_read_offset(lane, 0, db, 0) : ix::v_read_offset(lane, 0, db, 0));
+  constexpr int kVRow = kHalves ? ix::kHalfRow : 256;
 
-  f32x16 o_acc[4];
+  f32x16 o_acc[kU];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < kU; ++u)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o_acc[u][i] = 0.f;
   float l_run = 0.f, s_shift = 0.f;
@@ -215,9 +240,9 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   };
 
 #pragma unroll
-  for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(o_acc[u]));  // (ready before the wait)
+  for (int u = 0; u < kU; ++u) asm volatile("" : "+v"(o_acc[u]));  // (ready before the wait)
   asm volatile("" : "+v"(s_init));
-  wait_copies<R::kCopies>();
+  wait_copies<kVCopies>();
   wg_barrier();
   bf16x8 qf[8];
 #pragma unroll
@@ -228,7 +253,7 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
     asm volatile("" : "+v"(k_off[s]));
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(v_off[u]));
+  for (int u = 0; u < kU; ++u) asm volatile("" : "+v"(v_off[u]));
 
 #pragma unroll 1
   for (int i = 0;; ++i) {
@@ -236,7 +261,7 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
     bf16x8 f[8];
     asm volatile("" : "+v"(s_init));
     // ---- S of the tile. Its operands are read at one go, so that the next tile's copies can start
-    wait_copies<R::kCopies>();  // K of this tile (V may still be on its way)
+    wait_copies<kVCopies>();  // K of this tile (V may still be on its way)
 #pragma unroll
     for (int s = 0; s < 8; ++s) f[s] = *(lds_bf16x8 *)static_cast<uintptr_t>(k_off[s]);
     SDVG_SB();
@@ -269,7 +294,7 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
       const float d = fmaxf(tile_max(s_acc), 0.f);
       const float alpha = __builtin_amdgcn_exp2f(-d * p.scale_log2e);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < kU; ++u)
 #pragma unroll
         for (int j = 0; j < 16; ++j) o_acc[u][j] *= alpha;
       l_run *= alpha;
@@ -287,8 +312,8 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
     // The rows past a short tile's keys have P = 0, but 0 times an infinite value would be NaN.
     if (__builtin_expect(keys < R::kKeys, 0)) {
 #pragma unroll
-      for (int u = 0; u < R::kCopies; ++u)
-        if (ix::rows32_copy_row(lane, u) >= keys)
+      for (int u = 0; u < kVCopies; ++u)
+        if ((kHalves ? ix::rows32_half_copy_row(lane, u) : ix::rows32_copy_row(lane, u)) >= keys)
           *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + ix::rows32_copy_dst(wave, 1, 0) + u * 1024 + lane * 16) =
               f32x4{0.f, 0.f, 0.f, 0.f};
       wait_lds();
@@ -296,22 +321,22 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t vp = v_off[u] + j * 16 * 256;
+      for (int u = 0; u < kU; ++u) {
+        const uint32_t vp = v_off[u] + j * 16 * kVRow;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp + 8 * 256));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)static_cast<uintptr_t>(vp + 8 * kVRow));
         const __attribute__((ext_vector_type(8))) short a16 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        __builtin_memcpy(&f[4 * j + u], &a16, sizeof(bf16x8));
+        __builtin_memcpy(&f[kU * j + u], &a16, sizeof(bf16x8));
       }
     SDVG_SB();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) o_acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[u], pf[0], o_acc[u], 0, 0, 0);
+    for (int u = 0; u < kU; ++u) o_acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[u], pf[0], o_acc[u], 0, 0, 0);
     SDVG_SB();
     wait_lds();
     if (more) copy_tile(tile_of(i + 1), 1);
     SDVG_SB();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) o_acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[4 + u], pf[1], o_acc[u], 0, 0, 0);
+    for (int u = 0; u < kU; ++u) o_acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[kU + u], pf[1], o_acc[u], 0, 0, 0);
     SDVG_SB();
     if (!more) break;
   }
@@ -322,12 +347,13 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   //   O = sum_w 2^((m_w - m) scale*log2e) O_w, l likewise.
   const uint32_t part = lds0 + wave * R::kWavePart;
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < kU; ++u)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int c = 4 * u + g;
       const f32x4 o4 = {o_acc[u][4 * g], o_acc[u][4 * g + 1], o_acc[u][4 * g + 2], o_acc[u][4 * g + 3]};
-      *(lds_f32x4 *)static_cast<uintptr_t>(part + ix::merge_offset(c, hh, r32)) = o4;
+      const int at = kHalves ? ix::rows32_half_merge_offset(2 * c + hh, r32) : ix::merge_offset(c, hh, r32);
+      *(lds_f32x4 *)static_cast<uintptr_t>(part + at) = o4;
     }
   const float l_row = lane_sum32(l_run);
   if (hh == 0) *(lds_f32x2 *)static_cast<uintptr_t>(lds0 + R::kQ + (wave * 32 + r32) * 8) = f32x2{l_row, s_shift};
@@ -350,16 +376,25 @@ __global__ __launch_bounds__(512) void block_attn_rows32_kernel(
   for (int w = 0; w < ix::kWaves; ++w) {
     const float factor = __builtin_amdgcn_exp2f((shift_min - shift_w[w]) * p.scale_log2e);
     l_sum += factor * l_w[w];
-    const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::merge_offset(c, 0, row));
-    const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::merge_offset(c, 1, row));
+    const int at = kHalves ? ix::rows32_half_merge_offset(c, row) : ix::merge_offset(c, 0, row);
+    const f32x4 lo = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + at);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o_lo[e] += factor * lo[e];
-      o_hi[e] += factor * hi[e];
+    for (int e = 0; e < 4; ++e) o_lo[e] += factor * lo[e];
+    if constexpr (!kHalves) {
+      const f32x4 hi = *(lds_f32x4 *)static_cast<uintptr_t>(lds0 + w * R::kWavePart + ix::merge_offset(c, 1, row));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o_hi[e] += factor * hi[e];
     }
   }
   if (q_row >= p.n_q) return;
   const float inv_l = 1.0f / l_sum;
+  if constexpr (kHalves) {
+    bf16x4 out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = static_cast<__bf16>(o_lo[e] * inv_l);
+    *reinterpret_cast<bf16x4 *>(static_cast<uint16_t *>(it.out) + q_row * p.o_ts + head * p.o_hs + 64 * half + 4 * c) = out;
+    return;
+  }
   bf16x8 out;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -395,7 +430,8 @@ bool early_of(const AttnParams &p, Early &e) {
 namespace sdvg {
 
 hipError_t prepare_block_attn_rows32() {
-  for (const auto kernel : {block_attn_rows32_kernel<false>, block_attn_rows32_kernel<true>}) {
+  for (const auto kernel : {block_attn_rows32_kernel<false, false>, block_attn_rows32_kernel<true, false>,
+                            block_attn_rows32_kernel<false, true>, block_attn_rows32_kernel<true, true>}) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, R::kLdsBytes);
     if (e != hipSuccess) return e;
@@ -403,10 +439,17 @@ hipError_t prepare_block_attn_rows32() {
   return hipSuccess;
 }
 
-int launch_block_attn_rows32(AttnParams p, hipStream_t s) {
+int launch_block_attn_rows32(AttnParams p, bool halves, hipStream_t s) {
   p.n_tiles = ix::rows32_tiles(static_cast<int>(p.cache_len)) + ix::rows32_tiles(p.n_blk);
+  if (halves) {
+    p.total_work *= 2;
+    p.work_per_xcd = (p.total_work + 7) / 8;
+    p.copy_first_block = 8 * p.work_per_xcd;
+  }
   Early e{};
-  const auto kernel = early_of(p, e) ? block_attn_rows32_kernel<true> : block_attn_rows32_kernel<false>;
+  const bool early = early_of(p, e);
+  const auto kernel = halves ? (early ? block_attn_rows32_kernel<true, true> : block_attn_rows32_kernel<false, true>)
+                             : (early ? block_attn_rows32_kernel<true, false> : block_attn_rows32_kernel<false, false>);
   hipLaunchKernelGGL(kernel, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512), R::kLdsBytes, s, e.k, e.q, e.k_ts,
                      e.k_hs, e.q_ts, e.q_hs, e.n_q, e.div_m, e.div_s_qtiles, e.work, p);
   SDVG_HIP_CHECK(hipGetLastError());

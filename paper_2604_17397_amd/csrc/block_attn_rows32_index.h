@@ -63,6 +63,30 @@ SDVG_HD uint32_t rows32_short_offset(uint32_t pitch, int keys, int lane, int u, 
          static_cast<uint32_t>(swizzled_chunk(row, lane, is_v) * 16);
 }
 
+// ---- two workgroups per 32 query rows, each with half of the output dims: both need all of K, but a V tile is 128
+// bytes of each row. Copy u of a V tile moves rows 8 u .. 8 u + 7: lane i the physical 16-byte chunk i % 8 of row 8 u + i / 8,
+// whose 64-byte halves change places in every second pair of rows, so that the transposing read of 4 rows x 64
+// bytes touches every bank once.
+constexpr int kHalfRow = 128;
+constexpr int kHalfCopies = Rows32::kTile / 2 / 1024;
+SDVG_HD int rows32_half_copy_row(int lane, int u) { return 8 * u + (lane >> 3); }
+SDVG_HD int rows32_half_chunk(int row, int lane) { return (lane & 7) ^ (2 * (row & 2)); }
+SDVG_HD int rows32_half_copy_step(uint32_t pitch) { return static_cast<int>(8 * pitch) - 1024; }
+SDVG_HD uint32_t rows32_half_lane_offset(uint32_t pitch, int lane) {  // (the same for all u: 8 u is a multiple of 4)
+  return static_cast<uint32_t>(lane >> 3) * pitch + static_cast<uint32_t>(rows32_half_chunk(lane >> 3, lane) * 16);
+}
+SDVG_HD uint32_t rows32_half_short_offset(uint32_t pitch, int keys, int lane, int u) {
+  const int row = rows32_half_copy_row(lane, u);
+  return static_cast<uint32_t>(row < keys ? row : keys - 1) * pitch + static_cast<uint32_t>(rows32_half_chunk(row, lane) * 16);
+}
+// v_read_offset of such a tile (db 0 or 1).
+SDVG_HD int rows32_half_read_offset(int lane, int j, int db, int hi) {
+  const int i16 = lane & 15, b16 = (lane >> 4) & 1, hh = lane >> 5;
+  return (16 * j + 8 * hi + 4 * hh + (i16 >> 2)) * kHalfRow + ((db ^ (i16 >> 3)) * 64) + 32 * b16 + 8 * (i16 & 3);
+}
+// merge_offset for 64 dims: dims 4 q .. 4 q + 3 of a row.
+SDVG_HD int rows32_half_merge_offset(int q, int row) { return (q * 32 + (row ^ q)) * 16; }
+
 // Key tiles of a wave (at least one: a wave past the last tile goes through a tile that is masked).
 SDVG_HD int rows32_tiles_of(int wave, int n_tiles) { return wave < n_tiles ? (n_tiles - wave + kWaves - 1) / kWaves : 1; }
 
