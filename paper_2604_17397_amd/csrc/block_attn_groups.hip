@@ -26,6 +26,11 @@
 //   code fetched cold costs about 1 us), but its bookkeeping in the vector phase    59
 //   bookkeeping moved into the gaps of the matrix phase                              52
 //   a shorter way in and out (below)                                                 49
+//   copies from a scalar address and 32-bit offsets instead of a 64-bit address per
+//   lane; no tile holds keys of both sources, so that only short tiles need new ones 48
+// (Scalar addresses, us before / after, 2 groups: 12 x 1560 x 4680 52.9 / 51.3, 9 x 2000 x 8000 81.1 / 78.3, 5 x 4680 x 32760
+// 357 / 345. The wave that issues the MFMAs has one instruction in 4 cycles: 200 of them per 32-key tile, now 175, are what
+// the loop is short of. All that changes per tile, worked out anew for each, is slower again: 1 to 2 %.)
 // (Arguments of the first copies preloaded into registers, as in block_attn_rows32.hip: no gain. 64 rows per wave, every
 // wave with key tiles of its own, which halves the LDS reads and needs no barrier: 53, bound by the copies.)
 // What bounds it there, by counters: the matrix pipes are busy in 52 % of the SIMD cycles of the
@@ -60,10 +65,45 @@ __device__ __forceinline__ void wait_lds() {  // all but the N most recent LDS r
   __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
 }
 
+// One or two 1 KB copies (lane i's 16 bytes land at dst + kAt + imm + 16 i) from a scalar address plus the lanes' offsets.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int kAt, int kSecondImm>
+__device__ __forceinline__ void copy_pair(uint32_t off0, uint32_t off1, uint64_t base, uint32_t dst) {
+  if constexpr (kSecondImm == 0)
+    asm volatile(
+        "s_add_u32 m0, %2, %3\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %0, %1"
+        :
+        : "v"(off0), "s"(base), "s"(dst), "n"(kAt)
+        : "memory", "m0", "scc");
+  else
+    asm volatile(
+        "s_add_u32 m0, %3, %4\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %0, %2\n\t"
+        "global_load_lds_dwordx4 %1, %2 offset:%5"
+        :
+        : "v"(off0), "v"(off1), "s"(base), "s"(dst), "n"(kAt), "n"(kSecondImm)
+        : "memory", "m0", "scc");
+}
+#pragma clang diagnostic pop
+
+// Calls f with 0, kStep, 2 kStep ... below kEnd as constants.
+template <int kEnd, int kStep, int kAt = 0, class F>
+__device__ __forceinline__ void for_each(F f) {
+  if constexpr (kAt < kEnd) {
+    f(std::integral_constant<int, kAt>{});
+    for_each<kEnd, kStep, kAt + kStep>(f);
+  }
+}
+
 constexpr int kMergeSums = ix::kWaves * 32 * 512;  // O of all waves; row sums and shifts follow
 constexpr int kMergeBytes = kMergeSums + ix::kWaves * 32 * 8;
 
-template <int G>
+// kWide: a pitch is too large for 32-bit offsets (ix::group_takes).
+template <int G, bool kWide>
 __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams p) {
   using C = ix::Groups<G>;
   constexpr int R = C::kRowWaves, NK = C::kHalves;
@@ -90,51 +130,64 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
   const int item = static_cast<int>(p.div_heads.div(hq)), head = hq - item * p.n_heads;
   if (item != 0) it = kernarg_items()[item];
 
-  ix::Streams st;
-  st.kc = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.k_cache) + head * p.kv_hs);
-  st.vc = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.v_cache) + head * p.kv_hs);
-  st.kb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.k_blk) + head * p.blk_hs);
-  st.vb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(it.v_blk) + head * p.blk_hs);
-  st.kv_tsb = static_cast<uint32_t>(p.kv_ts * 2);
-  st.blk_tsb = static_cast<uint32_t>(p.blk_ts * 2);
-  st.c_len = static_cast<int>(p.cache_len);
-  st.n_k = p.n_k;
-  const int n_it = (p.n_tiles + G - 1) / G;  // the same for all groups: one past its tiles is masked
+  const int c_len = static_cast<int>(p.cache_len), n_blk = p.n_blk;
+  const uint32_t c_pitch = static_cast<uint32_t>(p.kv_ts * 2), b_pitch = static_cast<uint32_t>(p.blk_ts * 2);
+  const uint64_t kc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.k_cache) + head * p.kv_hs);
+  const uint64_t vc = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_cache) + head * p.kv_hs);
+  const uint64_t kb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.k_blk) + head * p.blk_hs);
+  const uint64_t vb = reinterpret_cast<uint64_t>(static_cast<const uint16_t *>(it.v_blk) + head * p.blk_hs);
+  const ix::GroupBounds bounds = ix::group_bounds<G>(c_len, n_blk);
+  const uint64_t row0[2] = {kc, vc}, block_base[2] = {ix::group_block_base<G>(bounds, kb, b_pitch), ix::group_block_base<G>(bounds, vb, b_pitch)};
+  const int n_it = (bounds.end + G - 1) / G;  // the same for all groups: one past its tiles is masked
   auto tile_of = [&](int i) __attribute__((always_inline)) { return grp + G * i; };
 
-  // ---- copies: the pointers of this lane's rows of a K tile and of a V tile. In a run of tiles of one
-  // source they are stepped by the copies themselves; elsewhere set_ptrs computes them, a few vector
-  // instructions per row that go into the vector phase, which is the shorter one.
-  const ix::GroupRuns runs = ix::group_runs<G>(st, grp);
-  ix::LaneBase k_lane[C::kVariants], v_lane;
+  // ---- copies of K [0] and V [1]: where the last tile's first row lies and how far the next one's is from there, the lanes'
+  // offsets for this kind of tile, and the first tile that may be of another kind.
+  uint64_t base[2], step[2];
+  int bound[2] = {0, 0}, keys[2];
+  uint32_t pitch[2], off[2][C::kCopies];
+  auto set_kind = [&](auto is_v, int t) __attribute__((always_inline)) {
+    bound[is_v] = ix::group_next_bound(bounds, t);
+    keys[is_v] = ix::group_tile_keys<G>(bounds, c_len, n_blk, t);
+    pitch[is_v] = t < bounds.block ? c_pitch : b_pitch;
+    step[is_v] = ix::group_step<G>(bounds, t, pitch[is_v]);
+    base[is_v] = ix::group_tile_base<G>(bounds, t, row0[is_v], block_base[is_v], pitch[is_v]) - step[is_v] -
+                 (kWide ? 0 : ix::group_max_imm<G>());
+    if constexpr (!kWide) {
 #pragma unroll
-  for (int v = 0; v < C::kVariants; ++v)
-    k_lane[v] = ix::group_lane_base(st, ix::group_copy_row<G>(wr, lane, v), lane, 0);
-  v_lane = ix::group_lane_base(st, ix::group_copy_row<G>(wr, lane, 0), lane, 1);
-  const int row0 = ix::group_copy_row<G>(wr, lane, 0);
-  const char *k_ptr[C::kCopies], *v_ptr[C::kCopies];
-  auto set_k_ptrs = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < C::kCopies; ++u)
-      k_ptr[u] = ix::group_key_ptr(st, k_lane[u % C::kVariants], t * C::kKeys + 4 * R * u + row0);
+      for (int u = 0; u < C::kCopies; ++u) off[is_v][u] = ix::group_lane_offset<G>(wr, lane, u, pitch[is_v], keys[is_v], is_v);
+    }
   };
-  auto set_v_ptrs = [&](int t) __attribute__((always_inline)) {
+  // Copies u .. u + kTogether - 1 of the tile.
+  auto start_copies = [&](auto is_v, auto u_c, uint32_t dst) __attribute__((always_inline)) {
+    constexpr int u = decltype(u_c)::value;
+    if constexpr (kWide) {
 #pragma unroll
-    for (int u = 0; u < C::kCopies; ++u) v_ptr[u] = ix::group_key_ptr(st, v_lane, t * C::kKeys + 4 * R * u + row0);
+      for (int v = u; v < u + C::kTogether; ++v) {
+        const int row = ix::group_copy_row<G>(wr, lane, v);
+        dma16(reinterpret_cast<const char *>(
+                  base[is_v] + static_cast<uint64_t>(static_cast<uint32_t>(ix::clamped_row(row, keys[is_v]))) * pitch[is_v] +
+                  ix::swizzled_chunk(row, lane, is_v) * 16),
+              dst + v * R * 1024);
+      }
+    } else {
+      copy_pair<u * R * 1024, ix::group_max_imm<G>()>(off[is_v][u], off[is_v][u + C::kTogether - 1], base[is_v], dst);
+    }
   };
+  auto copy_tile = [&](auto is_v, int i, uint32_t dst) __attribute__((always_inline)) {
+    if (tile_of(i) >= bound[is_v]) set_kind(is_v, tile_of(i));
+    base[is_v] += step[is_v];
+    for_each<C::kCopies, C::kTogether>([&](auto u) __attribute__((always_inline)) { start_copies(is_v, u, dst); });
+  };
+  constexpr std::integral_constant<int, 0> kK;
+  constexpr std::integral_constant<int, 1> kV;
   uint32_t k_dst = lds_addr0 + ix::group_copy_dst<G>(grp, wr, 0, 0, 0);
   uint32_t v_dst = lds_addr0 + ix::group_copy_dst<G>(grp, wr, 0, 0, 1);
   const uint32_t k_dst0 = k_dst, v_dst_sum = 2 * v_dst + C::kTile;
-  auto copy_k = [&](int i) __attribute__((always_inline)) {
-    set_k_ptrs(tile_of(i));
-#pragma unroll
-    for (int u = 0; u < C::kCopies; ++u) dma16(k_ptr[u], k_dst + u * R * 1024);
-    k_dst += C::kTile;
-  };
   int wt_count, wt_first;  // (computed behind the first copies)
   ix::group_start_steps([&](auto what) __attribute__((always_inline)) {
     if constexpr (what == ix::kStartK0) {
-      copy_k(0);
+      copy_tile(kK, 0, k_dst0);
     } else if constexpr (what == ix::kStartQ) {
       // The query rows (rows past the end re-read the last one and are not stored): 4 R per wave.
       wt_count = ix::wave_tiles_of_qtile(qt, p.wt_base, p.wt_rem);
@@ -148,12 +201,9 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       }
     } else if constexpr (what == ix::kStartK1K2) {
 #pragma unroll 1
-      for (int i = 1; i < 3; ++i) copy_k(i);
-      k_dst = k_dst0;  // slot of K(3)
+      for (int i = 1; i < 3; ++i) copy_tile(kK, i, k_dst0 + i * C::kTile);  // (k_dst: slot of K(3))
     } else {
-      set_v_ptrs(tile_of(0));
-#pragma unroll
-      for (int u = 0; u < C::kCopies; ++u) dma16(v_ptr[u], v_dst + u * R * 1024);
+      copy_tile(kV, 0, v_dst);
       v_dst += C::kTile;  // slot of V(1)
     }
   });
@@ -230,14 +280,21 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     mfma_op(cur[1], gi, 1);
     SDVG_SB();
   };
-  // Keys past n_k get -inf (the scores of tile t are in hand).
-  auto mask_tail = [&](int t) __attribute__((always_inline)) {
-    const int key0 = t * C::kKeys + 4 * hh;
+  // Rows past a tile's keys get -inf (its scores are in hand).
+  auto mask_tail = [&](int keys) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < NK; ++kb)
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (key0 + kb * 32 + 8 * (i >> 2) + (i & 3) >= p.n_k) s_acc[kb][i] = -INFINITY;
+        if (4 * hh + kb * 32 + 8 * (i >> 2) + (i & 3) >= keys) s_acc[kb][i] = -INFINITY;
+  };
+  // They have P = 0, but 0 times an infinite value would be NaN: their V becomes 0 once this wave's copies have landed.
+  auto clear_v = [&](int keys) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < C::kCopies; ++u)
+      if (ix::group_copy_row<G>(wr, lane, u) >= keys)
+        *(lds_f32x4 *)static_cast<uintptr_t>(v_dst_sum - v_dst + u * R * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+    wait_lds<0>();
   };
   // Softmax with the lazy running maximum of block_attn.hip.
   auto softmax_tile = [&]() __attribute__((always_inline)) {
@@ -282,7 +339,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       mfma_op(f[gi & 1][2], gi, 2);
       mfma_op(f[gi & 1][3], gi, 3);
     }
-    if ((tile_of(0) + 1) * C::kKeys > p.n_k) mask_tail(tile_of(0));
+    if (keys[kV] < C::kKeys) mask_tail(keys[kV]);
     auto first_max = [&](int g) __attribute__((always_inline)) -> float * {
       return reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + g * C::kGroup + C::kVSlots + C::kTile) +
              wr * 64 + lane;
@@ -321,16 +378,9 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     k_slot = k_slot == 2 ? 0 : k_slot + 1;
     k_move = k_slot == 2 ? -2 * C::kTile : C::kTile;
   };
-  int next_fresh = 1;
-  uint64_t next_step = 0;
-  auto plan_copies = [&](int i) __attribute__((always_inline)) {
-    asm volatile("" : "+s"(i));  // (where it stands, not earlier)
-    next_fresh = !ix::group_steady(runs, i);
-    next_step = ix::group_step(runs, i);
-  };
+  int keys_next = keys[kV];  // keys of the next iteration's tile; 0 past the last tile
   // Behind the third MFMA of group gi.
   auto chores = [&](int gi, int i) __attribute__((always_inline)) {
-    if (gi == 0) plan_copies(i + 1);
     if (gi == 2 * NK - 1) {  // all K operands are on their way
 #pragma unroll
       for (int s = 0; s < 8; ++s) k_off[s] += k_move;
@@ -349,17 +399,23 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
 #pragma unroll
   for (int s = 0; s < 8; ++s) k_off[s] += k_move;
   next_k_slot();
-  plan_copies(0);
 #pragma unroll 1
   for (int i = 0; i + 1 < n_it; ++i) {
-    uint64_t step = next_step;
-    const int fresh = next_fresh;  // this iteration's copies need fresh pointers
-    if (__builtin_expect(fresh, 0)) {
+    const int t_k = tile_of(i + 3), t_v = tile_of(i + 1);
+    if (__builtin_expect(t_k >= bound[kK] || t_v >= bound[kV], 0)) {
       asm volatile("" ::: "memory");  // a real branch: keep this arithmetic off the fast path
-      set_k_ptrs(tile_of(i + 3));
-      set_v_ptrs(tile_of(i + 1));
-      step = 0;
+      if (keys_next < C::kKeys) {     // of this tile (behind a short tile comes another kind)
+        wait_vmcnt0();
+        clear_v(keys_next);
+      }
+      if (t_k >= bound[kK]) set_kind(kK, t_k);
+      if (t_v >= bound[kV]) {
+        set_kind(kV, t_v);
+        keys_next = t_v < bounds.end ? keys[kV] : 0;
+      }
     }
+    base[kK] += step[kK];
+    base[kV] += step[kV];
     softmax_tile();
     asm volatile("" : "+v"(s_init));
 #pragma unroll
@@ -370,17 +426,16 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     wait_vmcnt0();  // the copies started in the previous matrix phase have landed
     wg_barrier();
     __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int gi = 0; gi < 4 * NK; ++gi) {
+    for_each<4 * NK, 1>([&](auto gi_c) __attribute__((always_inline)) {
+      constexpr int gi = decltype(gi_c)::value;
       run_group(gi, gi + 1 < 4 * NK);
-#pragma unroll
-      for (int c = gi * kPerGroup; c < (gi + 1) * kPerGroup; ++c) {
+      for_each<(gi + 1) * kPerGroup, C::kTogether, gi * kPerGroup>([&](auto c) __attribute__((always_inline)) {
         constexpr int n = C::kCopies;
-        if (c < n)
-          v_ptr[c] = dma16_step(v_ptr[c], step, v_dst + c * R * 1024);
+        if constexpr (c < n)
+          start_copies(kV, c, v_dst);
         else
-          k_ptr[c - n] = dma16_step(k_ptr[c - n], step, k_dst + (c - n) * R * 1024);
-      }
+          start_copies(kK, std::integral_constant<int, c - n>{}, k_dst);
+      });
       SDVG_SB();
       mfma_op(f[gi & 1][2], gi, 2);
       SDVG_SB();
@@ -388,10 +443,8 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       SDVG_SB();
       if (gi + 1 < 4 * NK) mfma_op(f[gi & 1][3], gi, 3);
       SDVG_SB();
-      if (gi == 2 * NK - 1 && __builtin_expect(fresh, 0)) {
-        if ((tile_of(i + 1) + 1) * C::kKeys > p.n_k) mask_tail(tile_of(i + 1));
-      }
-    }
+      if (gi == 2 * NK - 1 && __builtin_expect(keys_next < C::kKeys, 0)) mask_tail(keys_next);
+    });
     __builtin_amdgcn_s_setprio(2);
     wg_barrier();
     SDVG_SB();
@@ -404,10 +457,11 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
 #pragma unroll
   for (int j = 0; j < 2 * NK; ++j) asm volatile("" : "+v"(pf[j]));
   wait_vmcnt0();
+  if (__builtin_expect(keys_next < C::kKeys, 0)) clear_v(keys_next);
   wg_barrier();
   // A group that is past the last tile has only the last key's row there, with P = 0; it adds nothing,
   // because 0 times an infinite value would be NaN.
-  if (tile_of(n_it - 1) < p.n_tiles) {
+  if (tile_of(n_it - 1) < bounds.end) {
 #pragma unroll
     for (int a = 0; a < 4; ++a) read_op(f[0][a], 2 * NK, a);
 #pragma unroll
@@ -485,19 +539,33 @@ constexpr size_t lds_bytes() {
 namespace sdvg {
 
 hipError_t prepare_block_attn_groups() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_groups_kernel<2>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<2>());
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(block_attn_groups_kernel<4>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<4>());
+  const struct {
+    const void *kernel;
+    size_t lds_bytes;
+  } kernels[] = {{reinterpret_cast<const void *>(block_attn_groups_kernel<2, false>), lds_bytes<2>()},
+                 {reinterpret_cast<const void *>(block_attn_groups_kernel<2, true>), lds_bytes<2>()},
+                 {reinterpret_cast<const void *>(block_attn_groups_kernel<4, false>), lds_bytes<4>()},
+                 {reinterpret_cast<const void *>(block_attn_groups_kernel<4, true>), lds_bytes<4>()}};
+  for (const auto &k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(k.lds_bytes));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int G>
+static void launch(const AttnParams &p, hipStream_t s) {
+  const bool wide = (p.cache_len > 0 && !ix::group_takes(static_cast<uint64_t>(p.kv_ts) * 2)) ||
+                    !ix::group_takes(static_cast<uint64_t>(p.blk_ts) * 2);
+  const auto kernel = wide ? block_attn_groups_kernel<G, true> : block_attn_groups_kernel<G, false>;
+  hipLaunchKernelGGL(kernel, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512), lds_bytes<G>(), s, p);
 }
 
 int launch_block_attn_groups(const AttnParams &p, int groups, hipStream_t s) {
-  const dim3 grid(8 * p.work_per_xcd + p.n_copy_blocks);
   if (groups == 2)
-    hipLaunchKernelGGL(block_attn_groups_kernel<2>, grid, dim3(512), lds_bytes<2>(), s, p);
+    launch<2>(p, s);
   else
-    hipLaunchKernelGGL(block_attn_groups_kernel<4>, grid, dim3(512), lds_bytes<4>(), s, p);
+    launch<4>(p, s);
   SDVG_HIP_CHECK(hipGetLastError());
   return SDVG_OK;
 }

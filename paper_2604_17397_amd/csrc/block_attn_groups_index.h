@@ -3,6 +3,7 @@
 // pointer arithmetic, compiled into the kernel and into tests/host/attn_groups_replay.cpp.
 #pragma once
 #include <stddef.h>
+#include <stdint.h>
 
 #include <type_traits>
 #include <utility>
@@ -24,8 +25,7 @@ struct Groups {
   static constexpr int kVSlots = 3 * kTile;            // a group's LDS: K slots 0, 1, 2, then V slots 0, 1
   static constexpr int kGroup = 5 * kTile;
   static constexpr int kCopies = kKeys / (4 * kRowWaves);  // 1 KB copies per wave, tile and tensor
-  // K swizzles that occur among a lane's rows (the swizzle is a function of row % 16)
-  static constexpr int kVariants = kCopies < 16 / (4 * kRowWaves) ? kCopies : 16 / (4 * kRowWaves);
+  static constexpr int kTogether = kRowWaves * 1024 < 4096 ? 2 : 1;  // copies that share one LDS address (group_copy_imm)
 };
 
 // What a wave starts before the loop: K(0), its share of the query rows, K(1) and then K(2), V(0). The kernel goes through
@@ -89,44 +89,68 @@ SDVG_HD uint32_t group_query_tile(int wr) {
 }
 SDVG_HD int swizzled_chunk(int row, int lane, int is_v) { return (lane & 15) ^ (is_v ? 4 * (row & 3) : (row & 15)); }
 
-// Iteration i of a group (its i-th tile) copies V of its tile i + 1 and K of its tile i + 3. The copy
-// pointers move on from iteration i - 1 by the same step as long as all tiles concerned lie in the
-// cache (i < cache_end), or all in the block before the ragged end (block_first <= i < block_end).
-// Elsewhere (around the seam, at the end and past it) they are computed from the rows.
-struct GroupRuns {
-  int cache_end, block_first, block_end;
-  uint64_t step_c, step_b;  // G tiles of the cache / of the block, in bytes
+// Iteration i of a group (its i-th tile) copies V of its tile i + 1 and K of its tile i + 3. No tile holds keys of both the
+// cache and the block: the cache's tiles come first, then the block's, and the last tile of each may be short. A copy
+// then takes a scalar address and a 32-bit offset per lane, which only change with the source and with a short tile.
+// What follows the last key of a short tile repeats that key's row and is masked; past the last tile a group
+// takes the last one, masked as a whole.
+SDVG_HD int source_tiles(int n_keys, int per_tile) { return (n_keys + per_tile - 1) / per_tile; }
+// The first tiles that are not a whole tile of the cache, in the block, not a whole tile of the block, past the end.
+struct GroupBounds {
+  int cache_whole, block, block_whole, end;
 };
 template <int G>
-SDVG_HD GroupRuns group_runs(const Streams &s, int group) {
+SDVG_HD GroupBounds group_bounds(int c_len, int n_blk) {
   constexpr int n = Groups<G>::kKeys;
-  auto first_at = [&](int tile) { return (tile - group + G - 1 + 8 * G) / G - 8; };  // first i with group + G i >= tile
-  return GroupRuns{first_at(s.c_len / n) - 3, first_at((s.c_len + n - 1) / n), first_at(s.n_k / n) - 3,
-                   static_cast<uint64_t>(G * n) * s.kv_tsb, static_cast<uint64_t>(G * n) * s.blk_tsb};
+  const int block = source_tiles(c_len, n);
+  return GroupBounds{c_len / n, block, block + n_blk / n, block + source_tiles(n_blk, n)};
 }
-SDVG_HD bool group_steady(const GroupRuns &r, int i) {
-  return i < r.cache_end || (i >= r.block_first && i < r.block_end);
+// The next of them behind tile t, from which on the kind of tile may be another one.
+SDVG_HD int group_next_bound(const GroupBounds &b, int t) {
+  return t < b.cache_whole ? b.cache_whole : t < b.block ? b.block : t < b.block_whole ? b.block_whole
+                                                           : t < b.end ? b.end : INT32_MAX;
 }
-SDVG_HD uint64_t group_step(const GroupRuns &r, int i) { return i < r.cache_end ? r.step_c : r.step_b; }
-// Token 0 of one tensor's cache rows and the (virtual) token 0 of its block rows, were they numbered
-// like the cache's, plus this lane's swizzled 16-byte chunk: key j is at cache + j * kv_tsb or at
-// block + j * blk_tsb.
-struct LaneBase {
-  uint64_t cache, block;
-};
-SDVG_HD LaneBase group_lane_base(const Streams &s, int row, int lane, int is_v) {
-  const uint64_t chunk = swizzled_chunk(row, lane, is_v) * 16;
-  return LaneBase{reinterpret_cast<uint64_t>(is_v ? s.vc : s.kc) + chunk,
-                  reinterpret_cast<uint64_t>(is_v ? s.vb : s.kb) + chunk -
-                      static_cast<uint64_t>(static_cast<uint32_t>(s.c_len)) * s.blk_tsb};
+// Keys of tile t, and of the last tile for those past the end (which are masked).
+template <int G>
+SDVG_HD int group_tile_keys(const GroupBounds &b, int c_len, int n_blk, int t) {
+  constexpr int n = Groups<G>::kKeys;
+  if (t < b.block) return t < b.cache_whole ? n : c_len % n;
+  return t < b.block_whole || n_blk % n == 0 ? n : n_blk % n;
 }
-// Address of the row of key min(j, n_k - 1).
-SDVG_HD const char *group_key_ptr(const Streams &s, const LaneBase &b, int j) {
-  j = j < s.n_k ? j : s.n_k - 1;
-  const bool in_cache = j < s.c_len;
-  return reinterpret_cast<const char *>((in_cache ? b.cache : b.block) +
-                                        static_cast<uint64_t>(static_cast<uint32_t>(j)) *
-                                            (in_cache ? s.kv_tsb : s.blk_tsb));
+// Token 0 of the block's rows, were the tiles' rows numbered through: tile t's first row is at this + t * keys * pitch.
+template <int G>
+SDVG_HD uint64_t group_block_base(const GroupBounds &b, uint64_t block_row0, uint32_t pitch) {
+  return block_row0 - static_cast<uint64_t>(static_cast<uint32_t>(b.block * Groups<G>::kKeys)) * pitch;
+}
+template <int G>
+SDVG_HD uint64_t group_tile_base(const GroupBounds &b, int t, uint64_t cache_row0, uint64_t block_base, uint32_t pitch) {
+  t = t < b.end ? t : b.end - 1;
+  return (t < b.block ? cache_row0 : block_base) + static_cast<uint64_t>(static_cast<uint32_t>(t * Groups<G>::kKeys)) * pitch;
+}
+// From a group's tile to its next one of the same kind.
+template <int G>
+SDVG_HD uint64_t group_step(const GroupBounds &b, int t, uint32_t pitch) {
+  return t < b.end ? static_cast<uint64_t>(G * Groups<G>::kKeys) * pitch : 0;
+}
+// Pitches (bytes) for which the offsets fit 32 bits; with others a copy takes a 64-bit address per lane.
+SDVG_HD bool group_takes(uint64_t pitch) { return pitch < (uint64_t{1} << 26); }
+// The copy instruction adds its immediate to the LDS address as well as to the source address: of copies that share an LDS
+// address each has an offset that is less by its immediate, and the scalar address is kImm below the tile's first row, so
+// that no offset is negative.
+template <int G>
+SDVG_HD constexpr int group_copy_imm(int u) {
+  return u % Groups<G>::kTogether * Groups<G>::kRowWaves * 1024;
+}
+template <int G>
+SDVG_HD constexpr int group_max_imm() {
+  return group_copy_imm<G>(Groups<G>::kTogether - 1);
+}
+SDVG_HD int clamped_row(int row, int keys) { return row < keys ? row : keys - 1; }
+template <int G>
+SDVG_HD uint32_t group_lane_offset(int wr, int lane, int u, uint32_t pitch, int keys, int is_v) {
+  const int row = group_copy_row<G>(wr, lane, u);
+  return static_cast<uint32_t>(clamped_row(row, keys)) * pitch + static_cast<uint32_t>(swizzled_chunk(row, lane, is_v) * 16) +
+         static_cast<uint32_t>(group_max_imm<G>() - group_copy_imm<G>(u));
 }
 
 // Where the merge (of the 32-row kernel too) keeps O: the 16 bytes holding dims 8 c + 4 hh .. + 3 of a row, in the part of the wave

@@ -1,8 +1,8 @@
 // Host replay of the grouped attention kernel's copy schedule, from the index header the kernel
 // compiles in. For every configuration all 8 waves x 64 lanes perform the copies of
 // block_attn_groups.hip in its order with fake base addresses; at each point of use K slot / V slot
-// of every group must hold exactly the keys of that group's tile (clamped at the last key) with the
-// swizzle the reads undo, no copy may address a token at or past c_len in the cache or at or past
+// of every group must hold exactly the keys of that group's tile (the last one again past the end of a short tile) with the
+// swizzle the reads undo, every key is handled once, no copy may address a token at or past c_len in the cache or at or past
 // n_blk in the block, and every LDS address stays inside the workgroup's part. Exit code 0 = passed.
 #include <cstdint>
 #include <cstdio>
@@ -42,28 +42,58 @@ struct Replay {
     return true;
   }
 
-  // The lanes' copy pointers of one group, for K or for V: fresh or stepped, as the kernel does it.
-  struct Ptrs {
-    const char *p[C::kRowWaves][64][C::kCopies];
+  // One tensor's copies as the kernel makes them: set_kind and start_copies of block_attn_groups.hip.
+  struct Copies {
+    uint64_t base = 0, step = 0;
+    int bound = 0, keys = 0;
+    uint32_t pitch = 0;
+    uint32_t off[C::kRowWaves][64][C::kCopies] = {};
   };
-  void set(Ptrs &x, int t, int is_v) {
+  ix::GroupBounds bounds{};
+  bool wide = false;
+  void set_kind(Copies &x, int t, int is_v) {
+    x.bound = ix::group_next_bound(bounds, t);
+    x.keys = ix::group_tile_keys<G>(bounds, s.c_len, n_blk, t);
+    x.pitch = t < bounds.block ? s.kv_tsb : s.blk_tsb;
+    auto at = [&](const char *q) { return reinterpret_cast<uint64_t>(q); };
+    x.step = ix::group_step<G>(bounds, t, x.pitch);
+    x.base = ix::group_tile_base<G>(bounds, t, at(is_v ? s.vc : s.kc),
+                                    ix::group_block_base<G>(bounds, at(is_v ? s.vb : s.kb), s.blk_tsb), x.pitch) -
+             x.step - (wide ? 0 : ix::group_max_imm<G>());
+    if (wide) return;
     for (int wr = 0; wr < C::kRowWaves; ++wr)
       for (int lane = 0; lane < 64; ++lane)
-        for (int u = 0; u < C::kCopies; ++u) {
-          const int variant = is_v ? 0 : u % C::kVariants;
-          const ix::LaneBase b = ix::group_lane_base(s, ix::group_copy_row<G>(wr, lane, variant), lane, is_v);
-          x.p[wr][lane][u] = ix::group_key_ptr(
-              s, b, t * C::kKeys + 4 * C::kRowWaves * u + ix::group_copy_row<G>(wr, lane, 0));
-        }
+        for (int u = 0; u < C::kCopies; ++u)
+          x.off[wr][lane][u] = ix::group_lane_offset<G>(wr, lane, u, x.pitch, x.keys, is_v);
   }
-  bool copy(Ptrs &x, uint64_t step, int grp, int is_v, int slot) {
+  bool copy(Copies &x, int t, int grp, int is_v, int slot) {
+    if (t >= x.bound) set_kind(x, t, is_v);
+    if (x.keys < 1 || x.keys > C::kKeys) return error = "not a tile", false;
+    x.base += x.step;
     for (int wr = 0; wr < C::kRowWaves; ++wr)
       for (int lane = 0; lane < 64; ++lane)
         for (int u = 0; u < C::kCopies; ++u) {
-          x.p[wr][lane][u] += step;
-          if (!put(x.p[wr][lane][u], ix::group_copy_dst<G>(grp, wr, u, slot, is_v) + 16 * lane, is_v)) return false;
+          const uint32_t imm = ix::group_copy_imm<G>(u);
+          const int row = ix::group_copy_row<G>(wr, lane, u);
+          const uint64_t src = wide ? x.base + static_cast<uint64_t>(ix::clamped_row(row, x.keys)) * x.pitch +
+                                          ix::swizzled_chunk(row, lane, is_v) * 16
+                                    : x.base + x.off[wr][lane][u] + imm;
+          // copies that share an LDS address: the first one's, plus the immediate
+          const uint32_t dst = ix::group_copy_dst<G>(grp, wr, u - u % C::kTogether, slot, is_v) + imm;
+          if (dst != ix::group_copy_dst<G>(grp, wr, u, slot, is_v)) return error = "immediate and LDS address disagree", false;
+          if (!put(reinterpret_cast<const char *>(src), dst + 16 * lane, is_v)) return false;
         }
     return true;
+  }
+  // Keys of tile t by the definition: the cache's tiles, then the block's.
+  struct Tile {
+    int key0, keys;
+  };
+  Tile tile_at(int t) const {
+    const int n_cache = (s.c_len + C::kKeys - 1) / C::kKeys, n = n_cache + (n_blk + C::kKeys - 1) / C::kKeys;
+    t = t < n ? t : n - 1;
+    const int first = (t < n_cache ? t : t - n_cache) * C::kKeys, left = (t < n_cache ? s.c_len : n_blk) - first;
+    return Tile{(t < n_cache ? 0 : s.c_len) + first, left < C::kKeys ? left : C::kKeys};
   }
 
   // Reads the tile exactly as the matrix phase does (every operand of every lane).
@@ -72,7 +102,8 @@ struct Replay {
       const int r32 = lane & 31, hh = lane >> 5, i16 = lane & 15, b16 = (lane >> 4) & 1;
       const int base = grp * C::kGroup + is_v * C::kVSlots + slot * C::kTile;
       auto want = [&](int off, int row, int byte_in_row) {
-        const int jr = t * C::kKeys + row, j = jr < s.n_k ? jr : s.n_k - 1;
+        const Tile tile = tile_at(t);
+        const int j = tile.key0 + (row < tile.keys ? row : tile.keys - 1);
         const Cell &c = lds[(base + off) / 16];
         if (c.v == is_v && c.key == j && c.chunk == byte_in_row / 16 && (base + off) % 16 == byte_in_row % 16) return true;
         error = is_v ? "V tile holds the wrong rows" : "K tile holds the wrong rows";
@@ -97,38 +128,39 @@ struct Replay {
   bool run(int c_len, int nb, uint32_t kv_tsb, uint32_t blk_tsb) {
     s = ix::Streams{kBase, kBase + kSpan, kBase + 2 * kSpan, kBase + 3 * kSpan, kv_tsb, blk_tsb, c_len, c_len + nb};
     n_blk = nb;
-    const int n_tiles = (s.n_k + C::kKeys - 1) / C::kKeys, n_it = (n_tiles + G - 1) / G;
-    std::vector<char> seen(n_tiles, 0);
+    bounds = ix::group_bounds<G>(c_len, nb);
+    wide = (c_len > 0 && !ix::group_takes(kv_tsb)) || !ix::group_takes(blk_tsb);
+    const int n_it = (bounds.end + G - 1) / G;
+    std::vector<char> seen(s.n_k, 0);
     for (int g = 0; g < G; ++g) {
       auto tile_of = [&](int i) { return g + G * i; };
-      Ptrs k, v;
-      for (int i = 0; i < 3; ++i) {
-        set(k, tile_of(i), 0);
-        if (!copy(k, 0, g, 0, i)) return false;
-      }
-      set(v, tile_of(0), 1);
-      if (!copy(v, 0, g, 1, 0) || !check(g, 0, tile_of(0), 0)) return false;
-      const ix::GroupRuns runs = ix::group_runs<G>(s, g);
+      Copies k, v;
+      for (int i = 0; i < 3; ++i)
+        if (!copy(k, tile_of(i), g, 0, i)) return false;
+      if (!copy(v, tile_of(0), g, 1, 0) || !check(g, 0, tile_of(0), 0)) return false;
+      int keys_next = v.keys;
       for (int i = 0; i < n_it; ++i) {
-        uint64_t step = ix::group_step(runs, i);
-        const bool fresh = !ix::group_steady(runs, i);
-        if (fresh) {
-          set(k, tile_of(i + 3), 0);
-          set(v, tile_of(i + 1), 1);
-          step = 0;
+        // V(i) of a short tile is cleared past its keys: at the next change of kind, or behind the loop
+        const int keys_now = keys_next;
+        if (tile_of(i) < bounds.end && keys_now != tile_at(tile_of(i)).keys) return error = "wrong mask", false;
+        if (i + 1 < n_it && keys_now < C::kKeys && tile_of(i + 3) < k.bound && tile_of(i + 1) < v.bound)
+          return error = "a short tile that is not cleared", false;
+        if (i + 1 < n_it && tile_of(i + 1) >= v.bound) {
+          set_kind(v, tile_of(i + 1), 1);
+          keys_next = tile_of(i + 1) < bounds.end ? v.keys : 0;
         }
-        if (!fresh && (tile_of(i + 1) + 1) * C::kKeys > s.n_k) return error = "a tile that needs the mask is not fresh", false;
         // matrix phase i reads K(i+1) and V(i); its copies of V(i+1) and K(i+3) land at any time in it
         for (int late = 0; late < 2; ++late) {
-          if (late && i + 1 < n_it && (!copy(v, step, g, 1, (i + 1) % 2) || !copy(k, step, g, 0, i % 3))) return false;
+          if (late && i + 1 < n_it && (!copy(v, tile_of(i + 1), g, 1, (i + 1) % 2) || !copy(k, tile_of(i + 3), g, 0, i % 3)))
+            return false;
           if (i + 1 < n_it && !check(g, 0, tile_of(i + 1), (i + 1) % 3)) return false;
           if (!check(g, 1, tile_of(i), i % 2)) return false;
         }
-        if (tile_of(i) < n_tiles) seen[tile_of(i)]++;
+        for (int r = 0; tile_of(i) < bounds.end && r < keys_now; ++r) seen[tile_at(tile_of(i)).key0 + r]++;
       }
     }
     for (char c : seen)
-      if (c != 1) return error = "a tile is not handled exactly once", false;
+      if (c != 1) return error = "a key is not handled exactly once", false;
     return true;
   }
 };
@@ -146,6 +178,10 @@ long sweep(int &bad) {
   for (int k : {0, 1, 6})
     for (int nb : {312, 1031, 4680}) one(k * nb, nb, 12 * 256, 256);
   one(100, 100, 0xfffffff0u / 16 * 8, 0x7ffffff0u);  // the largest pitches
+  const uint32_t most = (1u << 26) - 16;             // the largest that 32-bit offsets take
+  if (!ix::group_takes(most) || ix::group_takes(most + 16)) std::printf("FAIL limit of the pitch\n"), ++bad;
+  one(130, 130, most, most);
+  one(300, 77, most, 256);
   // the query rows' tiles lie in second V slots, one beside the other
   using C = ix::Groups<G>;
   std::vector<char> taken(G * C::kGroup / 8192, 0);

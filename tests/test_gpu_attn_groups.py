@@ -291,3 +291,21 @@ def test_second_tile_has_landed_when_it_is_read(groups, n_q):
         assert torch.equal(P.block_attn(q, kc, vc, kb, vb, c_len), want)
         flush.fill_(i)
         assert torch.equal(P.block_attn_commit(q, kc, vc, kb, vb, c_len), want)
+
+
+# The cache's keys end inside a tile (218 = 6 x 32 + 26 = 3 x 64 + 26), and so do the block's: the rows behind them repeat the
+# last key with P = 0, which must not meet an infinite value.
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,n_q,n_blk,groups,rows", [(129, 64, 70, 4, 64), (36, 449, 680, 2, 128)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_infinite_value_in_the_last_key_of_each_source(H, n_q, n_blk, groups, rows, value):
+    import paper_2604_17397_amd as P
+    plan = attn_plan(H, n_q, 218 + n_blk)
+    assert plan.groups == groups and plan.rows == rows
+    q, kc, vc, kb, vb = si.attn_inputs(H, max(n_q, n_blk), 218, seed=6)
+    dev = [to_dev_bf16(np.ascontiguousarray(a)) for a in (q[:n_q], kc, vc, kb[:n_blk], vb[:n_blk])]
+    want = P.block_attn(*dev, 218)
+    dev[2][217, 0, 5] = dev[4][-1, 1, 7] = value
+    out = P.block_attn(*dev, 218)
+    want[:, 0, 5] = want[:, 1, 7] = value
+    assert torch.equal(torch.nan_to_num(out, 1.5, 2.5, 3.5), torch.nan_to_num(want, 1.5, 2.5, 3.5))
