@@ -112,7 +112,7 @@ def lib():
 
 class _PythonOnly:
     """Stands in for the marshalling module where it has not been built: Python handles every call."""
-    block_attn = rope = route = staticmethod(lambda *args: None)
+    block_attn = rope = route = batch = commit = rollback = snapshot = staticmethod(lambda *args: None)
 
 
 _NATIVE = None
@@ -132,8 +132,10 @@ def _bind_native(L):
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
     entry = [ctypes.cast(f, ctypes.c_void_p).value for f in
-             (L.sdvg_block_attn, L.sdvg_block_attn_commit, L.sdvg_rope, L.sdvg_worst_frame_route, L.sdvg_avg_frame_route)]
-    module.init(*entry, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, np.float32)
+             (L.sdvg_block_attn, L.sdvg_block_attn_commit, L.sdvg_rope, L.sdvg_worst_frame_route, L.sdvg_avg_frame_route,
+              L.sdvg_block_attn_batch, L.sdvg_block_attn_batch_static, L.sdvg_kv_commit, L.sdvg_kv_commit_rope,
+              L.sdvg_kv_rollback, L.sdvg_buffer_snapshot)]
+    module.init(*entry, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, np.float32, sdvg_kv_cache)
     _NATIVE = module
 
 
@@ -302,6 +304,13 @@ def block_attn_batch(qs, k_caches, v_caches, k_blks, v_blks, cache_len, outs=Non
     cache_len == 0); every item must have the same shapes and strides. `workspace`: optional
     device tensor (any dtype) the library may use to split keys over workgroups, under the policy
     `split` ("never", "auto", "always"). Returns outs."""
+    if type(split) is str and split in _SPLIT:
+        r = (_NATIVE or _native()).batch(qs, k_caches, v_caches, k_blks, v_blks, cache_len, outs, workspace,
+                                        _SPLIT[split], scale, None if stream is None else stream.cuda_stream, _static)
+        if r is not None:
+            if type(r) is int:
+                raise SdvgError(r, "sdvg_block_attn_batch_static" if _static else "sdvg_block_attn_batch")
+            return r
     cache_len = int(cache_len)
     n = len(qs)
     if k_caches is None:
@@ -340,6 +349,11 @@ def block_attn_batch(qs, k_caches, v_caches, k_blks, v_blks, cache_len, outs=Non
 
 def kv_commit(cache, k_blk, v_blk, slot, stream=None):
     """sdvg_kv_commit: k_blk, v_blk dense bf16 [layers, T, heads, 128]."""
+    r = (_NATIVE or _native()).commit(cache.c, k_blk, v_blk, slot, None if stream is None else stream.cuda_stream)
+    if r is not None:
+        if r != 0:
+            raise SdvgError(r, "sdvg_kv_commit")
+        return
     _check_dev(k_blk, v_blk)
     if not (k_blk.is_contiguous() and v_blk.is_contiguous()):
         raise ValueError("k_blk and v_blk must be dense")
@@ -387,6 +401,11 @@ def rope(x, cos, sin, out=None, stream=None):
 def kv_commit_rope(cache, k_blk, v_blk, slot, cos, sin, stream=None):
     """sdvg_kv_commit_rope: kv_commit with k_blk (dense bf16 [layers, T, heads, 128], BEFORE the
     rotary embedding) rotated on its way into the cache; cos, sin float32 [T, 64]."""
+    r = (_NATIVE or _native()).commit(cache.c, k_blk, v_blk, slot, None if stream is None else stream.cuda_stream, cos, sin)
+    if r is not None:
+        if r != 0:
+            raise SdvgError(r, "sdvg_kv_commit_rope")
+        return
     _check_dev(k_blk, v_blk)
     if not (k_blk.is_contiguous() and v_blk.is_contiguous()):
         raise ValueError("k_blk and v_blk must be dense")
@@ -403,6 +422,11 @@ def kv_commit_rope(cache, k_blk, v_blk, slot, cos, sin, stream=None):
 
 
 def kv_rollback(cache, new_len, stream=None):
+    r = (_NATIVE or _native()).rollback(cache.c, new_len, None if stream is None else stream.cuda_stream)
+    if r is not None:
+        if r != 0:
+            raise SdvgError(r, "sdvg_kv_rollback")
+        return
     st = lib().sdvg_kv_rollback(ctypes.byref(cache.c), int(new_len), _stream_ptr(stream))
     if st != 0:
         raise SdvgError(st, "sdvg_kv_rollback")
@@ -411,6 +435,11 @@ def kv_rollback(cache, new_len, stream=None):
 def buffer_snapshot(dst, src, n_bytes=None, stream=None):
     """sdvg_buffer_snapshot: dst[:n_bytes] = src[:n_bytes] for two device tensors viewed as bytes
     (n_bytes defaults to the size of src)."""
+    r = (_NATIVE or _native()).snapshot(dst, src, n_bytes, None if stream is None else stream.cuda_stream)
+    if r is not None:
+        if r != 0:
+            raise SdvgError(r, "sdvg_buffer_snapshot")
+        return
     _check_dev(dst, src)
     if not (dst.is_contiguous() and src.is_contiguous()):
         raise ValueError("buffer_snapshot needs contiguous tensors")
