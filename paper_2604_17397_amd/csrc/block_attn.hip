@@ -470,7 +470,9 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
 // One workgroup per wave tile (32 rows) of a query tile, one wave per 32 of its dims, lanes laid out
 // as in the attention kernel; the pieces are added in their order. Few heads mean few query tiles of
 // many pieces, so what bounds this kernel is the chain of loads over the pieces: it needs many waves
-// and several pieces' loads in flight (one 8-wave workgroup per query tile took up to 250 us). The last workgroup of a
+// and several pieces' loads in flight (one 8-wave workgroup per query tile took up to 250 us; with loops unrolled by 4,
+// whose remainders load one piece after the other, 2 heads x 2450 x 19600 65 us, now 61, 1 x 4680 x 32760 89 -> 85). With
+// more heads it is bound by the bytes: 5 x 4680 x 32760 12 us for 47 MB. The last workgroup of a
 // query tile to finish could merge instead, without a second kernel: it was slower (12 heads x 4680 x 14040 keys 406 us
 // against 376), because releasing and acquiring the partial results at device scope adds 5 to 12 us to every piece.
 __global__ __launch_bounds__(256) void block_attn_merge_kernel(const AttnParams p) {
@@ -488,24 +490,37 @@ __global__ __launch_bounds__(256) void block_attn_merge_kernel(const AttnParams 
   auto part_of = [&](int i) __attribute__((always_inline)) {
     return partial_of(p, ix::piece_slot(p.split, hq, i, p.n_hq, helper0), wt);
   };
-  float shift_min = part_of(0)[64 * 64 + 32 + r32];
-#pragma unroll 8
-  for (int i = 1; i < n_pieces; ++i) shift_min = fminf(shift_min, part_of(i)[64 * 64 + 32 + r32]);
+  // Pieces past the last one are read as the last one, so that all loads of a turn are on their way together, and not added.
+  float shift_min = INFINITY;
+  for (int i = 0; i < n_pieces; i += 8) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) shift_min = fminf(shift_min, part_of(min(i + j, n_pieces - 1))[64 * 64 + 32 + r32]);
+  }
   float o_acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) o_acc[i] = 0.f;
   float l = 0.f;
-#pragma unroll 4
-  for (int i = 0; i < n_pieces; ++i) {
-    const float *part = part_of(i);
-    const float f = __builtin_amdgcn_exp2f((shift_min - part[64 * 64 + 32 + r32]) * p.scale_log2e);
+  for (int i = 0; i < n_pieces; i += 4) {
+    f32x4 o4[4][4];
+    float l_j[4], shift_j[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 o4 = *reinterpret_cast<const f32x4 *>(part + ((4 * u + g) * 64 + lane) * 4);
+    for (int j = 0; j < 4; ++j) {
+      const float *part = part_of(min(i + j, n_pieces - 1));
+      shift_j[j] = part[64 * 64 + 32 + r32];
+      l_j[j] = part[64 * 64 + r32];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o_acc[4 * g + j] += f * o4[j];
+      for (int g = 0; g < 4; ++g) o4[j][g] = *reinterpret_cast<const f32x4 *>(part + ((4 * u + g) * 64 + lane) * 4);
     }
-    l += f * part[64 * 64 + r32];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool any = i + j < n_pieces;  // (0 times an infinite value would be NaN)
+      const float f = any ? __builtin_amdgcn_exp2f((shift_min - shift_j[j]) * p.scale_log2e) : 0.f;
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o_acc[4 * g + e] += f * (any ? o4[j][g][e] : 0.f);
+      l += f * (any ? l_j[j] : 0.f);
+    }
   }
   const float inv_l = 1.0f / l;
   if (q_row >= p.n_q) return;
