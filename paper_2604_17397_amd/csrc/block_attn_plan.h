@@ -16,10 +16,9 @@ constexpr int kPlanRows = 256;  // query rows of a workgroup without key groups
 
 // How a launch is cut into workgroups. Plain: one workgroup per query tile (units == n_tiles).
 // Key split: when the query tiles would leave a good part of the last round of workgroups idle
-// (a drafter-shaped layer has 12 heads x 19 query tiles = 228 workgroups for 256 compute units),
-// the (query tile, key tile) pairs are dealt out evenly over whole rounds instead, every
-// workgroup taking about the same number of pairs; the query tiles' pieces leave partial
-// results that a second, small kernel merges.
+// (5 heads x 19 query tiles are 95 workgroups for 256 compute units), every query tile's keys are cut into equal
+// columns, as many as there is room for, and the workgroups left over share what the columns leave (cut_keys); the
+// pieces leave partial results that a second, small kernel merges.
 struct Plan {
   int n_qtiles, n_hq, n_tiles;
   int units;     // key tiles of a workgroup; == n_tiles when nothing is split
@@ -34,22 +33,23 @@ struct Plan {
 // Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
 // compute units, times a fixed part plus the key tiles each group walks.
 // Measured on MI355X, us among others in a graph (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
-//   12 heads x 312 x 936 keys [24/36/60] 26.4 / 17.8 / 13.4; 12 x 1031 x 6186 [60/108/204] 107 / 65 / 50;
-//   12 x 1560 x 4680 [84/156/300] 85 / 53 / 75; 5 x 4680 x 32760 [95/185/370] 529 / 374 / 494;
-//   40 x 1031 x 3093 [200/360/680] 74 / 90 / 101; 16 x 4680 x 14040 [304/592/1184] 587 / 522 / 586;
-//   12 x 4680 x 14040 [228/444/888] 335 / 360 / 474.
+//   12 heads x 312 x 936 keys [24/36/60] 25.7 / 17.6 / 13.3; 12 x 1031 x 6186 [60/108/204] 105 / 63 / 48;
+//   12 x 1560 x 4680 [84/156/300] 82 / 52 / 72; 5 x 4680 x 32760 [95/185/370] 511 / 362 / 451;
+//   40 x 1031 x 3093 [200/360/680] 72 / 88 / 99; 16 x 4680 x 14040 [304/592/1184] 581 / 511 / 572;
+//   12 x 4680 x 14040 [228/444/888] 332 / 348 / 461.
 // A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value, and
 // the estimate is up to 25 % off in absolute terms; what counts is the order. Over 1 to 40 heads, 156
-// to 4680 rows and 193 to 32760 keys it is within 1.7 % of the fastest of the four in each of 299 launches
-// (profiles/attn_plan_sweep.txt, as the other figures here). Up to 192 keys it stays with 1 group, where more are
-// faster (3 heads x 250 rows x 128 keys 11.9 / 7.1 / 6.0).
+// to 4680 rows and 193 to 32760 keys it is within 1 % of the fastest of the four in 296 of 299 launches and 4 to 11 % off in
+// three, where 64 rows beat 32 (profiles/attn_plan_sweep.txt, as the other figures here). Up to 192 keys it stays with
+// 1 group, where more are faster (3 heads x 250 rows x 128 keys 11.7 / 7.4 / 6.2).
 // Of the launches of four groups, those whose 32-row workgroups need no more rounds than 64-row ones take the kernel
 // where the two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32). One round, us
-// with 64 / 32 rows: 12 x 312 x 936 13.5 / 10.6; 16 x 500 x 1000 14.4 / 12.2; 8 x 1024 x 6144 45.9 / 39.3, with keys from
-// HBM 64.0 / 46.3. (4 x 2000 x 14000 loses, 90.5 / 99.0, where the memory-side cache holds the layer's 29 MB; the layers of
-// a model of this size come from HBM, 132 / 96.) More rounds with as many workgroups (up to 32 rows): 300 x 32 x 512
-// 24.6 / 22.7; 259 x 1 x 936 34.7 / 33.2. In a round more than with 64 rows every workgroup walks all keys again:
-// 12 x 1031 x 1031 15.4 / 21.0; 320 x 33 x 256 16.8 / 20.3; 300 x 64 x 256 17.7 / 18.5.
+// with 64 / 32 rows: 12 x 312 x 936 13.3 / 9.4; 16 x 500 x 1000 13.7 / 12.1; 8 x 1024 x 6144 41.0 / 38.8, with keys from
+// HBM 62.2 / 46.2. (4 x 2000 x 14000 loses, 84.3 / 97.7, where the memory-side cache holds the layer's 29 MB; the layers of
+// a model of this size come from HBM, 129 / 95.) More rounds with as many workgroups (up to 32 rows), before the copies from
+// scalar addresses (block_attn_groups.hip), which gave 64 rows 1 to 2 %: 300 x 32 x 512 24.6 / 22.7; 259 x 1 x 936 34.7 / 33.2.
+// In a round more than with 64 rows every workgroup walks all keys again: 12 x 1031 x 1031 14.6 / 20.2; 320 x 33 x 256 16.8 /
+// 20.3; 300 x 64 x 256 17.7 / 18.5.
 struct Groups {
   int groups, rows;
   double us;  // the estimate
@@ -131,10 +131,11 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   const int rounds = (pl.n_hq + n_cu - 1) / n_cu;
   const double idle = 1.0 - static_cast<double>(pl.n_hq) / (static_cast<double>(rounds) * n_cu);
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
-  // a chip that is only partly busy clocks higher. Measured on MI355X, us plain / split, at 4680 rows:
-  //   11 % idle  12 heads x 14040 keys 335 / 351, x 32760 761 / 774, 24 x 14040 661 / 692
-  //   18 - 26 %  11 x 32760 728 / 710, 20 x 18720 758 / 763
-  //   33 - 48 %  9 x 32760 629 / 576, 8 x 32760 618 / 526, 8 x 14040 259 / 243, 14 x 23400 843 / 664
+  // a chip that is only partly busy clocks higher: 228 busy compute units take a tile in 1.46 us, 256 in 1.61, so
+  // that 11 % idle cost nothing. Measured on MI355X, us, the fastest without a split / split, at 4680 rows:
+  //   11 % idle  12 heads x 14040 keys 332 / 345, x 32760 752 / 760, 24 x 14040 659 / 678
+  //   18 - 26 %  11 x 32760 713 / 701, 20 x 18720 740 / 743
+  //   33 - 48 %  8 x 32760 573 / 518, 8 x 14040 253 / 237, 14 x 23400 821 / 665
   // From kAutoIdle on the estimates decide (below).
   if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
   if (split_mode == SDVG_SPLIT_AUTO && idle < auto_idle) return plain();
@@ -150,11 +151,12 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     pl.total_wg = pl.n_hq * pl.split.cols + pl.split.n_help;
   }
   // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
-  // unsplit, us: 1 head x 4680 x 32760 93 / 149, 5 heads 346 / 374; 4 x 4680 x 14040 132 / 141,
-  // 5 heads 160 / 162; 12 x 1560 x 4680 63 / 53, 16 x 1031 x 3093 49 / 38, 3 x 4680 x 4680 56 / 40.
+  // unsplit, us: 1 head x 4680 x 32760 83 / 145, 5 heads 331 / 362; 4 x 4680 x 14040 127 / 141,
+  // 5 heads 153 / 157; 12 x 1560 x 4680 59 / 52, 16 x 1031 x 3093 42 / 36, 3 x 4680 x 4680 47 / 39.
+  // (Of 299 launches without a batch 6 would gain 5 to 25 % from a split that the estimate does not take, 0.3 % on average.)
   // Below 60 % idle the unsplit estimate, made for a full chip, is a little high for one that is half busy: the split
   // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (1 to 3 items, up to 40 heads, 312 to 4680 rows,
-  // 1 to 7 blocks of keys) 31 are split, 3 to 20 % faster each; 13 more would have gained 4 to 14 %.
+  // 1 to 7 blocks of keys) 31 are split, 1.5 to 15 % faster each; 7 more would have gained 3 to 11 %.
   const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(even);
   const bool few = idle >= kAutoIdleStatic;
   if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us + (few ? 0.0 : 11.0)) {

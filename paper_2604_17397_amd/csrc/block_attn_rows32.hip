@@ -15,8 +15,8 @@
 //   - the arguments of the first copies are in registers when a wave starts, all others are asked for at once
 //     behind those copies; the query rows come through the LDS once per workgroup.
 // us among others in a graph, four sets of tensors in turn, with 64 rows / here (profiles/attn_plan_sweep.txt): 12 heads x 312 x
-// 936 keys 13.5 / 10.6, 12 x 312 x 312 8.7 / 6.6, 8 x 1024 x 6144 45.9 / 39.3; with keys from HBM 15.6 / 12.6, 9.9 / 7.3, 64.0 / 46.3.
-// Where it went at 12 x 312 x 936 while the first copies still waited 0.3 us for their arguments (9.2 us with one set of tensors
+// 936 keys 13.4 / 9.4, 12 x 312 x 312 8.7 / 6.0, 8 x 1024 x 6144 41.0 / 38.8; with keys from HBM 13.3 / 9.4, 9.3 / 6.1, 62.2 / 46.2.
+// Where it went at 12 x 312 x 936, one workgroup per 32 rows, while the first copies still waited 0.3 us for their arguments (9.2 us with one set of tensors
 // again and again): 0.9 launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1
 // merge and store.
 // Where these workgroups are few (block_attn_plan.h) there are two per 32 rows, each with half of the output dims: 96 KB of

@@ -3,8 +3,8 @@
 
 Builds (1) the C oracle with gcc -fsanitize=address,undefined, (2) libsdvg with the sanitizers
 applied to its HOST code only (the argument validation of every entry point; device code is left
-alone) and (3) the host programs over the kernels' index headers (the replays of both attention
-kernels' copy schedules, the row numbering of the copy kernels), each into a temporary directory, and
+alone) and (3) the host programs over the kernels' index headers (the replays of the attention
+kernels' copy schedules, the cuts of the key split, the row numbering of the copy kernels), each into a temporary directory, and
 runs the `-m "not gpu"` tests that exercise them (or the program itself) under the matching sanitizer
 runtime. Run from the repository root:
 
@@ -54,10 +54,11 @@ def main():
     env = dict(base, SDVG_LIBRARY=lib, LD_PRELOAD=rt)
     rc |= run([sys.executable, "-m", "pytest", "-x", "-q", "tests/test_abi.py"], env)
     # (3) the host programs over the kernels' index headers
-    for name in ("attn_index_replay", "attn_groups_replay", "attn_rows32_replay", "row_map_check"):
+    for name in ("attn_index_replay", "attn_groups_replay", "attn_rows32_replay", "attn_rows32_halves", "attn_split_check",
+                 "row_map_check"):
         exe = os.path.join(tmp, name + "_san")
         rc |= run(["g++", "-O1", "-g", "-std=c++17", "-fopenmp", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
-                   "-I", os.path.join(ROOT, "paper_2604_17397_amd", "csrc"),
+                   "-I", os.path.join(ROOT, "paper_2604_17397_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
                    os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe], base)
         rc |= run([exe], base)
     print("sanitizer pass:", "clean" if rc == 0 else "FAILED")
