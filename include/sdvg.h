@@ -88,7 +88,7 @@ typedef struct {
  *   scale must be finite and >= 0 (0 = 1/sqrt(head_dim)), else SDVG_ERR_RANGE. Inputs are
  *   assumed finite.
  * Asynchronous: enqueued on `stream`; returns SDVG_OK or a negative status. The call only
- * launches a kernel, so it may be recorded into a HIP graph -- but the first SDVG_BF16 call on
+ * launches kernels (one, or two over different heads or rows), so it may be recorded into a HIP graph -- but the first SDVG_BF16 call on
  * a device also raises that kernel's dynamic-LDS limit (once per device, thread-safe), which
  * is not a capturable operation: make one eager call on the device before capturing.
  */
@@ -99,7 +99,7 @@ int sdvg_block_attn(const sdvg_attn_desc *desc, const void *q, const void *k_cac
 /*
  * Attention with the commit fused in (paper Sec. 3 "Inference flow": the block the target keeps
  * -- an accepted draft, or the target's own regeneration -- updates its KV cache): sdvg_block_attn
- * for one layer (bf16 only), and in the same launch the block's K and V rows are copied into
+ * for one layer (bf16 only), and in the same launch (or two) the block's K and V rows are copied into
  * tokens [cache_len, cache_len + n_blk) of k_cache / v_cache (this layer's base pointers, which
  * must have room for them), addressed with the descriptor's kv strides. Meant for the LAST
  * denoising step of a block: the copy runs on compute units the attention leaves idle, so the
@@ -116,11 +116,11 @@ int sdvg_block_attn_commit(const sdvg_attn_desc *desc, const void *q, void *k_ca
 int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
 
 /*
- * The same attention for up to 8 independent (q, cache, block, out) sets in ONE launch -- e.g. the
+ * The same attention for up to 8 independent (q, cache, block, out) sets in ONE call -- e.g. the
  * conditional and the unconditional pass of classifier-free guidance (paper Sec. 4.1 "Models":
  * guidance scale 3.0), which share shapes and cache length but have their own tensors. Result
  * item by item as n_items calls of sdvg_block_attn (same softmax, same error bounds; also the same
- * bits where both take workgroups of the same shape, see below); one launch fills the chip better
+ * bits where both take workgroups of the same shape, see below); one launch for all fills the chip better
  * and halves the launch count.
  *   n_items   1 .. 8. q, k_cache, v_cache, k_blk, v_blk, out: HOST arrays of n_items device
  *             pointers (k_cache / v_cache and their entries may be NULL when cache_len == 0).
@@ -128,7 +128,8 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  *   workspace device, nullable, 16-byte aligned, workspace_bytes long; split_mode one of
  *             SDVG_SPLIT_*. Without a workspace (or with SDVG_SPLIT_NEVER) every query tile is
  *             one workgroup: 256 rows, or, when the launch has few of those, 128, 64 or 32 rows whose
- *             keys are dealt out over 2, 4 or 8 parts of the workgroup's waves. With a workspace of at least
+ *             keys are dealt out over 2, 4 or 8 parts of the workgroup's waves; where these fill some rounds and a small
+ *             part of another, the heads or rows of the whole rounds and the others are launched one after the other. With a workspace of at least
  *             sdvg_block_attn_workspace_bytes(desc, n_items, cache_len, split_mode) bytes the
  *             library may cut the keys of every query tile and deal them out about evenly over whole
  *             rounds of workgroups instead, so that a launch with few query tiles still fills the

@@ -611,11 +611,47 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   return SDVG_OK;
 }
 
+bool rows32_ok(const AttnParams &p) {
+  return ix::rows32_takes(static_cast<uint64_t>(p.blk_ts) * 2) &&
+         (p.cache_len == 0 || ix::rows32_takes(static_cast<uint64_t>(p.kv_ts) * 2));
+}
+
 // The launch plan of a checked call.
 Plan plan_of(const AttnParams &p, int n_cu, int split_mode, double auto_idle = sdvg::kAutoIdle) {
-  const bool rows32_ok = ix::rows32_takes(static_cast<uint64_t>(p.blk_ts) * 2) &&
-                         (p.cache_len == 0 || ix::rows32_takes(static_cast<uint64_t>(p.kv_ts) * 2));
-  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok, auto_idle);
+  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok(p), auto_idle);
+}
+
+void *advance(const void *ptr, int64_t elements) {
+  return ptr ? const_cast<uint16_t *>(static_cast<const uint16_t *>(ptr)) + elements : nullptr;
+}
+
+// The part of a launch that heads [h0, h0 + heads) and query rows [r0, r0 + rows) are.
+AttnParams part_of(const AttnParams &p, int h0, int heads, int r0, int rows) {
+  AttnParams part = p;
+  for (int i = 0; i < p.n_items; ++i) {
+    const sdvg::AttnItem &it = p.items[i];
+    part.items[i] = sdvg::AttnItem{advance(it.q, h0 * p.q_hs + r0 * p.q_ts), advance(it.k_cache, h0 * p.kv_hs),
+                                   advance(it.v_cache, h0 * p.kv_hs),        advance(it.k_blk, h0 * p.blk_hs),
+                                   advance(it.v_blk, h0 * p.blk_hs),         advance(it.out, h0 * p.o_hs + r0 * p.o_ts)};
+  }
+  part.k_commit_dst = advance(p.k_commit_dst, h0 * p.kv_hs);  // (a fused commit: each part copies the rows of its heads)
+  part.v_commit_dst = advance(p.v_commit_dst, h0 * p.kv_hs);
+  part.n_heads = heads;
+  part.n_q = rows;
+  return part;
+}
+
+// Launches a plan, without a split in two parts where that is faster.
+int launch_parts(const AttnParams &p, const Plan &pl, int n_cu, hipStream_t s) {
+  const sdvg::Cut cut = pl.split.cols ? sdvg::Cut{0, 0}
+                                      : sdvg::choose_cut(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, rows32_ok(p));
+  if (!cut.heads && !cut.rows) return launch_bf16(p, pl, n_cu, s);
+  AttnParams first = part_of(p, 0, cut.heads ? cut.heads : p.n_heads, 0, cut.rows ? cut.rows : p.n_q);
+  if (cut.rows) first.k_commit_dst = first.v_commit_dst = nullptr;  // same heads twice: the second part copies
+  const int st = launch_bf16(first, plan_of(first, n_cu, SDVG_SPLIT_NEVER), n_cu, s);
+  if (st != SDVG_OK) return st;
+  const AttnParams rest = part_of(p, cut.heads, p.n_heads - cut.heads, cut.rows, p.n_q - cut.rows);
+  return launch_bf16(rest, plan_of(rest, n_cu, SDVG_SPLIT_NEVER), n_cu, s);
 }
 
 // Host-side validation shared by the entry points; fills the shape part of the parameters.
@@ -714,7 +750,7 @@ int attn_batch(const sdvg_attn_desc *desc, int32_t n_items, const void *const *q
     pl = plan_of(p, dev->n_cu, SDVG_SPLIT_NEVER);
   }
   p.partials = static_cast<float *>(workspace);
-  return launch_bf16(p, pl, dev->n_cu, static_cast<hipStream_t>(stream));
+  return launch_parts(p, pl, dev->n_cu, static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -759,7 +795,7 @@ extern "C" int sdvg_block_attn_commit(const sdvg_attn_desc *desc, const void *q,
   st = device_info(&dev);
   if (st != SDVG_OK) return st;
   const Plan pl = plan_of(p, dev->n_cu, SDVG_SPLIT_NEVER);
-  return launch_bf16(p, pl, dev->n_cu, static_cast<hipStream_t>(stream));
+  return launch_parts(p, pl, dev->n_cu, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int sdvg_block_attn_batch(const sdvg_attn_desc *desc, int32_t n_items, const void *const *q,

@@ -75,6 +75,44 @@ inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int 
   return best;
 }
 
+// An unsplit launch in two, one behind the other on its stream: `heads` heads of every item, or `rows` query rows of every
+// head, and then the rest; 0, 0: one launch. Where the 256-row workgroups fill some rounds and a small part of another, one
+// launch takes that round for little (16 heads x 19 query tiles: 304 workgroups for 256 compute units) or takes
+// smaller workgroups for all rows, which copy and read every key tile for fewer rows. In two, the whole rounds
+// keep 256 rows and only the rest is cut finer. Nothing is merged, no row is computed in two parts. us, one / two launches:
+//   13 + 3 heads x 4680 x 14040 498 / 445, 13 + 1 x 4680 x 23400 801 / 667, 36 + 2 x 1757 x 12299 434 / 374,
+//   15 + 4 x 4112 x 24672 860 / 813, 21 + 9 x 3044 x 12176 466 / 460, 128 + 11 x 410 x 897 58 / 43, 256 + 3 x 183 x 342 36 / 28.
+// With the estimate of choose_groups, of 174 drawn launches of more than a round (3 to 400 heads, 1 to 4680 rows) that it
+// would rather cut, 108 are cut by this rule, 7.8 % faster on average (0.988 to 1.32 times as fast); without the 2 % and 8 us
+// (a launch's start and end, and compute units that wait for the slowest) two more are slower. A launch that
+// fills less than a round of 256-row workgroups never gains, although the estimate of a finer first part would have it so:
+// 18 heads x 1800 x 10800, 144 workgroups, 179 / 190, as fewer busy compute units run at a higher clock.
+struct Cut {
+  int heads, rows;
+};
+inline Cut choose_cut(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, bool rows32_ok) {
+  Cut best{0, 0};
+  const int64_t tiles = (n_q + kPlanRows - 1) / kPlanRows, per_head = n_items * tiles, all = n_heads * per_head;
+  if (n_cu <= 0 || all <= n_cu || all % n_cu == 0) return best;
+  const int64_t full = all / n_cu * n_cu;  // workgroups of the whole rounds
+  auto us = [&](int heads, int rows) { return choose_groups(n_items, rows, heads, n_k, n_cu, rows32_ok).us; };
+  double limit = (us(n_heads, n_q) - 8.0) / 1.02;
+  const int heads = static_cast<int>(full / per_head);
+  if (heads > 0) {  // (< n_heads, because full < all)
+    const double t = us(heads, n_q) + us(n_heads - heads, n_q);
+    if (t < limit) {
+      limit = t;
+      best = Cut{heads, 0};
+    }
+  }
+  const int64_t rows = full / (static_cast<int64_t>(n_items) * n_heads) * kPlanRows;
+  if (rows > 0 && rows < n_q) {
+    const double t = us(n_heads, static_cast<int>(rows)) + us(n_heads, static_cast<int>(n_q - rows));
+    if (t < limit) best = Cut{0, static_cast<int>(rows)};
+  }
+  return best;
+}
+
 // Cuts n_tiles key tiles of each of n_hq query tiles over `wgs` >= n_hq workgroups (block_attn_index.h, "key split").
 // As many whole columns as there is room for; the workgroups left over are helpers. A piece costs some 10 us beside its
 // tiles (arguments, query rows and first tiles 7, partial result 3, by clock stamps in the kernel), and a helper has
