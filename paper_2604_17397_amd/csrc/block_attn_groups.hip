@@ -289,11 +289,22 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
         if (4 * hh + kb * 32 + 8 * (i >> 2) + (i & 3) >= keys) s_acc[kb][i] = -INFINITY;
   };
   // They have P = 0, but 0 times an infinite value would be NaN: their V becomes 0 once this wave's copies have landed.
+  // Without branches, each of which would be a jump to code that a launch with its keys in HBM fetches from there, too.
   auto clear_v = [&](int keys) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < C::kCopies; ++u)
-      if (ix::group_copy_row<G>(wr, lane, u) >= keys)
-        *(lds_f32x4 *)static_cast<uintptr_t>(v_dst_sum - v_dst + u * R * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint32_t at = v_dst_sum - v_dst + lane * 16;
+    for_each<C::kCopies, 1>([&](auto u) __attribute__((always_inline)) {
+      constexpr int offset = decltype(u)::value * R * 1024;
+      const uint64_t past = __ballot(ix::group_copy_row<G>(wr, lane, u) >= keys);
+      const uint32_t to = at;
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      asm volatile(
+          "s_mov_b64 exec, %0\n\t"
+          "ds_write_b128 %1, %2 offset:%3\n\t"
+          "s_mov_b64 exec, -1"  // (all 64 lanes are active here)
+          :
+          : "s"(past), "v"(to), "v"(zero), "n"(offset)
+          : "memory");
+    });
     wait_lds<0>();
   };
   // Softmax with the lazy running maximum of block_attn.hip.
@@ -457,7 +468,9 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
 #pragma unroll
   for (int j = 0; j < 2 * NK; ++j) asm volatile("" : "+v"(pf[j]));
   wait_vmcnt0();
-  if (__builtin_expect(keys_next < C::kKeys, 0)) clear_v(keys_next);
+  // (A group past the last tile takes no product and clears nothing. That, and this and the mask in line: 12 heads x 780 x 780
+  // and 12 x 800 x 800 keys from HBM 14.4 / 14.1 and 14.7 / 14.2 us.)
+  if (__builtin_expect(keys_next < C::kKeys && keys_next > 0, 1)) clear_v(keys_next);
   wg_barrier();
   // A group that is past the last tile has only the last key's row there, with P = 0; it adds nothing,
   // because 0 times an infinite value would be NaN.
