@@ -83,7 +83,8 @@ inline Groups choose_groups(int n_items, int n_q, int n_heads, int64_t n_k, int 
 //   13 + 3 heads x 4680 x 14040 498 / 445, 13 + 1 x 4680 x 23400 801 / 667, 36 + 2 x 1757 x 12299 434 / 374,
 //   15 + 4 x 4112 x 24672 860 / 813, 21 + 9 x 3044 x 12176 466 / 460, 128 + 11 x 410 x 897 58 / 43, 256 + 3 x 183 x 342 36 / 28.
 // With the estimate of choose_groups, of 174 drawn launches of more than a round (3 to 400 heads, 1 to 4680 rows) that it
-// would rather cut, 108 are cut by this rule, 7.8 % faster on average (0.988 to 1.32 times as fast); without the 2 % and 8 us
+// would rather cut, 108 are cut by this rule, 7.8 % faster on average (0.988 to 1.32 times as fast;
+// profiles/attn_two_launches.txt); without the 2 % and 8 us
 // (a launch's start and end, and compute units that wait for the slowest) two more are slower. A launch that
 // fills less than a round of 256-row workgroups never gains, although the estimate of a finer first part would have it so:
 // 18 heads x 1800 x 10800, 144 workgroups, 179 / 190, as fewer busy compute units run at a higher clock.
@@ -194,7 +195,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   // (Of 299 launches without a batch 6 would gain 5 to 25 % from a split that the estimate does not take, 0.3 % on average.)
   // Below 60 % idle the unsplit estimate, made for a full chip, is a little high for one that is half busy: the split
   // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (1 to 3 items, up to 40 heads, 312 to 4680 rows,
-  // 1 to 7 blocks of keys) 31 are split, 1.5 to 15 % faster each; 7 more would have gained 3 to 11 %.
+  // 1 to 7 blocks of keys) 31 are split, 1.5 to 15 % faster each; 7 more would have gained 3 to 11 %. (Against one launch.
+  // Against two, choose_cut, which this does not weigh: of 80 drawn launches of more than a round 21 are split, 2.4 % faster on
+  // average, the worst 4 % slower; 7 more would have gained 3 to 8 %.)
   const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(even);
   const bool few = idle >= kAutoIdleStatic;
   if (split_mode == SDVG_SPLIT_AUTO && unsplit_best.us < split_us + (few ? 0.0 : 11.0)) {
