@@ -593,9 +593,11 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   constexpr size_t lds_bytes = 2 * kRing * kTileBytes;
   p.copy_first_block = 8 * p.work_per_xcd;
   // Fused commit: as many copying workgroups as the last round of attention workgroups leaves
-  // compute units idle (they then run beside it for its whole length); a full round otherwise.
-  const int idle_cus = n_cu > 0 && p.total_work % n_cu ? n_cu - p.total_work % n_cu : 0;
-  p.n_copy_blocks = !p.k_commit_dst ? 0 : (idle_cus >= 4 ? idle_cus : (n_cu > 0 ? n_cu : 256));
+  // compute units idle on every XCD (they then run beside it for its whole length); a full round if none. Workgroups go to
+  // the XCDs in turn, so that one more than has room on its XCD would begin when the round ends, although others have room:
+  // 12 heads x 4680 x 9360, 29 of 32 compute units of seven XCDs at work, took 28 us longer with 28 copying workgroups than with 24.
+  const int xcd_cus = n_cu > 8 ? n_cu / 8 : 32;
+  p.n_copy_blocks = p.k_commit_dst ? 8 * (xcd_cus - p.work_per_xcd % xcd_cus) : 0;
   if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, pl.halves, s);
   if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
   if (!p.split.cols) {

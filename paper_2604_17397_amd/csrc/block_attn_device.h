@@ -120,47 +120,52 @@ __device__ __forceinline__ void store_rows(const AttnParams &p, const AttnItem &
 // n_blk), 16 bytes per lane, while the attention workgroups (which only read tokens below
 // cache_len and the block itself) are still running. They are dispatched last and find their
 // compute units among those the last round of attention workgroups leaves idle.
+// They can be few (16 beside the 240 attention workgroups of 12 heads x 312 rows) and a copy is then a chain of
+// round trips to memory: K and V of four rows are in flight per lane (two rows: 12 x 312 x 312 7.4 us instead of 7.0; eight: 7.6), the
+// last ones too, and a row's token and head follow from the row before instead of a 64-bit division each. Ordinary
+// loads, because the attention reads the same rows from the memory-side cache then (nontemporal: 12 x 1031 x 1031 17.9
+// instead of 16.0). us of a launch with its commit, before / now (with their number, launch_bf16), keys from HBM: 12 x 312 x 312
+// 7.6 / 7.1, 24 x 312 x 936 13.7 / 13.3, 12 x 1031 x 1031 17.8 / 15.1, 5 x 1409 x 2818 27.9 / 23.0, 12 x 4680 x 9360 254 / 224.
 template <int kParamsAt = 0>
 __device__ __forceinline__ void commit_block_rows(const AttnParams &p) {
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+  constexpr int kRows = 4;
   const AttnItem it = kernarg_items<kParamsAt>()[0];
-  const int64_t chunks = static_cast<int64_t>(p.n_blk) * p.n_heads * 16;  // 16-byte chunks per tensor
-  const int64_t first = static_cast<int64_t>(blockIdx.x - p.copy_first_block) * 512 + threadIdx.x;
-  const int64_t stride = static_cast<int64_t>(p.n_copy_blocks) * 512;
-  auto locate = [&](int64_t g, const u32x4 *&src, u32x4 *&dst) __attribute__((always_inline)) {
-    const bool is_v = g >= chunks;
-    const int64_t c = is_v ? g - chunks : g;
-    const int64_t row = c >> 4;
-    const int ch = static_cast<int>(c & 15);
-    const int64_t tok = row / p.n_heads;
-    const int head = static_cast<int>(row - tok * p.n_heads);
-    src = reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(is_v ? it.v_blk : it.k_blk) + tok * p.blk_ts +
-                                          head * p.blk_hs + ch * 8);
-    dst = reinterpret_cast<u32x4 *>(static_cast<uint16_t *>(is_v ? p.v_commit_dst : p.k_commit_dst) + tok * p.kv_ts +
-                                    head * p.kv_hs + ch * 8);
-  };
-  // four chunks in flight per lane: the few workgroups that do this have to stream by themselves
-  int64_t g = first;
-  for (; g + 3 * stride < 2 * chunks; g += 4 * stride) {
-    const u32x4 *s0, *s1, *s2, *s3;
-    u32x4 *d0, *d1, *d2, *d3;
-    locate(g, s0, d0);
-    locate(g + stride, s1, d1);
-    locate(g + 2 * stride, s2, d2);
-    locate(g + 3 * stride, s3, d3);
-    const u32x4 a = __builtin_nontemporal_load(s0), b = __builtin_nontemporal_load(s1),
-                c = __builtin_nontemporal_load(s2), d = __builtin_nontemporal_load(s3);
-    __builtin_nontemporal_store(a, d0);
-    __builtin_nontemporal_store(b, d1);
-    __builtin_nontemporal_store(c, d2);
-    __builtin_nontemporal_store(d, d3);
+  const uint32_t n_heads = p.n_heads, n_blk = p.n_blk;
+  const uint32_t row = (blockIdx.x - p.copy_first_block) * 32 + threadIdx.x / 16, step = p.n_copy_blocks * 32;
+  const uint32_t step_tok = p.div_heads.div(step), step_head = step - step_tok * n_heads;
+  uint32_t tok = p.div_heads.div(row), head = row - tok * n_heads;
+  const int ch = threadIdx.x % 16;  // 16-byte chunk of the row
+  while (tok < n_blk) {
+    u32x4 k[kRows], v[kRows];
+    int64_t dst[kRows];
+    bool in[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      in[u] = tok < n_blk;
+      const int64_t src = tok * p.blk_ts + head * p.blk_hs + ch * 8;
+      dst[u] = tok * p.kv_ts + head * p.kv_hs + ch * 8;
+      if (in[u]) {
+        k[u] = *reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(it.k_blk) + src);
+        v[u] = *reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(it.v_blk) + src);
+      }
+      tok += step_tok;
+      head += step_head;
+      if (head >= n_heads) {
+        head -= n_heads;
+        ++tok;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (in[u]) {
+        __builtin_nontemporal_store(k[u], reinterpret_cast<u32x4 *>(static_cast<uint16_t *>(p.k_commit_dst) + dst[u]));
+        __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4 *>(static_cast<uint16_t *>(p.v_commit_dst) + dst[u]));
+      }
   }
-  for (; g < 2 * chunks; g += stride) {
-    const u32x4 *s0;
-    u32x4 *d0;
-    locate(g, s0, d0);
-    __builtin_nontemporal_store(__builtin_nontemporal_load(s0), d0);
-  }
+  // Where this path joins the attention's, the compiler would wait there for loads of this one (24 heads x 312 x 936 keys 13.9
+  // us instead of 13.2, without any commit).
+  __builtin_amdgcn_s_waitcnt(0);
 }
 
 // Vector phase: P^T = exp2(scale*log2e * (S^T - m)) rounded to bf16 in B-operand order, plus
