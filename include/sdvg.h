@@ -78,7 +78,8 @@ typedef struct {
  *   q         device [n_q][n_heads][128]; k_blk, v_blk device [n_blk][n_heads][128].
  *   k_cache, v_cache  device, ONE layer's base pointers, at least cache_len tokens; may be
  *             NULL when cache_len == 0. Tokens at or past cache_len are never read.
- *   out       device [n_q][n_heads][128], same dtype as the inputs; every element is written.
+ *   out       device [n_q][n_heads][128], same dtype as the inputs; every element is written. It may be q
+ *             itself (same address and strides: in place); any other overlap with an input is the caller's error.
  *   Arithmetic (bf16): products on the matrix cores with fp32 accumulation, fp32 softmax
  *   statistics, probabilities rounded to bf16 before the PV product (the row sum is taken over
  *   the rounded values), bf16 output (RNE). SDVG_F32 is a slow all-fp32 check path: a separate,
@@ -124,7 +125,8 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  * and halves the launch count.
  *   n_items   1 .. 8. q, k_cache, v_cache, k_blk, v_blk, out: HOST arrays of n_items device
  *             pointers (k_cache / v_cache and their entries may be NULL when cache_len == 0).
- *             All items share desc (shapes, strides, scale, dtype) and cache_len.
+ *             All items share desc (shapes, strides, scale, dtype) and cache_len. out[i] may be q[i], but
+ *             not overlap another item's tensors.
  *   workspace device, nullable, 16-byte aligned, workspace_bytes long; split_mode one of
  *             SDVG_SPLIT_*. Without a workspace (or with SDVG_SPLIT_NEVER) every query tile is
  *             one workgroup: 256 rows, or, when the launch has few of those, 128, 64 or 32 rows whose

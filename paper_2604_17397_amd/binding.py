@@ -227,7 +227,7 @@ def _attn_desc(q, k_cache, v_cache, k_blk, v_blk, cache_len, out, scale):
 def block_attn(q, k_cache, v_cache, k_blk, v_blk, cache_len, out=None, scale=None, stream=None):
     """sdvg_block_attn: q, k_blk, v_blk [tokens, heads, 128]; k_cache, v_cache one layer's
     [>= cache_len, heads, 128] (may be None when cache_len == 0). `scale=None` passes 0, which the
-    library reads as 1/sqrt(head_dim). Returns out."""
+    library reads as 1/sqrt(head_dim). `out` defaults to a new tensor; pass out=q for in place. Returns out."""
     r = (_NATIVE or _native()).block_attn(q, k_cache, v_cache, k_blk, v_blk, cache_len, out, scale,
                                          None if stream is None else stream.cuda_stream, False)
     if r is not None:

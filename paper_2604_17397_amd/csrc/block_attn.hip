@@ -618,9 +618,16 @@ bool rows32_ok(const AttnParams &p) {
          (p.cache_len == 0 || ix::rows32_takes(static_cast<uint64_t>(p.kv_ts) * 2));
 }
 
+bool in_place(const AttnParams &p) {
+  const int64_t q_bytes = sdvg::rows_bytes(p.n_q, p.n_heads, p.q_ts, p.q_hs), o_bytes = sdvg::rows_bytes(p.n_q, p.n_heads, p.o_ts, p.o_hs);
+  for (int i = 0; i < p.n_items; ++i)
+    if (sdvg::ranges_overlap(p.items[i].q, q_bytes, p.items[i].out, o_bytes)) return true;
+  return false;
+}
+
 // The launch plan of a checked call.
 Plan plan_of(const AttnParams &p, int n_cu, int split_mode, double auto_idle = sdvg::kAutoIdle) {
-  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok(p), auto_idle);
+  return make_plan(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, split_mode, rows32_ok(p), auto_idle, in_place(p));
 }
 
 void *advance(const void *ptr, int64_t elements) {
@@ -786,13 +793,11 @@ extern "C" int sdvg_block_attn_commit(const sdvg_attn_desc *desc, const void *q,
   p.k_commit_dst = static_cast<uint16_t *>(k_cache) + cache_len * desc->kv_token_stride;
   p.v_commit_dst = static_cast<uint16_t *>(v_cache) + cache_len * desc->kv_token_stride;
   // the block must not overlap the rows it is copied into
-  const int64_t dst_bytes = ((desc->n_blk - 1) * desc->kv_token_stride + (desc->n_heads - 1) * desc->kv_head_stride + 128) * 2;
-  const int64_t src_bytes = ((desc->n_blk - 1) * desc->blk_token_stride + (desc->n_heads - 1) * desc->blk_head_stride + 128) * 2;
+  const int64_t dst_bytes = sdvg::rows_bytes(p.n_blk, p.n_heads, p.kv_ts, p.kv_hs);
+  const int64_t src_bytes = sdvg::rows_bytes(p.n_blk, p.n_heads, p.blk_ts, p.blk_hs);
   for (const void *src : {k_blk, v_blk})
-    for (const void *dst : {static_cast<const void *>(p.k_commit_dst), static_cast<const void *>(p.v_commit_dst)}) {
-      const uintptr_t a = reinterpret_cast<uintptr_t>(src), b = reinterpret_cast<uintptr_t>(dst);
-      if (a < b + static_cast<uintptr_t>(dst_bytes) && b < a + static_cast<uintptr_t>(src_bytes)) return SDVG_ERR_RANGE;
-    }
+    for (const void *dst : {p.k_commit_dst, p.v_commit_dst})
+      if (sdvg::ranges_overlap(src, src_bytes, dst, dst_bytes)) return SDVG_ERR_RANGE;
   const DeviceInfo *dev = nullptr;
   st = device_info(&dev);
   if (st != SDVG_OK) return st;

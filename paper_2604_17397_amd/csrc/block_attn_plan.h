@@ -143,9 +143,18 @@ inline attn_index::KeySplit cut_keys(int n_hq, int n_tiles, int wgs) {
 // more shapes split there than have to.
 constexpr double kAutoIdle = 0.25, kAutoIdleStatic = 0.6;
 
-// rows32_ok: the strides are ones that the 32-row kernel takes.
+// Bytes from the first to the last of n_tokens x n_heads rows of 128 bf16 values, and whether two ranges share a byte.
+inline int64_t rows_bytes(int64_t n_tokens, int64_t n_heads, int64_t token_stride, int64_t head_stride) {
+  return ((n_tokens - 1) * token_stride + (n_heads - 1) * head_stride + 128) * 2;
+}
+inline bool ranges_overlap(const void *a, int64_t a_bytes, const void *b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
+}
+
+// rows32_ok: the strides are ones that the 32-row kernel takes. in_place: an item's result overlaps its query rows.
 inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, bool rows32_ok = true,
-                      double auto_idle = kAutoIdle) {
+                      double auto_idle = kAutoIdle, bool in_place = false) {
   auto unsplit = [&](int groups, int rows) {
     const int keys = groups == 4 ? 32 : attn_index::kBN;
     Plan pl;
@@ -158,8 +167,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     // 32-row workgroups that leave half of the compute units idle are doubled: each of a pair copies all of K but half of V,
     // and copies are what bounds them (block_attn_rows32.hip). Whole / halves, us: 12 heads x 312 x 936 keys 9.1 / 8.7, with
     // keys from the memory-side cache 10.5 / 9.0; 4 x 1000 x 4000 22.4 / 21.4, 24.6 / 21.7; 3 x 1300 x 9100 50 / 43, 58 / 47;
-    // the same where there is nothing to halve (1 x 33 x 99, 6.4). In a second round every pair would copy K again.
-    pl.halves = rows == 32 && 2 * pl.total_wg <= n_cu;
+    // the same where there is nothing to halve (1 x 33 x 99, 6.4). In a second round every pair would copy K again. Both of a
+    // pair read whole query rows and store half of them, at times of their own: not where the result lies over the query.
+    pl.halves = rows == 32 && 2 * pl.total_wg <= n_cu && !in_place;
     pl.workspace_bytes = 0;
     return pl;
   };

@@ -89,3 +89,9 @@ def attn_plan_rows(n_heads, n_q, n_k, n_items=1, split=0, n_cu=None, rows32_ok=1
 def attn_plan_static_workspace(n_heads, n_q, n_k, n_items=1, split=1, n_cu=MI355X_CUS):
     """Bytes of the library's own array that sdvg_block_attn_batch_static needs for such a launch."""
     return _plan_library().attn_plan_static_workspace(n_items, n_q, n_heads, ctypes.c_int64(n_k), n_cu, split)
+
+
+def attn_plan_halves(n_k, q, out, n_cu=MI355X_CUS):
+    """Whether two workgroups share 32 query rows in a call with these q and out ([tokens, heads, 128], any device)."""
+    return bool(_plan_library().attn_plan_halves(q.shape[0], q.shape[1], ctypes.c_int64(n_k), n_cu, *[
+        f for t in (q, out) for f in (ctypes.c_void_p(t.data_ptr()), ctypes.c_int64(t.stride(0)), ctypes.c_int64(t.stride(1)))]))

@@ -20,3 +20,10 @@ extern "C" int64_t attn_plan_static_workspace(int n_items, int n_q, int n_heads,
 extern "C" int attn_plan_rows(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, int rows32_ok) {
   return sdvg::make_plan(n_items, n_q, n_heads, n_k, n_cu, split_mode, rows32_ok != 0).rows;
 }
+
+// Whether two workgroups share 32 query rows, for a call whose q and out have these addresses and strides.
+extern "C" int attn_plan_halves(int n_q, int n_heads, int64_t n_k, int n_cu, const void *q, int64_t q_ts, int64_t q_hs, const void *out,
+                                int64_t o_ts, int64_t o_hs) {
+  const bool in_place = sdvg::ranges_overlap(q, sdvg::rows_bytes(n_q, n_heads, q_ts, q_hs), out, sdvg::rows_bytes(n_q, n_heads, o_ts, o_hs));
+  return sdvg::make_plan(1, n_q, n_heads, n_k, n_cu, 0, true, sdvg::kAutoIdle, in_place).halves;
+}
