@@ -583,7 +583,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   p.n_hq = pl.n_hq;
   p.n_tiles = pl.n_tiles;
   p.split = pl.split;
-  p.total_work = pl.total_wg;
+  p.total_work = sdvg::attention_workgroups(pl);
   p.work_per_xcd = (p.total_work + 7) / 8;
   const int n_wt = (p.n_q + 31) / 32;
   p.wt_base = n_wt / p.n_qtiles;
@@ -592,12 +592,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   p.div_heads = sdvg::FastDiv::of(p.n_heads);
   constexpr size_t lds_bytes = 2 * kRing * kTileBytes;
   p.copy_first_block = 8 * p.work_per_xcd;
-  // Fused commit: as many copying workgroups as the last round of attention workgroups leaves
-  // compute units idle on every XCD (they then run beside it for its whole length); a full round if none. Workgroups go to
-  // the XCDs in turn, so that one more than has room on its XCD would begin when the round ends, although others have room:
-  // 12 heads x 4680 x 9360, 29 of 32 compute units of seven XCDs at work, took 28 us longer with 28 copying workgroups than with 24.
-  const int xcd_cus = n_cu > 8 ? n_cu / 8 : 32;
-  p.n_copy_blocks = p.k_commit_dst ? 8 * (xcd_cus - p.work_per_xcd % xcd_cus) : 0;
+  p.n_copy_blocks = p.k_commit_dst ? sdvg::copy_workgroups(pl, static_cast<int64_t>(p.n_blk) * p.n_heads, n_cu) : 0;
   if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, pl.halves, s);
   if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
   if (!p.split.cols) {

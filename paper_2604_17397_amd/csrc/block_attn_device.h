@@ -120,12 +120,13 @@ __device__ __forceinline__ void store_rows(const AttnParams &p, const AttnItem &
 // n_blk), 16 bytes per lane, while the attention workgroups (which only read tokens below
 // cache_len and the block itself) are still running. They are dispatched last and find their
 // compute units among those the last round of attention workgroups leaves idle.
-// They can be few (16 beside the 240 attention workgroups of 12 heads x 312 rows) and a copy is then a chain of
-// round trips to memory: K and V of four rows are in flight per lane (two rows: 12 x 312 x 312 7.4 us instead of 7.0; eight: 7.6), the
-// last ones too, and a row's token and head follow from the row before instead of a 64-bit division each. Ordinary
-// loads, because the attention reads the same rows from the memory-side cache then (nontemporal: 12 x 1031 x 1031 17.9
-// instead of 16.0). us of a launch with its commit, before / now (with their number, launch_bf16), keys from HBM: 12 x 312 x 312
-// 7.6 / 7.1, 24 x 312 x 936 13.7 / 13.3, 12 x 1031 x 1031 17.8 / 15.1, 5 x 1409 x 2818 27.9 / 23.0, 12 x 4680 x 9360 254 / 224.
+// They can be few (copy_workgroups, block_attn_plan.h: 16 beside the 240 of 12 heads x 312 rows) and a copy is then a chain of
+// round trips to memory: K and V of four rows are in flight per lane (two / four / eight rows: 12 x 312 x 312 7.2 / 7.1 / 7.1 us,
+// 12 x 1031 x 1031 16.0 / 15.7 / 15.7), the last ones too, and a row's token and head follow from the row before
+// instead of a 64-bit division each. Ordinary loads, because the attention reads the same rows from the memory-side
+// cache then (nontemporal: 12 x 1031 x 1031 17.9 instead of 16.0).
+// us of a launch without / with its commit, keys from HBM: 12 x 312 x 312 6.4 / 6.5, 24 x 312 x 936 13.2 / 13.3, 12 x 1031 x
+// 1031 17.2 / 15.4, 5 x 1409 x 2818 23.8 / 23.2, 12 x 4680 x 9360 219 / 220.
 template <int kParamsAt = 0>
 __device__ __forceinline__ void commit_block_rows(const AttnParams &p) {
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;

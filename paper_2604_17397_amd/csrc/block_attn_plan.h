@@ -219,4 +219,21 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   return pl;
 }
 
+// Attention workgroups that an unsplit plan launches.
+inline int attention_workgroups(const Plan &pl) { return pl.halves ? 2 * pl.total_wg : pl.total_wg; }
+
+// Copying workgroups of a fused commit of `rows` rows (tokens x heads): as many as the last round of attention workgroups
+// leaves compute units idle on every XCD (they then run beside it for its whole length); a full round if none; none
+// without a row (32 rows per workgroup and pass). Workgroups go to the XCDs in turn, so that one more than has room on its
+// XCD would begin when the round ends, although others have room: 12 heads x 4680 x 9360, 29 of 32 compute units of seven
+// XCDs at work, took 28 us longer with 28 copying workgroups than with 24. Workgroups of 32 rows doubled, 16 / 136 beside
+// the 240 of 12 x 312 x 312 7.0 / 7.8 us, keys from HBM 6.6 / 7.2; x 936 10.0 / 10.5, 10.4 / 10.8; 16 / 136 beside the
+// 240 of 15 x 250 x 500 8.3 / 9.0, 7.9 / 8.8. Behind the full round of 8 x 500 x 1500 (256), 16 / 32 / 64 / 125 / 256
+// 15.9 / 14.0 / 13.4 / 12.9 / 13.1 us.
+inline int copy_workgroups(const Plan &pl, int64_t rows, int n_cu) {
+  const int xcd_cus = n_cu > 8 ? n_cu / 8 : 32;
+  const int room = 8 * (xcd_cus - (attention_workgroups(pl) + 7) / 8 % xcd_cus);
+  return static_cast<int>(room * int64_t{32} < rows ? room : (rows + 31) / 32);
+}
+
 }  // namespace sdvg

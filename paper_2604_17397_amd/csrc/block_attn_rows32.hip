@@ -441,11 +441,6 @@ hipError_t prepare_block_attn_rows32() {
 
 int launch_block_attn_rows32(AttnParams p, bool halves, hipStream_t s) {
   p.n_tiles = ix::rows32_tiles(static_cast<int>(p.cache_len)) + ix::rows32_tiles(p.n_blk);
-  if (halves) {
-    p.total_work *= 2;
-    p.work_per_xcd = (p.total_work + 7) / 8;
-    p.copy_first_block = 8 * p.work_per_xcd;
-  }
   Early e{};
   const bool early = early_of(p, e);
   const auto kernel = halves ? (early ? block_attn_rows32_kernel<true, true> : block_attn_rows32_kernel<false, true>)

@@ -95,3 +95,10 @@ def attn_plan_halves(n_k, q, out, n_cu=MI355X_CUS):
     """Whether two workgroups share 32 query rows in a call with these q and out ([tokens, heads, 128], any device)."""
     return bool(_plan_library().attn_plan_halves(q.shape[0], q.shape[1], ctypes.c_int64(n_k), n_cu, *[
         f for t in (q, out) for f in (ctypes.c_void_p(t.data_ptr()), ctypes.c_int64(t.stride(0)), ctypes.c_int64(t.stride(1)))]))
+
+
+def attn_plan_commit(n_heads, n_q, n_blk, n_k, n_cu=MI355X_CUS):
+    """Attention and copying workgroups of one launch with the commit fused in."""
+    out = (ctypes.c_int * 2)()
+    _plan_library().attn_plan_commit(n_q, n_blk, n_heads, ctypes.c_int64(n_k), n_cu, out)
+    return tuple(out)

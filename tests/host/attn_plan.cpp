@@ -27,3 +27,10 @@ extern "C" int attn_plan_halves(int n_q, int n_heads, int64_t n_k, int n_cu, con
   const bool in_place = sdvg::ranges_overlap(q, sdvg::rows_bytes(n_q, n_heads, q_ts, q_hs), out, sdvg::rows_bytes(n_q, n_heads, o_ts, o_hs));
   return sdvg::make_plan(1, n_q, n_heads, n_k, n_cu, 0, true, sdvg::kAutoIdle, in_place).halves;
 }
+
+// Attention and copying workgroups of a fused commit.
+extern "C" void attn_plan_commit(int n_q, int n_blk, int n_heads, int64_t n_k, int n_cu, int out[2]) {
+  const sdvg::Plan p = sdvg::make_plan(1, n_q, n_heads, n_k, n_cu, 0);
+  out[0] = sdvg::attention_workgroups(p);
+  out[1] = sdvg::copy_workgroups(p, static_cast<int64_t>(n_blk) * n_heads, n_cu);
+}

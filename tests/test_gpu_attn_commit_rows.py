@@ -3,6 +3,27 @@
 import pytest
 import torch
 
+from gpu_util import MI355X_CUS, attn_plan, attn_plan_commit
+
+
+def test_copying_workgroups_beside_the_attention():
+    """Of the workgroups that are launched, doubled ones counted twice: no more copying ones than the last round leaves room
+    for on an XCD, where it leaves any, and none without a row."""
+    assert attn_plan_commit(12, 312, 312, 936) == (240, 16)
+    assert attn_plan_commit(8, 312, 312, 936) == (160, 78) and attn_plan_commit(8, 500, 500, 500) == (256, 125)
+    n_doubled = 0
+    for H in range(3, 17):
+        for n_q in (33, 100, 250, 312, 400, 513, 800):
+            for n_k in (n_q, 2 * n_q, 5 * n_q):
+                work, copies = attn_plan_commit(H, n_q, n_q, n_k)
+                plan = attn_plan(H, n_q, n_k, n_cu=MI355X_CUS)
+                assert work == plan.workgroups * (2 if plan.rows == 32 and 2 * plan.workgroups <= MI355X_CUS else 1)
+                n_doubled += work != plan.workgroups
+                per_xcd = -(-work // 8)
+                assert 1 <= copies <= -(-H * n_q // 32)
+                assert per_xcd % 32 + -(-copies // 8) <= 32
+    assert n_doubled > 100
+
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("head_major", [False, True])
