@@ -103,8 +103,8 @@ int sdvg_block_attn(const sdvg_attn_desc *desc, const void *q, const void *k_cac
  * for one layer (bf16 only), and in the same launch (or two) the block's K and V rows are copied into
  * tokens [cache_len, cache_len + n_blk) of k_cache / v_cache (this layer's base pointers, which
  * must have room for them), addressed with the descriptor's kv strides. Meant for the LAST
- * denoising step of a block: the copy runs on compute units the attention leaves idle, so the
- * block's commit costs no extra pass over memory. The attention result is bit-identical to
+ * denoising step of a block: the copy runs on compute units the attention leaves idle (behind the
+ * attention where they would not be done in time), so the block's commit costs no extra launch and little or no time. The attention result is bit-identical to
  * sdvg_block_attn's; the copied rows are bit-exact. k_blk / v_blk must not overlap the
  * destination rows (SDVG_ERR_RANGE). The cache length is the caller's to advance: after the
  * call has been made for every layer, sdvg_kv_commit_mark(cache, slot) moves the descriptor's

@@ -28,6 +28,7 @@ struct Plan {
   int groups;               // key groups per workgroup (1: block_attn.hip, 2 or 4: block_attn_groups.hip)
   int rows;                 // query rows per workgroup (32: block_attn_rows32.hip)
   bool halves;              // two workgroups per 32 rows, each with half of the output dims
+  double us;                // estimated time without a split
 };
 
 // Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
@@ -155,6 +156,7 @@ inline bool ranges_overlap(const void *a, int64_t a_bytes, const void *b, int64_
 // rows32_ok: the strides are ones that the 32-row kernel takes. in_place: an item's result overlaps its query rows.
 inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, int split_mode, bool rows32_ok = true,
                       double auto_idle = kAutoIdle, bool in_place = false) {
+  const Groups unsplit_best = choose_groups(n_items, n_q, n_heads, n_k, n_cu, rows32_ok);
   auto unsplit = [&](int groups, int rows) {
     const int keys = groups == 4 ? 32 : attn_index::kBN;
     Plan pl;
@@ -171,9 +173,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     // pair read whole query rows and store half of them, at times of their own: not where the result lies over the query.
     pl.halves = rows == 32 && 2 * pl.total_wg <= n_cu && !in_place;
     pl.workspace_bytes = 0;
+    pl.us = unsplit_best.us;
     return pl;
   };
-  const Groups unsplit_best = choose_groups(n_items, n_q, n_heads, n_k, n_cu, rows32_ok);
   auto plain = [&]() { return unsplit(unsplit_best.groups, unsplit_best.rows); };
   if (split_mode == SDVG_SPLIT_NEVER || n_cu <= 0) return plain();
   Plan pl = unsplit(1, kPlanRows);
@@ -230,10 +232,21 @@ inline int attention_workgroups(const Plan &pl) { return pl.halves ? 2 * pl.tota
 // the 240 of 12 x 312 x 312 7.0 / 7.8 us, keys from HBM 6.6 / 7.2; x 936 10.0 / 10.5, 10.4 / 10.8; 16 / 136 beside the
 // 240 of 15 x 250 x 500 8.3 / 9.0, 7.9 / 8.8. Behind the full round of 8 x 500 x 1500 (256), 16 / 32 / 64 / 125 / 256
 // 15.9 / 14.0 / 13.4 / 12.9 / 13.1 us.
+// Copies that would outlast the round are not held up in these few workgroups: a full round of them takes what is left
+// when the attention ends. A pass of 32 x 4 rows beside the attention takes 2.5 to 3.6 us (kCopyPass), a full round of
+// 256 copies at the rate of HBM, 4.2 us for a pass. Attention alone / copies in the room / by a full round, us:
+// 40 x 4680 x 4680 384 / 720 / 411, x 18720 1416 / 1599 / 1436, x 32760 2438 / 2440 / 2457; 13 x 4680 x 4680 130 / 151 / 137,
+// x 9360 243 / 244 / 249; 30 x 2000 x 2000 65 / 76 / 72; 24 x 312 x 312 8.0 / 10.6 / 9.2, x 936 12.0 / 12.2 / 12.9.
+constexpr int kCopyRows = 32 * 4;  // rows of a copying workgroup and pass
+constexpr double kCopyPass = 2.7, kFullPass = 4.2;
 inline int copy_workgroups(const Plan &pl, int64_t rows, int n_cu) {
   const int xcd_cus = n_cu > 8 ? n_cu / 8 : 32;
-  const int room = 8 * (xcd_cus - (attention_workgroups(pl) + 7) / 8 % xcd_cus);
-  return static_cast<int>(room * int64_t{32} < rows ? room : (rows + 31) / 32);
+  const int work = attention_workgroups(pl), rounds = (work + 8 * xcd_cus - 1) / (8 * xcd_cus);
+  int n = 8 * (xcd_cus - (work + 7) / 8 % xcd_cus);
+  const int64_t passes = (rows + int64_t{n} * kCopyRows - 1) / (int64_t{n} * kCopyRows);
+  const double late_us = static_cast<double>(passes) * kCopyPass - pl.us / rounds;
+  if (late_us > 1.0 + kFullPass * static_cast<double>(rows) / (8.0 * xcd_cus * kCopyRows)) n = 8 * xcd_cus;
+  return static_cast<int>(n * int64_t{32} < rows ? n : (rows + 31) / 32);
 }
 
 }  // namespace sdvg

@@ -8,7 +8,7 @@ from gpu_util import MI355X_CUS, attn_plan, attn_plan_commit
 
 def test_copying_workgroups_beside_the_attention():
     """Of the workgroups that are launched, doubled ones counted twice: no more copying ones than the last round leaves room
-    for on an XCD, where it leaves any, and none without a row."""
+    for on an XCD, or a full round, and none without a row."""
     assert attn_plan_commit(12, 312, 312, 936) == (240, 16)
     assert attn_plan_commit(8, 312, 312, 936) == (160, 78) and attn_plan_commit(8, 500, 500, 500) == (256, 125)
     n_doubled = 0
@@ -21,8 +21,15 @@ def test_copying_workgroups_beside_the_attention():
                 n_doubled += work != plan.workgroups
                 per_xcd = -(-work // 8)
                 assert 1 <= copies <= -(-H * n_q // 32)
-                assert per_xcd % 32 + -(-copies // 8) <= 32
+                assert per_xcd % 32 + -(-copies // 8) <= 32 or copies == min(256, -(-H * n_q // 32))
     assert n_doubled > 100
+
+
+def test_copies_that_would_outlast_the_round_take_a_full_one():
+    n = lambda H, T, cached: attn_plan_commit(H, T, T, (cached + 1) * T)[1]
+    assert [n(40, 4680, c) for c in (0, 1, 3, 6)] == [256, 256, 256, 8]
+    assert [n(13, 4680, c) for c in (0, 1)] == [256, 8] and n(30, 2000, 0) == 256 and n(12, 4680, 0) == 24
+    assert [n(24, 312, c) for c in (0, 2)] == [234, 16] and n(12, 312, 0) == 16
 
 
 @pytest.mark.gpu
