@@ -328,6 +328,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     l_run += dl;
   };
 
+  int keys_next = ix::group_counted_keys(bounds, tile_of(0), keys[kV]);  // of the tile whose scores come next
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ix::group_left_at_scores<G>()) : "memory");  // K(0) and the query rows
   wg_barrier();
 #pragma unroll
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       mfma_op(f[gi & 1][2], gi, 2);
       mfma_op(f[gi & 1][3], gi, 3);
     }
-    if (keys[kV] < C::kKeys) mask_tail(keys[kV]);
+    if (keys_next < C::kKeys) mask_tail(keys_next);
     auto first_max = [&](int g) __attribute__((always_inline)) -> float * {
       return reinterpret_cast<float *>(reinterpret_cast<char *>(smem) + g * C::kGroup + C::kVSlots + C::kTile) +
              wr * 64 + lane;
@@ -389,7 +390,6 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
     k_slot = k_slot == 2 ? 0 : k_slot + 1;
     k_move = k_slot == 2 ? -2 * C::kTile : C::kTile;
   };
-  int keys_next = keys[kV];  // keys of the next iteration's tile; 0 past the last tile
   // Behind the third MFMA of group gi.
   auto chores = [&](int gi, int i) __attribute__((always_inline)) {
     if (gi == 2 * NK - 1) {  // all K operands are on their way
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(512) void block_attn_groups_kernel(const AttnParams
       if (t_k >= bound[kK]) set_kind(kK, t_k);
       if (t_v >= bound[kV]) {
         set_kind(kV, t_v);
-        keys_next = t_v < bounds.end ? keys[kV] : 0;
+        keys_next = ix::group_counted_keys(bounds, t_v, keys[kV]);
       }
     }
     base[kK] += step[kK];

@@ -117,6 +117,8 @@ SDVG_HD int group_tile_keys(const GroupBounds &b, int c_len, int n_blk, int t) {
   if (t < b.block) return t < b.cache_whole ? n : c_len % n;
   return t < b.block_whole || n_blk % n == 0 ? n : n_blk % n;
 }
+// Keys of tile t that count: all `keys` of it, none past the end.
+SDVG_HD int group_counted_keys(const GroupBounds &b, int t, int keys) { return t < b.end ? keys : 0; }
 // Token 0 of the block's rows, were the tiles' rows numbered through: tile t's first row is at this + t * keys * pitch.
 template <int G>
 SDVG_HD uint64_t group_block_base(const GroupBounds &b, uint64_t block_row0, uint32_t pitch) {

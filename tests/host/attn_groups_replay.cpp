@@ -138,16 +138,16 @@ struct Replay {
       for (int i = 0; i < 3; ++i)
         if (!copy(k, tile_of(i), g, 0, i)) return false;
       if (!copy(v, tile_of(0), g, 1, 0) || !check(g, 0, tile_of(0), 0)) return false;
-      int keys_next = v.keys;
+      int keys_next = ix::group_counted_keys(bounds, tile_of(0), v.keys);
       for (int i = 0; i < n_it; ++i) {
         // V(i) of a short tile is cleared past its keys: at the next change of kind, or behind the loop
         const int keys_now = keys_next;
-        if (tile_of(i) < bounds.end && keys_now != tile_at(tile_of(i)).keys) return error = "wrong mask", false;
+        if (keys_now != (tile_of(i) < bounds.end ? tile_at(tile_of(i)).keys : 0)) return error = "wrong mask", false;
         if (i + 1 < n_it && keys_now < C::kKeys && tile_of(i + 3) < k.bound && tile_of(i + 1) < v.bound)
           return error = "a short tile that is not cleared", false;
         if (i + 1 < n_it && tile_of(i + 1) >= v.bound) {
           set_kind(v, tile_of(i + 1), 1);
-          keys_next = tile_of(i + 1) < bounds.end ? v.keys : 0;
+          keys_next = ix::group_counted_keys(bounds, tile_of(i + 1), v.keys);
         }
         // matrix phase i reads K(i+1) and V(i); its copies of V(i+1) and K(i+3) land at any time in it
         for (int late = 0; late < 2; ++late) {
@@ -156,7 +156,7 @@ struct Replay {
           if (i + 1 < n_it && !check(g, 0, tile_of(i + 1), (i + 1) % 3)) return false;
           if (!check(g, 1, tile_of(i), i % 2)) return false;
         }
-        for (int r = 0; tile_of(i) < bounds.end && r < keys_now; ++r) seen[tile_at(tile_of(i)).key0 + r]++;
+        for (int r = 0; r < keys_now; ++r) seen[tile_at(tile_of(i)).key0 + r]++;
       }
     }
     for (char c : seen)
