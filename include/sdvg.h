@@ -138,8 +138,7 @@ int sdvg_kv_commit_mark(sdvg_kv_cache *cache, int32_t slot);
  *             chip, and merge the partial results in a second small kernel on the same stream. SDVG_SPLIT_AUTO does so when at least a quarter of the
  *             workgroup slots of the launch's rounds would idle (few heads or short blocks) and the keys are many
  *             enough for it to be the faster way (otherwise the workspace stays unused); SDVG_SPLIT_ALWAYS
- *             whenever the query tiles do not fill whole rounds and the workgroups left over can take on
- *             a part of the keys in the same time (more than 1 slot in 23 idle at 14080 keys). For the paper's own shapes the
+ *             whenever the query tiles do not fill whole rounds. For the paper's own shapes the
  *             split does not pay (a 12-head drafter layer has 228 query tiles for 256 compute
  *             units; the split costs more than the 11 % it could win) and AUTO leaves them alone.
  *             Same softmax and same error bounds; not bit-identical to the unsplit result (P is

@@ -595,7 +595,7 @@ int launch_bf16(const AttnParams &p_in, const Plan &pl, int n_cu, hipStream_t s)
   p.n_copy_blocks = p.k_commit_dst ? sdvg::copy_workgroups(pl, static_cast<int64_t>(p.n_blk) * p.n_heads, n_cu) : 0;
   if (pl.rows == 32) return sdvg::launch_block_attn_rows32(p, pl.halves, s);
   if (pl.groups > 1) return sdvg::launch_block_attn_groups(p, pl.groups, s);
-  if (!p.split.cols) {
+  if (!p.split.any()) {
     hipLaunchKernelGGL(block_attn_bf16_kernel<false>, dim3(8 * p.work_per_xcd + p.n_copy_blocks), dim3(512),
                        lds_bytes, s, p);
     SDVG_HIP_CHECK(hipGetLastError());
@@ -647,7 +647,7 @@ AttnParams part_of(const AttnParams &p, int h0, int heads, int r0, int rows) {
 
 // Launches a plan, without a split in two parts where that is faster.
 int launch_parts(const AttnParams &p, const Plan &pl, int n_cu, hipStream_t s) {
-  const sdvg::Cut cut = pl.split.cols ? sdvg::Cut{0, 0}
+  const sdvg::Cut cut = pl.split.any() ? sdvg::Cut{0, 0}
                                       : sdvg::choose_cut(p.n_items, p.n_q, p.n_heads, p.n_k, n_cu, rows32_ok(p));
   if (!cut.heads && !cut.rows) return launch_bf16(p, pl, n_cu, s);
   AttnParams first = part_of(p, 0, cut.heads ? cut.heads : p.n_heads, 0, cut.rows ? cut.rows : p.n_q);

@@ -176,6 +176,7 @@ SDVG_HD int v_read_offset(int lane, int j, int db, int hi) {
 struct KeySplit {
   int cols, col;     // columns, and the key tiles of each (the last one may be shorter where there are no helpers)
   int n_help, run;   // helpers, and the pairs of each
+  SDVG_HD bool any() const { return cols + n_help > 0; }
 };
 
 // A run of pairs cut at the boundaries between query tiles; `n_tiles` is the key tiles of a query tile that the runs cover.

@@ -26,7 +26,7 @@ struct AttnParams {
   int32_t n_items, n_q, n_k, n_heads, n_qtiles;
   int32_t n_hq;       // query tiles of the launch: n_items * n_heads * n_qtiles
   int32_t n_tiles;    // key tiles: n_k / 64, rounded up (4 key groups: of 32 keys)
-  attn_index::KeySplit split;  // how the keys are cut over workgroups; cols == 0 when they are not
+  attn_index::KeySplit split;  // how the keys are cut over workgroups, if they are
   int32_t total_work; // workgroups with work
   int32_t work_per_xcd;
   int32_t wt_base, wt_rem;  // 32-row wave tiles per query tile: wt_base, plus one for the first wt_rem

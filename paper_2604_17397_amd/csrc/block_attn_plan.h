@@ -23,7 +23,7 @@ struct Plan {
   int n_qtiles, n_hq, n_tiles;
   int units;     // key tiles of a workgroup; == n_tiles when nothing is split
   int total_wg;  // workgroups
-  attn_index::KeySplit split;  // cols == 0 when nothing is split
+  attn_index::KeySplit split;
   int64_t workspace_bytes;  // what a caller is asked for; 0 when no split was considered
   int groups;               // key groups per workgroup (1: block_attn.hip, 2 or 4: block_attn_groups.hip)
   int rows;                 // query rows per workgroup (32: block_attn_rows32.hip)
@@ -128,11 +128,18 @@ inline attn_index::KeySplit cut_keys(int n_hq, int n_tiles, int wgs) {
   const int64_t part = static_cast<int64_t>(n_tiles + (ks.n_help ? kPieceTiles : 0)) * n_hq;
   ks.col = static_cast<int>(ks.n_help ? (part + wgs - 1) / wgs : (n_tiles + ks.cols - 1) / ks.cols);
   const int64_t rest = n_tiles - static_cast<int64_t>(ks.cols) * ks.col;
-  if (rest < 1) {  // nothing for helpers to do
+  if (rest < 1 && ks.cols > 1) {  // nothing for helpers to do
     ks.n_help = 0;
     ks.col = (n_tiles + ks.cols - 1) / ks.cols;
-    ks.cols = ks.cols == 1 ? 0 : (n_tiles + ks.col - 1) / ks.col;
+    ks.cols = (n_tiles + ks.col - 1) / ks.col;
     return ks;
+  }
+  if (rest < 1) {
+    // Few workgroups are left over for many query tiles (ALWAYS only): equal runs of all pairs, at most two pieces each. 250
+    // query tiles of 220 key tiles, 50 heads x 1250 x 14080: 388 us, 374 unsplit; six helpers would have 42 pieces each.
+    const int64_t all = static_cast<int64_t>(n_hq) * n_tiles;
+    const int run = static_cast<int>((all + wgs - 1) / wgs);
+    return run < n_tiles ? attn_index::KeySplit{0, 0, static_cast<int>((all + run - 1) / run), run} : attn_index::KeySplit{0, 0, 0, 0};
   }
   ks.run = static_cast<int>((n_hq * rest + ks.n_help - 1) / ks.n_help);
   ks.n_help = static_cast<int>((n_hq * rest + ks.run - 1) / ks.run);
@@ -197,8 +204,8 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   const int max_wg = static_cast<int>((all + even - 1) / even);
   pl.workspace_bytes = static_cast<int64_t>(pl.n_hq + max_wg) * kPartialFloats * 4;
   pl.split = cut_keys(pl.n_hq, pl.n_tiles, max_wg);
-  if (pl.split.cols) {
-    pl.units = pl.split.col;
+  if (pl.split.any()) {
+    pl.units = pl.split.cols ? pl.split.col : pl.split.run;
     pl.total_wg = pl.n_hq * pl.split.cols + pl.split.n_help;
   }
   // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /

@@ -59,7 +59,14 @@ int main() {
       for (int n_tiles : {32, 33, 36, 64, 97, 147, 220, 512, 1025}) {
         if (static_cast<int64_t>(n_hq) * n_tiles > 300000) continue;
         const sdvg::Plan pl = sdvg::make_plan(1, 256, n_hq, static_cast<int64_t>(n_tiles) * 64 - 3, n_cu, SDVG_SPLIT_ALWAYS);
-        if (!pl.split.cols) continue;
+        // split unless the query tiles fill the rounds, or almost: a workgroup's share is all tiles of one, or too few tiles
+        const int64_t all = static_cast<int64_t>(n_hq) * n_tiles, slots = (n_hq + n_cu - 1) / n_cu * static_cast<int64_t>(n_cu);
+        const int64_t even = (all + slots - 1) / slots;
+        if (pl.split.any() != (n_hq % n_cu != 0 && even >= 16 && even < n_tiles)) {
+          std::printf("FAIL cus %d query tiles %d key tiles %d: split %d\n", n_cu, n_hq, n_tiles, pl.split.any());
+          return 1;
+        }
+        if (!pl.split.any()) continue;
         if (pl.n_hq != n_hq || pl.n_tiles != n_tiles || pl.units >= n_tiles || !check(n_hq, n_tiles, pl)) {
           std::printf("FAIL cus %d query tiles %d key tiles %d: cols %d x %d, helpers %d x %d\n", n_cu, n_hq, n_tiles,
                       pl.split.cols, pl.split.col, pl.split.n_help, pl.split.run);

@@ -23,9 +23,9 @@ def test_every_pair_once_and_every_piece_where_the_merge_looks(tmp_path):
 
 
 # (heads, queries, cached keys, block keys, workgroups on 256 compute units): two columns each and no helper; two columns
-# and helpers, the seam and the ragged end among the helpers' tiles; one column of all but a few tiles
+# and helpers, the seam and the ragged end among the helpers' tiles; one column of all but a few tiles; equal runs
 @pytest.mark.gpu
-@pytest.mark.parametrize("H,n_q,c_len,n_blk,wgs", [(128, 40, 2100, 40, 256), (95, 70, 3200, 77, 256), (230, 33, 6000, 391, 256)])
+@pytest.mark.parametrize("H,n_q,c_len,n_blk,wgs", [(128, 40, 2100, 40, 256), (95, 70, 3200, 77, 256), (230, 33, 6000, 391, 256), (250, 33, 6000, 391, 256)])
 def test_cut_matches_oracle(H, n_q, c_len, n_blk, wgs):
     import paper_2604_17397_amd as P
     q, kc, vc, kb, vb = si.attn_inputs(H, max(n_q, n_blk), c_len, seed=900 + H, jitter=True, cache_capacity=c_len)
