@@ -434,7 +434,7 @@ __global__ __launch_bounds__(512) void block_attn_bf16_kernel(const AttnParams p
   if constexpr (!kSplit) {
     const int work = ix::work_of_block(blockIdx.x, p.work_per_xcd);
     if (work >= p.total_work) return;
-    run_piece(p, ix::Piece{work, 0, p.n_tiles, true}, 0);
+    run_piece(p, ix::Piece{work, 0, p.n_tiles}, 0);
   } else {
     const ix::SplitWork w = ix::split_work(p.split, p.n_hq, p.total_work, blockIdx.x, p.work_per_xcd);
     if (!w.any) return;

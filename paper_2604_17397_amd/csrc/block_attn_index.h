@@ -185,7 +185,6 @@ struct KeySplit {
 struct Piece {
   int hq;        // query tile (item, head, q-tile flattened)
   int t_first, t_end;  // its key tiles handled here
-  bool whole;    // the piece covers all key tiles: the result is final, no partial is written
 };
 SDVG_HD Piece piece_at(int64_t u, int64_t u_end, int n_tiles) {
   Piece pc;
@@ -193,7 +192,6 @@ SDVG_HD Piece piece_at(int64_t u, int64_t u_end, int n_tiles) {
   pc.t_first = static_cast<int>(u - static_cast<int64_t>(pc.hq) * n_tiles);
   const int64_t left = u_end - u;
   pc.t_end = left < n_tiles - pc.t_first ? pc.t_first + static_cast<int>(left) : n_tiles;
-  pc.whole = pc.t_first == 0 && pc.t_end == n_tiles;
   return pc;
 }
 // First and last run that hold a piece of query tile hq.
@@ -209,14 +207,13 @@ SDVG_HD int split_rest(const KeySplit &ks, int n_tiles) { return ks.n_help ? n_t
 // Key tiles of column c, and piece `pc` of the helpers' runs as a piece of the query tile.
 SDVG_HD Piece column_piece(const KeySplit &ks, int hq, int c, int n_tiles) {
   const int end = (c + 1) * ks.col;
-  return Piece{hq, c * ks.col, end < n_tiles ? end : n_tiles, false};
+  return Piece{hq, c * ks.col, end < n_tiles ? end : n_tiles};
 }
 SDVG_HD Piece helper_piece(const KeySplit &ks, int64_t u, int64_t u_end, int n_tiles) {
   const int rest = split_rest(ks, n_tiles);
   Piece pc = piece_at(u, u_end, rest);
   pc.t_first += n_tiles - rest;
   pc.t_end += n_tiles - rest;
-  pc.whole = false;
   return pc;
 }
 // Pieces of a query tile: the columns, then the helpers' in their order. Slot of piece i in the partial buffer.

@@ -239,9 +239,8 @@ bool check_key_split(Failure &f) {
           while (u < u_end) {
             const ix::Piece pc = ix::piece_at(u, u_end, n_tiles);
             const bool ok = pc.hq >= 0 && pc.hq < n_hq && pc.t_first >= 0 && pc.t_end > pc.t_first &&
-                            pc.t_end <= n_tiles && pc.whole == (pc.t_first == 0 && pc.t_end == n_tiles) &&
-                            w >= ix::first_wg_of(pc.hq, n_tiles, units) && w <= ix::last_wg_of(pc.hq, n_tiles, units) &&
-                            (pc.whole == (ix::first_wg_of(pc.hq, n_tiles, units) == ix::last_wg_of(pc.hq, n_tiles, units)));
+                            pc.t_end <= n_tiles && w >= ix::first_wg_of(pc.hq, n_tiles, units) &&
+                            w <= ix::last_wg_of(pc.hq, n_tiles, units);
             if (!ok || slot_used[ix::partial_slot(pc.hq, w)]++) {
               f = {"key split: bad piece or slot used twice", n_hq, n_tiles, units, w, pc.hq};
               return false;

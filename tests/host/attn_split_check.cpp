@@ -16,7 +16,7 @@ static bool check(int n_hq, int n_tiles, const sdvg::Plan &pl) {
   std::vector<char> taken(static_cast<size_t>(n_hq) * n_tiles), slot_used(slots);
   std::vector<int> pieces(n_hq), seen(wgs);
   auto piece = [&](const ix::Piece &pc, int slot, int order) {
-    if (pc.whole || pc.hq < 0 || pc.hq >= n_hq || pc.t_first < 0 || pc.t_end <= pc.t_first || pc.t_end > n_tiles) return false;
+    if (pc.hq < 0 || pc.hq >= n_hq || pc.t_first < 0 || pc.t_end <= pc.t_first || pc.t_end > n_tiles) return false;
     if (slot < 0 || slot >= slots || slot_used[slot]++) return false;
     for (int t = pc.t_first; t < pc.t_end; ++t)
       if (taken[static_cast<size_t>(pc.hq) * n_tiles + t]++) return false;
