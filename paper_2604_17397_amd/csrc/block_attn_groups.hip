@@ -33,8 +33,8 @@
 // the loop is short of. All that changes per tile, worked out anew for each, is slower again: 1 to 2 %.)
 // (Arguments of the first copies preloaded into registers, as in block_attn_rows32.hip: no gain. 64 rows per wave, every
 // wave with key tiles of its own, which halves the LDS reads and needs no barrier: 53, bound by the copies.)
-// What bounds it there, by counters: the matrix pipes are busy in 57 % of the SIMD cycles of the
-// compute units at work (2 groups 70 %, the 256-row kernel 84 %). With the copies, the softmax or the MFMAs
+// What bounds it there, by counters: the matrix pipes are busy in 58 % of the SIMD cycles of the
+// compute units at work (2 groups 70 %, the 256-row kernel 86 %). With the copies, the softmax or the MFMAs
 // left out (not a result, a timing) a launch is 3, 7 and 11 % shorter: no unit is the limit, but the
 // hand-over between the phases, some 250 cycles for every 16 MFMAs (512 cycles) of a group's 32-key tile.
 // The way in and out: all arguments asked for at once, the work index by multiplication, the query rows

@@ -34,22 +34,22 @@ struct Plan {
 // Key groups per workgroup, and the query rows they share. Estimated time: rounds of workgroups over the
 // compute units, times a fixed part plus the key tiles each group walks.
 // Measured on MI355X, us among others in a graph (1 / 2 / 4 groups; workgroups of 256 / 128 / 64 rows in brackets):
-//   12 heads x 312 x 936 keys [24/36/60] 25.7 / 17.6 / 13.3; 12 x 1031 x 6186 [60/108/204] 105 / 63 / 48;
-//   12 x 1560 x 4680 [84/156/300] 82 / 52 / 72; 5 x 4680 x 32760 [95/185/370] 511 / 362 / 451;
-//   40 x 1031 x 3093 [200/360/680] 72 / 88 / 99; 16 x 4680 x 14040 [304/592/1184] 581 / 511 / 572;
-//   12 x 4680 x 14040 [228/444/888] 332 / 348 / 461.
+//   12 heads x 312 x 936 keys [24/36/60] 25.7 / 17.5 / 13.1; 12 x 1031 x 6186 [60/108/204] 104 / 62 / 47;
+//   12 x 1560 x 4680 [84/156/300] 83 / 51 / 70; 5 x 4680 x 32760 [95/185/370] 505 / 350 / 448;
+//   40 x 1031 x 3093 [200/360/680] 73 / 86 / 97; 16 x 4680 x 14040 [304/592/1184] 554 / 482 / 543;
+//   12 x 4680 x 14040 [228/444/888] 314 / 337 / 450.
 // A tile takes 1.0 us alone on the chip and 1.5 us on a full one (power), hence the middle value, and
 // the estimate is up to 25 % off in absolute terms; what counts is the order. Over 1 to 40 heads, 156
-// to 4680 rows and 193 to 32760 keys it is within 1 % of the fastest of the four in 296 of 299 launches and 4 to 11 % off in
+// to 4680 rows and 193 to 32760 keys it is within 1 % of the fastest of the four in 296 of 299 launches and 4 to 9 % off in
 // three, where 64 rows beat 32 (profiles/attn_plan_sweep.txt, as the other figures here). Up to 192 keys it stays with
-// 1 group, where more are faster (3 heads x 250 rows x 128 keys 11.7 / 7.4 / 6.2).
+// 1 group, where more are faster (3 heads x 250 rows x 128 keys 11.8 / 7.4 / 6.3).
 // Of the launches of four groups, those whose 32-row workgroups need no more rounds than 64-row ones take the kernel
 // where the two waves of a group share 32 rows and deal the group's tiles out as well (rows = 32). One round, us
-// with 64 / 32 rows: 12 x 312 x 936 13.3 / 9.4; 16 x 500 x 1000 13.7 / 12.1; 8 x 1024 x 6144 41.0 / 38.8, with keys from
-// HBM 62.2 / 46.2. (4 x 2000 x 14000 loses, 84.3 / 97.7, where the memory-side cache holds the layer's 29 MB; the layers of
+// with 64 / 32 rows: 12 x 312 x 936 13.1 / 9.4; 16 x 500 x 1000 13.8 / 12.1; 8 x 1024 x 6144 41.1 / 39.3, with keys from
+// HBM 61.4 / 46.1. (4 x 2000 x 14000 loses, 83.5 / 96.2, where the memory-side cache holds the layer's 29 MB; the layers of
 // a model of this size come from HBM, 129 / 95.) More rounds with as many workgroups (up to 32 rows), before the copies from
 // scalar addresses (block_attn_groups.hip), which gave 64 rows 1 to 2 %: 300 x 32 x 512 24.6 / 22.7; 259 x 1 x 936 34.7 / 33.2.
-// In a round more than with 64 rows every workgroup walks all keys again: 12 x 1031 x 1031 14.6 / 20.2; 320 x 33 x 256 16.8 /
+// In a round more than with 64 rows every workgroup walks all keys again: 12 x 1031 x 1031 14.1 / 20.1; 320 x 33 x 256 16.8 /
 // 20.3; 300 x 64 x 256 17.7 / 18.5.
 struct Groups {
   int groups, rows;
@@ -174,9 +174,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     pl.n_tiles = pl.units = static_cast<int>((n_k + keys - 1) / keys);
     pl.split = attn_index::KeySplit{0, 0, 0, 0};
     // 32-row workgroups that leave half of the compute units idle are doubled: each of a pair copies all of K but half of V,
-    // and copies are what bounds them (block_attn_rows32.hip). Whole / halves, us: 12 heads x 312 x 936 keys 9.1 / 8.7, with
-    // keys from the memory-side cache 10.5 / 9.0; 4 x 1000 x 4000 22.4 / 21.4, 24.6 / 21.7; 3 x 1300 x 9100 50 / 43, 58 / 47;
-    // the same where there is nothing to halve (1 x 33 x 99, 6.4). In a second round every pair would copy K again. Both of a
+    // and copies are what bounds them (block_attn_rows32.hip). Whole / halves, us in a graph with one set of tensors, four sets in
+    // turn, keys from HBM: 12 heads x 312 x 936 keys 9.3 / 8.6, 10.3 / 8.9, 12.5 / 10.5; 4 x 1000 x 4000 22.4 / 21.0, 24.7 / 21.4,
+    // 31.9 / 25.8; 3 x 1300 x 9100 50 / 42, 50 / 42, 60 / 48. In a second round every pair would copy K again. Both of a
     // pair read whole query rows and store half of them, at times of their own: not where the result lies over the query.
     pl.halves = rows == 32 && 2 * pl.total_wg <= n_cu && !in_place;
     pl.workspace_bytes = 0;
@@ -191,9 +191,9 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
   // The split costs a second kernel, the partial results' traffic and a slower main kernel, and
   // a chip that is only partly busy clocks higher: 228 busy compute units take a tile in 1.46 us, 256 in 1.61, so
   // that 11 % idle cost nothing. Measured on MI355X, us, the fastest without a split / split, at 4680 rows:
-  //   11 % idle  12 heads x 14040 keys 332 / 345, x 32760 752 / 760, 24 x 14040 659 / 678
-  //   18 - 26 %  11 x 32760 713 / 701, 20 x 18720 740 / 743
-  //   33 - 48 %  8 x 32760 573 / 518, 8 x 14040 253 / 237, 14 x 23400 821 / 665
+  //   11 % idle  12 heads x 14040 keys 314 / 319, x 32760 710 / 694, 24 x 14040 619 / 637
+  //   18 - 26 %  11 x 32760 676 / 641, 20 x 18720 700 / 700
+  //   33 - 48 %  8 x 32760 557 / 482, 8 x 14040 242 / 224, 14 x 23400 782 / 631
   // From kAutoIdle on the estimates decide (below).
   if (pl.n_hq % n_cu == 0 || rounds > 4 || pl.n_tiles < 32) return plain();
   if (split_mode == SDVG_SPLIT_AUTO && idle < auto_idle) return plain();
@@ -209,12 +209,12 @@ inline Plan make_plan(int n_items, int n_q, int n_heads, int64_t n_k, int n_cu, 
     pl.total_wg = pl.n_hq * pl.split.cols + pl.split.n_help;
   }
   // Launch, merge and 1.53 us per key tile of a workgroup, against the estimate without a split. Split /
-  // unsplit, us: 1 head x 4680 x 32760 83 / 145, 5 heads 331 / 362; 4 x 4680 x 14040 127 / 141,
-  // 5 heads 153 / 157; 12 x 1560 x 4680 59 / 52, 16 x 1031 x 3093 42 / 36, 3 x 4680 x 4680 47 / 39.
-  // (Of 299 launches without a batch 6 would gain 5 to 25 % from a split that the estimate does not take, 0.3 % on average.)
+  // unsplit, us: 1 head x 4680 x 32760 80 / 146, 5 heads 307 / 350; 4 x 4680 x 14040 121 / 139,
+  // 5 heads 146 / 153; 12 x 1560 x 4680 57 / 51, 16 x 1031 x 3093 41 / 37, 3 x 4680 x 4680 46 / 38.
+  // (Of 299 launches without a batch 10 would gain 3 to 22 % from a split that the estimate does not take, 0.3 % on average.)
   // Below 60 % idle the unsplit estimate, made for a full chip, is a little high for one that is half busy: the split
   // has to win by 11 us there. Of 110 launches drawn at 25 to 60 % idle (1 to 3 items, up to 40 heads, 312 to 4680 rows,
-  // 1 to 7 blocks of keys) 31 are split, 1.5 to 15 % faster each; 7 more would have gained 3 to 11 %. (Against one launch.
+  // 1 to 7 blocks of keys) 31 are split, 4 to 15 % faster each; 10 more would have gained 4 to 11 %. (Against one launch.
   // Against two, choose_cut, which this does not weigh: of 80 drawn launches of more than a round 21 are split, 2.4 % faster on
   // average, the worst 4 % slower; 7 more would have gained 3 to 8 %.)
   const double split_us = 33.0 + 1.53 * rounds * static_cast<double>(even);

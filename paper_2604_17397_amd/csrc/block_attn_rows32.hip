@@ -15,13 +15,14 @@
 //   - the arguments of the first copies are in registers when a wave starts, all others are asked for at once
 //     behind those copies; the query rows come through the LDS once per workgroup.
 // us among others in a graph, four sets of tensors in turn, with 64 rows / here (profiles/attn_plan_sweep.txt): 12 heads x 312 x
-// 936 keys 13.4 / 9.4, 12 x 312 x 312 8.7 / 6.0, 8 x 1024 x 6144 41.0 / 38.8; with keys from HBM 13.3 / 9.4, 9.3 / 6.1, 62.2 / 46.2.
+// 936 keys 13.1 / 9.4, 12 x 312 x 312 8.5 / 6.1, 8 x 1024 x 6144 41.1 / 39.3; with keys from HBM 15.9 / 10.6, 9.9 / 6.4, 61.4 / 46.1.
 // Where it went at 12 x 312 x 936, one workgroup per 32 rows, while the first copies still waited 0.3 us for their arguments (9.2 us with one set of tensors
 // again and again): 0.9 launch, 1.5 until the first tiles have landed, 0.6 first scores, 0.4 common maximum, 4.4 loop, 1.1
 // merge and store.
 // Where these workgroups are few (block_attn_plan.h) there are two per 32 rows, each with half of the output dims: 96 KB of
-// copies per 8 x 32 keys instead of 128, and half of the merge. 12 x 312 x 936 9.1 -> 8.7, keys from the memory-side cache
-// 10.5 -> 9.0; 12 x 312 x 312 6.1 -> 5.6, 6.4 -> 5.7; 5 x 800 x 5600 32.5 -> 28.8, 40.1 -> 32.6. (The LDS that half a V tile leaves
+// copies per 8 x 32 keys instead of 128, and half of the merge. us in a graph with one set of tensors, four sets in turn, keys from
+// HBM: 12 x 312 x 936 9.3 -> 8.6, 10.3 -> 8.9, 12.5 -> 10.5 (9.1 -> 8.3 as calls with one set); 12 x 312 x 312 6.4 -> 5.8, 6.4 -> 5.8,
+// 7.2 -> 6.4; 5 x 800 x 5600 32.9 -> 28.1, 33.1 -> 28.1, 40.0 -> 32.8. (The LDS that half a V tile leaves
 // free as a second K slot, K copied two tiles ahead: 1 us slower throughout, 9.0 -> 9.8.)
 // The loop is bound by the copies: 8 waves bring 128 KB per 8 x 32 keys, which takes 1.13 - 1.18 us, and a
 // loop of nothing but such copies from L2 reaches 62 bytes per clock and compute unit, 1.13 us. So

@@ -50,3 +50,12 @@ def test_out_is_q(n, H, n_q, c_len, n_blk, rows, packed):
     P.block_attn_batch(*lists, c_len, outs=lists[0], workspace=ws, split=split)
     for q, w in zip(lists[0], want):
         assert torch.equal(q, w)
+
+
+@pytest.mark.gpu
+def test_out_is_q_in_fp32():
+    import paper_2604_17397_amd as P
+    g = torch.Generator(device="cuda").manual_seed(2)
+    q, kc, vc, kb, vb = (torch.randn((t, 3, 128), device="cuda", generator=g) for t in (200, 90, 90, 70, 70))
+    want = P.block_attn(q, kc, vc, kb, vb, 90)
+    assert torch.equal(P.block_attn(q, kc, vc, kb, vb, 90, out=q), want)
