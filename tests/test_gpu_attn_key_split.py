@@ -1,4 +1,4 @@
-"""The key split's cut: on the CPU, every workgroup of some two thousand launches walked with the functions that the
+"""The key split's cut: on the CPU, every workgroup of some three thousand launches walked with the functions that the
 kernel uses (tests/host/attn_split_check.cpp); on the GPU, the cuts that other tests do not reach."""
 import os
 import subprocess
@@ -19,7 +19,7 @@ def test_every_pair_once_and_every_piece_where_the_merge_looks(tmp_path):
                     os.path.join(ROOT, "paper_2604_17397_amd", "csrc"),
                     os.path.join(ROOT, "tests", "host", "attn_split_check.cpp"), "-o", exe], check=True)
     res = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=300)
-    assert res.returncode == 0 and int(res.stdout.split()[1]) > 1500, res.stdout
+    assert res.returncode == 0 and int(res.stdout.split()[1]) > 3000, res.stdout
 
 
 # (heads, queries, cached keys, block keys, workgroups on 256 compute units): two columns each and no helper; two columns
